@@ -58,7 +58,10 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15 };
+
+// Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp) and keep re-laid-out operands in the workspace.
+static inline bool is_split_kind(int kind) { return kind == KIND_XCONV; }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
 
@@ -86,13 +89,14 @@ static void dconv_frame(const Geom &g, int pass, GemmParams &p)
     p.dWo.set(p.Wo); p.dHoWo.set(p.Ho * p.Wo);
 }
 
-// LDS panel rows the direct kernel needs for BM-row tiles, or -1 when the pass does not qualify.
-static long direct_panel_rows(const Geom &g, int pass, const PassDims &dm, long BM = 128)
+// LDS panel rows a tile of BM consecutive output pixels of a stride-1 pass needs, or -1 when its input pixels are not
+// one contiguous run.
+static long panel_rows(const Geom &g, int pass, const PassDims &dm, long BM)
 {
-    if (pass == OWT_PASS_BWD_FILTER || g.sh != 1 || g.sw != 1 || g.R * g.S == 1) return -1;
+    if (pass == OWT_PASS_BWD_FILTER || g.sh != 1 || g.sw != 1) return -1;
     GemmParams f; memset(&f, 0, sizeof(f));
     dconv_frame(g, pass, f);
-    if (f.Ho > f.Hi || f.Wo > f.Wi || f.Cred % 4 || (pass == OWT_PASS_BWD_DATA && dm.Ncols % 4)) return -1;
+    if (f.Ho > f.Hi || f.Wo > f.Wi) return -1;
     auto pin = [&](long m) {
         const long n = m / (f.Ho * f.Wo), rem = m % (f.Ho * f.Wo);
         return n * f.Hi * f.Wi + (rem / f.Wo - f.pah) * f.Wi + (rem % f.Wo - f.paw);
@@ -104,6 +108,14 @@ static long direct_panel_rows(const Geom &g, int pass, const PassDims &dm, long 
         if (rows > need) need = rows;
     }
     return need;
+}
+
+// The same for the direct kernel, or -1 when the pass does not qualify.
+static long direct_panel_rows(const Geom &g, int pass, const PassDims &dm, long BM = 128)
+{
+    if (pass == OWT_PASS_BWD_FILTER || g.R * g.S == 1) return -1;
+    if ((pass == OWT_PASS_FWD ? g.C : g.K) % 4 || (pass == OWT_PASS_BWD_DATA && dm.Ncols % 4)) return -1;
+    return panel_rows(g, pass, dm, BM);
 }
 
 // Geometry of the bf16-MFMA small-channel strided forward kernel; false when it does not apply (bf16
@@ -398,6 +410,38 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             add(KIND_DIRECT, t, pr, chunks, s, macs, t == TILE_128x64 ? 5 : (t == TILE_128x64H ? 3 : 2),
                 t == TILE_128x64 ? 1.1 : 1.25);
             if (force_split > 0) break;
+        }
+    }
+    // fp32 storage on the bf16 matrix unit with split operands: stride 1, at most 32 taps, 32-bit byte offsets
+    if (!g.bf16 && pass != OWT_PASS_BWD_FILTER && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && g.R * g.S <= 32 &&
+        (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull) {
+        for (int v = 0; v < kNumXConvVariants; v++) {
+            if (force_tile >= 0 && force_tile != kXConvFirstTile + v) continue;
+            const XConvVariant &xv = kXConvVariants[v];
+            const long BM = 32 * xv.MB * xv.WM, BN = 64 * xv.WN, rows = panel_rows(g, pass, dm, BM);
+            if (rows < 0 || (xv.occ == 4 && xv.WM == 4 && pass == OWT_PASS_BWD_DATA && g.masked)) continue;
+            int pr = 0;
+            for (int q = 2; q >= 0; q--)
+                if (xv.prs[q] >= rows) pr = xv.prs[q];
+            const long tm = cdiv(dm.M, BM), tn = cdiv(dm.Ncols, BN), chunks = cdiv(cred, 16);
+            const size_t packed = (size_t)chunks * g.R * g.S * tn * 2 * xv.WN * 3072;
+            if (!pr || packed >= 0x7fffffffull) continue;
+            const double macs = (double)BM * BN * 16 * g.R * g.S / 1.75;      // against the fp32 instruction's rate
+            for (long s0 : kSplits) {
+                if (s0 > 1 && force_split <= 0 && (s0 > chunks || s0 > 16)) break;
+                const long s = force_split > 0 ? (force_split < chunks ? force_split : chunks) : s0;
+                const long per = cdiv(chunks, s), splits = cdiv(chunks, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_XCONV; l.tile = v; l.pr = pr; l.splits = (int)splits; l.steps = (int)chunks; l.steps_per_split = (int)per;
+                l.tiles_m = (int)tm; l.tiles_n = (int)tn;
+                l.pre_bytes = pad256(packed);
+                if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                l.cost = model_cost(tm * tn * splits, xv.WM * xv.WN, xv.occ, macs * per, xv.eff, splits, dm.M, dm.Ncols) + 8000.0;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
         }
     }
     if (g.bf16 && cred % 8 == 0 && !forced(OWT_FORCE_NO_BF16_MFMA)) {      // the bf16 MFMA: 64-channel chunks, or 32 in the 512x64 tile
@@ -725,26 +769,32 @@ static bool variants_forced()
 
 static std::map<PlanKey, Launch> g_modelled;   // the cost model's choice per geometry (untimed), so that a call plans once
 
-static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, bool want_db, bool use_cache)
+// ws_bytes: the scratch the call was given.  A plan whose operands are split into the workspace is passed over when it does
+// not fit, so a caller that sized its scratch for the kernels that multiply in fp32 is served by those.
+static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, bool want_db, bool use_cache, size_t ws_bytes = (size_t)-1)
 {
     const bool cached = use_cache && !variants_forced();
     if (cached) {
         std::lock_guard<std::mutex> lk(g_tuned_mutex);
+        const auto fits = [&](const Launch &l) { return !is_split_kind(l.kind) || l.ws_bytes() <= ws_bytes; };
         auto it = g_tuned.find(plan_key(g, pass, dt));
-        if (it != g_tuned.end()) return it->second;
+        if (it != g_tuned.end() && fits(it->second)) return it->second;
+        const bool tuned = it != g_tuned.end();
         it = g_modelled.find(plan_key(g, pass, dt));
-        if (it != g_modelled.end()) return it->second;
+        if (!tuned && it != g_modelled.end() && fits(it->second)) return it->second;
     }
     std::vector<Launch> c;
     enumerate(g, pass, dm, want_db, c);
     bool only_direct = forced(OWT_FORCE_ONLY_DIRECT), any_direct = false;   // test hook
     for (const Launch &l : c) any_direct |= l.kind != KIND_GATHER;
     size_t best = c.size();
+    bool shrunk = false;
     for (size_t i = 0; i < c.size(); i++) {
         if (only_direct && any_direct && c[i].kind == KIND_GATHER) continue;
+        if (is_split_kind(c[i].kind) && c[i].ws_bytes() > ws_bytes) { shrunk = true; continue; }
         if (best == c.size() || c[i].cost < c[best].cost) best = i;
     }
-    if (cached) {
+    if (cached && !shrunk) {
         std::lock_guard<std::mutex> lk(g_tuned_mutex);
         g_modelled[plan_key(g, pass, dt)] = c[best];
     }
@@ -783,7 +833,12 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
     frame_params(g, dm, l, ws, p);
     const bool bf = dt == OWT_BF16;
     hipError_t e;
-    if (l.kind == KIND_FCGEMM) {
+    if (l.kind == KIND_XCONV) {
+        dconv_frame(g, pass, p);
+        const bool vec = p.Cred % 4 == 0;
+        if (pass == OWT_PASS_FWD) e = vec ? owt_launch_xconv_fwd_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_fwd_vec0(l.tile, l.pr, p, ws, s);
+        else e = vec ? owt_launch_xconv_data_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_data_vec0(l.tile, l.pr, p, ws, s);
+    } else if (l.kind == KIND_FCGEMM) {
         e = owt_launch_fcgemm(pass, l.tile, p, (float *)ws, s);
     } else if (l.kind == KIND_DIRECT16) {
         dconv_frame(g, pass, p);
@@ -871,6 +926,11 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         return snprintf(buf, n, "fcgemm %s %s tile%dx%dx32 splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * ft.MB * ft.WM,
                         32 * ft.NB * ft.WN, l.splits, l.tiles_m * l.tiles_n, l.splits,
                         (long)l.tiles_m * l.tiles_n * l.splits * 64 * ft.WM * ft.WN);
+    }
+    if (l.kind == KIND_XCONV) {
+        const XConvVariant &v = kXConvVariants[l.tile];
+        return snprintf(buf, n, "xconv %s %s tile%dx%dx16 waves%dx%d panel%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.MB * v.WM, 64 * v.WN,
+                        v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
     }
     if (l.kind == KIND_SCONV16)
         return snprintf(buf, n, "sconv16 %s %s rows%d grid%dx%d threads%ld", pn[pass], ds, kSConv16TP, l.tiles_m, l.tiles_n,
@@ -976,7 +1036,7 @@ static owt_status conv_pass(const Geom &g, int pass, owt_dtype dt, const GemmPar
                             void *ws, size_t ws_bytes, hipStream_t s, bool use_cache)
 {
     const PassDims dm = conv_dims(g, pass);
-    const Launch l = choose(g, pass, dt, dm, want_db, use_cache);
+    const Launch l = choose(g, pass, dt, dm, want_db, use_cache, ws ? ws_bytes : 0);
     OWT_TRY(check_ws(l, ws, ws_bytes));
     return launch(g, pass, dt, dm, p, l, ws, s);
 }

@@ -1,0 +1,277 @@
+// Direct stride-1 convolution, fp32 storage, on the bf16 matrix unit with operands split in three (split3.hpp):
+// forward and backward-data of the stride-1 layers (Section 4 of the paper, forward step 2 / backward step 2).
+//
+// Panel-resident like dconv.hpp: the input pixels under a tile of BM consecutive output pixels are one contiguous run
+// of NHWC pixels, loaded once per 16-channel chunk and read by every filter tap at a shifted row.  What bounds it is
+// the matrix pipe (six 32-cycle instructions per 32x32x16 block product), so everything else is arranged around that:
+//  * a wavefront owns 64 pixels x 64 filters: 2 x 2 blocks with two accumulators each (128 registers), and per tap and
+//    chunk it reads 6 + 6 fragments of 1 KB for 24 matrix instructions (half a fragment per instruction; the LDS could
+//    deliver about one), two wavefronts per SIMD;
+//  * the panel's values are split once, on their way from global memory into LDS (R*S taps and the tile's filter blocks
+//    reuse them): 6 vector instructions per value, 3-7 % of the matrix time for a 3x3 layer, where writing the three
+//    parts to memory and reading them back would move 10 bytes per value;
+//  * the filters are split and laid out once per call in the order the fragments are read (xconv_pack_kernel), so a
+//    tap's slice is a few 1 KB pieces that go straight into LDS, and a fragment read is 64 consecutive 16-byte pieces;
+//  * the panel is kept as six planes (part, 8-channel half) of one 16-byte piece per pixel: a fragment read of 32
+//    consecutive pixels is 512 consecutive bytes whatever the tap's shift, so there is nothing to pad or swizzle;
+//  * slices sit in a ring of three, so one barrier per tap is enough and a slice has two taps' time to arrive.
+// Taps that fall outside the image read the row of zeros behind each plane.
+#pragma once
+#include "igemm.hpp"
+#include "split3.hpp"
+
+namespace owt {
+
+// Filters -> [chunk][tap][32-column block][part][lane][8 values], zero-padded: column = 32 * block + lane % 32 (a filter
+// in forward, an input channel in backward-data), reduction index = 16 * chunk + 8 * (lane / 32) + j.  Backward-data
+// reads w[k][R-1-r][S-1-s][c] with k as the reduction index.  One thread per (chunk, tap, block, lane).
+template <bool BWD>
+__global__ void __launch_bounds__(256) xconv_pack_kernel(const float *__restrict__ w, uint4 *__restrict__ out, int K, int RS,
+                                                         int C, int chunks, int nblocks)
+{
+    const int total = chunks * RS * nblocks * 64;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+        const int lane = i & 63, q = i >> 6, nb = q % nblocks, ct = q / nblocks, tap = ct % RS, ch = ct / RS;
+        const int col = nb * 32 + (lane & 31), red = ch * 16 + (lane >> 5) * 8;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const int kd = red + j;
+            if (BWD) v[j] = (col < C && kd < K) ? w[((size_t)kd * RS + (RS - 1 - tap)) * C + col] : 0.f;
+            else v[j] = (col < K && kd < C) ? w[((size_t)col * RS + tap) * C + kd] : 0.f;
+        }
+        uint4 h, m, l;
+        split3_pack8(v, h, m, l);
+        uint4 *o = out + (size_t)q * 192 + lane;
+        o[0] = h; o[64] = m; o[128] = l;
+    }
+}
+
+// WM x WN wavefronts of 32*MB pixels x 64 filters; PR panel rows; NPB panel buffers (two: the next chunk is written while
+// the last tap of this one is still being read, no extra barrier); VEC: channels a multiple of 4 (16-byte loads);
+// MASKED: dy is masked by y > 0 on its way in.  At most 32 taps; 32-bit byte offsets in every tensor (host-checked).
+template <class Epi, bool BWD, int WM, int WN, int MB, int PR, int NPB, bool VEC, bool MASKED>
+__global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160 ? 4 : 3) : 2) xconv_kernel(const GemmParams p)
+{
+    constexpr int NW = WM * WN, NT = 64 * NW, BM = 32 * MB * WM, BN = 64 * WN;
+    constexpr int PL = PR + 1, PANEL = 6 * PL;                       // 16-byte units: a plane, a panel buffer
+    constexpr int SL = BN / 32 * 3;                                  // 1 KB pieces of a filter slice
+    constexpr int PU = (2 * PR + NT - 1) / NT;                       // (row, half) pairs of the panel per thread
+    constexpr unsigned OOB = 0x80000000u;                            // a byte offset no descriptor here reaches
+
+    __shared__ __attribute__((aligned(1024))) uint4 slices[3 * SL * 64];
+    __shared__ __attribute__((aligned(16))) uint4 panel[NPB * PANEL];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lh = lane >> 5;
+    const int wm = wave / WN, wn = wave - wm * WN;
+
+    const int ntiles = p.tiles_m * p.tiles_n;
+    const int b = blockIdx.x, xcd = b & 7;
+    const int logical = xcd * (ntiles >> 3) + min(xcd, ntiles & 7) + (b >> 3);
+    const int tm = logical / p.tiles_n, tn = logical - tm * p.tiles_n;
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int split = blockIdx.y;
+    const int ch_beg = split * p.ksteps_per_split, ch_end = min(p.ksteps, ch_beg + p.ksteps_per_split);
+
+    const int R = p.g.R, S = p.g.S, RS = R * S, Hi = p.Hi, Wi = p.Wi, Cred = p.Cred;
+    const int HoWo = p.Ho * p.Wo;
+
+    auto pin = [&](int m, int &hh, int &ww) {
+        const int n = p.dHoWo.div(m), rem = m - n * HoWo;
+        const int ho = p.dWo.div(rem), wo = rem - ho * p.Wo;
+        hh = ho - p.pah; ww = wo - p.paw;
+        return n * Hi * Wi + hh * Wi + ww;
+    };
+    int th, tw;
+    const int ps = pin(m0, th, tw);
+    const int nrows = pin(min(m0 + BM, p.M) - 1, th, tw) + (R - 1) * Wi + S - ps;   // <= PR (host-checked)
+
+    // per 32-pixel block of this lane: its panel row at tap (0,0), and one bit per tap that falls inside the image
+    int prow[MB];
+    unsigned inside[MB];
+#pragma unroll
+    for (int bm = 0; bm < MB; bm++) {
+        const int m = m0 + (wm * MB + bm) * 32 + li;
+        prow[bm] = 0;
+        inside[bm] = 0u;
+        if (m < p.M) {
+            int hh, ww;
+            prow[bm] = pin(m, hh, ww) - ps;
+            for (int r = 0, tap = 0; r < R; r++)
+                for (int s = 0; s < S; s++, tap++)
+                    if ((unsigned)(hh + r) < (unsigned)Hi && (unsigned)(ww + s) < (unsigned)Wi) inside[bm] |= 1u << tap;
+        }
+    }
+
+    // ---- panel loader: thread -> (row, 8-channel half) pairs u = tid + i * NT.  Rows before the first or past the last
+    // pixel of the tensor and rows the tile does not need get an offset outside the descriptor and read as zeros.
+    const __amdgpu_buffer_rsrc_t ars = owt_make_rsrc(p.a, (unsigned)(p.g.N * Hi * Wi) * (unsigned)Cred * 4u);
+    const __amdgpu_buffer_rsrc_t mrs = owt_make_rsrc(MASKED ? p.mask : p.a, (unsigned)(p.g.N * Hi * Wi) * (unsigned)Cred * 4u);
+    unsigned rowoff[PU];
+#pragma unroll
+    for (int i = 0; i < PU; i++) {
+        const int u = tid + i * NT, row = u >> 1, pix = ps + row;
+        rowoff[i] = (row < nrows && (unsigned)pix < (unsigned)(p.g.N * Hi * Wi)) ? (unsigned)pix * (unsigned)Cred * 4u : OOB;
+    }
+    float preg[PU][8], yreg[MASKED ? PU : 1][8];
+    auto load8 = [&](__amdgpu_buffer_rsrc_t rs, unsigned base, int c, float (&v)[8]) __attribute__((always_inline)) {
+        if (VEC) {
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                const float4 f = buffer_load4(rs, c + 4 * q < Cred ? base + (unsigned)(c + 4 * q) * 4u : OOB);
+                v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(c + j < Cred ? base + (unsigned)(c + j) * 4u : OOB), 0, 0));
+        }
+    };
+    auto load_panel = [&](int ch) __attribute__((always_inline)) {
+        const int c = ch * 16 + (tid & 1) * 8;
+#pragma unroll
+        for (int i = 0; i < PU; i++) {
+            load8(ars, rowoff[i], c, preg[i]);
+            if (MASKED) load8(mrs, rowoff[i], c, yreg[MASKED ? i : 0]);
+        }
+    };
+    auto store_panel = [&](uint4 *dst) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < PU; i++) {
+            const int u = tid + i * NT, row = u >> 1, half = u & 1;
+            if (MASKED) {
+#pragma unroll
+                for (int j = 0; j < 8; j++) preg[i][j] = yreg[MASKED ? i : 0][j] > 0.f ? preg[i][j] : 0.f;
+            }
+            uint4 h, m, l;
+            split3_pack8(preg[i], h, m, l);
+            if (row < PR) {
+                uint4 *q = dst + half * PL + row;
+                q[0] = h; q[2 * PL] = m; q[4 * PL] = l;
+            }
+        }
+    };
+
+    // ---- filter slices: SL pieces of 1 KB, dealt to the wavefronts in turn
+    const int nblocks = p.tiles_n * (BN / 32);
+    const owt_i32x4 brs = make_rsrc(p.b, (unsigned)(p.ksteps * RS * nblocks) * 3072u);
+    const unsigned slice_lds = (unsigned)(size_t)(__attribute__((address_space(3))) uint4 *)slices;
+    const unsigned bpiece = (unsigned)(tn * (BN / 32)) * 3072u + (unsigned)wave * 1024u + (unsigned)lane * 16u;
+    constexpr int SQ = SL / NW, SREM = SL % NW;                      // pieces per wavefront: SQ, one more for the first SREM
+    auto fetch_slice = [&](int ch, int tap, int slot) __attribute__((always_inline)) {
+        const unsigned off = bpiece + (unsigned)((ch * RS + tap) * nblocks) * 3072u;
+        const unsigned dst = slice_lds + (unsigned)(slot * SL + wave) * 1024u;
+#pragma unroll
+        for (int i = 0; i < SQ; i++) buffer_load16_to_lds(brs, off + (unsigned)(i * NW) * 1024u, dst + (unsigned)(i * NW) * 1024u);
+        if (SREM && wave < SREM) buffer_load16_to_lds(brs, off + (unsigned)(SQ * NW) * 1024u, dst + (unsigned)(SQ * NW) * 1024u);
+    };
+    // All LDS accesses of this wavefront are done and its slice pieces have landed, except those of the `younger` slices
+    // (0 or 1) requested last; then the work-group meets.
+    auto meet = [&](bool younger) __attribute__((always_inline)) {
+        if (!younger) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else if (SREM && wave < SREM) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(SQ + 1) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(SQ) : "memory");
+    };
+
+    split_acc big[MB][2], small[MB][2];
+#pragma unroll
+    for (int i = 0; i < MB; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) big[i][j][r] = small[i][j][r] = 0.f;
+
+    if (tid < 6 * NPB) panel[tid * PL + PR] = make_uint4(0u, 0u, 0u, 0u);     // the row of zeros of every plane
+    const int nsteps = (ch_end - ch_beg) * RS;                                // one step per (chunk, tap); at least one
+    load_panel(ch_beg);
+    store_panel(panel);
+    fetch_slice(ch_beg, 0, 0);
+    if (nsteps > 1) fetch_slice(RS > 1 ? ch_beg : ch_beg + 1, RS > 1 ? 1 : 0, 1);
+
+    int ch = ch_beg, tap = 0, r = 0, s = 0, slot = 0, pbuf = 0;
+    int ch2 = ch_beg + 2 / RS, tap2 = 2 % RS;                                 // two steps ahead
+    for (int t = 0; t < nsteps; t++) {
+        meet(t + 1 < nsteps);
+        // the panel of the next chunk is requested before the slice of step t + 2, so that the next step's wait for its
+        // own slice covers it; it is held in registers until this chunk's last tap
+        if (tap == 0 && ch + 1 < ch_end) load_panel(ch + 1);
+        if (t + 2 < nsteps) fetch_slice(ch2, tap2, slot == 0 ? 2 : slot - 1); // the slot step t - 1 was done with
+        const uint4 *pp = panel + pbuf * PANEL + lh * PL, *bp = slices + (slot * SL + wn * 6) * 64 + lane;
+        const int shift = r * Wi + s;
+        split_frag a[MB][3], f[2][3];
+        const uint4 *row[MB];
+#pragma unroll
+        for (int bm = 0; bm < MB; bm++) row[bm] = pp + (((inside[bm] >> tap) & 1u) ? prow[bm] + shift : PR);
+        // all reads first, in the order the products need them; left alone, the compiler reuses fragment registers and
+        // waits for a read right behind its issue
+        constexpr int RO[3] = {0, 2, 1};
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+#pragma unroll
+            for (int bn = 0; bn < 2; bn++) f[bn][RO[q]] = __builtin_bit_cast(split_frag, bp[(bn * 3 + RO[q]) * 64]);
+#pragma unroll
+            for (int bm = 0; bm < MB; bm++) a[bm][RO[q]] = __builtin_bit_cast(split_frag, row[bm][2 * RO[q] * PL]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int bm = 0; bm < MB; bm++)
+#pragma unroll
+            for (int bn = 0; bn < 2; bn++)
+                big[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bm][0], f[bn][0], big[bm][bn], 0, 0, 0);
+        constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};       // the five small products
+#pragma unroll
+        for (int q = 0; q < 5; q++)
+#pragma unroll
+            for (int bm = 0; bm < MB; bm++)
+#pragma unroll
+                for (int bn = 0; bn < 2; bn++)
+                    small[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bm][PA[q]], f[bn][PB[q]], small[bm][bn], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (tap == RS - 1 && ch + 1 < ch_end) {
+            if (NPB == 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // everyone is done with the panel
+            else pbuf ^= 1;
+            store_panel(panel + pbuf * PANEL);
+        }
+        slot = slot == 2 ? 0 : slot + 1;
+        if (++tap2 == RS) { tap2 = 0; ch2++; }
+        tap++;
+        if (++s == S) { s = 0; r++; }
+        if (tap == RS) { tap = 0; r = 0; s = 0; ch++; }
+    }
+
+    // ---- epilogue: register r of lane (li, lh) of block (bm, bn) is pixel 8*(r/4) + 4*lh + r%4, column li.  Columns past
+    // the end and pixels past the last get an offset outside the descriptor: their stores are dropped.
+    const bool part = p.splits > 1;
+    const unsigned out_bytes = (unsigned)p.M * (unsigned)p.Ncols * 4u;
+    const __amdgpu_buffer_rsrc_t ors = owt_make_rsrc(part ? (const void *)(p.partial + (size_t)split * p.M * p.Ncols) : p.out, out_bytes);
+    const __amdgpu_buffer_rsrc_t xrs = owt_make_rsrc(BWD && p.xmask ? p.xmask : p.a, BWD && p.xmask ? out_bytes : 0u);
+    const bool xm = BWD && !part && p.xmask != nullptr;
+    auto rowstep = [&](int q) { return (unsigned)(8 * (q / 4) + q % 4) * (unsigned)p.Ncols * 4u; };   // an offset past OOB stays past it
+#pragma unroll
+    for (int bn = 0; bn < 2; bn++) {
+        const int n = n0 + wn * 64 + bn * 32 + li;
+        const float bias = (!BWD && !part && (p.flags & 1u) && n < p.Ncols) ? p.bias[n] : 0.f;
+        const bool relu = !BWD && !part && (p.flags & 2u);
+#pragma unroll
+        for (int bm = 0; bm < MB; bm++) {
+            const unsigned m = (unsigned)(m0 + (wm * MB + bm) * 32 + 4 * lh);
+            const unsigned base = n < p.Ncols ? (m * (unsigned)p.Ncols + (unsigned)n) * 4u : OOB;
+            float x[16];
+            if (xm) {
+#pragma unroll
+                for (int q = 0; q < 16; q++)
+                    x[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xrs, (int)(base + rowstep(q)), 0, 0));
+            }
+#pragma unroll
+            for (int q = 0; q < 16; q++) {
+                float v = big[bm][bn][q] + small[bm][bn][q] + bias;
+                if (relu) v = v > 0.f ? v : 0.f;
+                if (xm) v = x[q] > 0.f ? v : 0.f;
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ors, (int)(base + rowstep(q)), 0, 0);
+            }
+        }
+    }
+}
+
+}  // namespace owt

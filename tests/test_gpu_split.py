@@ -1,0 +1,141 @@
+"""The kernels that multiply fp32 operands on the bf16 matrix unit, each operand split into three bf16 values, against
+the CPU oracle at the sizes where they can go wrong.
+
+Elementwise bound.  With S = sum |a*b| of an output (the oracle on absolute values): a 16-deep matrix instruction adds
+exact products to an fp32 accumulator and rounds; whatever order it adds in, an error of 16 ulp of the largest partial
+sum, 16 * 2^-24 S, per instruction is far more than it can make, and in practice the instructions of a reduction of
+length L round independently.  The products left out are at most 2^-25 S in all.  Taken here: (L/16 + 16) * 2^-24 * S,
+one rounding of S per instruction plus one instruction's worth.
+2-norm bound.  Independent roundings of half an ulp give sqrt(L/16) * 0.29 * 2^-23 relative; 2^-23 * sqrt(L/16 + 4) is
+taken.  Leaving out any of the six products taken would show 2^-17 or more."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from gpu_util import ConvCase, empty, force, owt, to_dev, to_host, workspace  # noqa: E402
+
+
+def check(got, ref, size, L, what):
+    got, ref = got.astype(np.float64), ref.astype(np.float64)
+    worst = np.max(np.abs(got - ref) / ((L / 16 + 16) * 2.0 ** -24 * size + 1e-30))
+    norm = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print("  %s: %.3f of the elementwise bound, relative 2-norm error %.2e of %.2e" % (what, worst, norm, 2.0 ** -23 * np.sqrt(L / 16 + 4)))
+    sys.stdout.flush()
+    assert worst <= 1.0, what
+    assert norm <= 2.0 ** -23 * np.sqrt(L / 16 + 4), what
+
+
+def tensors(shape, seed, scale=1.0):
+    N, C, H, W, K, R, S = shape[:7]
+    g = np.random.default_rng(seed)
+    case = ConvCase(*shape[:7], 1, shape[7], "f32", True, False)
+    x = g.standard_normal(case.shape_x, dtype=np.float32) * np.float32(scale)
+    w = g.standard_normal(case.shape_w, dtype=np.float32) * np.float32(0.05)
+    b = g.standard_normal((K,), dtype=np.float32) * np.float32(scale)
+    dy = g.standard_normal(case.shape_y, dtype=np.float32)
+    y = g.standard_normal(case.shape_y, dtype=np.float32)
+    return x, w, b, dy, y
+
+
+# N, C, H, W, K, R, S, pad: one pixel tile less or more than full, channel counts with a short last chunk (a multiple of
+# four and not), ragged column tiles, one tap, one chunk of many taps, maps narrower than a 32-pixel block
+SHAPES = [(4, 40, 13, 13, 136, 3, 3, 1), (1, 16, 16, 16, 64, 1, 1, 0), (3, 64, 27, 27, 71, 5, 5, 2), (2, 37, 9, 14, 12, 3, 5, (1, 2)),
+          (1, 3, 5, 5, 4, 3, 3, 1), (5, 50, 6, 7, 66, 3, 3, 0)]
+
+
+@pytest.mark.parametrize("variant,split", [(0, 1), (1, 1), (2, 1), (3, 1), (4, 1), (0, 3), (1, 2), (2, 7), (3, 2), (4, 5)])
+def test_split_convolution_kernel(variant, split):
+    m = owt()
+    for i, shape in enumerate(SHAPES):
+        N, C, H, W, K, R, S, pad = shape
+        x, w, b, dy, y = tensors(shape, 900 + i)
+        for relu in (False, True):
+            case = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", True, relu)
+            with force(40 + variant, split):
+                plans = [m.owt_conv_plan_describe(case.desc, ps) for ps in (0, 1)]
+                print("case", shape, "relu", relu, plans)
+                sys.stdout.flush()
+                wide = variant == 4 and (R == 5 or H == 6)    # 128 pixels need more panel rows than it has
+                masked = variant == 4 and relu          # ... and it takes dy as it is
+                same = all(2 * p == r - 1 for p, r in zip((pad, pad) if isinstance(pad, int) else pad, (R, S)))
+                assert plans[0].startswith("xconv") or wide, plans[0]
+                assert plans[1].startswith("xconv") or wide or masked or not same, plans[1]
+                got = case.fwd(x, w, b)
+                dx = case.bwd_data(dy, y, w)
+            size = oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), 1, pad, False)
+            check(got, oracle.conv_fwd(x, w, b, 1, pad, relu), size, R * S * C, "y")
+            size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad, y=y if relu else None)
+            check(dx, oracle.conv_bwd_data(dy, w, (H, W), 1, pad, y=y if relu else None), size, R * S * K, "dx")
+
+
+def test_split_convolution_with_the_mask_of_the_layer_below():
+    m = owt()
+    N, C, H, W, K, R, S, pad = shape = (4, 40, 13, 13, 136, 3, 3, 1)
+    x, w, b, dy, y = tensors(shape, 930)
+    case = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", True, False)
+    ref = oracle.conv_bwd_data(dy, w, (H, W), 1, pad) * (x > 0)
+    size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad)
+    for split in (1, 3):
+        for variant in (0, 3, 4):
+            with force(40 + variant, split):
+                dx = empty(case.shape_x)
+                m.owt_conv_bwd_data_relu_in(case.desc, to_dev(dy), None, to_dev(w), to_dev(x), dx, case.ws(1))
+                torch.cuda.synchronize()
+            check(to_host(dx), ref, size, R * S * K, "dx masked by x > 0")
+
+
+def test_split_products_keep_infinities_nans_and_the_ends_of_the_range():
+    # an infinite, a NaN and two finite values beyond the largest bf16 among the inputs, tiny values elsewhere: every
+    # output is what fp32 products give -- the infinity of the right sign, NaN where a NaN enters, finite otherwise
+    m = owt()
+    N, C, H, W, K, R, S, pad = shape = (1, 24, 9, 9, 40, 3, 3, 1)
+    x, w, b, dy, y = tensors(shape, 940)
+    x[0, 1, 1, 3], x[0, 1, 6, 9], x[0, 6, 1, 20], x[0, 6, 6, 0] = np.inf, -np.inf, np.nan, np.float32(3.4e38)
+    x[0, 4, 4, :] *= np.float32(1e-30)
+    x[0, 8, 8, 5] = np.float32(-3.4028234e38)
+    w[:, :, :, 0] *= np.float32(0.01)
+    with np.errstate(all="ignore"):
+        want = np.zeros((H, W, K))
+        xp = np.zeros((H + 2, W + 2, C)); xp[1:-1, 1:-1] = x[0]
+        for r in range(R):
+            for s in range(S):
+                want += xp[r:r + H, s:s + W] @ w[:, r, s].astype(np.float64).T
+        want = want.astype(np.float32)
+    for variant in (0, 2, 3):
+        with force(40 + variant, 1):
+            got = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", False, False).fwd(x, w, None)[0]
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+        fine = np.isfinite(want)
+        assert fine.any() and np.max(np.abs(got[fine] - want[fine]) / (np.abs(want[fine]) + 1e-4 * np.median(np.abs(want[fine])))) < 1e-3
+
+
+def test_calls_with_the_scratch_of_the_fp32_kernels_still_run():
+    # the split filters need workspace; a call that brings none, or too little, is served as it always was
+    m = owt()
+    N, C, H, W, K, R, S, pad = shape = (2, 32, 13, 13, 64, 3, 3, 1)
+    x, w, b, dy, y = tensors(shape, 950)
+    case = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", True, True)
+    assert m.owt_conv_plan_describe(case.desc, 0).startswith("xconv")
+    ref = oracle.conv_fwd(x, w, b, 1, pad, True)
+    size = oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), 1, pad, False)
+    need = m.owt_conv_workspace_bytes(case.desc, 0)
+    outs = {}
+    for nbytes in (need, 4096, need):
+        out = empty(case.shape_y)
+        try:
+            m.owt_conv_fwd(case.desc, to_dev(x), to_dev(w), to_dev(b), out, workspace(nbytes))
+        except m.OwtError as e:
+            assert e.status == m.OWT_EWORKSPACE and nbytes == 4096      # the fp32 kernel's own split does not fit either
+            continue
+        torch.cuda.synchronize()
+        outs.setdefault(nbytes, []).append(to_host(out))
+        assert np.max(np.abs(outs[nbytes][-1] - ref)) <= 1e-4 * np.max(np.abs(ref))
+    check(outs[need][0], ref, size, R * S * C, "y")
+    assert np.array_equal(outs[need][0], outs[need][1])
