@@ -34,6 +34,7 @@ def _units():
                           ["-DOWT_INST_PASS=%d" % ps, "-DOWT_INST_VEC=%d" % vec]))
     for ps, pname in ((0, "fwd"), (1, "data")):
         units.append(("dconv16_%s.o" % pname, "dconv_bf16_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
+    units.append(("xfilter.o", "xfilter_inst.hip", []))
     units.append(("fcgemm.o", "fcgemm_inst.hip", []))
     units.append(("dfilter2.o", "dfilter2_inst.hip", []))
     units.append(("dfilter16.o", "dfilter_bf16_inst.hip", []))

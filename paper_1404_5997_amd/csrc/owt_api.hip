@@ -58,10 +58,10 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16 };
 
-// Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp) and keep re-laid-out operands in the workspace.
-static inline bool is_split_kind(int kind) { return kind == KIND_XCONV; }
+// Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp).
+static inline bool is_split_kind(int kind) { return kind == KIND_XCONV || kind == KIND_XFILTER; }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
 
@@ -579,6 +579,38 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if (force_split > 0) break;
         }
     }
+    // fp32 storage on the bf16 matrix unit with split operands: stride 1, one wavefront per (filters, channels, filter row);
+    // the bias gradient is summed by the filter row that meets every output row, which there is when P <= H
+    if (pass == OWT_PASS_BWD_FILTER && !g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
+        (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull) {
+        for (int v = 0; v < kNumXFilterVariants; v++) {
+            const XFilterVariant &xv = kXFilterVariants[v];
+            if ((force_tile >= 0 && force_tile != kXFilterFirstTile + v) || g.S != xv.S) continue;
+            const long tm = cdiv(g.K, 32 * xv.KB), ctl = cdiv(g.C, 32), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
+            for (long s0 : split_ladder(tiles, 1024)) {
+                long s = s0;
+                if (force_split > 0) s = force_split < steps ? force_split : steps;
+                else if (s > 1 && (steps / s < 4 || tiles * s > 4096)) break;
+                const long per = cdiv(steps, s), splits = cdiv(steps, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_XFILTER; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
+                l.tiles_m = (int)tm; l.tiles_n = (int)(ctl * g.R); l.ctiles = (int)ctl; l.taps = g.S; l.groups = g.R;
+                if (splits > 1) {
+                    l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                    l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
+                }
+                // a wavefront's clocks: matrix instructions (32 each) per position, the row starts, loading and storing the
+                // tile; whole rounds of 1024 wavefronts (one per SIMD).  0.6 = the other kernels' model against their clocks
+                const double clocks = per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0;
+                l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
+                if (splits > 1) l.cost += 14000.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
     if (pass == OWT_PASS_BWD_FILTER && !no_direct) {
         for (int v = 0; v < kNumDFilterVariants; v++) {
             int taps, groups;
@@ -769,8 +801,8 @@ static bool variants_forced()
 
 static std::map<PlanKey, Launch> g_modelled;   // the cost model's choice per geometry (untimed), so that a call plans once
 
-// ws_bytes: the scratch the call was given.  A plan whose operands are split into the workspace is passed over when it does
-// not fit, so a caller that sized its scratch for the kernels that multiply in fp32 is served by those.
+// ws_bytes: the scratch the call was given.  A plan of the kernels that split their operands is passed over when its
+// scratch does not fit, so a caller that sized its scratch for the kernels that multiply in fp32 is served by those.
 static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, bool want_db, bool use_cache, size_t ws_bytes = (size_t)-1)
 {
     const bool cached = use_cache && !variants_forced();
@@ -882,6 +914,9 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
         sfilter_geom(g, sg);
         sg.units_per_wg = l.steps_per_split;
         e = bf ? owt_launch_sfilter_bf16(p, sg, l.tiles_m, s) : owt_launch_sfilter_f32(p, sg, l.tiles_m, s);
+    } else if (l.kind == KIND_XFILTER) {
+        p.ctiles = l.ctiles;
+        e = owt_launch_xfilter(l.tile, p, s);
     } else if (l.kind == KIND_DFILTER16B) {
         p.Hp = g.H + 2 * g.ph; p.Wp = g.W + 2 * g.pw; p.taps = l.taps; p.groups = l.groups; p.ctiles = l.ctiles;
         p.dWp.set(p.Wp); p.dHpWp.set(p.Hp * p.Wp);
@@ -932,6 +967,10 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         return snprintf(buf, n, "xconv %s %s tile%dx%dx16 waves%dx%d panel%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.MB * v.WM, 64 * v.WN,
                         v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
     }
+    if (l.kind == KIND_XFILTER)
+        return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
+                        32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
+                        (long)l.tiles_m * l.tiles_n * l.splits * 64);
     if (l.kind == KIND_SCONV16)
         return snprintf(buf, n, "sconv16 %s %s rows%d grid%dx%d threads%ld", pn[pass], ds, kSConv16TP, l.tiles_m, l.tiles_n,
                         (long)l.tiles_m * l.tiles_n * kSConv16NT);

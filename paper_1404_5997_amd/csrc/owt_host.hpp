@@ -58,6 +58,14 @@ hipError_t owt_launch_xconv_fwd_vec1(int variant, int pr, const GemmParams &, vo
 hipError_t owt_launch_xconv_data_vec0(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 hipError_t owt_launch_xconv_data_vec1(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 
+// Stride-1 filter gradient for fp32 storage on the bf16 MFMA with split operands (xfilter_inst.hip): one wavefront per
+// work-group holds KB filter blocks of 32 x 32 channels x the S taps of a filter row.  The test hook numbers the
+// variants from 50.
+struct XFilterVariant { int KB, S; };
+constexpr int kNumXFilterVariants = 2, kXFilterFirstTile = 50;
+constexpr XFilterVariant kXFilterVariants[kNumXFilterVariants] = {{2, 3}, {1, 5}};
+hipError_t owt_launch_xfilter(int variant, const GemmParams &, hipStream_t);
+
 // Panel-resident stride-1 kernels on the bf16 MFMA (dconv_bf16_inst.hip, dconv_bf16p.hpp for the 512x64 tile).  The backward-data
 // launcher first writes the flipped, transposed filters to the front of `ws`.
 hipError_t owt_launch_dconv16_fwd(int tile, int pr, const GemmParams &, hipStream_t);

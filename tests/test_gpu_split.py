@@ -139,3 +139,74 @@ def test_calls_with_the_scratch_of_the_fp32_kernels_still_run():
         assert np.max(np.abs(outs[nbytes][-1] - ref)) <= 1e-4 * np.max(np.abs(ref))
     check(outs[need][0], ref, size, R * S * C, "y")
     assert np.array_equal(outs[need][0], outs[need][1])
+
+
+# N, C, H, W, K, R, S, pad: fewer than 16 images, one more than 16, three groups; ragged filters and channels; rows of one
+# and of two positions, filter rows that meet no output row (H = 1), filter height 1, an even number of taps left out by
+# the borders, no padding
+FILTER_SHAPES = {0: [(16, 40, 13, 13, 136, 3, 3, 1), (1, 5, 1, 1, 3, 3, 3, 1), (17, 33, 7, 2, 70, 3, 3, 1), (5, 8, 9, 6, 12, 1, 3, (0, 1)),
+                     (33, 16, 6, 5, 64, 5, 3, (2, 0))],
+                 1: [(18, 64, 27, 27, 72, 5, 5, 2), (1, 3, 2, 9, 4, 5, 5, 2), (3, 40, 11, 8, 33, 3, 5, (1, 2)), (16, 32, 6, 5, 32, 5, 5, 0)]}
+
+
+@pytest.mark.parametrize("variant,split", [(0, 1), (0, 2), (0, 7), (1, 1), (1, 3), (1, 16)])
+def test_split_filter_gradient_kernel(variant, split):
+    m = owt()
+    for i, shape in enumerate(FILTER_SHAPES[variant]):
+        N, C, H, W, K, R, S, pad = shape
+        x, w, b, dy, y = tensors(shape, 960 + i)
+        for relu, alpha, beta in ((False, 1.0, 0.0), (True, 0.5, -0.25)):
+            case = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", True, relu)
+            g = np.random.default_rng(970 + i)
+            dw0 = g.standard_normal(case.shape_w, dtype=np.float32) if beta else None
+            db0 = g.standard_normal((K,), dtype=np.float32) if beta else None
+            with force(50 + variant, split):
+                plan = m.owt_conv_plan_describe(case.desc, 2)
+                print("case", shape, "relu", relu, plan)
+                sys.stdout.flush()
+                assert plan.startswith("xfilter"), plan
+                dw, db = case.bwd_filter(x, dy, y if relu else None, alpha, beta, dw0, db0)
+                alone, none = case.bwd_filter(x, dy, y if relu else None, alpha, beta, dw0, db0, want_db=False)
+            assert none is None and np.array_equal(alone, dw)
+            mask = y if relu else None
+            ref, rdb = oracle.conv_bwd_filter(x, dy, (R, S), 1, pad, y=mask, alpha=alpha, beta=beta, dw=dw0, db=db0)
+            size, sdb = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), (R, S), 1, pad, y=mask, alpha=alpha, beta=abs(beta),
+                                               dw=None if dw0 is None else np.abs(dw0), db=None if db0 is None else np.abs(db0))
+            L = N * case.P * case.Q
+            check(dw, ref, size, L, "dw")
+            check(db, rdb, sdb, L, "db")
+
+
+def test_split_filter_gradient_keeps_infinities_nans_and_the_ends_of_the_range():
+    # as for the forward pass: the wavefronts whose sums are not finite start over with the careful split
+    m = owt()
+    N, C, H, W, K, R, S, pad = shape = (3, 40, 6, 7, 70, 3, 3, 1)
+    x, w, b, dy, y = tensors(shape, 980)
+    x[0, 1, 1, 3], x[1, 5, 6, 9], x[2, 3, 3, 20], x[0, 4, 2, 33] = np.inf, -np.inf, np.nan, np.float32(3.4e38)
+    dy[:, :, :, 5] = 0.0                 # inf * 0 is NaN in fp32, too
+    dy[1, 2, 2, 7], dy[0, 0, 0, 64] = np.inf, np.float32(-3.4028234e38)
+    dy[0, 3:6, 1:4, :] *= np.float32(1e-3)
+    with np.errstate(all="ignore"):
+        want = np.zeros((K, R, S, C))
+        xp = np.zeros((N, H + 2, W + 2, C)); xp[:, 1:-1, 1:-1] = x
+        for r in range(R):
+            for s in range(S):
+                lo = max(0, 1 - r), min(H, H + 1 - r)         # rows of taps outside the image count as zeros, whatever dz holds
+                z = dy[:, lo[0]:lo[1]].astype(np.float64)
+                cols = max(0, 1 - s), min(W, W + 1 - s)
+                want[:, r, s] = np.einsum("nhwk,nhwc->kc", z[:, :, cols[0]:cols[1]],
+                                          xp[:, lo[0] + r:lo[1] + r, cols[0] + s:cols[1] + s])
+        want = want.astype(np.float32)
+    for split in (1, 4):
+        with force(50, split):
+            got, _ = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", False, False).bwd_filter(x, dy, None, want_db=False)
+        # a column outside the image is multiplied as a zero, so there an infinite dz gives NaN: leave those filters' edge taps out
+        inner = np.ones((K, R, S, C), bool)
+        inner[[7], :, :, :] = False
+        assert np.array_equal(np.isnan(got)[inner], np.isnan(want)[inner])
+        assert np.array_equal(np.isposinf(got)[inner], np.isposinf(want)[inner])
+        assert np.array_equal(np.isneginf(got)[inner], np.isneginf(want)[inner])
+        fine = np.isfinite(want) & inner
+        scale = np.median(np.abs(want[fine]))
+        assert fine.any() and np.max(np.abs(got[fine].astype(np.float64) - want[fine]) / (np.abs(want[fine]) + 1e-4 * scale)) < 1e-3
+        assert not np.isfinite(got[7]).all()
