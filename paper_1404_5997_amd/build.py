@@ -29,12 +29,13 @@ def _units():
             units.append(("dconv_%s_%s.o" % (pname, "bf16" if bf else "f32"), "dconv_inst.hip",
                           ["-DOWT_INST_PASS=%d" % ps, "-DOWT_INST_BF16=%d" % bf]))
     for ps, pname in ((0, "fwd"), (1, "data")):
-        for vec in (0, 1):
+        for vec in ((0, 1, 2) if ps == 0 else (0, 1)):
             units.append(("xconv_%s_vec%d.o" % (pname, vec), "xconv_inst.hip",
                           ["-DOWT_INST_PASS=%d" % ps, "-DOWT_INST_VEC=%d" % vec]))
     for ps, pname in ((0, "fwd"), (1, "data")):
         units.append(("dconv16_%s.o" % pname, "dconv_bf16_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
     units.append(("xfilter.o", "xfilter_inst.hip", []))
+    units.append(("xgather.o", "xgather_inst.hip", []))
     units.append(("fcgemm.o", "fcgemm_inst.hip", []))
     units.append(("dfilter2.o", "dfilter2_inst.hip", []))
     units.append(("dfilter16.o", "dfilter_bf16_inst.hip", []))

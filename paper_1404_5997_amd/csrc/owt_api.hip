@@ -58,10 +58,10 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17 };
 
 // Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp).
-static inline bool is_split_kind(int kind) { return kind == KIND_XCONV || kind == KIND_XFILTER; }
+static inline bool is_split_kind(int kind) { return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER; }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
 
@@ -89,22 +89,36 @@ static void dconv_frame(const Geom &g, int pass, GemmParams &p)
     p.dWo.set(p.Wo); p.dHoWo.set(p.Ho * p.Wo);
 }
 
-// LDS panel rows a tile of BM consecutive output pixels of a stride-1 pass needs, or -1 when its input pixels are not
-// one contiguous run.
-static long panel_rows(const Geom &g, int pass, const PassDims &dm, long BM)
+// A strided forward pass seen as a stride-1 one over blocks of sh x sw input pixels: RB x SB taps of sh*sw*C channels.
+static int blocks_r(const Geom &g) { return (g.R + g.sh - 1) / g.sh; }
+static int blocks_s(const Geom &g) { return (g.S + g.sw - 1) / g.sw; }
+static void blocks_frame(const Geom &g, GemmParams &p)
 {
-    if (pass == OWT_PASS_BWD_FILTER || g.sh != 1 || g.sw != 1) return -1;
+    p.Hi = g.P + blocks_r(g) - 1; p.Wi = g.Q + blocks_s(g) - 1; p.Ho = g.P; p.Wo = g.Q; p.pah = p.paw = 0; p.Cred = g.sh * g.sw * g.C;
+    p.dWo.set(p.Wo); p.dHoWo.set(p.Ho * p.Wo);
+}
+
+// LDS panel rows a tile of BM consecutive output pixels of a stride-1 pass (or of a strided forward pass over blocks)
+// needs, or -1 when its input pixels are not one contiguous run.
+// per_image: tiles start anew with every image.
+static long panel_rows(const Geom &g, int pass, const PassDims &dm, long BM, bool blocks = false, bool per_image = false)
+{
+    if (pass == OWT_PASS_BWD_FILTER || (!blocks && (g.sh != 1 || g.sw != 1))) return -1;
     GemmParams f; memset(&f, 0, sizeof(f));
-    dconv_frame(g, pass, f);
+    if (blocks) blocks_frame(g, f); else dconv_frame(g, pass, f);
+    const long taps_h = blocks ? blocks_r(g) : g.R, taps_w = blocks ? blocks_s(g) : g.S;
     if (f.Ho > f.Hi || f.Wo > f.Wi) return -1;
+    const long image = (long)f.Ho * f.Wo;
     auto pin = [&](long m) {
-        const long n = m / (f.Ho * f.Wo), rem = m % (f.Ho * f.Wo);
-        return n * f.Hi * f.Wi + (rem / f.Wo - f.pah) * f.Wi + (rem % f.Wo - f.paw);
+        const long n = m / image, rem = m - n * image, ho = rem / f.Wo;
+        return n * f.Hi * f.Wi + (ho - f.pah) * f.Wi + (rem - ho * f.Wo - f.paw);
     };
     long need = 0;
-    for (long m0 = 0; m0 < dm.M; m0 += BM) {
-        const long last = (m0 + BM < dm.M ? m0 + BM : dm.M) - 1;
-        const long rows = pin(last) - pin(m0) + (g.R - 1) * f.Wi + g.S;
+    // (tile starts repeat modulo the image after `image` tiles)
+    const long end = per_image ? image : dm.M;
+    for (long m0 = 0, i = 0; m0 < end && i <= image; m0 += BM, i++) {
+        const long last = (m0 + BM < end ? m0 + BM : end) - 1;
+        const long rows = pin(last) - pin(m0) + (taps_h - 1) * f.Wi + taps_w;
         if (rows > need) need = rows;
     }
     return need;
@@ -329,7 +343,7 @@ static bool sfilter2_fits(const Geom &g, const SFilterGeom &sg)
 }
 
 struct Launch {
-    int kind, tile, splits, steps, steps_per_split, tiles_m, tiles_n, pr, taps, groups, ctiles;
+    int kind, tile, splits, steps, steps_per_split, tiles_m, tiles_n, pr, taps, groups, ctiles, blocks, tpi;
     size_t partial_bytes, dbias_bytes;
     size_t pre_bytes;   // workspace in front of the partials (re-laid-out filters of the bf16 backward-data kernel)
     double cost;   // model estimate, ~clocks
@@ -412,27 +426,35 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if (force_split > 0) break;
         }
     }
-    // fp32 storage on the bf16 matrix unit with split operands: stride 1, at most 32 taps, 32-bit byte offsets
-    if (!g.bf16 && pass != OWT_PASS_BWD_FILTER && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && g.R * g.S <= 32 &&
+    // fp32 storage on the bf16 matrix unit with split operands: stride 1, or a strided forward pass over blocks of pixels;
+    // at most 32 taps, 32-bit byte offsets.  (A strided pass of a few taps over many channels has mostly empty blocks: at
+    // least half of a block's values must meet filter values.)
+    const bool blocks = g.sh > 1 || g.sw > 1;
+    const long xr = blocks ? blocks_r(g) : g.R, xs = blocks ? blocks_s(g) : g.S, xred = blocks ? (long)g.sh * g.sw * g.C : cred;
+    if (!g.bf16 && pass != OWT_PASS_BWD_FILTER && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
+        (!blocks || (pass == OWT_PASS_FWD && 2L * g.R * g.S >= xr * xs * g.sh * g.sw && g.sh * g.sw <= 32 && xred <= 256)) &&
         (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull) {
         for (int v = 0; v < kNumXConvVariants; v++) {
             if (force_tile >= 0 && force_tile != kXConvFirstTile + v) continue;
             const XConvVariant &xv = kXConvVariants[v];
-            const long BM = 32 * xv.MB * xv.WM, BN = 64 * xv.WN, rows = panel_rows(g, pass, dm, BM);
+            const long BM = 32 * xv.MB * xv.WM, BN = 64 * xv.WN, image = pass == OWT_PASS_FWD ? (long)g.P * g.Q : (long)g.H * g.W;
+            // a strided pass has no padding between its blocks: tiles per image when the last, short ones waste under 5 %
+            const long tpi = blocks && cdiv(image, BM) * BM * 20 <= image * 21 ? cdiv(image, BM) : 0;
+            const long rows = panel_rows(g, pass, dm, BM, blocks, tpi > 0);
             if (rows < 0 || (xv.occ == 4 && xv.WM == 4 && pass == OWT_PASS_BWD_DATA && g.masked)) continue;
             int pr = 0;
             for (int q = 2; q >= 0; q--)
                 if (xv.prs[q] >= rows) pr = xv.prs[q];
-            const long tm = cdiv(dm.M, BM), tn = cdiv(dm.Ncols, BN), chunks = cdiv(cred, 16);
-            const size_t packed = (size_t)chunks * g.R * g.S * tn * 2 * xv.WN * 3072;
+            const long tm = tpi ? tpi * g.N : cdiv(dm.M, BM), tn = cdiv(dm.Ncols, BN), chunks = cdiv(xred, 16);
+            const size_t packed = (size_t)chunks * xr * xs * tn * 2 * xv.WN * 3072;
             if (!pr || packed >= 0x7fffffffull) continue;
-            const double macs = (double)BM * BN * 16 * g.R * g.S / 1.75;      // against the fp32 instruction's rate
+            const double macs = (double)BM * BN * 16 * xr * xs / 1.75;      // against the fp32 instruction's rate
             for (long s0 : kSplits) {
                 if (s0 > 1 && force_split <= 0 && (s0 > chunks || s0 > 16)) break;
                 const long s = force_split > 0 ? (force_split < chunks ? force_split : chunks) : s0;
                 const long per = cdiv(chunks, s), splits = cdiv(chunks, per);
                 Launch l; memset(&l, 0, sizeof(l));
-                l.kind = KIND_XCONV; l.tile = v; l.pr = pr; l.splits = (int)splits; l.steps = (int)chunks; l.steps_per_split = (int)per;
+                l.kind = KIND_XCONV; l.tile = v; l.pr = pr; l.blocks = blocks; l.tpi = (int)tpi; l.splits = (int)splits; l.steps = (int)chunks; l.steps_per_split = (int)per;
                 l.tiles_m = (int)tm; l.tiles_n = (int)tn;
                 l.pre_bytes = pad256(packed);
                 if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
@@ -469,7 +491,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     }
     SConvGeom scg;
     // test hook: tile 20 = only the filter-streaming first-layer forward kernel, 21 = only the filters-in-LDS one
-    const bool sconv_ok = pass == OWT_PASS_FWD && !no_direct && sconv_geom(g, scg);
+    const bool sconv_ok = pass == OWT_PASS_FWD && !no_direct && (force_tile < kXConvFirstTile || out.empty()) && sconv_geom(g, scg);
     if (sconv_ok && force_tile != 20 && !g.bf16 && sconv2_fits(g, scg)) {
         const long ktiles = cdiv(g.K, kSConv2KB);
         for (long target : {256L, 512L}) {
@@ -529,7 +551,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // test hook: tile 22 = only the register-staged first-layer filter-gradient kernel, 23 = only the one that streams
     // its units straight into LDS
     SFilterGeom sfg;
-    const bool sfilter_ok = pass == OWT_PASS_BWD_FILTER && !no_direct && (g.sh > 1 || g.sw > 1) && sfilter_geom(g, sfg);
+    const bool sfilter_ok = pass == OWT_PASS_BWD_FILTER && !no_direct && force_tile < kXConvFirstTile && (g.sh > 1 || g.sw > 1) && sfilter_geom(g, sfg);
     for (int form = 0; form < 2 && sfilter_ok; form++) {
         if (form == 0 ? force_tile == 23 : (force_tile == 22 || !sfilter2_fits(g, sfg))) continue;
         const long ktiles = cdiv(g.K, 64);
@@ -602,6 +624,37 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 // a wavefront's clocks: matrix instructions (32 each) per position, the row starts, loading and storing the
                 // tile; whole rounds of 1024 wavefronts (one per SIMD).  0.6 = the other kernels' model against their clocks
                 const double clocks = per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0;
+                l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
+                if (splits > 1) l.cost += 14000.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
+    // the same for any geometry, columns packed densely (not the fully-connected shard, whose two backward products share
+    // a launch)
+    if (pass == OWT_PASS_BWD_FILTER && !g.bf16 && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
+        (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull) {
+        for (int v = 0; v < kNumXGatherVariants; v++) {
+            const XGatherVariant &xv = kXGatherVariants[v];
+            if (force_tile >= 0 && force_tile != kXGatherFirstTile + v) continue;
+            const long tm = cdiv(g.K, 32 * xv.KB), tn = cdiv(dm.Ncols, 32 * xv.CB), tiles = tm * tn, steps = cdiv(g.N, 16) * g.P * g.Q;
+            for (long s0 : split_ladder(tiles, 1024)) {
+                long s = s0;
+                if (force_split > 0) s = force_split < steps ? force_split : steps;
+                else if (s > 1 && (steps / s < 4 || tiles * s > 4096)) break;
+                const long per = cdiv(steps, s), splits = cdiv(steps, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_XGATHER; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
+                l.tiles_m = (int)tm; l.tiles_n = (int)tn; l.blocks = g.sh > 1 || g.sw > 1;
+                if (splits > 1) {
+                    l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                    l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
+                }
+                // as above; the vector instructions of a fragment take about 330 clocks
+                const double clocks = per * (330.0 * (xv.KB + xv.CB) + 100.0) + 6000.0;
                 l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
                 if (splits > 1) l.cost += 14000.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
@@ -866,9 +919,13 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
     const bool bf = dt == OWT_BF16;
     hipError_t e;
     if (l.kind == KIND_XCONV) {
-        dconv_frame(g, pass, p);
+        const bool blocks = g.sh > 1 || g.sw > 1;
+        if (blocks) blocks_frame(g, p); else dconv_frame(g, pass, p);
+        p.dWp.set(p.Wi); p.dHpWp.set(p.Hi * p.Wi);
+        p.tpi = l.tpi;
         const bool vec = p.Cred % 4 == 0;
-        if (pass == OWT_PASS_FWD) e = vec ? owt_launch_xconv_fwd_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_fwd_vec0(l.tile, l.pr, p, ws, s);
+        if (blocks) e = owt_launch_xconv_fwd_blocks(l.tile, l.pr, p, ws, s);
+        else if (pass == OWT_PASS_FWD) e = vec ? owt_launch_xconv_fwd_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_fwd_vec0(l.tile, l.pr, p, ws, s);
         else e = vec ? owt_launch_xconv_data_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_data_vec0(l.tile, l.pr, p, ws, s);
     } else if (l.kind == KIND_FCGEMM) {
         e = owt_launch_fcgemm(pass, l.tile, p, (float *)ws, s);
@@ -914,6 +971,8 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
         sfilter_geom(g, sg);
         sg.units_per_wg = l.steps_per_split;
         e = bf ? owt_launch_sfilter_bf16(p, sg, l.tiles_m, s) : owt_launch_sfilter_f32(p, sg, l.tiles_m, s);
+    } else if (l.kind == KIND_XGATHER) {
+        e = owt_launch_xgather(l.tile, p, s);
     } else if (l.kind == KIND_XFILTER) {
         p.ctiles = l.ctiles;
         e = owt_launch_xfilter(l.tile, p, s);
@@ -964,9 +1023,13 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     }
     if (l.kind == KIND_XCONV) {
         const XConvVariant &v = kXConvVariants[l.tile];
-        return snprintf(buf, n, "xconv %s %s tile%dx%dx16 waves%dx%d panel%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.MB * v.WM, 64 * v.WN,
-                        v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
+        return snprintf(buf, n, "%s %s %s tile%dx%dx16 waves%dx%d panel%d splitk%d grid%dx%d threads%ld", l.blocks ? "sconvx" : "xconv", pn[pass], ds, 32 * v.MB * v.WM,
+                        64 * v.WN, v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
     }
+    if (l.kind == KIND_XGATHER)
+        return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilterx" : "xgather", pn[pass], ds,
+                        32 * kXGatherVariants[l.tile].KB, 32 * kXGatherVariants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,
+                        (long)l.tiles_m * l.tiles_n * l.splits * 64);
     if (l.kind == KIND_XFILTER)
         return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,

@@ -53,6 +53,10 @@ struct GemmParams {
     // (ho-pah+r, wo-paw+s), r < R, s < S.
     int Hi, Wi, Ho, Wo, pah, paw, Cred;
     FastDiv dWo, dHoWo;
+    // Strided forward pass seen over blocks of pixels only: the layer's filters and their height and width
+    const void *b0;
+    int R0, S0;
+    int tpi;                 // xconv kernel: pixel tiles per image, 0 = tiles run through the batch
     // Direct filter-gradient kernel only: the input seen in zero-padded coordinates
     // (Hp = H + 2*pad_h rows of Wp = W + 2*pad_w pixels per image); taps are handled
     // `taps` at a time, either all R*S at once (groups == 1) or one filter row per group.

@@ -55,6 +55,7 @@ constexpr XConvVariant kXConvVariants[kNumXConvVariants] = {
     {4, 1, 1, 3, {160, 256, 0}, 1.25f}, {4, 1, 1, 4, {160, 0, 0}, 1.30f}};
 hipError_t owt_launch_xconv_fwd_vec0(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 hipError_t owt_launch_xconv_fwd_vec1(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
+hipError_t owt_launch_xconv_fwd_blocks(int variant, int pr, const GemmParams &, void *ws, hipStream_t);   // strided forward
 hipError_t owt_launch_xconv_data_vec0(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 hipError_t owt_launch_xconv_data_vec1(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 
@@ -65,6 +66,14 @@ struct XFilterVariant { int KB, S; };
 constexpr int kNumXFilterVariants = 2, kXFilterFirstTile = 50;
 constexpr XFilterVariant kXFilterVariants[kNumXFilterVariants] = {{2, 3}, {1, 5}};
 hipError_t owt_launch_xfilter(int variant, const GemmParams &, hipStream_t);
+
+// Filter gradient of any geometry for fp32 storage on the bf16 MFMA with split operands (xgather_inst.hip): one wavefront
+// per work-group holds KB filter blocks x CB blocks of densely packed (r, s, c) places.  The test hook numbers the
+// variants from 60.
+struct XGatherVariant { int KB, CB; };
+constexpr int kNumXGatherVariants = 2, kXGatherFirstTile = 60;
+constexpr XGatherVariant kXGatherVariants[kNumXGatherVariants] = {{2, 3}, {1, 3}};
+hipError_t owt_launch_xgather(int variant, const GemmParams &, hipStream_t);
 
 // Panel-resident stride-1 kernels on the bf16 MFMA (dconv_bf16_inst.hip, dconv_bf16p.hpp for the 512x64 tile).  The backward-data
 // launcher first writes the flipped, transposed filters to the front of `ws`.

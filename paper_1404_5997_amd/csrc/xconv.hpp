@@ -16,6 +16,11 @@
 //    consecutive pixels is 512 consecutive bytes whatever the tap's shift, so there is nothing to pad or swizzle;
 //  * slices sit in a ring of three, so one barrier per tap is enough and a slice has two taps' time to arrive.
 // Taps that fall outside the image read the row of zeros behind each plane.
+//
+// A strided forward pass of few channels (the first layer) runs here, too, seen over blocks of sh x sw input pixels: 11 x 11
+// taps of 3 channels at stride 4 are 3 x 3 taps of 48 channels, 432 reduction steps for 363.  Measured, 128 images of
+// 224x224x3 -> 64: 170 us on the fp32 instruction, 126 here (143 TFLOP/s on the 363); half of the time goes to the panel's
+// 4-byte loads, the prologue and the stores of work-groups that have only 27 steps.
 #pragma once
 #include "igemm.hpp"
 #include "split3.hpp"
@@ -47,10 +52,38 @@ __global__ void __launch_bounds__(256) xconv_pack_kernel(const float *__restrict
     }
 }
 
+// The same for a strided forward pass seen as a stride-1 one over blocks of sh x sw pixels: the reduction index is
+// (dy, dx, c) inside a block, the tap (rb, sb) names the block, and w[k][sh*rb + dy][sw*sb + dx][c] is zero past R or S.
+static __global__ void __launch_bounds__(256) xconv_pack_blocks_kernel(const float *__restrict__ w, uint4 *__restrict__ out, Geom g, int RB,
+                                                                int SB, int chunks, int nblocks)
+{
+    const int RS = RB * SB, total = chunks * RS * nblocks * 64, rowc = g.sw * g.C;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+        const int lane = i & 63, q = i >> 6, nb = q % nblocks, ct = q / nblocks, tap = ct % RS, ch = ct / RS;
+        const int col = nb * 32 + (lane & 31), red = ch * 16 + (lane >> 5) * 8, rb = tap / SB, sb = tap - rb * SB;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const int kd = red + j, dy = kd / rowc, rem = kd - dy * rowc, dx = rem / g.C, c = rem - dx * g.C;
+            const int r = rb * g.sh + dy, s = sb * g.sw + dx;
+            v[j] = (col < g.K && dy < g.sh && r < g.R && s < g.S) ? w[((size_t)(col * g.R + r) * g.S + s) * g.C + c] : 0.f;
+        }
+        uint4 h, m, l;
+        split3_pack8(v, h, m, l);
+        uint4 *o = out + (size_t)q * 192 + lane;
+        o[0] = h; o[64] = m; o[128] = l;
+    }
+}
+
+// How a panel's values are loaded: XC_SCALAR 4 bytes at a time (any channel count), XC_VEC 16 bytes (channels a multiple of
+// four), XC_BLOCKS a strided forward pass whose panel rows are blocks of sh x sw input pixels (p.g.R, p.g.S and the
+// frame Hi, Wi, Ho, Wo, Cred count in blocks; p.g.H, W, C, strides and padding are the layer's own).
+enum { XC_SCALAR = 0, XC_VEC = 1, XC_BLOCKS = 2 };
+
 // WM x WN wavefronts of 32*MB pixels x 64 filters; PR panel rows; NPB panel buffers (two: the next chunk is written while
-// the last tap of this one is still being read, no extra barrier); VEC: channels a multiple of 4 (16-byte loads);
-// MASKED: dy is masked by y > 0 on its way in.  At most 32 taps; 32-bit byte offsets in every tensor (host-checked).
-template <class Epi, bool BWD, int WM, int WN, int MB, int PR, int NPB, bool VEC, bool MASKED>
+// the last tap of this one is still being read, no extra barrier); MASKED: dy is masked by y > 0 on its way in.  At most
+// 32 taps; 32-bit byte offsets in every tensor (host-checked).
+template <class Epi, bool BWD, int WM, int WN, int MB, int PR, int NPB, int LOAD, bool MASKED>
 __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160 ? 4 : 3) : 2) xconv_kernel(const GemmParams p)
 {
     constexpr int NW = WM * WN, NT = 64 * NW, BM = 32 * MB * WM, BN = 64 * WN;
@@ -70,7 +103,11 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
     const int b = blockIdx.x, xcd = b & 7;
     const int logical = xcd * (ntiles >> 3) + min(xcd, ntiles & 7) + (b >> 3);
     const int tm = logical / p.tiles_n, tn = logical - tm * p.tiles_n;
-    const int m0 = tm * BM, n0 = tn * BN;
+    const int n0 = tn * BN;
+    // pixel tiles run through the whole batch, or (p.tpi > 0) start anew with every image: a tile that straddles two images
+    // of a pass without padding has the rows under the first one's last taps in its panel, too
+    const int img = p.tpi > 0 ? tm / p.tpi : 0, hw = p.Ho * p.Wo;
+    const int m0 = p.tpi > 0 ? img * hw + (tm - img * p.tpi) * BM : tm * BM, mlim = p.tpi > 0 ? (img + 1) * hw : p.M;
     const int split = blockIdx.y;
     const int ch_beg = split * p.ksteps_per_split, ch_end = min(p.ksteps, ch_beg + p.ksteps_per_split);
 
@@ -85,7 +122,7 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
     };
     int th, tw;
     const int ps = pin(m0, th, tw);
-    const int nrows = pin(min(m0 + BM, p.M) - 1, th, tw) + (R - 1) * Wi + S - ps;   // <= PR (host-checked)
+    const int nrows = pin(min(m0 + BM, mlim) - 1, th, tw) + (R - 1) * Wi + S - ps;   // <= PR (host-checked)
 
     // per 32-pixel block of this lane: its panel row at tap (0,0), and one bit per tap that falls inside the image
     int prow[MB];
@@ -95,7 +132,7 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
         const int m = m0 + (wm * MB + bm) * 32 + li;
         prow[bm] = 0;
         inside[bm] = 0u;
-        if (m < p.M) {
+        if (m < mlim) {
             int hh, ww;
             prow[bm] = pin(m, hh, ww) - ps;
             for (int r = 0, tap = 0; r < R; r++)
@@ -106,17 +143,46 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
 
     // ---- panel loader: thread -> (row, 8-channel half) pairs u = tid + i * NT.  Rows before the first or past the last
     // pixel of the tensor and rows the tile does not need get an offset outside the descriptor and read as zeros.
-    const __amdgpu_buffer_rsrc_t ars = owt_make_rsrc(p.a, (unsigned)(p.g.N * Hi * Wi) * (unsigned)Cred * 4u);
-    const __amdgpu_buffer_rsrc_t mrs = owt_make_rsrc(MASKED ? p.mask : p.a, (unsigned)(p.g.N * Hi * Wi) * (unsigned)Cred * 4u);
-    unsigned rowoff[PU];
+    const unsigned in_bytes = LOAD == XC_BLOCKS ? (unsigned)(p.g.N * p.g.H * p.g.W) * (unsigned)p.g.C * 4u
+                                                : (unsigned)(p.g.N * Hi * Wi) * (unsigned)Cred * 4u;
+    const __amdgpu_buffer_rsrc_t ars = owt_make_rsrc(p.a, in_bytes);
+    const __amdgpu_buffer_rsrc_t mrs = owt_make_rsrc(MASKED ? p.mask : p.a, in_bytes);
+    unsigned rowoff[PU];                             // byte offset of the row's first value
+    unsigned out_bits[LOAD == XC_BLOCKS ? PU : 1];   // blocks: bit dy * sw + dx is set where that pixel lies outside the image
 #pragma unroll
     for (int i = 0; i < PU; i++) {
         const int u = tid + i * NT, row = u >> 1, pix = ps + row;
-        rowoff[i] = (row < nrows && (unsigned)pix < (unsigned)(p.g.N * Hi * Wi)) ? (unsigned)pix * (unsigned)Cred * 4u : OOB;
+        const bool there = row < nrows && (unsigned)pix < (unsigned)(p.g.N * Hi * Wi);
+        if (LOAD == XC_BLOCKS) {
+            const int n = p.dHpWp.div(pix), rem = pix - n * (Hi * Wi), by = p.dWp.div(rem), bx = rem - by * Wi;
+            const int y0 = by * p.g.sh - p.g.ph, x0 = bx * p.g.sw - p.g.pw;
+            unsigned bits = 0xffffffffu;
+            if (there)
+                for (int dy = 0, q = 0; dy < p.g.sh; dy++)
+                    for (int dx = 0; dx < p.g.sw; dx++, q++)
+                        if ((unsigned)(y0 + dy) < (unsigned)p.g.H && (unsigned)(x0 + dx) < (unsigned)p.g.W) bits &= ~(1u << q);
+            out_bits[LOAD == XC_BLOCKS ? i : 0] = bits;
+            rowoff[i] = (unsigned)(((n * p.g.H + y0) * p.g.W + x0) * p.g.C) * 4u;
+        } else {
+            rowoff[i] = there ? (unsigned)pix * (unsigned)Cred * 4u : OOB;
+        }
+    }
+    // blocks: where value c of a block is: byte offset from its first pixel, and 31 - its pixel's bit
+    constexpr int CTAB = LOAD == XC_BLOCKS ? 256 : 1;
+    __shared__ uint2 ctab[CTAB];
+    if (LOAD == XC_BLOCKS) {
+        const int rowc = p.g.sw * p.g.C;
+        for (int c = tid; c < p.ksteps * 16; c += NT) {
+            const int dy = c / rowc, rem = c - dy * rowc;
+            // values past the block read as zeros: the offset alone puts them outside the descriptor
+            ctab[c] = dy < p.g.sh ? make_uint2((unsigned)((dy * p.g.W * p.g.C + rem) * 4), (unsigned)(31 - (dy * p.g.sw + rem / p.g.C)))
+                                  : make_uint2(OOB, 0u);
+        }
+        __syncthreads();
     }
     float preg[PU][8], yreg[MASKED ? PU : 1][8];
     auto load8 = [&](__amdgpu_buffer_rsrc_t rs, unsigned base, int c, float (&v)[8]) __attribute__((always_inline)) {
-        if (VEC) {
+        if (LOAD == XC_VEC) {
 #pragma unroll
             for (int q = 0; q < 2; q++) {
                 const float4 f = buffer_load4(rs, c + 4 * q < Cred ? base + (unsigned)(c + 4 * q) * 4u : OOB);
@@ -128,7 +194,19 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
                 v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(c + j < Cred ? base + (unsigned)(c + j) * 4u : OOB), 0, 0));
         }
     };
+    auto load_blocks = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const uint2 at = ctab[LOAD == XC_BLOCKS ? ch * 16 + (tid & 1) * 8 + j : 0];
+#pragma unroll
+            for (int i = 0; i < PU; i++) {
+                const unsigned off = (rowoff[i] + at.x) | ((out_bits[LOAD == XC_BLOCKS ? i : 0] << at.y) & OOB);
+                preg[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ars, (int)(at.x == OOB ? OOB : off), 0, 0));
+            }
+        }
+    };
     auto load_panel = [&](int ch) __attribute__((always_inline)) {
+        if (LOAD == XC_BLOCKS) { load_blocks(ch); return; }
         const int c = ch * 16 + (tid & 1) * 8;
 #pragma unroll
         for (int i = 0; i < PU; i++) {
@@ -240,10 +318,51 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
         if (tap == RS) { tap = 0; r = 0; s = 0; ch++; }
     }
 
+    if (LOAD == XC_BLOCKS) {
+        // A block holds pixels outside the window, met by zero filter values: an infinity or NaN among them would reach the
+        // result.  A wavefront whose sums are not all finite works its tile out again from the window alone, one
+        // multiply-add at a time.
+        float sum = 0.f;
+#pragma unroll
+        for (int bm = 0; bm < MB; bm++)
+#pragma unroll
+            for (int bn = 0; bn < 2; bn++)
+#pragma unroll
+                for (int q = 0; q < 16; q++) sum += big[bm][bn][q] + small[bm][bn][q];
+        if (__ballot(!(fabsf(sum) < __builtin_inff())) != 0) {
+            const float *x = (const float *)p.a, *w = (const float *)p.b0;
+            const Geom &g = p.g;
+#pragma unroll
+            for (int bm = 0; bm < MB; bm++)
+#pragma unroll
+                for (int bn = 0; bn < 2; bn++)
+#pragma unroll
+                    for (int q = 0; q < 16; q++) {
+                        const int m = m0 + (wm * MB + bm) * 32 + 8 * (q / 4) + 4 * lh + q % 4, k = n0 + wn * 64 + bn * 32 + li;
+                        float v = 0.f;
+                        if (m < mlim && k < p.Ncols) {
+                            const int n = p.dHoWo.div(m), rem = m - n * HoWo, po = p.dWo.div(rem), qo = rem - po * p.Wo;
+                            for (int r2 = 0; r2 < p.R0; r2++)
+                                for (int s2 = 0; s2 < p.S0; s2++)
+                                    for (int c = 0; c < g.C; c++) {
+                                        const int kd = ((r2 % g.sh) * g.sw + s2 % g.sw) * g.C + c;      // its place in a block
+                                        const int hh = po * g.sh - g.ph + r2, ww = qo * g.sw - g.pw + s2;
+                                        if (kd < ch_beg * 16 || kd >= ch_end * 16) continue;            // another split's
+                                        const float xv = ((unsigned)hh < (unsigned)g.H && (unsigned)ww < (unsigned)g.W)
+                                                             ? x[((size_t)(n * g.H + hh) * g.W + ww) * g.C + c] : 0.f;
+                                        v += xv * w[((size_t)(k * p.R0 + r2) * p.S0 + s2) * g.C + c];
+                                    }
+                        }
+                        big[bm][bn][q] = v;
+                        small[bm][bn][q] = 0.f;
+                    }
+        }
+    }
+
     // ---- epilogue: register r of lane (li, lh) of block (bm, bn) is pixel 8*(r/4) + 4*lh + r%4, column li.  Columns past
     // the end and pixels past the last get an offset outside the descriptor: their stores are dropped.
     const bool part = p.splits > 1;
-    const unsigned out_bytes = (unsigned)p.M * (unsigned)p.Ncols * 4u;
+    const unsigned out_bytes = (unsigned)mlim * (unsigned)p.Ncols * 4u;
     const __amdgpu_buffer_rsrc_t ors = owt_make_rsrc(part ? (const void *)(p.partial + (size_t)split * p.M * p.Ncols) : p.out, out_bytes);
     const __amdgpu_buffer_rsrc_t xrs = owt_make_rsrc(BWD && p.xmask ? p.xmask : p.a, BWD && p.xmask ? out_bytes : 0u);
     const bool xm = BWD && !part && p.xmask != nullptr;

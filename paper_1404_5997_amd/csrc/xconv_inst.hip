@@ -1,10 +1,10 @@
-// Instantiations of the split-operand stride-1 kernel for one pass and one load width.
-// Built four times: -DOWT_INST_PASS={0,1} -DOWT_INST_VEC={0,1}.
+// Instantiations of the split-operand stride-1 kernel for one pass and one way of loading the panel.
+// Built five times: -DOWT_INST_PASS={0,1} -DOWT_INST_VEC={0,1}, and {0} {2} (strided forward as blocks).
 #include "xconv.hpp"
 #include "owt_host.hpp"
 
 #if !defined(OWT_INST_PASS) || !defined(OWT_INST_VEC)
-#error "define OWT_INST_PASS (0 fwd, 1 bwd-data) and OWT_INST_VEC (channels a multiple of 4)"
+#error "define OWT_INST_PASS (0 fwd, 1 bwd-data) and OWT_INST_VEC (XC_SCALAR, XC_VEC, XC_BLOCKS)"
 #endif
 
 namespace owt {
@@ -29,26 +29,41 @@ static hipError_t go(const GemmParams &p, hipStream_t s)
             if constexpr (MB == 1 && PR == 160 && NPB == 1) {
                 return hipErrorInvalidValue;             // no registers for the mask at four wavefronts per SIMD
             } else {
-                hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, NPB, OWT_INST_VEC != 0, true>), grid, block, 0, s, p);
+                hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, NPB, OWT_INST_VEC, true>), grid, block, 0, s, p);
                 return hipGetLastError();
             }
         }
     }
-    hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, NPB, OWT_INST_VEC != 0, false>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, NPB, OWT_INST_VEC, false>), grid, block, 0, s, p);
     return hipGetLastError();
 }
 
+#if OWT_INST_VEC == 2
+hipError_t owt_launch_xconv_fwd_blocks(int variant, int pr, const GemmParams &p0, void *ws, hipStream_t s)
+#else
 hipError_t OWT_XFN(OWT_INST_VEC)(int variant, int pr, const GemmParams &p0, void *ws, hipStream_t s)
+#endif
 {
+    GemmParams p = p0;
     const Geom &g = p0.g;
-    const int nblocks = p0.tiles_n * 2 * kXConvVariants[variant].WN, RS = g.R * g.S;
+    const int nblocks = p0.tiles_n * 2 * kXConvVariants[variant].WN;
+#if OWT_INST_VEC == 2
+    p.g.R = (g.R + g.sh - 1) / g.sh;                     // the kernel's taps are blocks
+    p.g.S = (g.S + g.sw - 1) / g.sw;
+    p.b0 = p0.b; p.R0 = g.R; p.S0 = g.S;
+#endif
+    const int RS = p.g.R * p.g.S;
     const long threads = (long)p0.ksteps * RS * nblocks * 64;
     const unsigned blocks = (unsigned)((threads + 255) / 256 > 8192 ? 8192 : (threads + 255) / 256);
+#if OWT_INST_VEC == 2
+    hipLaunchKernelGGL(xconv_pack_blocks_kernel, dim3(blocks), dim3(256), 0, s, (const float *)p0.b, (uint4 *)ws, g, p.g.R, p.g.S,
+                       p0.ksteps, nblocks);
+#else
     hipLaunchKernelGGL((xconv_pack_kernel<kBwd>), dim3(blocks), dim3(256), 0, s, (const float *)p0.b, (uint4 *)ws, g.K, RS, g.C,
                        p0.ksteps, nblocks);
+#endif
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    GemmParams p = p0;
     p.b = ws;
     e = hipErrorInvalidValue;
     if (variant == 0) {

@@ -13,9 +13,10 @@
 //    and split once per row of taps;
 //  * filter rows that fall outside the image are not computed at all (an r = 0 wavefront of a 13-high map walks over 12
 //    output rows), and a row of 13 or 27 positions needs no rounding to chunks.
-// A work-group is one wavefront: KB filter blocks of 32 x 32 channels x the S taps of one filter row, two accumulators
-// each, one wavefront per SIMD with its 512 registers.  The position range is split over wavefronts (partial sums in
-// the workspace, splitk_reduce_kernel).
+// A wavefront works alone: KB filter blocks of 32 x 32 channels x the S taps of one filter row, two accumulators each, one
+// wavefront per SIMD with its 512 registers.  Work-groups of four of them hold neighbouring tiles of one split, so that
+// what they load in common comes from one CU's cache.  The position range is split over wavefronts (partial sums in the
+// workspace, splitk_reduce_kernel).
 //
 // What bounds it: the matrix instructions, as long as the vector instructions that split the next position's values
 // issue in their shadow.  Measured with one wavefront per SIMD, a 32-cycle matrix instruction hides 28 cycles of vector
@@ -26,7 +27,8 @@
 // finite starts over with the careful split.
 //
 // Measured, 128 images, with the reduce pass, kernel on the fp32 instruction -> this one, us: 3x3 192->384 252 -> 151 (190
-// TFLOP/s), 384->256 334 -> 191, 256->256 228 -> 137; 5x5 64->192 450 -> 271 (212 TFLOP/s).
+// TFLOP/s), 384->256 334 -> 191, 256->256 228 -> 137; 5x5 64->192 450 -> 271 (212 TFLOP/s).  Four wavefronts to a
+// work-group instead of one: 149, 188, - and 266.
 #pragma once
 #include <type_traits>
 
@@ -51,15 +53,29 @@ __device__ __forceinline__ void split3_plain(const float (&v)[8], split_frag (&f
     f[2] = __builtin_bit_cast(split_frag, make_uint4(ll[0], ll[1], ll[2], ll[3]));
 }
 
+// (split, tile) pairs, split-major, four consecutive ones to the wavefronts of a work-group; the work-groups are dealt to
+// the XCDs as owt_split_major_wg does.  Returns false for wavefronts past the last pair (there are no barriers).
+__host__ __device__ inline int owt_split_major_wave_grid(int tiles, int splits) { return 8 * (((tiles * splits + 3) / 4 + 7) / 8); }
+__device__ __forceinline__ bool owt_split_major_wave(int ntiles, int splits, int &tile, int &split)
+{
+    const int total = ntiles * splits, wgs = (total + 3) >> 2, xcd = blockIdx.x & 7, jx = blockIdx.x >> 3;
+    if (jx >= (wgs >> 3) + (xcd < (wgs & 7) ? 1 : 0)) return false;
+    const int pair = (xcd * (wgs >> 3) + min(xcd, wgs & 7) + jx) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (pair >= total) return false;
+    split = pair / ntiles;
+    tile = pair - split * ntiles;
+    return true;
+}
+
 template <int KB, int S, bool MASKED>
-__global__ void __launch_bounds__(64, 1) xfilter_kernel(const GemmParams p)
+__global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
 {
     constexpr int M = 6 * KB * S;                  // matrix instructions per position
 
     const Geom &g = p.g;
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     int tile, split;
-    if (!owt_split_major_wg(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
+    if (!owt_split_major_wave(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
     const int kt = tile / p.tiles_n, rem = tile - kt * p.tiles_n;
     const int r = rem / p.ctiles, ct = rem - r * p.ctiles;
     const int k0 = kt * 32 * KB, c0 = ct * 32;

@@ -8,9 +8,9 @@ template <int V>
 static hipError_t go(const GemmParams &p, hipStream_t s)
 {
     constexpr XFilterVariant v = kXFilterVariants[V];
-    const dim3 grid(owt_split_major_grid(p.tiles_m * p.tiles_n, p.splits));
-    if (p.mask) hipLaunchKernelGGL((xfilter_kernel<v.KB, v.S, true>), grid, dim3(64), 0, s, p);
-    else hipLaunchKernelGGL((xfilter_kernel<v.KB, v.S, false>), grid, dim3(64), 0, s, p);
+    const dim3 grid(owt_split_major_wave_grid(p.tiles_m * p.tiles_n, p.splits));
+    if (p.mask) hipLaunchKernelGGL((xfilter_kernel<v.KB, v.S, true>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((xfilter_kernel<v.KB, v.S, false>), grid, dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<EpiFilter>(p, s);
     return e;

@@ -7,7 +7,8 @@ sum, 16 * 2^-24 S, per instruction is far more than it can make, and in practice
 length L round independently.  The products left out are at most 2^-25 S in all.  Taken here: (L/16 + 16) * 2^-24 * S,
 one rounding of S per instruction plus one instruction's worth.
 2-norm bound.  Independent roundings of half an ulp give sqrt(L/16) * 0.29 * 2^-23 relative; 2^-23 * sqrt(L/16 + 4) is
-taken.  Leaving out any of the six products taken would show 2^-17 or more."""
+taken.  Leaving out any of the six products taken would show 2^-17 or more.  It holds for a tensor of many values; a
+bias gradient may be one value that cancels, so it gets the elementwise bound alone."""
 import sys
 
 import numpy as np
@@ -21,14 +22,14 @@ torch = pytest.importorskip("torch")
 from gpu_util import ConvCase, empty, force, owt, to_dev, to_host, workspace  # noqa: E402
 
 
-def check(got, ref, size, L, what):
+def check(got, ref, size, L, what, norm_too=True):
     got, ref = got.astype(np.float64), ref.astype(np.float64)
     worst = np.max(np.abs(got - ref) / ((L / 16 + 16) * 2.0 ** -24 * size + 1e-30))
     norm = np.linalg.norm(got - ref) / np.linalg.norm(ref)
     print("  %s: %.3f of the elementwise bound, relative 2-norm error %.2e of %.2e" % (what, worst, norm, 2.0 ** -23 * np.sqrt(L / 16 + 4)))
     sys.stdout.flush()
     assert worst <= 1.0, what
-    assert norm <= 2.0 ** -23 * np.sqrt(L / 16 + 4), what
+    assert not norm_too or norm <= 2.0 ** -23 * np.sqrt(L / 16 + 4), what
 
 
 def tensors(shape, seed, scale=1.0):
@@ -174,7 +175,7 @@ def test_split_filter_gradient_kernel(variant, split):
                                                dw=None if dw0 is None else np.abs(dw0), db=None if db0 is None else np.abs(db0))
             L = N * case.P * case.Q
             check(dw, ref, size, L, "dw")
-            check(db, rdb, sdb, L, "db")
+            check(db, rdb, sdb, L, "db", norm_too=False)
 
 
 def test_split_filter_gradient_keeps_infinities_nans_and_the_ends_of_the_range():
@@ -210,3 +211,89 @@ def test_split_filter_gradient_keeps_infinities_nans_and_the_ends_of_the_range()
         scale = np.median(np.abs(want[fine]))
         assert fine.any() and np.max(np.abs(got[fine].astype(np.float64) - want[fine]) / (np.abs(want[fine]) + 1e-4 * scale)) < 1e-3
         assert not np.isfinite(got[7]).all()
+
+
+# N, C, H, W, K, R, S, stride, pad: the first layer's geometry on small images (tiles of several images, one per image),
+# blocks that hang over every border, strides that differ, a short last chunk, blocks with values past the filter
+STRIDED = [(3, 3, 36, 28, 64, 11, 11, 4, 2), (2, 4, 23, 20, 8, 7, 7, 4, 2), (4, 12, 15, 15, 36, 3, 3, 2, 1), (2, 5, 9, 8, 16, 3, 2, (2, 1), (1, 0)),
+           (1, 3, 96, 92, 40, 11, 11, 4, 2)]
+
+
+def strided_tensors(shape, seed):
+    N, C, H, W, K, R, S, stride, pad = shape
+    g = np.random.default_rng(seed)
+    case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, False)
+    return (g.standard_normal(case.shape_x, dtype=np.float32), g.standard_normal(case.shape_w, dtype=np.float32) * np.float32(0.05),
+            g.standard_normal((K,), dtype=np.float32), g.standard_normal(case.shape_y, dtype=np.float32),
+            g.standard_normal(case.shape_y, dtype=np.float32))
+
+
+@pytest.mark.parametrize("variant,split", [(1, 1), (3, 1), (1, 2), (3, 3), (0, 1)])
+def test_split_strided_forward_over_blocks(variant, split):
+    m = owt()
+    ran = 0
+    for i, shape in enumerate(STRIDED):
+        N, C, H, W, K, R, S, stride, pad = shape
+        x, w, b, dy, y = strided_tensors(shape, 1000 + i)
+        case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, True)
+        with force(40 + variant, split, m.OWT_FORCE_ONLY_DIRECT):
+            plan = m.owt_conv_plan_describe(case.desc, 0)
+            print("case", shape, plan)
+            sys.stdout.flush()
+            ran += plan.startswith("sconvx")
+            got = case.fwd(x, w, b)
+        check(got, oracle.conv_fwd(x, w, b, stride, pad, True), oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), stride, pad, False),
+              R * S * C, "y")
+    assert ran >= 1
+
+
+def test_split_strided_forward_meets_no_value_outside_its_windows():
+    # an infinity and a NaN next to windows, inside the blocks that zero filter values meet: outputs whose windows do not
+    # hold them stay finite and exact
+    m = owt()
+    shape = N, C, H, W, K, R, S, stride, pad = (2, 3, 39, 43, 24, 5, 6, 4, 2)
+    x, w, b, dy, y = strided_tensors(shape, 1010)
+    ref = oracle.conv_fwd(x, w, b, stride, pad, False)
+    bad = np.zeros((N, H, W), bool)
+    for n, h, ww, v in ((0, 7, 13, np.inf), (1, 20, 0, np.nan), (1, 38, 42, -np.inf)):
+        x[n, h, ww, 1] = v
+        bad[n, h, ww] = True
+    P, Q = ref.shape[1:3]
+    hit = np.zeros((N, P, Q), bool)
+    for p in range(P):
+        for q in range(Q):
+            h0, w0 = p * stride - pad, q * stride - pad
+            hit[:, p, q] = bad[:, max(0, h0):h0 + R, max(0, w0):w0 + S].any(axis=(1, 2))
+    assert hit.any() and not hit.all()
+    for variant, split in ((1, 1), (3, 2)):
+        with force(40 + variant, split):
+            got = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, False).fwd(x, w, b)
+        assert not np.isfinite(got[hit]).any()
+        assert np.isfinite(got[~hit]).all() and np.max(np.abs(got[~hit] - ref[~hit])) <= 1e-5 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("variant,split", [(0, 1), (0, 3), (1, 1), (1, 7)])
+def test_split_filter_gradient_of_any_geometry(variant, split):
+    m = owt()
+    for i, shape in enumerate(STRIDED + [(17, 5, 6, 7, 70, 3, 3, 1, 1), (8, 3, 12, 12, 16, 5, 5, 1, 2), (1, 1, 8, 8, 1, 3, 3, 1, 1),
+                                         (5, 36, 4, 4, 40, 1, 1, 1, 0), (2, 8, 7, 9, 4, 7, 9, 1, 0), (3, 4, 5, 5, 4, 3, 3, 1, 2)]):
+        N, C, H, W, K, R, S, stride, pad = shape
+        x, w, b, dy, y = strided_tensors(shape, 1020 + i)
+        for relu, alpha, beta in ((False, 1.0, 0.0), (True, 0.5, -0.25)):
+            case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, relu)
+            g = np.random.default_rng(1040 + i)
+            dw0 = g.standard_normal(case.shape_w, dtype=np.float32) if beta else None
+            db0 = g.standard_normal((K,), dtype=np.float32) if beta else None
+            with force(60 + variant, split):
+                plan = m.owt_conv_plan_describe(case.desc, 2)
+                assert plan.startswith(("sfilterx", "xgather")), plan
+                print("case", shape, "relu", relu, plan)
+                sys.stdout.flush()
+                dw, db = case.bwd_filter(x, dy, y if relu else None, alpha, beta, dw0, db0)
+            mask = y if relu else None
+            ref, rdb = oracle.conv_bwd_filter(x, dy, (R, S), stride, pad, y=mask, alpha=alpha, beta=beta, dw=dw0, db=db0)
+            size, sdb = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), (R, S), stride, pad, y=mask, alpha=alpha, beta=abs(beta),
+                                               dw=None if dw0 is None else np.abs(dw0), db=None if db0 is None else np.abs(db0))
+            L = N * case.P * case.Q
+            check(dw, ref, size, L, "dw")
+            check(db, rdb, sdb, L, "db", norm_too=False)
