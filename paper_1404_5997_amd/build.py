@@ -36,6 +36,7 @@ def _units():
         units.append(("dconv16_%s.o" % pname, "dconv_bf16_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
     units.append(("xfilter.o", "xfilter_inst.hip", []))
     units.append(("xgather.o", "xgather_inst.hip", []))
+    units.append(("xfc.o", "xfc_inst.hip", []))
     units.append(("fcgemm.o", "fcgemm_inst.hip", []))
     units.append(("dfilter2.o", "dfilter2_inst.hip", []))
     units.append(("dfilter16.o", "dfilter_bf16_inst.hip", []))

@@ -58,10 +58,10 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18 };
 
-// Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp).
-static inline bool is_split_kind(int kind) { return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER; }
+// Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), and the shard's for either storage type.
+static inline bool is_split_kind(int kind) { return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC; }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
 
@@ -431,7 +431,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // least half of a block's values must meet filter values.)
     const bool blocks = g.sh > 1 || g.sw > 1;
     const long xr = blocks ? blocks_r(g) : g.R, xs = blocks ? blocks_s(g) : g.S, xred = blocks ? (long)g.sh * g.sw * g.C : cred;
-    if (!g.bf16 && pass != OWT_PASS_BWD_FILTER && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
+    if (!g.bf16 && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
         (!blocks || (pass == OWT_PASS_FWD && 2L * g.R * g.S >= xr * xs * g.sh * g.sw && g.sh * g.sw <= 32 && xred <= 256)) &&
         (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull) {
         for (int v = 0; v < kNumXConvVariants; v++) {
@@ -811,11 +811,40 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                 if (pass != OWT_PASS_FWD) l.pre_bytes = pad256((size_t)((g.N + 31) & ~31) * ((g.K + 31) & ~31) * 4);     // padded dz
                 l.cost = model_cost(tm * tn * splits, 4, ft.occ, (double)BM * BN * 32 * per, 1.6, splits, dm.M, dm.Ncols);
+                if (pass != OWT_PASS_FWD) l.cost += 4000.0;               // half of the launch that forms dz
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
                 if (force_split > 0) break;
             }
+        }
+    }
+    // the shard on the bf16 matrix unit: 64 x 64 tiles, 16-deep steps; only the forward pass splits the reduction over
+    // work-groups (its result is small).  32-bit byte offsets, a tile past the end included.
+    const bool plain = g.H == 1 && g.W == 1 && g.R == 1 && g.S == 1;
+    const long rows64 = g.N + 64 > g.K + 64 ? g.N + 64 : g.K + 64;
+    if (plain && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA | OWT_FORCE_FC_ONE_LAUNCH | OWT_FORCE_FC_TWO_LAUNCHES) &&
+        (force_tile < 0 || force_tile == kXFcTile) && (double)rows64 * (g.C + 64) * 4 < 2147483647.0 &&
+        (double)(g.N + 64) * (g.K + 64) * 4 < 2147483647.0) {
+        const long tm = cdiv(dm.M, 64), tn = cdiv(dm.Ncols, 64), steps = cdiv(dm.Kd, 16);
+        const double step_clocks = g.bf16 ? 1500.0 : 2000.0;             // a wavefront's step, its loads' latency included
+        for (long s0 : split_ladder(tm * tn, 256)) {
+            long s = s0;
+            if (force_split > 0) s = force_split < steps ? force_split : steps;
+            if (pass != OWT_PASS_FWD) s = 1;
+            else if (force_split <= 0 && s > 1 && (steps / s < 4 || s > 64)) break;
+            const long per = cdiv(steps, s), splits = cdiv(steps, per);
+            Launch l; memset(&l, 0, sizeof(l));
+            l.kind = KIND_XFC; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per; l.tiles_m = (int)tm; l.tiles_n = (int)tn;
+            if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+            const bool alone = pass == OWT_PASS_BWD_FILTER && tm * tn > kXFcOneTiles;      // a wavefront per tile
+            const long wgs = alone ? tm * cdiv(tn, 4) : tm * tn * splits;
+            l.cost = 0.6 * (6000.0 + cdiv(per, alone ? 1 : 4) * step_clocks) * (0.5 + 0.5 * cdiv(wgs, 256));
+            if (splits > 1) l.cost += 5000.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+            bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+            for (const Launch &o : out) dup |= o.kind == l.kind && o.splits == l.splits;
+            if (!dup) out.push_back(l);
+            if (force_split > 0 || pass != OWT_PASS_FWD) break;
         }
     }
     // the gather kernel is the fallback of the stride-1 forward / backward-data kernel, and an
@@ -918,7 +947,10 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
     frame_params(g, dm, l, ws, p);
     const bool bf = dt == OWT_BF16;
     hipError_t e;
-    if (l.kind == KIND_XCONV) {
+    if (l.kind == KIND_XFC) {
+        e = pass == OWT_PASS_FWD ? owt_launch_xfc_fwd(bf, p, s)
+                                 : owt_launch_xfc_bwd(bf, pass == OWT_PASS_BWD_DATA ? &p : nullptr, pass == OWT_PASS_BWD_DATA ? nullptr : &p, s);
+    } else if (l.kind == KIND_XCONV) {
         const bool blocks = g.sh > 1 || g.sw > 1;
         if (blocks) blocks_frame(g, p); else dconv_frame(g, pass, p);
         p.dWp.set(p.Wi); p.dHpWp.set(p.Hi * p.Wi);
@@ -1025,6 +1057,11 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         const XConvVariant &v = kXConvVariants[l.tile];
         return snprintf(buf, n, "%s %s %s tile%dx%dx16 waves%dx%d panel%d splitk%d grid%dx%d threads%ld", l.blocks ? "sconvx" : "xconv", pn[pass], ds, 32 * v.MB * v.WM,
                         64 * v.WN, v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
+    }
+    if (l.kind == KIND_XFC) {
+        const bool alone = pass == OWT_PASS_BWD_FILTER && (long)l.tiles_m * l.tiles_n > kXFcOneTiles;
+        const long wgs = alone ? l.tiles_m * cdiv(l.tiles_n, 4) : (long)l.tiles_m * l.tiles_n * l.splits;
+        return snprintf(buf, n, "xfc %s %s tile64x64x16 splitk%d grid%ld threads%ld", pn[pass], ds, l.splits, wgs, wgs * 256);
     }
     if (l.kind == KIND_XGATHER)
         return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilterx" : "xgather", pn[pass], ds,
@@ -1167,15 +1204,15 @@ static GemmParams filter_params(const owt_conv_desc *d, const void *x, const voi
 }
 
 // Backward pass of a fully-connected shard when both of its products run on the dense kernel.
-struct FcPair { Launch ld, lf; bool fused; };
+struct FcPair { Launch ld, lf; bool fused, xfc; };
 static std::map<PlanKey, int> g_fc_fused;      // timed by owt_fc_autotune: 1 = one launch for both products
 
-static bool find_fc_launch(const Geom &g, int pass, int tile, Launch &out)
+static bool find_fc_launch(const Geom &g, int pass, int kind, int tile, Launch &out)
 {
     std::vector<Launch> c;
     enumerate(g, pass, conv_dims(g, pass), pass == OWT_PASS_BWD_FILTER, c);
     for (const Launch &l : c)
-        if (l.kind == KIND_FCGEMM && l.tile == tile && l.splits == 1) { out = l; return true; }
+        if (l.kind == kind && l.tile == tile && l.splits == 1) { out = l; return true; }
     return false;
 }
 
@@ -1193,11 +1230,19 @@ static bool fc_pair_plan(const Geom &g, owt_dtype dt, FcPair &fp)
     fp.fused = false;
     fp.ld = choose(g, OWT_PASS_BWD_DATA, dt, conv_dims(g, OWT_PASS_BWD_DATA), false, true);
     fp.lf = choose(g, OWT_PASS_BWD_FILTER, dt, conv_dims(g, OWT_PASS_BWD_FILTER), true, true);
-    if (fp.ld.kind == KIND_FCGEMM && fp.lf.kind == KIND_FCGEMM) {
+    fp.xfc = false;
+    if (fp.ld.kind == KIND_XFC || fp.lf.kind == KIND_XFC) {
+        // one of the two chose the kernel that runs both in one launch and forms dz itself: the other joins it
+        Launch fd, ff;
+        if (find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_XFC, 0, fd) && find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_XFC, 0, ff)) {
+            ok = fp.xfc = true;
+            fp.ld = fd; fp.lf = ff;
+        }
+    } else if (fp.ld.kind == KIND_FCGEMM && fp.lf.kind == KIND_FCGEMM) {
         ok = true;
         Launch fd, ff;
-        if (!forced(OWT_FORCE_FC_TWO_LAUNCHES) && find_fc_launch(g, OWT_PASS_BWD_DATA, kFcPairTile, fd) &&
-            find_fc_launch(g, OWT_PASS_BWD_FILTER, kFcPairTile, ff)) {
+        if (!forced(OWT_FORCE_FC_TWO_LAUNCHES) && find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_FCGEMM, kFcPairTile, fd) &&
+            find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_FCGEMM, kFcPairTile, ff)) {
             int fused = 1;                       // untimed: one launch
             {
                 std::lock_guard<std::mutex> lk(g_tuned_mutex);
@@ -1219,7 +1264,8 @@ static owt_status launch_fc_pair(const Geom &g, const FcPair &fp, GemmParams pd,
 {
     frame_params(g, conv_dims(g, OWT_PASS_BWD_DATA), fp.ld, ws, pd);
     frame_params(g, conv_dims(g, OWT_PASS_BWD_FILTER), fp.lf, ws, pf);
-    const hipError_t e = owt_launch_fcgemm_bwd(fp.ld.tile, fp.lf.tile, fp.fused, pd, pf, (float *)ws, s);
+    const hipError_t e = fp.xfc ? owt_launch_xfc_bwd(g.bf16 != 0, &pd, &pf, s)
+                                : owt_launch_fcgemm_bwd(fp.ld.tile, fp.lf.tile, fp.fused, pd, pf, (float *)ws, s);
     if (e != hipSuccess) return fail(OWT_ELAUNCH, "HIP launch failed: %s", hipGetErrorString(e));
     return OWT_OK;
 }
@@ -1437,7 +1483,12 @@ owt_status owt_conv_autotune(const owt_conv_desc *d, int pass, const void *x, co
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(OWT_ELAUNCH, "hipEventCreate failed"); }
     int best = -1; float best_ms = 0.f;
     owt_status st = OWT_OK;
+    // candidates that the cost model puts past three times the cheapest are not timed: the model is within a factor of two
+    // (timing all of them, the kernels on the fp32 instruction among them, took a step's tuning from 2.2 to 3.4 s)
+    double least = c[0].cost;
+    for (const Launch &l : c) least = l.cost < least ? l.cost : least;
     for (size_t i = 0; i < c.size() && st == OWT_OK; i++) {
+        if (c[i].cost > 3.0 * least) continue;
         st = launch(g, pass, d->dtype, dm, p, c[i], ws, s);                       // warm-up
         if (st != OWT_OK) break;
         // 3 launches; a variant that takes under 50 us is timed again over 12 (launch jitter is a few us)
@@ -1582,14 +1633,14 @@ owt_status owt_fc_autotune(const owt_fc_desc *d, const void *x, const void *w, c
                               hip_stream));
     // both backward products on the dense kernel: two launches (the tiles just timed) or one for both?
     Launch fd, ff;
-    if (variants_forced() || !find_fc_launch(g, OWT_PASS_BWD_DATA, kFcPairTile, fd) || !find_fc_launch(g, OWT_PASS_BWD_FILTER, kFcPairTile, ff))
+    if (variants_forced() || !find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_FCGEMM, kFcPairTile, fd) || !find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_FCGEMM, kFcPairTile, ff))
         return OWT_OK;
     FcPair two;
     two.ld = choose(g, OWT_PASS_BWD_DATA, d->dtype, conv_dims(g, OWT_PASS_BWD_DATA), false, true);
     two.lf = choose(g, OWT_PASS_BWD_FILTER, d->dtype, conv_dims(g, OWT_PASS_BWD_FILTER), true, true);
-    two.fused = false;
+    two.fused = two.xfc = false;
     if (two.ld.kind != KIND_FCGEMM || two.lf.kind != KIND_FCGEMM) return OWT_OK;
-    FcPair one; one.ld = fd; one.lf = ff; one.fused = true;
+    FcPair one; one.ld = fd; one.lf = ff; one.fused = true; one.xfc = false;
     const void *mask = (d->flags & OWT_RELU) ? y : nullptr;
     GemmParams pd; memset(&pd, 0, sizeof(pd));
     pd.a = dy; pd.b = w; pd.out = dx_partial; pd.flags = d->flags; pd.mask = mask;

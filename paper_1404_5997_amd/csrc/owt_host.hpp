@@ -75,6 +75,12 @@ constexpr int kNumXGatherVariants = 2, kXGatherFirstTile = 60;
 constexpr XGatherVariant kXGatherVariants[kNumXGatherVariants] = {{2, 3}, {1, 3}};
 hipError_t owt_launch_xgather(int variant, const GemmParams &, hipStream_t);
 
+// The fully-connected shard on the bf16 MFMA (xfc_inst.hip), both storage types; test-hook number 70.  Backward: one launch
+// for the products whose parameters are given.
+constexpr int kXFcTile = 70, kXFcOneTiles = 256;
+hipError_t owt_launch_xfc_fwd(bool bf16, const GemmParams &, hipStream_t);
+hipError_t owt_launch_xfc_bwd(bool bf16, const GemmParams *data, const GemmParams *filter, hipStream_t);
+
 // Panel-resident stride-1 kernels on the bf16 MFMA (dconv_bf16_inst.hip, dconv_bf16p.hpp for the 512x64 tile).  The backward-data
 // launcher first writes the flipped, transposed filters to the front of `ws`.
 hipError_t owt_launch_dconv16_fwd(int tile, int pr, const GemmParams &, hipStream_t);

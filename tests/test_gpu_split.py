@@ -297,3 +297,45 @@ def test_split_filter_gradient_of_any_geometry(variant, split):
             L = N * case.P * case.Q
             check(dw, ref, size, L, "dw")
             check(db, rdb, sdb, L, "db", norm_too=False)
+
+
+# N, I, O: single values, one step and tile less, exactly and more than full, odd rows (2-byte aligned in bf16), more tiles
+# of dw than CUs (a wavefront per tile)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("split", [1, 3])
+def test_fully_connected_shard_on_the_bf16_matrix_unit(dt, split):
+    m = owt()
+    rnd = oracle.round_bf16 if dt == "bf16" else (lambda a: a)
+    code = m.OWT_BF16 if dt == "bf16" else m.OWT_F32
+    for i, (N, I, O) in enumerate([(1, 1, 1), (5, 17, 3), (16, 64, 64), (33, 100, 65), (64, 16, 128), (130, 131, 70), (20, 5000, 260)]):
+        g = np.random.default_rng(1100 + i)
+        x, w = rnd(g.standard_normal((N, I), dtype=np.float32)), rnd(g.standard_normal((O, I), dtype=np.float32) * np.float32(0.05))
+        b, dy, y = g.standard_normal((O,), dtype=np.float32), rnd(g.standard_normal((N, O), dtype=np.float32)), rnd(g.standard_normal((N, O), dtype=np.float32))
+        dw0, db0 = g.standard_normal((O, I), dtype=np.float32), g.standard_normal((O,), dtype=np.float32)
+        for relu, alpha, beta in ((False, 1.0, 0.0), (True, 0.5, -0.25)):
+            d = m.fc_desc(N, I, O, 1, 0, code, m.OWT_BIAS | (m.OWT_RELU if relu else 0))
+            yin = y if relu else None
+            with force(70, split):
+                print("case", dt, (N, I, O), "relu", relu, "split", split)
+                sys.stdout.flush()
+                ws = workspace(max(m.owt_fc_workspace_bytes(d, 0), m.owt_fc_workspace_bytes(d, 1)))
+                yd, dx, dw, db = empty((N, O), dt), empty((N, I), dt), to_dev(dw0), to_dev(db0)
+                m.owt_fc_shard_fwd(d, to_dev(x, dt), to_dev(w, dt), to_dev(b), yd, ws)
+                m.owt_fc_shard_bwd(d, to_dev(x, dt), to_dev(w, dt), to_dev(yin, dt), to_dev(dy, dt), alpha, beta, dx, dw, db, ws)
+                dw2 = to_dev(dw0)
+                m.owt_fc_shard_bwd(d, to_dev(x, dt), to_dev(w, dt), to_dev(yin, dt), to_dev(dy, dt), alpha, beta, None, dw2, None, ws)
+                torch.cuda.synchronize()
+            assert torch.equal(dw, dw2)
+            dz = dy * (y > 0) if relu else dy
+            f64 = lambda a: a.astype(np.float64)
+            lin = f64(x) @ f64(w).T + b
+            refs = {"y": (to_host(yd), np.maximum(lin, 0) if relu else lin, np.abs(f64(x)) @ np.abs(f64(w)).T + np.abs(b), I),
+                    "dx": (to_host(dx), f64(dz) @ f64(w), np.abs(f64(dz)) @ np.abs(f64(w)), O),
+                    "dw": (to_host(dw), alpha * (f64(dz).T @ f64(x)) + beta * dw0, abs(alpha) * (np.abs(f64(dz)).T @ np.abs(f64(x))) + abs(beta) * np.abs(dw0), N),
+                    "db": (to_host(db), alpha * f64(dz).sum(0) + beta * db0, abs(alpha) * np.abs(f64(dz)).sum(0) + abs(beta) * np.abs(db0), N)}
+            for name, (got, ref, size, L) in refs.items():
+                bound = (L / 16 + 16) * 2.0 ** -24 * size + 1e-30
+                if dt == "bf16" and name in ("y", "dx"):
+                    bound += 2.0 ** -8 * np.abs(ref)              # rounded to bf16 when stored
+                worst = np.max(np.abs(got - ref) / bound)
+                assert worst <= 1.0, (name, worst)
