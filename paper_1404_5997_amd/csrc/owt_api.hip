@@ -441,7 +441,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             // a strided pass has no padding between its blocks: tiles per image when the last, short ones waste under 5 %
             const long tpi = blocks && cdiv(image, BM) * BM * 20 <= image * 21 ? cdiv(image, BM) : 0;
             const long rows = panel_rows(g, pass, dm, BM, blocks, tpi > 0);
-            if (rows < 0 || (xv.occ == 4 && xv.WM == 4 && pass == OWT_PASS_BWD_DATA && g.masked)) continue;
+            if (rows < 0) continue;
             int pr = 0;
             for (int q = 2; q >= 0; q--)
                 if (xv.prs[q] >= rows) pr = xv.prs[q];
@@ -458,7 +458,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 l.tiles_m = (int)tm; l.tiles_n = (int)tn;
                 l.pre_bytes = pad256(packed);
                 if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
-                l.cost = model_cost(tm * tn * splits, xv.WM * xv.WN, xv.occ, macs * per, xv.eff, splits, dm.M, dm.Ncols) + 8000.0;
+                l.cost = model_cost(tm * tn * splits, xv.WM * xv.WN, xv.occ, macs * per, xv.eff, splits, dm.M, dm.Ncols) + 5000.0;
+                if (splits > 1) l.cost -= 7500.0;             // the reduce pass measures about 5 us on these results
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -625,7 +626,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 // tile; whole rounds of 1024 wavefronts (one per SIMD).  0.6 = the other kernels' model against their clocks
                 const double clocks = per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0;
                 l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
-                if (splits > 1) l.cost += 14000.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+                if (splits > 1) l.cost += 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -656,7 +657,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 // as above; the vector instructions of a fragment take about 330 clocks
                 const double clocks = per * (330.0 * (xv.KB + xv.CB) + 100.0) + 6000.0;
                 l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
-                if (splits > 1) l.cost += 14000.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+                if (splits > 1) l.cost += 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -860,7 +861,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         const double macs = (double)ti.BM * 64 * ti.WN * ti.BK;
         for (long s : split_ladder(tiles)) {
             if (s > 1 && (ksteps / s < 4 || tiles * s > 4096)) break;
-            add(KIND_GATHER, t, 0, ksteps, s, macs, t == TILE_128x128 ? 2 : 5, ti.eff);
+            // (4-byte gathers: 8 images 32x32x3 -> 16, 5x5 forward takes 21 us here, 16.6 with split operands)
+            add(KIND_GATHER, t, 0, ksteps, s, macs, t == TILE_128x128 ? 2 : 5, vec ? ti.eff : 0.6 * ti.eff);
             if (force_split > 0) break;
         }
     }

@@ -43,16 +43,15 @@ hipError_t owt_launch_dconv_data_bf16(int tile, int pr, const GemmParams &, hipS
 // Panel-resident stride-1 kernel for fp32 storage on the bf16 MFMA with split operands (xconv_inst.hip), forward and
 // backward-data: WM x WN wavefronts of 32*MB pixels x 64 filters, occ work-groups per CU; prs = the panel sizes it is
 // built for; eff = relative rate of a filled chip, for the planner.  Measured on fp32 layers of 128 images, TFLOP/s (3x3
-// 192->384 / 3x3 256->256 / 5x5 64->192 forward): 128x128 tile 197 / 157 / 181, 256x64 211 / 162 / 209, 128x64 of two
-// wavefronts 211 / 175 / 193, of four 193 / 188 / 225, of four with one panel buffer and four per CU 204 / 182 / -;
-// the kernels on the fp32 instruction 132 / 117 / 127.  Which wins is how the tile count divides over the CUs.  The
-// last variant has no registers left for the mask of dy and is for calls without one.
+// 192->384 / 3x3 256->256 / 5x5 64->192 forward): 128x128 tile 212 / 169 / 186, 256x64 226 / 179 / 229, 128x64 of two
+// wavefronts 217 / 189 / 203, of four 209 / 199 / 230; the kernels on the fp32 instruction 132 / 117 / 127.  Which wins is
+// how the tile count divides over the CUs.  (Four wavefronts per SIMD on the last one: 212 / 195 / -, seven spills; gone.)
 // The split, laid-out filters go to the front of `ws`.  The test hook numbers the variants from 40.
 struct XConvVariant { int WM, WN, MB, occ, prs[3]; float eff; };
-constexpr int kNumXConvVariants = 5, kXConvFirstTile = 40;
+constexpr int kNumXConvVariants = 4, kXConvFirstTile = 40;
 constexpr XConvVariant kXConvVariants[kNumXConvVariants] = {
-    {2, 2, 2, 2, {160, 256, 0}, 1.10f}, {4, 1, 2, 2, {288, 384, 512}, 1.20f}, {2, 1, 2, 4, {160, 256, 0}, 1.15f},
-    {4, 1, 1, 3, {160, 256, 0}, 1.25f}, {4, 1, 1, 4, {160, 0, 0}, 1.30f}};
+    {2, 2, 2, 2, {160, 288, 0}, 1.12f}, {4, 1, 2, 2, {288, 384, 512}, 1.35f}, {2, 1, 2, 4, {160, 288, 0}, 1.18f},
+    {4, 1, 1, 3, {160, 288, 0}, 1.32f}};
 hipError_t owt_launch_xconv_fwd_vec0(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 hipError_t owt_launch_xconv_fwd_vec1(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 hipError_t owt_launch_xconv_fwd_blocks(int variant, int pr, const GemmParams &, void *ws, hipStream_t);   // strided forward

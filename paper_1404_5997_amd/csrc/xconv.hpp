@@ -14,12 +14,16 @@
 //    tap's slice is a few 1 KB pieces that go straight into LDS, and a fragment read is 64 consecutive 16-byte pieces;
 //  * the panel is kept as six planes (part, 8-channel half) of one 16-byte piece per pixel: a fragment read of 32
 //    consecutive pixels is 512 consecutive bytes whatever the tap's shift, so there is nothing to pad or swizzle;
-//  * slices sit in a ring of three, so one barrier per tap is enough and a slice has two taps' time to arrive.
+//  * slices sit in a ring of four: one barrier per tap is enough, a slice has two taps' time to arrive, and the fragments
+//    of a tap are read during the tap before, each into the registers of a fragment that has just had its last product.
 // Taps that fall outside the image read the row of zeros behind each plane.
+// Measured, 128 images, kernel on the fp32 instruction -> this one, us: forward 3x3 192->384 218 -> 127 (226 TFLOP/s), 256->256
+// 218 -> 128, 384->256 320 -> 187, 5x5 64->192 453 -> 250; backward-data 232 -> 142, - , - , 444 -> 260.  With each tap's
+// fragments read behind the tap's own barrier instead of during the tap before (and the panel twice): 135, 136, 198, 255.
 //
 // A strided forward pass of few channels (the first layer) runs here, too, seen over blocks of sh x sw input pixels: 11 x 11
 // taps of 3 channels at stride 4 are 3 x 3 taps of 48 channels, 432 reduction steps for 363.  Measured, 128 images of
-// 224x224x3 -> 64: 170 us on the fp32 instruction, 126 here (143 TFLOP/s on the 363); half of the time goes to the panel's
+// 224x224x3 -> 64: 170 us on the fp32 instruction, 123 here (146 TFLOP/s on the 363); half of the time goes to the panel's
 // 4-byte loads, the prologue and the stores of work-groups that have only 27 steps.
 #pragma once
 #include "igemm.hpp"
@@ -80,11 +84,10 @@ static __global__ void __launch_bounds__(256) xconv_pack_blocks_kernel(const flo
 // frame Hi, Wi, Ho, Wo, Cred count in blocks; p.g.H, W, C, strides and padding are the layer's own).
 enum { XC_SCALAR = 0, XC_VEC = 1, XC_BLOCKS = 2 };
 
-// WM x WN wavefronts of 32*MB pixels x 64 filters; PR panel rows; NPB panel buffers (two: the next chunk is written while
-// the last tap of this one is still being read, no extra barrier); MASKED: dy is masked by y > 0 on its way in.  At most
+// WM x WN wavefronts of 32*MB pixels x 64 filters; PR panel rows; OCC wavefronts per SIMD the registers are cut for; MASKED: dy is masked by y > 0 on its way in.  At most
 // 32 taps; 32-bit byte offsets in every tensor (host-checked).
-template <class Epi, bool BWD, int WM, int WN, int MB, int PR, int NPB, int LOAD, bool MASKED>
-__global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160 ? 4 : 3) : 2) xconv_kernel(const GemmParams p)
+template <class Epi, bool BWD, int WM, int WN, int MB, int PR, int OCC, int LOAD, bool MASKED>
+__global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmParams p)
 {
     constexpr int NW = WM * WN, NT = 64 * NW, BM = 32 * MB * WM, BN = 64 * WN;
     constexpr int PL = PR + 1, PANEL = 6 * PL;                       // 16-byte units: a plane, a panel buffer
@@ -92,8 +95,8 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
     constexpr int PU = (2 * PR + NT - 1) / NT;                       // (row, half) pairs of the panel per thread
     constexpr unsigned OOB = 0x80000000u;                            // a byte offset no descriptor here reaches
 
-    __shared__ __attribute__((aligned(1024))) uint4 slices[3 * SL * 64];
-    __shared__ __attribute__((aligned(16))) uint4 panel[NPB * PANEL];
+    __shared__ __attribute__((aligned(1024))) uint4 slices[4 * SL * 64];
+    __shared__ __attribute__((aligned(16))) uint4 panel[PANEL];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, lh = lane >> 5;
@@ -244,12 +247,17 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
         for (int i = 0; i < SQ; i++) buffer_load16_to_lds(brs, off + (unsigned)(i * NW) * 1024u, dst + (unsigned)(i * NW) * 1024u);
         if (SREM && wave < SREM) buffer_load16_to_lds(brs, off + (unsigned)(SQ * NW) * 1024u, dst + (unsigned)(SQ * NW) * 1024u);
     };
-    // All LDS accesses of this wavefront are done and its slice pieces have landed, except those of the `younger` slices
-    // (0 or 1) requested last; then the work-group meets.
-    auto meet = [&](bool younger) __attribute__((always_inline)) {
-        if (!younger) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        else if (SREM && wave < SREM) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(SQ + 1) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(SQ) : "memory");
+    // This wavefront's slice pieces have landed, except those of the slice requested last (`younger`) and the panel loads
+    // requested before it (`panel_too`); then the work-group meets.  Fragment reads stay in flight across the barrier: what
+    // is overwritten after it was read before the previous one.
+    constexpr int NPL = PU * (LOAD == XC_VEC ? 2 : 8) * (MASKED ? 2 : 1);      // panel loads per thread
+    auto meet = [&](bool younger, bool panel_too) __attribute__((always_inline)) {
+        if (!younger) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        else if (NPL + SQ + 1 <= 63 && panel_too) {
+            if (SREM && wave < SREM) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NPL + SQ + 1) & 63) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NPL + SQ) & 63) : "memory");
+        } else if (SREM && wave < SREM) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(SQ + 1) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(SQ) : "memory");
     };
 
     split_acc big[MB][2], small[MB][2];
@@ -260,62 +268,82 @@ __global__ void __launch_bounds__(64 * WM * WN, MB == 1 ? (NPB == 1 && PR <= 160
 #pragma unroll
             for (int r = 0; r < 16; r++) big[i][j][r] = small[i][j][r] = 0.f;
 
-    if (tid < 6 * NPB) panel[tid * PL + PR] = make_uint4(0u, 0u, 0u, 0u);     // the row of zeros of every plane
+    if (tid < 6) panel[tid * PL + PR] = make_uint4(0u, 0u, 0u, 0u);           // the row of zeros of every plane
     const int nsteps = (ch_end - ch_beg) * RS;                                // one step per (chunk, tap); at least one
     load_panel(ch_beg);
     store_panel(panel);
-    fetch_slice(ch_beg, 0, 0);
-    if (nsteps > 1) fetch_slice(RS > 1 ? ch_beg : ch_beg + 1, RS > 1 ? 1 : 0, 1);
+    auto next_step = [&](int &c, int &t) { if (++t == RS) { t = 0; c++; } };
+    int ch3 = ch_beg, tap3 = 0;                                               // the next slice to request
+    for (int i = 0; i < 3 && i < nsteps; i++) { fetch_slice(ch3, tap3, i); next_step(ch3, tap3); }
 
-    int ch = ch_beg, tap = 0, r = 0, s = 0, slot = 0, pbuf = 0;
-    int ch2 = ch_beg + 2 / RS, tap2 = 2 % RS;                                 // two steps ahead
-    for (int t = 0; t < nsteps; t++) {
-        meet(t + 1 < nsteps);
-        // the panel of the next chunk is requested before the slice of step t + 2, so that the next step's wait for its
-        // own slice covers it; it is held in registers until this chunk's last tap
-        if (tap == 0 && ch + 1 < ch_end) load_panel(ch + 1);
-        if (t + 2 < nsteps) fetch_slice(ch2, tap2, slot == 0 ? 2 : slot - 1); // the slot step t - 1 was done with
-        const uint4 *pp = panel + pbuf * PANEL + lh * PL, *bp = slices + (slot * SL + wn * 6) * 64 + lane;
+    // The fragments of a step are read during the step before it, each right behind the last product that needs its old
+    // value: parts of a step, in the order of their last use, l of the pixels, l of the filters, m, m, h, h.
+    split_frag a[MB][3], f[2][3];
+    const uint4 *arow[MB], *bp;
+    auto aim = [&](int tap, int r, int s, int slot) __attribute__((always_inline)) {
         const int shift = r * Wi + s;
-        split_frag a[MB][3], f[2][3];
-        const uint4 *row[MB];
 #pragma unroll
-        for (int bm = 0; bm < MB; bm++) row[bm] = pp + (((inside[bm] >> tap) & 1u) ? prow[bm] + shift : PR);
-        // all reads first, in the order the products need them; left alone, the compiler reuses fragment registers and
-        // waits for a read right behind its issue
-        constexpr int RO[3] = {0, 2, 1};
+        for (int bm = 0; bm < MB; bm++) arow[bm] = panel + lh * PL + (((inside[bm] >> tap) & 1u) ? prow[bm] + shift : PR);
+        bp = slices + (slot * SL + wn * 6) * 64 + lane;
+    };
+    auto read_a = [&](int q) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < 3; q++) {
+        for (int bm = 0; bm < MB; bm++) a[bm][q] = __builtin_bit_cast(split_frag, arow[bm][2 * q * PL]);
+    };
+    auto read_b = [&](int q) __attribute__((always_inline)) {
 #pragma unroll
-            for (int bn = 0; bn < 2; bn++) f[bn][RO[q]] = __builtin_bit_cast(split_frag, bp[(bn * 3 + RO[q]) * 64]);
-#pragma unroll
-            for (int bm = 0; bm < MB; bm++) a[bm][RO[q]] = __builtin_bit_cast(split_frag, row[bm][2 * RO[q] * PL]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        for (int bn = 0; bn < 2; bn++) f[bn][q] = __builtin_bit_cast(split_frag, bp[(bn * 3 + q) * 64]);
+    };
+    auto product = [&](int qa, int qb) __attribute__((always_inline)) {
 #pragma unroll
         for (int bm = 0; bm < MB; bm++)
 #pragma unroll
-            for (int bn = 0; bn < 2; bn++)
-                big[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bm][0], f[bn][0], big[bm][bn], 0, 0, 0);
-        constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};       // the five small products
-#pragma unroll
-        for (int q = 0; q < 5; q++)
-#pragma unroll
-            for (int bm = 0; bm < MB; bm++)
-#pragma unroll
-                for (int bn = 0; bn < 2; bn++)
-                    small[bm][bn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bm][PA[q]], f[bn][PB[q]], small[bm][bn], 0, 0, 0);
+            for (int bn = 0; bn < 2; bn++) {
+                split_acc &acc = qa + qb == 0 ? big[bm][bn] : small[bm][bn];
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bm][qa], f[bn][qb], acc, 0, 0, 0);
+            }
         __builtin_amdgcn_sched_barrier(0);
-        if (tap == RS - 1 && ch + 1 < ch_end) {
-            if (NPB == 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // everyone is done with the panel
-            else pbuf ^= 1;
-            store_panel(panel + pbuf * PANEL);
+    };
+
+    // slices 0 and 1 have landed (meet() leaves the youngest in flight), the panel is written
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    meet(nsteps > 2, false);
+    aim(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 3; q++) { read_a(q); read_b(q); }
+    // A step begins with the meeting that says the next step's slice has landed, and requests the slice three steps ahead into
+    // the slot of the step before it.  A chunk's first step requests the next chunk's panel in between (held in registers
+    // until the last tap), so its loads have two steps' time before a meeting waits for them.
+    int t = 0, slot = 0;
+    auto begin = [&](int load, bool panel_too) __attribute__((always_inline)) {
+        if (t > 0) meet(t + 2 < nsteps, panel_too);
+        if (load < ch_end) load_panel(load);
+        if (t + 3 < nsteps) { fetch_slice(ch3, tap3, slot == 0 ? 3 : slot - 1); next_step(ch3, tap3); }
+        slot = slot == 3 ? 0 : slot + 1;
+        t++;
+    };
+    for (int ch = ch_beg; ch < ch_end; ch++) {
+        for (int tap = 1, r = 0, s = 0; tap < RS; tap++) {                    // the step of tap - 1
+            begin(tap == 1 ? ch + 1 : ch_end, tap == 2 && ch + 1 < ch_end);
+            if (++s == S) { s = 0; r++; }
+            aim(tap, r, s, slot);
+            product(1, 1);
+            product(2, 0); read_a(2);
+            product(0, 2); read_b(2);
+            product(1, 0); read_a(1);
+            product(0, 1); read_b(1);
+            product(0, 0); read_a(0); read_b(0);
         }
-        slot = slot == 2 ? 0 : slot + 1;
-        if (++tap2 == RS) { tap2 = 0; ch2++; }
-        tap++;
-        if (++s == S) { s = 0; r++; }
-        if (tap == RS) { tap = 0; r = 0; s = 0; ch++; }
+        begin(RS == 1 ? ch + 1 : ch_end, false);                              // the last tap
+        product(1, 1); product(2, 0); product(0, 2); product(1, 0); product(0, 1); product(0, 0);
+        if (ch + 1 < ch_end) {
+            asm volatile("s_barrier" ::: "memory");                           // everyone has its fragments of the old panel
+            store_panel(panel);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            aim(0, 0, 0, slot);
+#pragma unroll
+            for (int q = 0; q < 3; q++) { read_a(q); read_b(q); }
+        }
     }
 
     if (LOAD == XC_BLOCKS) {

@@ -20,21 +20,17 @@ constexpr bool kBwd = true;
 #endif
 #define OWT_XFN(v) OWT_XFN_(v)
 
-template <int WM, int WN, int MB, int PR, int NPB>
+template <int WM, int WN, int MB, int PR, int OCC>
 static hipError_t go(const GemmParams &p, hipStream_t s)
 {
     const dim3 grid(p.tiles_m * p.tiles_n, p.splits), block(64 * WM * WN);
     if constexpr (kBwd) {
         if (p.mask) {
-            if constexpr (MB == 1 && PR == 160 && NPB == 1) {
-                return hipErrorInvalidValue;             // no registers for the mask at four wavefronts per SIMD
-            } else {
-                hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, NPB, OWT_INST_VEC, true>), grid, block, 0, s, p);
-                return hipGetLastError();
-            }
+            hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, OCC, OWT_INST_VEC, true>), grid, block, 0, s, p);
+            return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, NPB, OWT_INST_VEC, false>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((xconv_kernel<OE, kBwd, WM, WN, MB, PR, OCC, OWT_INST_VEC, false>), grid, block, 0, s, p);
     return hipGetLastError();
 }
 
@@ -68,19 +64,17 @@ hipError_t OWT_XFN(OWT_INST_VEC)(int variant, int pr, const GemmParams &p0, void
     e = hipErrorInvalidValue;
     if (variant == 0) {
         if (pr <= 160) e = go<2, 2, 2, 160, 2>(p, s);
-        else if (pr <= 256) e = go<2, 2, 2, 256, 1>(p, s);
+        else if (pr <= 288) e = go<2, 2, 2, 288, 2>(p, s);
     } else if (variant == 1) {
         if (pr <= 288) e = go<4, 1, 2, 288, 2>(p, s);
-        else if (pr <= 384) e = go<4, 1, 2, 384, 1>(p, s);
-        else if (pr <= 512) e = go<4, 1, 2, 512, 1>(p, s);
+        else if (pr <= 384) e = go<4, 1, 2, 384, 2>(p, s);
+        else if (pr <= 512) e = go<4, 1, 2, 512, 2>(p, s);
     } else if (variant == 2) {
-        if (pr <= 160) e = go<2, 1, 2, 160, 1>(p, s);
-        else if (pr <= 256) e = go<2, 1, 2, 256, 1>(p, s);
+        if (pr <= 160) e = go<2, 1, 2, 160, 2>(p, s);
+        else if (pr <= 288) e = go<2, 1, 2, 288, 2>(p, s);
     } else if (variant == 3) {
-        if (pr <= 160) e = go<4, 1, 1, 160, 2>(p, s);
-        else if (pr <= 256) e = go<4, 1, 1, 256, 1>(p, s);
-    } else if (variant == 4) {
-        if (pr <= 160) e = go<4, 1, 1, 160, 1>(p, s);
+        if (pr <= 160) e = go<4, 1, 1, 160, 3>(p, s);
+        else if (pr <= 288) e = go<4, 1, 1, 288, 3>(p, s);
     }
     if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<OE>(p, s);
     return e;

@@ -50,7 +50,7 @@ SHAPES = [(4, 40, 13, 13, 136, 3, 3, 1), (1, 16, 16, 16, 64, 1, 1, 0), (3, 64, 2
           (1, 3, 5, 5, 4, 3, 3, 1), (5, 50, 6, 7, 66, 3, 3, 0)]
 
 
-@pytest.mark.parametrize("variant,split", [(0, 1), (1, 1), (2, 1), (3, 1), (4, 1), (0, 3), (1, 2), (2, 7), (3, 2), (4, 5)])
+@pytest.mark.parametrize("variant,split", [(0, 1), (1, 1), (2, 1), (3, 1), (0, 3), (1, 2), (2, 7), (3, 2)])
 def test_split_convolution_kernel(variant, split):
     m = owt()
     for i, shape in enumerate(SHAPES):
@@ -62,11 +62,9 @@ def test_split_convolution_kernel(variant, split):
                 plans = [m.owt_conv_plan_describe(case.desc, ps) for ps in (0, 1)]
                 print("case", shape, "relu", relu, plans)
                 sys.stdout.flush()
-                wide = variant == 4 and (R == 5 or H == 6)    # 128 pixels need more panel rows than it has
-                masked = variant == 4 and relu          # ... and it takes dy as it is
                 same = all(2 * p == r - 1 for p, r in zip((pad, pad) if isinstance(pad, int) else pad, (R, S)))
-                assert plans[0].startswith("xconv") or wide, plans[0]
-                assert plans[1].startswith("xconv") or wide or masked or not same, plans[1]
+                assert plans[0].startswith("xconv"), plans[0]
+                assert plans[1].startswith("xconv") or not same, plans[1]
                 got = case.fwd(x, w, b)
                 dx = case.bwd_data(dy, y, w)
             size = oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), 1, pad, False)
@@ -83,7 +81,7 @@ def test_split_convolution_with_the_mask_of_the_layer_below():
     ref = oracle.conv_bwd_data(dy, w, (H, W), 1, pad) * (x > 0)
     size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad)
     for split in (1, 3):
-        for variant in (0, 3, 4):
+        for variant in (0, 1, 3):
             with force(40 + variant, split):
                 dx = empty(case.shape_x)
                 m.owt_conv_bwd_data_relu_in(case.desc, to_dev(dy), None, to_dev(w), to_dev(x), dx, case.ws(1))
