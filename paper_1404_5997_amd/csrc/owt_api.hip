@@ -838,9 +838,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             Launch l; memset(&l, 0, sizeof(l));
             l.kind = KIND_XFC; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per; l.tiles_m = (int)tm; l.tiles_n = (int)tn;
             if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
-            const bool alone = pass == OWT_PASS_BWD_FILTER && tm * tn > kXFcOneTiles;      // a wavefront per tile
-            const long wgs = alone ? tm * cdiv(tn, 4) : tm * tn * splits;
-            l.cost = 0.6 * (6000.0 + cdiv(per, alone ? 1 : 4) * step_clocks) * (0.5 + 0.5 * cdiv(wgs, 256));
+            l.cost = 0.6 * (6000.0 + cdiv(per, 4) * step_clocks) * (0.5 + 0.5 * cdiv(tm * tn * splits, 256));
             if (splits > 1) l.cost += 5000.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
             bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
             for (const Launch &o : out) dup |= o.kind == l.kind && o.splits == l.splits;
@@ -916,6 +914,8 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
     }
     return c[best];
 }
+
+static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per geometry: listing the candidates takes 10-60 us
 
 // Workspace every candidate fits in (so a tuned choice never outgrows the caller's buffer).
 static size_t max_workspace(const Geom &g, int pass, const PassDims &dm, bool want_db)
@@ -1061,8 +1061,7 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
                         64 * v.WN, v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
     }
     if (l.kind == KIND_XFC) {
-        const bool alone = pass == OWT_PASS_BWD_FILTER && (long)l.tiles_m * l.tiles_n > kXFcOneTiles;
-        const long wgs = alone ? l.tiles_m * cdiv(l.tiles_n, 4) : (long)l.tiles_m * l.tiles_n * l.splits;
+        const long wgs = (long)l.tiles_m * l.tiles_n * l.splits;
         return snprintf(buf, n, "xfc %s %s tile64x64x16 splitk%d grid%ld threads%ld", pn[pass], ds, l.splits, wgs, wgs * 256);
     }
     if (l.kind == KIND_XGATHER)
@@ -1363,7 +1362,19 @@ size_t owt_conv_workspace_bytes(const owt_conv_desc *d, int pass)
     Geom g;
     if (pass < 0 || pass > 2) { fail(OWT_EINVAL, "pass must be 0, 1 or 2"); return (size_t)-1; }
     if (check_conv(d, g) != OWT_OK) return (size_t)-1;
-    return max_workspace(g, pass, conv_dims(g, pass), pass == OWT_PASS_BWD_FILTER);
+    g.masked = 0;                                      // the bound covers calls with and without the mask
+    const bool cached = !variants_forced();
+    if (cached) {
+        std::lock_guard<std::mutex> lk(g_tuned_mutex);
+        auto it = g_workspace.find(plan_key(g, pass, d->dtype));
+        if (it != g_workspace.end()) return it->second;
+    }
+    const size_t need = max_workspace(g, pass, conv_dims(g, pass), pass == OWT_PASS_BWD_FILTER);
+    if (cached) {
+        std::lock_guard<std::mutex> lk(g_tuned_mutex);
+        g_workspace[plan_key(g, pass, d->dtype)] = need;
+    }
+    return need;
 }
 
 int owt_conv_plan_describe(const owt_conv_desc *d, int pass, char *buf, size_t buf_bytes)

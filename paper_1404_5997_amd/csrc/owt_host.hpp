@@ -76,7 +76,7 @@ hipError_t owt_launch_xgather(int variant, const GemmParams &, hipStream_t);
 
 // The fully-connected shard on the bf16 MFMA (xfc_inst.hip), both storage types; test-hook number 70.  Backward: one launch
 // for the products whose parameters are given.
-constexpr int kXFcTile = 70, kXFcOneTiles = 256;
+constexpr int kXFcTile = 70;
 hipError_t owt_launch_xfc_fwd(bool bf16, const GemmParams &, hipStream_t);
 hipError_t owt_launch_xfc_bwd(bool bf16, const GemmParams *data, const GemmParams *filter, hipStream_t);
 

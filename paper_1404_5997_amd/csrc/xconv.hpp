@@ -250,10 +250,11 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
     // This wavefront's slice pieces have landed, except those of the slice requested last (`younger`) and the panel loads
     // requested before it (`panel_too`); then the work-group meets.  Fragment reads stay in flight across the barrier: what
     // is overwritten after it was read before the previous one.
-    constexpr int NPL = PU * (LOAD == XC_VEC ? 2 : 8) * (MASKED ? 2 : 1);      // panel loads per thread
+    // (Only 16-byte panel loads are counted: two smaller ones could become one in the compiler's hands.)
+    constexpr int NPL = LOAD == XC_VEC ? PU * 2 * (MASKED ? 2 : 1) : 0;        // panel loads per thread
     auto meet = [&](bool younger, bool panel_too) __attribute__((always_inline)) {
         if (!younger) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-        else if (NPL + SQ + 1 <= 63 && panel_too) {
+        else if (NPL > 0 && NPL + SQ + 1 <= 63 && panel_too) {
             if (SREM && wave < SREM) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NPL + SQ + 1) & 63) : "memory");
             else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NPL + SQ) & 63) : "memory");
         } else if (SREM && wave < SREM) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(SQ + 1) : "memory");

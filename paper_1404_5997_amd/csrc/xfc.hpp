@@ -12,12 +12,16 @@
 // is zeroed in the last step, rows and columns past the result read something harmless and are not stored.  dz = dy * [y > 0]
 // is formed on the way into the fragments and the bias gradient in the filter product's wavefronts, so a backward call
 // is one launch for both products.
-//  * forward and data: the four wavefronts of a work-group take every fourth 16-deep step of the work-group's share of the
-//    reduction on one 64 x 64 tile and add up through LDS in a fixed order; forward splits the reduction over work-groups,
-//    too (partial sums, splitk_reduce_kernel);
-//  * filter: where there are more tiles than CUs, a wavefront per 64 x 64 tile and the whole batch as its reduction;
-//    otherwise a work-group per tile as above (a step takes a lone wavefront 1.7 us in fp32: loads, split and products
-//    one after the other).
+// The four wavefronts of a work-group take every fourth 16-deep step of the reduction on one 64 x 64 tile and add up through
+// LDS in a fixed order; forward splits the reduction over work-groups, too (partial sums, splitk_reduce_kernel).  (A step
+// takes a lone wavefront 1.7 us in fp32: loads, split and products one after the other.  A wavefront per tile of dw, the
+// whole batch as its reduction: 34 us instead of 30 for the backward call of 128 x 9216 -> 512, 18.3 instead of 8.4 for
+// 4096 -> 125.)
+//
+// Measured, 128 images, us, before (fp32: direct-to-LDS GEMM on the fp32 instruction and a launch for dz; bf16: gather
+// kernel) -> here: fp32 9216 -> 512 forward 20.1 -> 18.4, backward 32.6 -> 29.8; 4096 -> 512 16.0 -> 13.2 and 22.6 -> 16.2;
+// 4096 -> 125 10.6 -> 10.7 and 11.0 -> 8.4.  bf16 9216 -> 512 39 -> 17.5 and 107 -> 19.8; 4096 -> 512 27.5 -> 11.8 and 75 -> 13.0;
+// 4096 -> 125 19.3 -> 10.2 and 102 -> 8.4.
 #pragma once
 #include "igemm.hpp"
 #include "split3.hpp"
@@ -213,9 +217,8 @@ __global__ void __launch_bounds__(256, 2) xfc_fwd_kernel(const GemmParams p)
     });
 }
 
-// Work-groups below pd.tiles_m * pd.tiles_n: a tile of dx; the others: four tiles of dw (64 filters x 256 inputs), or one with
-// ONE.  Without dx the first range is empty.
-template <bool BF, bool MASKED, bool ONE>
+// Work-groups below pd.tiles_m * pd.tiles_n: a tile of dx; the others: a tile of dw.  Either range may be empty.
+template <bool BF, bool MASKED>
 __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, const GemmParams pf)
 {
     __shared__ float red[4 * 4096];
@@ -236,59 +239,32 @@ __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, co
         });
         return;
     }
-    const int t = blockIdx.x - ndx, wide = ONE ? pf.tiles_n : (pf.tiles_n + 3) >> 2;
-    const int tm = t / wide, tn = ONE ? t - tm * wide : (t - tm * wide) * 4 + wave;
-    if (tn >= pf.tiles_n) return;                                // (not with ONE: no barrier follows)
-    const int m0 = tm * 64, n0 = tn * 64, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int t = blockIdx.x - ndx, tm = t / pf.tiles_n, tn = t - tm * pf.tiles_n;
+    const int m0 = tm * 64, n0 = tn * 64, tid = threadIdx.x, lane = tid & 63;
     const bool do_db = tn == 0 && pf.dbias != nullptr;
     if (do_db)
-        xfc_tile<BF, false, false, MASKED, true>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, ONE ? wave : 0,
-                                                 ONE ? 4 : 1, (N + 15) >> 4, big, small, db);
+        xfc_tile<BF, false, false, MASKED, true>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
+                                                 (N + 15) >> 4, big, small, db);
     else
-        xfc_tile<BF, false, false, MASKED, false>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, ONE ? wave : 0,
-                                                  ONE ? 4 : 1, (N + 15) >> 4, big, small, db);
+        xfc_tile<BF, false, false, MASKED, false>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
+                                                  (N + 15) >> 4, big, small, db);
     float *out = (float *)pf.out;
-    if constexpr (ONE) {
-        xfc_combine(red, big, small, [&](int r, int c, float v) {
-            const int o = m0 + r, n = n0 + c;
-            if (o >= O || n >= I) return;
-            const size_t at = (size_t)o * I + n;
-            out[at] = pf.alpha * v + (pf.beta != 0.f ? pf.beta * out[at] : 0.f);
-        });
-        if (do_db) {
-            __syncthreads();                                     // everyone has read the tile's sums
-#pragma unroll
-            for (int i = 0; i < 2; i++) red[wave * 128 + i * 64 + lane] = db[i];
-            __syncthreads();
-            const int tid = threadIdx.x, o = m0 + tid;
-            if (tid < 64 && o < O) {
-                float v = 0.f;
-                for (int w = 0; w < 4; w++) v += red[w * 128 + (tid >> 5) * 64 + (tid & 31)] + red[w * 128 + (tid >> 5) * 64 + 32 + (tid & 31)];
-                pf.dbias[o] = pf.alpha * v + (pf.beta != 0.f ? pf.beta * pf.dbias[o] : 0.f);
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-            const int n = n0 + j * 32 + li;
-            if (n >= I) continue;
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int o = m0 + i * 32 + 8 * (e / 4) + 4 * lh + e % 4;
-                if (o >= O) continue;
-                const size_t at = (size_t)o * I + n;
-                out[at] = pf.alpha * (big[i][j][e] + small[i][j][e]) + (pf.beta != 0.f ? pf.beta * out[at] : 0.f);
-            }
-        }
+    xfc_combine(red, big, small, [&](int r, int c, float v) {
+        const int o = m0 + r, n = n0 + c;
+        if (o >= O || n >= I) return;
+        const size_t at = (size_t)o * I + n;
+        out[at] = pf.alpha * v + (pf.beta != 0.f ? pf.beta * out[at] : 0.f);
+    });
     if (do_db) {
+        __syncthreads();                                         // everyone has read the tile's sums
 #pragma unroll
-        for (int i = 0; i < 2; i++) {
-            const float v = db[i] + __shfl_xor(db[i], 32);
-            const int o = m0 + i * 32 + li;
-            if (lh == 0 && o < O) pf.dbias[o] = pf.alpha * v + (pf.beta != 0.f ? pf.beta * pf.dbias[o] : 0.f);
+        for (int i = 0; i < 2; i++) red[wave * 128 + i * 64 + lane] = db[i];
+        __syncthreads();
+        const int o = m0 + tid;
+        if (tid < 64 && o < O) {
+            float v = 0.f;
+            for (int w = 0; w < 4; w++) v += red[w * 128 + (tid >> 5) * 64 + (tid & 31)] + red[w * 128 + (tid >> 5) * 64 + 32 + (tid & 31)];
+            pf.dbias[o] = pf.alpha * v + (pf.beta != 0.f ? pf.beta * pf.dbias[o] : 0.f);
         }
     }
 }

@@ -16,12 +16,12 @@ static hipError_t fwd(const GemmParams &p, hipStream_t s)
     return e;
 }
 
-template <bool BF, bool ONE>
+template <bool BF>
 static hipError_t bwd(const GemmParams &pd, const GemmParams &pf, hipStream_t s)
 {
-    const int wgs = pd.tiles_m * pd.tiles_n + pf.tiles_m * (ONE ? pf.tiles_n : (pf.tiles_n + 3) / 4);
-    if (pf.mask) hipLaunchKernelGGL((xfc_bwd_kernel<BF, true, ONE>), dim3(wgs), dim3(256), 0, s, pd, pf);
-    else hipLaunchKernelGGL((xfc_bwd_kernel<BF, false, ONE>), dim3(wgs), dim3(256), 0, s, pd, pf);
+    const int wgs = pd.tiles_m * pd.tiles_n + pf.tiles_m * pf.tiles_n;
+    if (pf.mask) hipLaunchKernelGGL((xfc_bwd_kernel<BF, true>), dim3(wgs), dim3(256), 0, s, pd, pf);
+    else hipLaunchKernelGGL((xfc_bwd_kernel<BF, false>), dim3(wgs), dim3(256), 0, s, pd, pf);
     return hipGetLastError();
 }
 
@@ -36,9 +36,7 @@ hipError_t owt_launch_xfc_bwd(bool bf16, const GemmParams *pd, const GemmParams 
     if (pd) d = *pd;
     else { d = *pf; d.tiles_m = 0; }
     if (pd && pf && (pd->M != pf->Kd || pd->Kd != pf->M || pd->Ncols != pf->Ncols || pd->mask != pf->mask)) return hipErrorInvalidValue;
-    // a work-group per tile of dw up to kXFcOneTiles tiles, a wavefront beyond
-    if ((long)f.tiles_m * f.tiles_n <= kXFcOneTiles) return bf16 ? bwd<true, true>(d, f, s) : bwd<false, true>(d, f, s);
-    return bf16 ? bwd<true, false>(d, f, s) : bwd<false, false>(d, f, s);
+    return bf16 ? bwd<true>(d, f, s) : bwd<false>(d, f, s);
 }
 
 }  // namespace owt

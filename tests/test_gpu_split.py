@@ -298,7 +298,7 @@ def test_split_filter_gradient_of_any_geometry(variant, split):
 
 
 # N, I, O: single values, one step and tile less, exactly and more than full, odd rows (2-byte aligned in bf16), more tiles
-# of dw than CUs (a wavefront per tile)
+# than CUs
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("split", [1, 3])
 def test_fully_connected_shard_on_the_bf16_matrix_unit(dt, split):
