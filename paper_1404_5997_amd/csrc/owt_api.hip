@@ -1176,7 +1176,7 @@ static owt_status conv_pass(const Geom &g, int pass, owt_dtype dt, const GemmPar
                             void *ws, size_t ws_bytes, hipStream_t s, bool use_cache)
 {
     const PassDims dm = conv_dims(g, pass);
-    const Launch l = choose(g, pass, dt, dm, want_db, use_cache, ws ? ws_bytes : 0);
+    const Launch l = choose(g, pass, dt, dm, want_db, use_cache, ws && aligned16(ws) ? ws_bytes : 0);
     OWT_TRY(check_ws(l, ws, ws_bytes));
     return launch(g, pass, dt, dm, p, l, ws, s);
 }
@@ -1488,6 +1488,9 @@ owt_status owt_conv_autotune(const owt_conv_desc *d, int pass, const void *x, co
     const PassDims dm = conv_dims(g, pass);
     std::vector<Launch> c;
     enumerate(g, pass, dm, pass == OWT_PASS_BWD_FILTER, c);
+    // as a call does (choose()), tuning passes over split-operand plans that the scratch is too small for
+    const size_t usable = ws && aligned16(ws) ? ws_bytes : 0;
+    c.erase(std::remove_if(c.begin(), c.end(), [&](const Launch &l) { return is_split_kind(l.kind) && l.ws_bytes() > usable; }), c.end());
     for (const Launch &l : c) OWT_TRY(check_ws(l, ws, ws_bytes));
     hipStream_t s = (hipStream_t)hip_stream;
     if (c.empty()) return fail(OWT_EUNSUPPORTED, "no kernel variant for this geometry");

@@ -140,6 +140,25 @@ def test_calls_with_the_scratch_of_the_fp32_kernels_still_run():
     assert np.array_equal(outs[need][0], outs[need][1])
 
 
+def test_tuning_without_scratch_and_calls_with_unaligned_scratch_still_run():
+    # the fp32 kernels need no workspace for this layer: tuning without one, and a pointer the split kernels cannot use
+    m = owt()
+    N, C, H, W, K, R, S, pad = shape = (1, 8, 6, 7, 8, 3, 3, 1)
+    x, w, b, dy, y = tensors(shape, 955)
+    case = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", True, True)
+    ref = oracle.conv_fwd(x, w, b, 1, pad, True)
+    out, args = empty(case.shape_y), (to_dev(x), to_dev(w), to_dev(b))
+    m.owt_conv_fwd(case.desc, *args, out, workspace(m.owt_conv_workspace_bytes(case.desc, 0) + 16)[4:])
+    torch.cuda.synchronize()
+    assert np.max(np.abs(to_host(out) - ref)) <= 1e-4 * np.max(np.abs(ref))
+    m.owt_conv_autotune(case.desc, 0, *args, out, None, None, None, None)
+    assert not m.owt_conv_plan_describe(case.desc, 0).startswith("xconv")
+    out.fill_(float("nan"))
+    m.owt_conv_fwd(case.desc, *args, out)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(to_host(out) - ref)) <= 1e-4 * np.max(np.abs(ref))
+
+
 # N, C, H, W, K, R, S, pad: fewer than 16 images, one more than 16, three groups; ragged filters and channels; rows of one
 # and of two positions, filter rows that meet no output row (H = 1), filter height 1, an even number of taps left out by
 # the borders, no padding
