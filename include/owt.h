@@ -22,13 +22,16 @@
  *    default stream) and the call returns without waiting for it.
  *  - `ws` is caller-provided device scratch of at least the number of bytes the
  *    matching *_workspace_bytes query returns (may be NULL when that is 0).
- *    Its contents are undefined after the call.
+ *    Its contents are undefined after the call.  An fp32 convolution that is
+ *    given less runs on a kernel that fits, where there is one.
  *  - Return value OWT_OK, or an error code; on error nothing was launched and
  *    no output was touched.  owt_last_error() gives a message for the calling
  *    thread's most recent error.
  *  - Results are deterministic run to run (no floating-point atomics).
  *  - dtype names the STORAGE type of x, w, y, dy, dx.  Products are
- *    accumulated in fp32; bias, dw and dbias are always fp32.  bf16 results are
+ *    accumulated in fp32 (fp32 operands may be multiplied as sums of three bf16
+ *    values that hold every bit of them; the error against exact products is
+ *    below that of the fp32 matrix instruction); bias, dw and dbias are always fp32.  bf16 results are
  *    rounded to nearest-even once, when stored.
  *  - Output size P = floor((H + 2*pad_h - R)/stride_h) + 1, Q likewise.
  */
@@ -169,8 +172,8 @@ owt_status owt_fc_shard_fwd(const owt_fc_desc *d, const void *x, const void *w, 
  *   dw[o,i] = alpha * sum_n dz[n,o] * x[n,i] + beta * dw;   dbias[o] likewise (NULL to skip)
  * dy, y [N,O_local]; dx_partial [N,I]; dw [O_local,I] fp32; dbias [O_local] fp32.
  * ws (owt_fc_workspace_bytes of pass OWT_PASS_BWD_DATA; that figure covers both
- * products) holds a masked, zero-padded copy of dz and the partial sums of a split
- * reduction while the call runs. */
+ * products) holds the partial sums of a split reduction and, for some kernels, a
+ * masked, zero-padded copy of dz while the call runs. */
 owt_status owt_fc_shard_bwd(const owt_fc_desc *d, const void *x, const void *w, const void *y_or_null,
                             const void *dy, float alpha, float beta, void *dx_partial_or_null,
                             float *dw, float *dbias_or_null, void *ws, size_t ws_bytes,
@@ -259,7 +262,9 @@ const char *owt_last_error(void);
  * gradient with the pixel split inside the work-group, 16..19 the dense shard kernel's four tiles, 20/21 and
  * 22/23 the two fp32 first-layer forward / filter-gradient kernels, 24/25 the two bf16 first-layer
  * filter-gradient kernels, 30..36 the bf16 filter gradient that
- * streams its operands into LDS), `splitk` > 0 forces the
+ * streams its operands into LDS; fp32 with split operands on the bf16 matrix unit: 40..43 stride-1 forward /
+ * backward-data and strided forward, 50/51 stride-1 filter gradient, 60/61 filter gradient of any geometry,
+ * 70 the dense shard, both storage types), `splitk` > 0 forces the
  * split count of the reduction (clamped to the number of reduction steps), `flags` is a set of
  * OWT_FORCE_* bits.  While an override is active, tuned and cached plans are ignored.  The three
  * values are stored atomically, but a launch that runs concurrently with this call may see the old

@@ -1,7 +1,7 @@
 """Builds libowt.so (HIP, gfx950 only) in-tree with hipcc.
 
-The implicit-GEMM kernels are instantiated once per (pass, storage type) in
-separate objects so the six compile in parallel.
+Kernels that exist per pass, storage type or load width are instantiated once per
+combination in separate objects, which compile in parallel.
 """
 import os
 import subprocess
@@ -13,7 +13,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libowt.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-# packed-fp32 VALU forms are switched off on purpose (they have misbehaved on the test machines)
+# packed-fp32 VALU forms are switched off on purpose (they have misbehaved on this hardware)
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
