@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, co
                                                  (O + 15) >> 4, big, small, db);
         xfc_combine(red, big, small, [&](int r, int c, float v) {
             const int m = m0 + r, n = n0 + c;
-            if (m < N && n < I) store1((T *)pd.out, (size_t)m * I + n, v);
+            if (m < N && n < I) store1((T *)pd.out, (size_t)m * I + n, EpiData<T>::op(pd, m, n, v));
         });
         return;
     }

@@ -89,6 +89,34 @@ def test_split_convolution_with_the_mask_of_the_layer_below():
             check(to_host(dx), ref, size, R * S * K, "dx masked by x > 0")
 
 
+# N, C, K of 1x1 maps, where backward-data is a plain matrix product: less than a tile, ragged, more than a tile
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("tile", [-1, 70])
+@pytest.mark.parametrize("N,C,K", [(1, 1, 1), (37, 100, 72), (128, 256, 256), (70, 132, 20)])
+def test_mask_of_the_layer_below_on_maps_of_one_pixel(dt, tile, N, C, K):
+    m = owt()
+    rnd = oracle.round_bf16 if dt == "bf16" else (lambda a: a)
+    g = np.random.default_rng(935)
+    x, dy, y = (rnd(g.standard_normal(s, dtype=np.float32)) for s in ((N, 1, 1, C), (N, 1, 1, K), (N, 1, 1, K)))
+    w = rnd(g.standard_normal((K, 1, 1, C), dtype=np.float32))
+    x[0, 0, 0, 0] = -1.0
+    for relu in (False, True):
+        case = ConvCase(N, C, 1, 1, K, 1, 1, 1, 0, dt, True, relu)
+        dz = dy * (y > 0) if relu else dy
+        f64 = lambda a: a.reshape(a.shape[0], -1).astype(np.float64)
+        ref = f64(dz) @ f64(w) * (f64(x) > 0)
+        with force(tile):
+            print("case", dt, (N, C, K), "relu", relu, m.owt_conv_plan_describe(case.desc, 1))
+            sys.stdout.flush()
+            dx = empty(case.shape_x, dt)
+            m.owt_conv_bwd_data_relu_in(case.desc, to_dev(dy, dt), to_dev(y, dt) if relu else None, to_dev(w, dt), to_dev(x, dt), dx, case.ws(1))
+            torch.cuda.synchronize()
+        got = to_host(dx).reshape(N, C)
+        bound = (K / 16 + 16) * 2.0 ** -24 * (np.abs(f64(dz)) @ np.abs(f64(w))) + (2.0 ** -8 * np.abs(ref) if dt == "bf16" else 0.0) + 1e-30
+        assert np.max(np.abs(got - ref) / bound) <= 1.0
+        assert not got[f64(x) <= 0].any()
+
+
 def test_split_products_keep_infinities_nans_and_the_ends_of_the_range():
     # an infinite, a NaN and two finite values beyond the largest bf16 among the inputs, tiny values elsewhere: every
     # output is what fp32 products give -- the infinity of the right sign, NaN where a NaN enters, finite otherwise
