@@ -368,6 +368,17 @@ static double model_cost(long wgs, int waves_per_wg, int occ, double macs_per_wg
 
 static const size_t kMaxPartialBytes = (size_t)192 << 20;
 
+// The filter-gradient kernels that take 16 images per matrix instruction form 32-bit byte offsets for whole groups of 16 and
+// leave it to the buffer descriptor to read the images past the last as zeros, so no offset may come round past 2^32 into the
+// tensor again.  xfilter: every image of the last group, and up to 1 KB past its end for a ragged tile.  xgather: also a place
+// outside the image, which gets the offset N * image, at the first seven images of the last group's second half.
+static bool image_groups_fit(const Geom &g, bool xgather)
+{
+    const double groups = 16.0 * (double)cdiv(g.N, 16), images = xgather && g.N + groups - 9.0 > groups ? g.N + groups - 9.0 : groups;
+    const double x = (double)g.H * g.W * g.C * 4.0, z = (double)g.P * g.Q * g.K * 4.0;
+    return g.N * x < 2147483644.0 && g.N * z < 2147483644.0 && images * x + 1024.0 <= 4294967296.0 && images * z + 1024.0 <= 4294967296.0;
+}
+
 // What owt_test_force_variant asked for (tests only; -1 / 0 = the planner decides).
 static std::atomic<int> g_force_tile{-1}, g_force_split{-1};
 static std::atomic<unsigned> g_force_flags{0};
@@ -605,7 +616,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // fp32 storage on the bf16 matrix unit with split operands: stride 1, one wavefront per (filters, channels, filter row);
     // the bias gradient is summed by the filter row that meets every output row, which there is when P <= H
     if (pass == OWT_PASS_BWD_FILTER && !g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
-        (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull) {
+        image_groups_fit(g, false)) {
         for (int v = 0; v < kNumXFilterVariants; v++) {
             const XFilterVariant &xv = kXFilterVariants[v];
             if ((force_tile >= 0 && force_tile != kXFilterFirstTile + v) || g.S != xv.S) continue;
@@ -637,7 +648,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // the same for any geometry, columns packed densely (not the fully-connected shard, whose two backward products share
     // a launch)
     if (pass == OWT_PASS_BWD_FILTER && !g.bf16 && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
-        (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull) {
+        image_groups_fit(g, true)) {
         for (int v = 0; v < kNumXGatherVariants; v++) {
             const XGatherVariant &xv = kXGatherVariants[v];
             if (force_tile >= 0 && force_tile != kXGatherFirstTile + v) continue;

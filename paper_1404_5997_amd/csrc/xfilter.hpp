@@ -88,7 +88,8 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
 
     const unsigned imgx = (unsigned)(g.H * g.W * g.C) * 4u, imgz = (unsigned)(g.P * Q * g.K) * 4u;
     const unsigned xall = imgx * (unsigned)g.N, zall = imgz * (unsigned)g.N;
-    // Byte offsets of a lane's eight images.  Images past the last are past the descriptor and read as zeros; channels and
+    // Byte offsets of a lane's eight images.  Images past the last are past the descriptor and read as zeros (the host has
+    // checked that no offset of a group of 16 wraps round); channels and
     // filters past a ragged tile read whatever is there (inside the tensor, or zeros past its end) and only reach
     // accumulator rows and columns that are never stored.
     unsigned xo[8], zo[8];

@@ -26,7 +26,6 @@ template <int KB, int CB, bool MASKED>
 __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
 {
     constexpr int M = 6 * KB * CB, F = KB + CB;    // matrix instructions and fragments per position
-    constexpr unsigned OOB = 0x80000000u;
 
     const Geom &g = p.g;
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
@@ -39,8 +38,11 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
     const int o_beg = min(total, split * p.ksteps_per_split), o_end = min(total, o_beg + p.ksteps_per_split);
 
     const unsigned imgx = (unsigned)(g.H * g.W * g.C) * 4u, imgz = (unsigned)(P * Q * g.K) * 4u;
-    const __amdgpu_buffer_rsrc_t xrs = owt_make_rsrc(p.b, imgx * (unsigned)g.N), zrs = owt_make_rsrc(p.a, imgz * (unsigned)g.N);
-    const __amdgpu_buffer_rsrc_t yrs = owt_make_rsrc(MASKED ? p.mask : p.a, imgz * (unsigned)g.N);
+    // what must read as zero gets an offset of xall or zall, the end of its tensor; with the scalar part added it stays below
+    // 2^32 (host-checked)
+    const unsigned xall = imgx * (unsigned)g.N, zall = imgz * (unsigned)g.N;
+    const __amdgpu_buffer_rsrc_t xrs = owt_make_rsrc(p.b, xall), zrs = owt_make_rsrc(p.a, zall);
+    const __amdgpu_buffer_rsrc_t yrs = owt_make_rsrc(MASKED ? p.mask : p.a, zall);
 
     // This lane's places: byte offset from the window's corner (of the image 8*lh past the group's first), filter row and
     // column.  A place past the last is far outside every image.  Images past the last and filters past a ragged tile:
@@ -85,15 +87,15 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
             const int h0 = pp * g.sh - g.ph, w0 = qq * g.sw - g.pw;
             const bool live = o < o_end;
             // the corner may lie outside the image: its offset is folded into the lanes' part, modulo 2^32
-            xoff = (unsigned)n0 * imgx;
+            xoff = live ? (unsigned)n0 * imgx : 0u;
             const int corner = (h0 * g.W + w0) * g.C * 4;
 #pragma unroll
             for (int cb = 0; cb < CB; cb++) {
                 const bool in = (unsigned)(h0 + cr[cb]) < (unsigned)g.H && (unsigned)(w0 + cs[cb]) < (unsigned)g.W;
-                place[cb] = live && in ? (unsigned)(coff[cb] + corner) : OOB;
+                place[cb] = live && in ? (unsigned)(coff[cb] + corner) : xall;
             }
-            zoff = (unsigned)n0 * imgz + (unsigned)((pp * Q + qq) * g.K) * 4u;
-            zbase = live ? (int)zo : (int)OOB;
+            zoff = live ? (unsigned)n0 * imgz + (unsigned)((pp * Q + qq) * g.K) * 4u : 0u;
+            zbase = (int)(live ? zo : zall);
             o++;
             const bool row_end = qq + 1 == Q, image_end = row_end && pp + 1 == P;
             qq = row_end ? 0 : qq + 1;

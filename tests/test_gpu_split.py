@@ -344,6 +344,48 @@ def test_split_filter_gradient_of_any_geometry(variant, split):
             check(db, rdb, sdb, L, "db", norm_too=False)
 
 
+# N, C, H, W, K, tile: images of which some past the last would come round to an offset inside the tensor (default plan:
+# a kernel that does not address 16 at a time), and tensors of nearly 2^31 bytes whose missing images lie past 2^31 (x, then dz)
+@pytest.mark.parametrize("N,C,H,W,K,R,tile", [(3, 16, 2100, 2200, 1, 3, -1), (3, 1, 2100, 2200, 16, 3, -1), (3, 1, 4200, 4300, 4, 5, -1),
+                                              (17, 32, 992, 992, 4, 3, 50), (17, 4, 992, 992, 32, 3, 50),
+                                              (24, 20, 1000, 1100, 3, 3, 61), (24, 3, 1000, 1100, 20, 3, 61)])
+def test_split_filter_gradient_of_large_images(N, C, H, W, K, R, tile):
+    m = owt()
+    g = torch.Generator(device="cuda").manual_seed(1060)
+    x = torch.randn((N, H, W, C), generator=g, device="cuda")
+    dy = torch.randn((N, H, W, K), generator=g, device="cuda")
+    d = m.conv_desc(N, C, H, W, K, R, R, 1, R // 2, m.OWT_F32, m.OWT_BIAS)
+    dw, db = empty((K, R, R, C)), empty((K,))
+    with force(tile):
+        plan = m.owt_conv_plan_describe(d, 2)
+        print("case", (N, C, H, W, K, R), plan)
+        sys.stdout.flush()
+        assert plan.startswith(("xfilter", "xgather")) == (tile >= 0), plan
+        m.owt_conv_bwd_filter(d, x, dy, None, 1.0, 0.0, dw, db, workspace(m.owt_conv_workspace_bytes(d, 2)))
+        torch.cuda.synchronize()
+    ref, rdb = torch.zeros((K, R, R, C), device="cuda", dtype=torch.float64), torch.zeros((K,), device="cuda", dtype=torch.float64)
+    pad = R // 2
+    for n in range(N):
+        xp = torch.zeros((H + 2 * pad, W + 2 * pad, C), device="cuda", dtype=torch.float64)
+        xp[pad:pad + H, pad:pad + W] = x[n]
+        z = dy[n].double().view(-1, K)
+        rdb += z.sum(0)
+        for r in range(R):
+            for s in range(R):
+                xs = xp[r:r + H, s:s + W].reshape(-1, C)
+                if K < C:                                         # (a product this long and narrow is slow)
+                    ref[:, r, s] += torch.stack([(xs * z[:, k:k + 1]).sum(0) for k in range(K)])
+                else:
+                    ref[:, r, s] += torch.stack([(z * xs[:, c:c + 1]).sum(0) for c in range(C)], 1)
+    # sums of L products of independent normal values are sqrt(L) large and their rounding errors at most 2^-24 sqrt(L) each
+    # time a partial sum is rounded, L/16 times at random: 2^-24 L/4 absolute.  One image too many moves them by sqrt(L/N).
+    L = N * H * W
+    bound = max(2.0 ** -24 * L / 4, 1e-3)
+    assert bound < 0.1 * np.sqrt(L / N)
+    assert (dw - ref).abs().max().item() <= bound and (db - rdb).abs().max().item() <= bound
+    print("  largest error %.3f and %.3f of the bound" % ((dw - ref).abs().max().item() / bound, (db - rdb).abs().max().item() / bound))
+
+
 # N, I, O: single values, one step and tile less, exactly and more than full, odd rows (2-byte aligned in bf16), more tiles
 # than CUs
 @pytest.mark.parametrize("dt", ["f32", "bf16"])

@@ -1,0 +1,56 @@
+"""The planner's choices and refusals, without a GPU: which kernel a geometry gets, what a call with little scratch is
+served by, what the workspace queries ask for."""
+import pytest
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_1404_5997_amd as mod
+    return mod
+
+
+def plan(m, shape, p, relu=False, dtype=0):
+    N, C, H, W, K, R, S, stride, pad = shape
+    return m.owt_conv_plan_describe(m.conv_desc(N, C, H, W, K, R, S, stride, pad, dtype, m.OWT_BIAS | (m.OWT_RELU if relu else 0)), p)
+
+
+def wraps(images, image_bytes, all_bytes):
+    """Does an image past the last, addressed in 32 bits, land inside the tensor again?"""
+    return any((n * image_bytes) % 2 ** 32 < all_bytes for n in range(images, 16 * ((images + 15) // 16)))
+
+
+# N, C, H, W, K, R, S, stride, pad: images of more than 2^32 / 15 bytes, where some image of the last group of 16 comes round
+WRAPPING = [(7, 64, 1024, 1100, 64, 3, 3, 1, 1), (6, 64, 1152, 1152, 64, 3, 3, 1, 1), (5, 64, 1280, 1280, 64, 3, 3, 1, 1),
+            (4, 64, 1408, 1408, 64, 3, 3, 1, 1), (7, 128, 768, 768, 128, 3, 3, 1, 1), (7, 512, 384, 384, 512, 3, 3, 1, 1),
+            (3, 37, 2100, 2100, 37, 3, 3, 1, 1), (7, 64, 1080, 1080, 64, 1, 1, 1, 0), (4, 32, 1536, 1500, 32, 3, 3, 1, 1),
+            (3, 10, 4000, 4000, 10, 3, 3, 1, 1), (7, 2, 1080, 1080, 64, 3, 3, 1, 1), (7, 64, 1080, 1080, 2, 3, 3, 1, 1),
+            (2, 3, 6000, 6000, 7, 5, 5, 1, 2)]
+
+
+@pytest.mark.parametrize("shape", WRAPPING)
+def test_large_images_stay_off_the_kernels_that_address_16_at_a_time(m, shape):
+    N, C, H, W, K, R, S, stride, pad = shape
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    assert wraps(N, H * W * C * 4, N * H * W * C * 4) or wraps(N, P * Q * K * 4, N * P * Q * K * 4)
+    for relu in (False, True):
+        for tile in (-1, 50, 51, 60, 61):
+            m.owt_test_force_variant(tile, 0, 0)
+            try:
+                p = plan(m, shape, 2, relu)
+            finally:
+                m.owt_test_force_variant(-1, 0, 0)
+            assert not p.startswith(("xfilter", "xgather", "sfilterx")), (tile, p)
+
+
+def test_images_that_do_not_wrap_keep_those_kernels(m):
+    for tile, kernel, shape in ((50, "xfilter", (8, 64, 1000, 1040, 64, 3, 3, 1, 1)), (50, "xfilter", (1, 64, 1000, 1040, 64, 3, 3, 1, 1)),
+                                (50, "xfilter", (17, 32, 992, 992, 4, 3, 3, 1, 1)), (60, "xgather", (24, 32, 800, 860, 32, 3, 3, 1, 1)),
+                                (61, "xgather", (16, 5, 2000, 2100, 7, 3, 3, 1, 1))):
+        N, C, H, W, K = shape[:5]
+        assert not wraps(N, H * W * C * 4, N * H * W * C * 4) and not wraps(N, H * W * K * 4, N * H * W * K * 4)
+        m.owt_test_force_variant(tile, 0, 0)
+        try:
+            assert plan(m, shape, 2).startswith(kernel), shape
+        finally:
+            m.owt_test_force_variant(-1, 0, 0)
+    assert plan(m, (8, 64, 1000, 1040, 64, 3, 3, 1, 1), 2).startswith("xfilter")
