@@ -912,13 +912,17 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
     enumerate(g, pass, dm, want_db, c);
     bool only_direct = forced(OWT_FORCE_ONLY_DIRECT), any_direct = false;   // test hook
     for (const Launch &l : c) any_direct |= l.kind != KIND_GATHER;
-    size_t best = c.size();
+    // `fits`: the cheapest of those that may be taken; `any`: the scratch left out of account, for the caller's check to refuse
+    // where nothing fits (the test hook can leave a geometry with split-operand kernels alone)
+    size_t fits = c.size(), any = c.size();
     bool shrunk = false;
     for (size_t i = 0; i < c.size(); i++) {
         if (only_direct && any_direct && c[i].kind == KIND_GATHER) continue;
+        if (any == c.size() || c[i].cost < c[any].cost) any = i;
         if (is_split_kind(c[i].kind) && c[i].ws_bytes() > ws_bytes) { shrunk = true; continue; }
-        if (best == c.size() || c[i].cost < c[best].cost) best = i;
+        if (fits == c.size() || c[i].cost < c[fits].cost) fits = i;
     }
+    const size_t best = fits < c.size() ? fits : any;
     if (cached && !shrunk) {
         std::lock_guard<std::mutex> lk(g_tuned_mutex);
         g_modelled[plan_key(g, pass, dt)] = c[best];

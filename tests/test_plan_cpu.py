@@ -54,3 +54,33 @@ def test_images_that_do_not_wrap_keep_those_kernels(m):
         finally:
             m.owt_test_force_variant(-1, 0, 0)
     assert plan(m, (8, 64, 1000, 1040, 64, 3, 3, 1, 1), 2).startswith("xfilter")
+
+
+# the 1x1 filter has no kernel but those and the gather kernel, which flag 2 (only the direct kernels) leaves out
+@pytest.mark.parametrize("tile,flags,shape", [(t, 0, (2, 32, 13, 13, 64, 3, 3, 1, 1)) for t in (40, 41, 43, 50, 61)] +
+                         [(40, 2, (2, 32, 13, 13, 64, 3, 3, 1, 1)), (-1, 2, (2, 32, 13, 13, 64, 1, 1, 1, 0)), (70, 0, (20, 512, 1, 1, 64, 1, 1, 1, 0))])
+def test_split_kernels_left_alone_without_their_scratch_are_refused_with_their_need(m, tile, flags, shape):
+    N, C, H, W, K, R, S, stride, pad = shape
+    d = m.conv_desc(N, C, H, W, K, R, S, stride, pad, 0, m.OWT_BIAS)
+    refused = 0
+    for split in (1, 2):
+        for p in range(3):
+            m.owt_test_force_variant(tile, split, flags)
+            try:
+                name, bound = m.owt_conv_plan_describe(d, p), m.owt_conv_workspace_bytes(d, p)
+                # those that need none: the filter gradients and the shard's forward pass unsplit, the shard's backward pass
+                if name.startswith("xconv") or (name.startswith(("xfilter", "xgather", "xfc fwd")) and split == 2):
+                    with pytest.raises(m.OwtError) as ei:
+                        if p == 0:
+                            m.owt_conv_fwd(d, 256, 512, 768, 1024, None, 0)
+                        elif p == 1:
+                            m.owt_conv_bwd_data(d, 256, None, 512, 1024, None, 0)
+                        else:
+                            m.owt_conv_bwd_filter(d, 256, 512, None, 1.0, 0.0, 1024, 768, None, 0)
+                    assert ei.value.status == m.OWT_EWORKSPACE, str(ei.value)
+                    need = int(str(ei.value).split("need ")[1].split()[0])
+                    assert 0 < need <= bound, str(ei.value)
+                    refused += 1
+            finally:
+                m.owt_test_force_variant(-1, 0, 0)
+    assert refused
