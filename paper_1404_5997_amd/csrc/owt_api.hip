@@ -894,6 +894,10 @@ static bool variants_forced()
 
 static std::map<PlanKey, Launch> g_modelled;   // the cost model's choice per geometry (untimed), so that a call plans once
 
+// The model's choice for scratch too small for some of the split-operand plans: any size in [lo, hi) admits the same plans.
+struct SmallScratchPlan { size_t lo, hi; Launch l; };
+static std::map<PlanKey, SmallScratchPlan> g_modelled_small;   // the last one per geometry
+
 // ws_bytes: the scratch the call was given.  A plan of the kernels that split their operands is passed over when its
 // scratch does not fit, so a caller that sized its scratch for the kernels that multiply in fp32 is served by those.
 static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, bool want_db, bool use_cache, size_t ws_bytes = (size_t)-1)
@@ -907,6 +911,8 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
         const bool tuned = it != g_tuned.end();
         it = g_modelled.find(plan_key(g, pass, dt));
         if (!tuned && it != g_modelled.end() && fits(it->second)) return it->second;
+        auto sm = g_modelled_small.find(plan_key(g, pass, dt));
+        if (sm != g_modelled_small.end() && sm->second.lo <= ws_bytes && ws_bytes < sm->second.hi) return sm->second.l;
     }
     std::vector<Launch> c;
     enumerate(g, pass, dm, want_db, c);
@@ -915,17 +921,22 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
     // `fits`: the cheapest of those that may be taken; `any`: the scratch left out of account, for the caller's check to refuse
     // where nothing fits (the test hook can leave a geometry with split-operand kernels alone)
     size_t fits = c.size(), any = c.size();
-    bool shrunk = false;
+    SmallScratchPlan small = {0, (size_t)-1, {}};
     for (size_t i = 0; i < c.size(); i++) {
         if (only_direct && any_direct && c[i].kind == KIND_GATHER) continue;
         if (any == c.size() || c[i].cost < c[any].cost) any = i;
-        if (is_split_kind(c[i].kind) && c[i].ws_bytes() > ws_bytes) { shrunk = true; continue; }
+        if (is_split_kind(c[i].kind)) {
+            const size_t need = c[i].ws_bytes();
+            if (need > ws_bytes) { small.hi = std::min(small.hi, need); continue; }
+            small.lo = std::max(small.lo, need);
+        }
         if (fits == c.size() || c[i].cost < c[fits].cost) fits = i;
     }
     const size_t best = fits < c.size() ? fits : any;
-    if (cached && !shrunk) {
+    if (cached) {
         std::lock_guard<std::mutex> lk(g_tuned_mutex);
-        g_modelled[plan_key(g, pass, dt)] = c[best];
+        if (small.hi == (size_t)-1) g_modelled[plan_key(g, pass, dt)] = c[best];
+        else { small.l = c[best]; g_modelled_small[plan_key(g, pass, dt)] = small; }
     }
     return c[best];
 }

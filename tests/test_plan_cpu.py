@@ -1,5 +1,8 @@
 """The planner's choices and refusals, without a GPU: which kernel a geometry gets, what a call with little scratch is
 served by, what the workspace queries ask for."""
+import ctypes
+import time
+
 import pytest
 
 
@@ -84,3 +87,40 @@ def test_split_kernels_left_alone_without_their_scratch_are_refused_with_their_n
             finally:
                 m.owt_test_force_variant(-1, 0, 0)
     assert refused
+
+
+def fastest(call, rounds=20, calls=100):
+    best = float("inf")
+    for _ in range(rounds):
+        t = time.perf_counter()
+        for _ in range(calls):
+            call()
+        best = min(best, (time.perf_counter() - t) / calls)
+    return best
+
+
+def test_calls_with_little_scratch_plan_once(m):
+    # what such a call runs is remembered, as for any other call: one that is refused (the fp32 kernel that it falls to splits
+    # its reduction and needs more than 4 KB, so no launch comes into it) costs about what a query of the plan costs (1-2 us),
+    # not a listing of the candidates (8-22 us)
+    for shape in ((1, 64, 56, 56, 64, 3, 3, 1, 1), (16, 128, 56, 56, 128, 3, 3, 1, 1), (128, 64, 27, 27, 192, 5, 5, 1, 2)):
+        N, C, H, W, K, R, S, stride, pad = shape
+        d, text = m.conv_desc(N, C, H, W, K, R, S, stride, pad, 0, m.OWT_BIAS), ctypes.create_string_buffer(256)
+
+        def call(nbytes=4096):
+            return m._lib.owt_conv_bwd_filter(ctypes.byref(d), 256, 512, None, 1.0, 0.0, 1024, 768, 4096, nbytes, 0)
+
+        def need(nbytes):
+            m.owt_test_force_variant(-1, 0, m.OWT_FORCE_NO_BF16_MFMA)
+            try:
+                assert "splitk1 " not in plan(m, shape, 2), shape
+            finally:
+                m.owt_test_force_variant(-1, 0, 0)
+            assert call(nbytes) == m.OWT_EWORKSPACE
+            return int(m.owt_last_error().split("need ")[1].split()[0])
+
+        full = plan(m, shape, 2)
+        first = need(4096)
+        assert fastest(call) < 2 * fastest(lambda: m._lib.owt_conv_plan_describe(ctypes.byref(d), 2, text, 256)) + 1e-6
+        # the size still decides, whatever was asked before
+        assert need(16) == first and need(4096) == first and plan(m, shape, 2) == full
