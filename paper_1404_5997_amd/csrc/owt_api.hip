@@ -943,7 +943,24 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
 
 static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per geometry: listing the candidates takes 10-60 us
 
-// Workspace every candidate fits in (so a tuned choice never outgrows the caller's buffer).
+// Whether tuning times a candidate, `least` being the cheapest modelled cost, and whether the workspace bound covers it.  Tuned
+// without this rule on the draws of the layers' ranges, the fastest candidate was modelled at up to 2.8 times the cheapest in 418
+// fp32 passes, 1.8 in 200 bf16 passes, 1.6 in 150 of shards, so four times leaves none out; all candidates took 32.7 s to time
+// in the 418 passes, these take 6.8 s.  Split-operand kernels that split their reduction, too, were the fastest up to 1.85
+// times: past twice they only raise the bound (the first layer's forward pass 0.3 -> 199 MB).  choose() sees every candidate.
+static bool worth_timing(const Launch &l, double least)
+{
+    return l.cost <= (is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 4.0) * least;
+}
+static bool worth_workspace(const Launch &l, double least) { return !is_split_kind(l.kind) || l.splits == 1 || worth_timing(l, least); }
+static double least_cost(const std::vector<Launch> &c)
+{
+    double least = c.empty() ? 0.0 : c[0].cost;
+    for (const Launch &l : c) least = std::min(least, l.cost);
+    return least;
+}
+
+// Workspace every candidate that may be tuned to, or is the model's choice, fits in (so neither outgrows the caller's buffer).
 static size_t max_workspace(const Geom &g, int pass, const PassDims &dm, bool want_db)
 {
     // with and without the ReLU' mask flag: a caller may size its buffer with one descriptor of a layer and call
@@ -954,7 +971,9 @@ static size_t max_workspace(const Geom &g, int pass, const PassDims &dm, bool wa
         gm.masked = masked != 0;
         std::vector<Launch> c;
         enumerate(gm, pass, dm, want_db, c);
-        for (const Launch &l : c) m = l.ws_bytes() > m ? l.ws_bytes() : m;
+        const double least = least_cost(c);
+        for (const Launch &l : c)
+            if (worth_workspace(l, least) || variants_forced()) m = l.ws_bytes() > m ? l.ws_bytes() : m;
     }
     return m;
 }
@@ -1370,10 +1389,11 @@ int owt_selftest_host(void)
             enumerate(g, pass, dm, pass == OWT_PASS_BWD_FILTER, c);
             if (c.empty()) { fail(OWT_EINVAL, "no candidate for shape N=%d C=%d pass %d", sh[0], sh[1], pass); return 3; }
             const size_t bound = max_workspace(g, pass, dm, pass == OWT_PASS_BWD_FILTER);
+            const double least = least_cost(c);
             for (const Launch &l : c) {
                 const long parts = (l.kind == KIND_SCONV || l.kind == KIND_SCONV2 || l.kind == KIND_SCONV16) ? l.tiles_n : l.splits;   // who shares the steps
                 if (l.splits < 1 || parts * l.steps_per_split < l.steps ||
-                    (parts - 1) * l.steps_per_split >= l.steps || l.ws_bytes() > bound ||
+                    (parts - 1) * l.steps_per_split >= l.steps || (l.ws_bytes() > bound && worth_workspace(l, least)) ||
                     ((l.kind == KIND_DIRECT || l.kind == KIND_DIRECT16) && (l.pr > 624 || direct_panel_rows(g, pass, dm, kTiles[l.tile].BM) > l.pr))) {
                     fail(OWT_EINVAL, "bad candidate for shape N=%d C=%d pass %d", sh[0], sh[1], pass); return 4;
                 }
@@ -1525,12 +1545,9 @@ owt_status owt_conv_autotune(const owt_conv_desc *d, int pass, const void *x, co
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(OWT_ELAUNCH, "hipEventCreate failed"); }
     int best = -1; float best_ms = 0.f;
     owt_status st = OWT_OK;
-    // candidates that the cost model puts past three times the cheapest are not timed: the model is within a factor of two
-    // (timing all of them, the kernels on the fp32 instruction among them, took a step's tuning from 2.2 to 3.4 s)
-    double least = c[0].cost;
-    for (const Launch &l : c) least = l.cost < least ? l.cost : least;
+    const double least = least_cost(c);
     for (size_t i = 0; i < c.size() && st == OWT_OK; i++) {
-        if (c[i].cost > 3.0 * least) continue;
+        if (!worth_timing(c[i], least) && !variants_forced()) continue;
         st = launch(g, pass, d->dtype, dm, p, c[i], ws, s);                       // warm-up
         if (st != OWT_OK) break;
         // 3 launches; a variant that takes under 50 us is timed again over 12 (launch jitter is a few us)

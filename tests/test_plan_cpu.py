@@ -124,3 +124,21 @@ def test_calls_with_little_scratch_plan_once(m):
         assert fastest(call) < 2 * fastest(lambda: m._lib.owt_conv_plan_describe(ctypes.byref(d), 2, text, 256)) + 1e-6
         # the size still decides, whatever was asked before
         assert need(16) == first and need(4096) == first and plan(m, shape, 2) == full
+
+
+# scratch in MB that the fp32 kernels alone ask for, and the most that may be asked for with the split-operand kernels among
+# the candidates: their split filters, and partial sums only of splits that the model puts within twice its choice
+@pytest.mark.parametrize("shape,p,alone,most", [((128, 3, 224, 224, 64, 11, 11, 4, 2), 0, 0.1, 0.4), ((1, 64, 56, 56, 64, 3, 3, 1, 1), 2, 5.9, 48.0),
+                                                ((16, 256, 14, 14, 256, 1, 1, 1, 0), 0, 12.9, 20.0), ((2, 512, 7, 7, 512, 3, 3, 1, 1), 2, 18.9, 19.0),
+                                                ((7, 64, 1024, 1100, 64, 3, 3, 1, 1), 0, 0.0, 0.0), ((128, 64, 27, 27, 192, 5, 5, 1, 2), 0, 143.3, 146.0)])
+def test_workspace_bounds(m, shape, p, alone, most):
+    N, C, H, W, K, R, S, stride, pad = shape
+    d = m.conv_desc(N, C, H, W, K, R, S, stride, pad, 0, m.OWT_BIAS)
+    bound = m.owt_conv_workspace_bytes(d, p)
+    print(shape, p, bound)
+    assert bound <= most * 1e6
+    m.owt_test_force_variant(-1, 0, m.OWT_FORCE_NO_BF16_MFMA)
+    try:
+        assert m.owt_conv_workspace_bytes(d, p) <= alone * 1e6 + 1e5
+    finally:
+        m.owt_test_force_variant(-1, 0, 0)
