@@ -1251,7 +1251,10 @@ static GemmParams filter_params(const owt_conv_desc *d, const void *x, const voi
 
 // Backward pass of a fully-connected shard when both of its products run on the dense kernel.
 struct FcPair { Launch ld, lf; bool fused, xfc; };
-static std::map<PlanKey, int> g_fc_fused;      // timed by owt_fc_autotune: 1 = one launch for both products
+// How the two products run: each as its own pass, both on the dense kernel in two launches or in one, or in one launch on the
+// bf16 matrix unit.  Untimed, one product that chose the latter takes the other along, and two dense ones share a launch.
+enum { FC_SEPARATE, FC_DENSE_TWO, FC_DENSE_ONE, FC_XFC };
+static std::map<PlanKey, int> g_fc_way;        // timed by owt_fc_autotune
 
 static bool find_fc_launch(const Geom &g, int pass, int kind, int tile, Launch &out)
 {
@@ -1260,6 +1263,34 @@ static bool find_fc_launch(const Geom &g, int pass, int kind, int tile, Launch &
     for (const Launch &l : c)
         if (l.kind == kind && l.tile == tile && l.splits == 1) { out = l; return true; }
     return false;
+}
+
+// The pair of launches for `way` (-1: the model's), false where both products are passes of their own.  Where the plans that
+// the products chose since (tuned alone) no longer allow `way`, the model's.
+static bool fc_pair_of(const Geom &g, owt_dtype dt, int way, FcPair &fp)
+{
+    fp.ld = choose(g, OWT_PASS_BWD_DATA, dt, conv_dims(g, OWT_PASS_BWD_DATA), false, true);
+    fp.lf = choose(g, OWT_PASS_BWD_FILTER, dt, conv_dims(g, OWT_PASS_BWD_FILTER), true, true);
+    fp.fused = fp.xfc = false;
+    const bool dense = fp.ld.kind == KIND_FCGEMM && fp.lf.kind == KIND_FCGEMM;
+    Launch fd, ff;
+    if (way == FC_SEPARATE) return false;
+    if (way == FC_DENSE_TWO && dense) return true;
+    if (way == FC_XFC || (way != FC_DENSE_ONE && (fp.ld.kind == KIND_XFC || fp.lf.kind == KIND_XFC))) {
+        if (find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_XFC, 0, fd) && find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_XFC, 0, ff)) {
+            fp.xfc = true;
+            fp.ld = fd; fp.lf = ff;
+            return true;
+        }
+        return dense;
+    }
+    if (way != FC_DENSE_ONE && !dense) return false;
+    if (!forced(OWT_FORCE_FC_TWO_LAUNCHES) && find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_FCGEMM, kFcPairTile, fd) &&
+        find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_FCGEMM, kFcPairTile, ff)) {
+        fp.ld = fd; fp.lf = ff; fp.fused = true;
+        return true;
+    }
+    return dense;
 }
 
 static std::map<PlanKey, std::pair<bool, FcPair>> g_fc_pairs;     // planned once per geometry; owt_fc_autotune erases its entry
@@ -1272,33 +1303,13 @@ static bool fc_pair_plan(const Geom &g, owt_dtype dt, FcPair &fp)
         auto it = g_fc_pairs.find(plan_key(g, 3, dt));
         if (it != g_fc_pairs.end()) { fp = it->second.second; return it->second.first; }
     }
-    bool ok = false;
-    fp.fused = false;
-    fp.ld = choose(g, OWT_PASS_BWD_DATA, dt, conv_dims(g, OWT_PASS_BWD_DATA), false, true);
-    fp.lf = choose(g, OWT_PASS_BWD_FILTER, dt, conv_dims(g, OWT_PASS_BWD_FILTER), true, true);
-    fp.xfc = false;
-    if (fp.ld.kind == KIND_XFC || fp.lf.kind == KIND_XFC) {
-        // one of the two chose the kernel that runs both in one launch and forms dz itself: the other joins it
-        Launch fd, ff;
-        if (find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_XFC, 0, fd) && find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_XFC, 0, ff)) {
-            ok = fp.xfc = true;
-            fp.ld = fd; fp.lf = ff;
-        }
-    } else if (fp.ld.kind == KIND_FCGEMM && fp.lf.kind == KIND_FCGEMM) {
-        ok = true;
-        Launch fd, ff;
-        if (!forced(OWT_FORCE_FC_TWO_LAUNCHES) && find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_FCGEMM, kFcPairTile, fd) &&
-            find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_FCGEMM, kFcPairTile, ff)) {
-            int fused = 1;                       // untimed: one launch
-            {
-                std::lock_guard<std::mutex> lk(g_tuned_mutex);
-                auto it = g_fc_fused.find(plan_key(g, 3, dt));
-                if (it != g_fc_fused.end()) fused = it->second;
-            }
-            if (forced(OWT_FORCE_FC_ONE_LAUNCH)) fused = 1;
-            if (fused) { fp.ld = fd; fp.lf = ff; fp.fused = true; }
-        }
+    int way = -1;
+    if (cached) {
+        std::lock_guard<std::mutex> lk(g_tuned_mutex);
+        auto it = g_fc_way.find(plan_key(g, 3, dt));
+        if (it != g_fc_way.end()) way = it->second;
     }
+    const bool ok = fc_pair_of(g, dt, way, fp);
     if (cached) {
         std::lock_guard<std::mutex> lk(g_tuned_mutex);
         g_fc_pairs[plan_key(g, 3, dt)] = std::make_pair(ok, fp);
@@ -1690,16 +1701,18 @@ owt_status owt_fc_autotune(const owt_fc_desc *d, const void *x, const void *w, c
                               hip_stream));
     OWT_TRY(owt_conv_autotune(&c, OWT_PASS_BWD_FILTER, x, w, nullptr, y, dy, nullptr, dw, dbias_or_null, ws, ws_bytes,
                               hip_stream));
-    // both backward products on the dense kernel: two launches (the tiles just timed) or one for both?
-    Launch fd, ff;
-    if (variants_forced() || !find_fc_launch(g, OWT_PASS_BWD_DATA, KIND_FCGEMM, kFcPairTile, fd) || !find_fc_launch(g, OWT_PASS_BWD_FILTER, KIND_FCGEMM, kFcPairTile, ff))
-        return OWT_OK;
-    FcPair two;
-    two.ld = choose(g, OWT_PASS_BWD_DATA, d->dtype, conv_dims(g, OWT_PASS_BWD_DATA), false, true);
-    two.lf = choose(g, OWT_PASS_BWD_FILTER, d->dtype, conv_dims(g, OWT_PASS_BWD_FILTER), true, true);
-    two.fused = two.xfc = false;
-    if (two.ld.kind != KIND_FCGEMM || two.lf.kind != KIND_FCGEMM) return OWT_OK;
-    FcPair one; one.ld = fd; one.lf = ff; one.fused = true; one.xfc = false;
+    // the ways to run the two backward products of a call that wants both
+    if (variants_forced()) return OWT_OK;
+    std::vector<std::pair<int, FcPair>> ways;
+    for (int way : {FC_SEPARATE, FC_DENSE_TWO, FC_DENSE_ONE, FC_XFC}) {
+        FcPair fp;
+        const bool pair = fc_pair_of(g, d->dtype, way, fp);
+        const bool dense = fp.ld.kind == KIND_FCGEMM && fp.lf.kind == KIND_FCGEMM;
+        if (way == FC_SEPARATE ? !dense && !(fp.ld.kind == KIND_XFC && fp.lf.kind == KIND_XFC)
+                               : pair && fp.xfc == (way == FC_XFC) && fp.fused == (way == FC_DENSE_ONE))
+            ways.push_back(std::make_pair(way, fp));
+    }
+    if (ways.empty()) return OWT_OK;
     const void *mask = (d->flags & OWT_RELU) ? y : nullptr;
     GemmParams pd; memset(&pd, 0, sizeof(pd));
     pd.a = dy; pd.b = w; pd.out = dx_partial; pd.flags = d->flags; pd.mask = mask;
@@ -1709,22 +1722,29 @@ owt_status owt_fc_autotune(const owt_fc_desc *d, const void *x, const void *w, c
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return fail(OWT_ELAUNCH, "hipEventCreate failed");
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(OWT_ELAUNCH, "hipEventCreate failed"); }
-    float ms[2] = {0.f, 0.f};
+    float best_ms = 0.f;
+    int best = -1;
     owt_status st = OWT_OK;
-    for (int v = 0; v < 2 && st == OWT_OK; v++) {
-        const FcPair &fp = v ? one : two;
-        st = launch_fc_pair(g, fp, pd, pf, ws, s);                                 // warm-up
+    const auto run = [&](int way, const FcPair &fp) {
+        if (way != FC_SEPARATE) return launch_fc_pair(g, fp, pd, pf, ws, s);
+        const owt_status sd = launch(g, OWT_PASS_BWD_DATA, d->dtype, conv_dims(g, OWT_PASS_BWD_DATA), pd, fp.ld, ws, s);
+        return sd != OWT_OK ? sd : launch(g, OWT_PASS_BWD_FILTER, d->dtype, conv_dims(g, OWT_PASS_BWD_FILTER), pf, fp.lf, ws, s);
+    };
+    for (size_t v = 0; v < ways.size() && st == OWT_OK; v++) {
+        float ms = 0.f;
+        st = run(ways[v].first, ways[v].second);                                   // warm-up
         bool ok = st == OWT_OK && hipEventRecord(e0, s) == hipSuccess;
-        for (int r = 0; r < 12 && st == OWT_OK; r++) st = launch_fc_pair(g, fp, pd, pf, ws, s);
+        for (int r = 0; r < 12 && st == OWT_OK; r++) st = run(ways[v].first, ways[v].second);
         if (st != OWT_OK) break;
         ok = ok && hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
-             hipEventElapsedTime(&ms[v], e0, e1) == hipSuccess;
+             hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
         if (!ok) st = fail(OWT_ELAUNCH, "timing the backward pair failed: %s", hipGetErrorString(hipGetLastError()));
+        if (best < 0 || ms < best_ms) { best = (int)v; best_ms = ms; }
     }
     (void)hipEventDestroy(e0); (void)hipEventDestroy(e1);
     if (st != OWT_OK) return st;
     std::lock_guard<std::mutex> lk(g_tuned_mutex);
-    g_fc_fused[plan_key(g, 3, d->dtype)] = ms[1] < ms[0] ? 1 : 0;
+    g_fc_way[plan_key(g, 3, d->dtype)] = ways[best].first;
     g_fc_pairs.erase(plan_key(g, 3, d->dtype));
     return OWT_OK;
 }

@@ -426,3 +426,39 @@ def test_fully_connected_shard_on_the_bf16_matrix_unit(dt, split):
                     bound += 2.0 ** -8 * np.abs(ref)              # rounded to bf16 when stored
                 worst = np.max(np.abs(got - ref) / bound)
                 assert worst <= 1.0, (name, worst)
+
+
+# tuned: whichever way of running the two backward products was the fastest (one launch on the bf16 matrix unit, the dense
+# kernel in one or two, each a pass of its own) gives the results; tuned twice, and the products tuned alone in between
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("N,I,O", [(128, 512, 512), (29, 868, 499), (130, 131, 70), (256, 4096, 64), (2, 103, 41)])
+def test_tuned_shard_backward(dt, N, I, O):
+    m = owt()
+    rnd = oracle.round_bf16 if dt == "bf16" else (lambda a: a)
+    g = np.random.default_rng(1150)
+    x, w = rnd(g.standard_normal((N, I), dtype=np.float32)), rnd(g.standard_normal((O, I), dtype=np.float32) * np.float32(0.05))
+    dy, y = rnd(g.standard_normal((N, O), dtype=np.float32)), rnd(g.standard_normal((N, O), dtype=np.float32))
+    code = m.OWT_BF16 if dt == "bf16" else m.OWT_F32
+    d = m.fc_desc(N, I, O, 1, 0, code, m.OWT_RELU)
+    c = m.conv_desc(N, I, 1, 1, O, 1, 1, 1, 0, code, m.OWT_RELU)
+    ws = workspace(max(m.owt_fc_workspace_bytes(d, 0), m.owt_fc_workspace_bytes(d, 1)))
+    xd, wd, yd, dyd = to_dev(x, dt), to_dev(w, dt), to_dev(y, dt), to_dev(dy, dt)
+    f64 = lambda a: a.astype(np.float64)
+    dz = f64(dy) * (y > 0)
+    refs = {"dx": (dz @ f64(w), np.abs(dz) @ np.abs(f64(w)), O), "dw": (dz.T @ f64(x), np.abs(dz).T @ np.abs(f64(x)), N), "db": (dz.sum(0), np.abs(dz).sum(0), N)}
+    for again in range(3):
+        out = {"dx": empty((N, I), dt), "dw": empty((O, I)), "db": empty((O,))}
+        if again == 2:
+            for p in (1, 2):
+                m.owt_conv_autotune(c, p, xd, wd, None, yd, dyd, out["dx"], out["dw"], out["db"], ws)
+        else:
+            m.owt_fc_autotune(d, xd, wd, None, empty((N, O), dt), dyd, out["dx"], out["dw"], out["db"], ws)
+        for t in out.values():
+            t.fill_(float("nan"))
+        m.owt_fc_shard_bwd(d, xd, wd, yd, dyd, 1.0, 0.0, out["dx"], out["dw"], out["db"], ws)
+        torch.cuda.synchronize()
+        for name, (ref, size, L) in refs.items():
+            bound = (L / 2 + 16) * 2.0 ** -24 * size + 1e-30        # the fp32 instruction rounds every second product
+            if dt == "bf16" and name == "dx":
+                bound += 2.0 ** -8 * np.abs(ref)
+            assert np.max(np.abs(to_host(out[name]) - ref) / bound) <= 1.0, (name, again)
