@@ -347,47 +347,6 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
         }
     }
 
-    if (LOAD == XC_BLOCKS) {
-        // A block holds pixels outside the window, met by zero filter values: an infinity or NaN among them would reach the
-        // result.  A wavefront whose sums are not all finite works its tile out again from the window alone, one
-        // multiply-add at a time.
-        float sum = 0.f;
-#pragma unroll
-        for (int bm = 0; bm < MB; bm++)
-#pragma unroll
-            for (int bn = 0; bn < 2; bn++)
-#pragma unroll
-                for (int q = 0; q < 16; q++) sum += big[bm][bn][q] + small[bm][bn][q];
-        if (__ballot(!(fabsf(sum) < __builtin_inff())) != 0) {
-            const float *x = (const float *)p.a, *w = (const float *)p.b0;
-            const Geom &g = p.g;
-#pragma unroll
-            for (int bm = 0; bm < MB; bm++)
-#pragma unroll
-                for (int bn = 0; bn < 2; bn++)
-#pragma unroll
-                    for (int q = 0; q < 16; q++) {
-                        const int m = m0 + (wm * MB + bm) * 32 + 8 * (q / 4) + 4 * lh + q % 4, k = n0 + wn * 64 + bn * 32 + li;
-                        float v = 0.f;
-                        if (m < mlim && k < p.Ncols) {
-                            const int n = p.dHoWo.div(m), rem = m - n * HoWo, po = p.dWo.div(rem), qo = rem - po * p.Wo;
-                            for (int r2 = 0; r2 < p.R0; r2++)
-                                for (int s2 = 0; s2 < p.S0; s2++)
-                                    for (int c = 0; c < g.C; c++) {
-                                        const int kd = ((r2 % g.sh) * g.sw + s2 % g.sw) * g.C + c;      // its place in a block
-                                        const int hh = po * g.sh - g.ph + r2, ww = qo * g.sw - g.pw + s2;
-                                        if (kd < ch_beg * 16 || kd >= ch_end * 16) continue;            // another split's
-                                        const float xv = ((unsigned)hh < (unsigned)g.H && (unsigned)ww < (unsigned)g.W)
-                                                             ? x[((size_t)(n * g.H + hh) * g.W + ww) * g.C + c] : 0.f;
-                                        v += xv * w[((size_t)(k * p.R0 + r2) * p.S0 + s2) * g.C + c];
-                                    }
-                        }
-                        big[bm][bn][q] = v;
-                        small[bm][bn][q] = 0.f;
-                    }
-        }
-    }
-
     // ---- epilogue: register r of lane (li, lh) of block (bm, bn) is pixel 8*(r/4) + 4*lh + r%4, column li.  Columns past
     // the end and pixels past the last get an offset outside the descriptor: their stores are dropped.
     const bool part = p.splits > 1;
@@ -396,11 +355,12 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
     const __amdgpu_buffer_rsrc_t xrs = owt_make_rsrc(BWD && p.xmask ? p.xmask : p.a, BWD && p.xmask ? out_bytes : 0u);
     const bool xm = BWD && !part && p.xmask != nullptr;
     auto rowstep = [&](int q) { return (unsigned)(8 * (q / 4) + q % 4) * (unsigned)p.Ncols * 4u; };   // an offset past OOB stays past it
+    const bool relu = !BWD && !part && (p.flags & 2u);
+    float sum = 0.f;                                                          // not finite if an output is not
 #pragma unroll
     for (int bn = 0; bn < 2; bn++) {
         const int n = n0 + wn * 64 + bn * 32 + li;
         const float bias = (!BWD && !part && (p.flags & 1u) && n < p.Ncols) ? p.bias[n] : 0.f;
-        const bool relu = !BWD && !part && (p.flags & 2u);
 #pragma unroll
         for (int bm = 0; bm < MB; bm++) {
             const unsigned m = (unsigned)(m0 + (wm * MB + bm) * 32 + 4 * lh);
@@ -413,11 +373,48 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
             }
 #pragma unroll
             for (int q = 0; q < 16; q++) {
-                float v = big[bm][bn][q] + small[bm][bn][q] + bias;
+                float v = big[bm][bn][q] + small[bm][bn][q];
+                if (LOAD == XC_BLOCKS) sum += v;
+                v += bias;
                 if (relu) v = v > 0.f ? v : 0.f;
                 if (xm) v = x[q] > 0.f ? v : 0.f;
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ors, (int)(base + rowstep(q)), 0, 0);
             }
+        }
+    }
+
+    // A block of a strided pass holds pixels outside the window, met by zero filter values: an infinity or NaN among them reaches
+    // the sum.  Outputs that are not finite are worked out again from the window alone, each lane its own, one multiply-add at a
+    // time and only until the sum is NaN (which it then stays), and stored over the first result.
+    if (LOAD == XC_BLOCKS && __ballot(!(fabsf(sum) < __builtin_inff())) != 0) {
+        unsigned long long redo = 0;                                          // bit 32 * bm + 16 * bn + q
+#pragma unroll
+        for (int i = 0; i < MB * 32; i++)
+            if (!(fabsf(big[i >> 5][(i >> 4) & 1][i & 15] + small[i >> 5][(i >> 4) & 1][i & 15]) < __builtin_inff())) redo |= 1ull << i;
+        const float *x = (const float *)p.a, *w = (const float *)p.b0;
+        const Geom &g = p.g;
+        const int kd_beg = ch_beg * 16, kd_end = ch_end * 16;                 // this split's places of a block
+        for (; redo; redo &= redo - 1) {
+            const int i = __ffsll(redo) - 1;
+            const int m = m0 + (wm * MB + (i >> 5)) * 32 + 8 * ((i & 15) / 4) + 4 * lh + i % 4, n = n0 + wn * 64 + ((i >> 4) & 1) * 32 + li;
+            if (m >= mlim || n >= p.Ncols) continue;
+            const int im = p.dHoWo.div(m), rem = m - im * HoWo, po = p.dWo.div(rem), qo = rem - po * p.Wo;
+            float v = 0.f;
+            for (int r2 = 0, dy = 0; r2 < p.R0 && v == v; r2++, dy = dy + 1 == g.sh ? 0 : dy + 1) {
+                const int hh = po * g.sh - g.ph + r2;
+                for (int s2 = 0, dx = 0; s2 < p.S0 && v == v; s2++, dx = dx + 1 == g.sw ? 0 : dx + 1) {
+                    const int ww = qo * g.sw - g.pw + s2, kd = (dy * g.sw + dx) * g.C;
+                    const bool in = (unsigned)hh < (unsigned)g.H && (unsigned)ww < (unsigned)g.W;
+                    const float *xp = x + ((size_t)(im * g.H + (in ? hh : 0)) * g.W + (in ? ww : 0)) * g.C;
+                    const float *wp = w + ((size_t)(n * p.R0 + r2) * p.S0 + s2) * g.C;
+                    for (int c = max(0, kd_beg - kd); c < min(g.C, kd_end - kd); c++) v += (in ? xp[c] : 0.f) * wp[c];
+                }
+            }
+            if (!part) {
+                if (p.flags & 1u) v += p.bias[n];
+                if (relu) v = v > 0.f ? v : 0.f;
+            }
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ors, (int)(((unsigned)m * (unsigned)p.Ncols + (unsigned)n) * 4u), 0, 0);
         }
     }
 }

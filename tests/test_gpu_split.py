@@ -296,7 +296,7 @@ def test_split_strided_forward_meets_no_value_outside_its_windows():
     # an infinity and a NaN next to windows, inside the blocks that zero filter values meet: outputs whose windows do not
     # hold them stay finite and exact
     m = owt()
-    shape = N, C, H, W, K, R, S, stride, pad = (2, 3, 39, 43, 24, 5, 6, 4, 2)
+    shape = N, C, H, W, K, R, S, stride, pad = (2, 3, 39, 43, 24, 5, 7, 4, 2)
     x, w, b, dy, y = strided_tensors(shape, 1010)
     ref = oracle.conv_fwd(x, w, b, stride, pad, False)
     bad = np.zeros((N, H, W), bool)
@@ -312,9 +312,45 @@ def test_split_strided_forward_meets_no_value_outside_its_windows():
     assert hit.any() and not hit.all()
     for variant, split in ((1, 1), (3, 2)):
         with force(40 + variant, split):
-            got = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, False).fwd(x, w, b)
+            case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, False)
+            assert owt().owt_conv_plan_describe(case.desc, 0).startswith("sconvx")
+            got = case.fwd(x, w, b)
         assert not np.isfinite(got[hit]).any()
         assert np.isfinite(got[~hit]).all() and np.max(np.abs(got[~hit] - ref[~hit])) <= 1e-5 * np.max(np.abs(ref))
+
+
+def test_split_strided_forward_is_not_held_up_by_values_that_are_not_finite():
+    # outputs that are not finite are worked out again one multiply-add at a time: a batch full of NaN or of infinities may take
+    # some times as long as a clean one (6 to 9; 39 for one infinity where a wavefront worked its whole tile out again)
+    m = owt()
+    N, C, H, W, K, R, S, stride, pad = 32, 3, 224, 224, 64, 11, 11, 4, 2
+    case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, True)
+    assert m.owt_conv_plan_describe(case.desc, 0).startswith("sconvx")
+    g = torch.Generator(device="cuda").manual_seed(1015)
+    w, b, y, ws = torch.randn(case.shape_w, generator=g, device="cuda"), torch.randn((K,), generator=g, device="cuda"), empty(case.shape_y), case.ws(0)
+    clean = torch.randn(case.shape_x, generator=g, device="cuda")
+    one, nans, infs, image = clean.clone(), torch.full_like(clean, float("nan")), torch.full_like(clean, float("inf")), clean.clone()
+    one[3, 100, 100, 1] = float("inf")
+    image[5] = float("nan")
+
+    def ms(x):
+        best = float("inf")
+        for _ in range(4):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(3):
+                m.owt_conv_fwd(case.desc, x, w, b, y, ws)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1) / 3)
+        return best
+
+    base = ms(clean)
+    for name, x in (("one infinity", one), ("an image of NaN", image), ("all NaN", nans), ("all infinite", infs)):
+        t = ms(x)
+        print("  clean %.3f ms, %s %.3f ms" % (base, name, t))
+        sys.stdout.flush()
+        assert t < 16 * base, name
 
 
 @pytest.mark.parametrize("variant,split", [(0, 1), (0, 3), (1, 1), (1, 7)])
