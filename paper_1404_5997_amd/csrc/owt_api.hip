@@ -944,13 +944,14 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
 static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per geometry: listing the candidates takes 10-60 us
 
 // Whether tuning times a candidate, `least` being the cheapest modelled cost, and whether the workspace bound covers it.  Tuned
-// without this rule on the draws of the layers' ranges, the fastest candidate was modelled at up to 2.8 times the cheapest in 418
-// fp32 passes, 1.8 in 200 bf16 passes, 1.6 in 150 of shards, so four times leaves none out; all candidates took 32.7 s to time
-// in the 418 passes, these take 6.8 s.  Split-operand kernels that split their reduction, too, were the fastest up to 1.85
+// without this rule on draws of the layers' ranges, the fastest candidate was modelled at up to 2.82 times the cheapest in 418
+// fp32 passes, 1.75 in 200 bf16 passes, 1.57 in 150 of shards, so three times left none out; timing every candidate of the 418
+// passes took 32.7 s, these take 5.3 s (up to four times the cheapest 6.8 s, and a training step's tuning 0.79 s instead of
+// 0.63).  Split-operand kernels that split their reduction, too, were the fastest up to 1.85
 // times: past twice they only raise the bound (the first layer's forward pass 0.3 -> 199 MB).  choose() sees every candidate.
 static bool worth_timing(const Launch &l, double least)
 {
-    return l.cost <= (is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 4.0) * least;
+    return l.cost <= (is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 3.0) * least;
 }
 static bool worth_workspace(const Launch &l, double least) { return !is_split_kind(l.kind) || l.splits == 1 || worth_timing(l, least); }
 static double least_cost(const std::vector<Launch> &c)
