@@ -8,7 +8,7 @@
 //    chunk it reads 6 + 6 fragments of 1 KB for 24 matrix instructions (half a fragment per instruction; the LDS could
 //    deliver about one), two wavefronts per SIMD;
 //  * the panel's values are split once, on their way from global memory into LDS (R*S taps and the tile's filter blocks
-//    reuse them): 6 vector instructions per value, 3-7 % of the matrix time for a 3x3 layer, where writing the three
+//    reuse them): 7 vector instructions per value, 4-8 % of the matrix time for a 3x3 layer, where writing the three
 //    parts to memory and reading them back would move 10 bytes per value;
 //  * the filters are split and laid out once per call in the order the fragments are read (xconv_pack_kernel), so a
 //    tap's slice is a few 1 KB pieces that go straight into LDS, and a fragment read is 64 consecutive 16-byte pieces;
@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(256) xconv_pack_kernel(const float *__restrict
             else v[j] = (col < K && kd < C) ? w[((size_t)col * RS + tap) * C + kd] : 0.f;
         }
         uint4 h, m, l;
-        split3_pack8(v, h, m, l);
+        split3_scaled(v, h, m, l);
         uint4 *o = out + (size_t)q * 192 + lane;
         o[0] = h; o[64] = m; o[128] = l;
     }
@@ -73,7 +73,7 @@ static __global__ void __launch_bounds__(256) xconv_pack_blocks_kernel(const flo
             v[j] = (col < g.K && dy < g.sh && r < g.R && s < g.S) ? w[((size_t)(col * g.R + r) * g.S + s) * g.C + c] : 0.f;
         }
         uint4 h, m, l;
-        split3_pack8(v, h, m, l);
+        split3_scaled(v, h, m, l);
         uint4 *o = out + (size_t)q * 192 + lane;
         o[0] = h; o[64] = m; o[128] = l;
     }
@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
                 for (int j = 0; j < 8; j++) preg[i][j] = yreg[MASKED ? i : 0][j] > 0.f ? preg[i][j] : 0.f;
             }
             uint4 h, m, l;
-            split3_pack8(preg[i], h, m, l);
+            split3_scaled(preg[i], h, m, l);
             if (row < PR) {
                 uint4 *q = dst + half * PL + row;
                 q[0] = h; q[2 * PL] = m; q[4 * PL] = l;
@@ -349,6 +349,8 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
 
     // ---- epilogue: register r of lane (li, lh) of block (bm, bn) is pixel 8*(r/4) + 4*lh + r%4, column li.  Columns past
     // the end and pixels past the last get an offset outside the descriptor: their stores are dropped.
+    // (the lane's place is worked out anew: kept over the loop, it is spilled where registers are short)
+    const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), eli = elane & 31, elh = elane >> 5;
     const bool part = p.splits > 1;
     const unsigned out_bytes = (unsigned)mlim * (unsigned)p.Ncols * 4u;
     const __amdgpu_buffer_rsrc_t ors = owt_make_rsrc(part ? (const void *)(p.partial + (size_t)split * p.M * p.Ncols) : p.out, out_bytes);
@@ -356,14 +358,14 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
     const bool xm = BWD && !part && p.xmask != nullptr;
     auto rowstep = [&](int q) { return (unsigned)(8 * (q / 4) + q % 4) * (unsigned)p.Ncols * 4u; };   // an offset past OOB stays past it
     const bool relu = !BWD && !part && (p.flags & 2u);
-    float sum = 0.f;                                                          // not finite if an output is not
+    float sum = 0.f;                                                          // not finite if an output may have to be worked out again
 #pragma unroll
     for (int bn = 0; bn < 2; bn++) {
-        const int n = n0 + wn * 64 + bn * 32 + li;
+        const int n = n0 + wn * 64 + bn * 32 + eli;
         const float bias = (!BWD && !part && (p.flags & 1u) && n < p.Ncols) ? p.bias[n] : 0.f;
 #pragma unroll
         for (int bm = 0; bm < MB; bm++) {
-            const unsigned m = (unsigned)(m0 + (wm * MB + bm) * 32 + 4 * lh);
+            const unsigned m = (unsigned)(m0 + (wm * MB + bm) * 32 + 4 * elh);
             const unsigned base = n < p.Ncols ? (m * (unsigned)p.Ncols + (unsigned)n) * 4u : OOB;
             float x[16];
             if (xm) {
@@ -373,9 +375,9 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
             }
 #pragma unroll
             for (int q = 0; q < 16; q++) {
-                float v = big[bm][bn][q] + small[bm][bn][q];
-                if (LOAD == XC_BLOCKS) sum += v;
-                v += bias;
+                const float t = big[bm][bn][q] + small[bm][bn][q];
+                sum += LOAD == XC_BLOCKS ? t : big[bm][bn][q];
+                float v = t * kSplitUnscale + bias;
                 if (relu) v = v > 0.f ? v : 0.f;
                 if (xm) v = x[q] > 0.f ? v : 0.f;
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ors, (int)(base + rowstep(q)), 0, 0);
@@ -383,36 +385,56 @@ __global__ void __launch_bounds__(64 * WM * WN, OCC) xconv_kernel(const GemmPara
         }
     }
 
-    // A block of a strided pass holds pixels outside the window, met by zero filter values: an infinity or NaN among them reaches
-    // the sum.  Outputs that are not finite are worked out again from the window alone, each lane its own, one multiply-add at a
-    // time and only until the sum is NaN (which it then stays), and stored over the first result.
-    if (LOAD == XC_BLOCKS && __ballot(!(fabsf(sum) < __builtin_inff())) != 0) {
+    // Outputs worked out again, each lane its own, one multiply-add at a time and only until the sum is NaN (which it then
+    // stays), and stored over the first result:
+    //  * those whose large products left the range of the scaled operands (a sum past 2^80, a value past 2^104).  Infinities and
+    //    NaN among the operands leave the large products finite (split3_scaled) and are right as they are;
+    //  * a block of a strided pass holds pixels outside the window, met by zero filter values: an infinity or NaN among them
+    //    reaches the sum, so there it is every output that is not finite.
+    if (__ballot(!(fabsf(sum) < __builtin_inff())) != 0) {
         unsigned long long redo = 0;                                          // bit 32 * bm + 16 * bn + q
 #pragma unroll
-        for (int i = 0; i < MB * 32; i++)
-            if (!(fabsf(big[i >> 5][(i >> 4) & 1][i & 15] + small[i >> 5][(i >> 4) & 1][i & 15]) < __builtin_inff())) redo |= 1ull << i;
-        const float *x = (const float *)p.a, *w = (const float *)p.b0;
+        for (int i = 0; i < MB * 32; i++) {
+            const float t = big[i >> 5][(i >> 4) & 1][i & 15] + (LOAD == XC_BLOCKS ? small[i >> 5][(i >> 4) & 1][i & 15] : 0.f);
+            if (!(fabsf(t) < __builtin_inff())) redo |= 1ull << i;
+        }
+        const float *x = (const float *)p.a, *y = (const float *)p.mask, *w = (const float *)p.b0;
         const Geom &g = p.g;
-        const int kd_beg = ch_beg * 16, kd_end = ch_end * 16;                 // this split's places of a block
+        const int kd_beg = ch_beg * 16, kd_end = ch_end * 16;                 // this split's part of the reduction
         for (; redo; redo &= redo - 1) {
             const int i = __ffsll(redo) - 1;
-            const int m = m0 + (wm * MB + (i >> 5)) * 32 + 8 * ((i & 15) / 4) + 4 * lh + i % 4, n = n0 + wn * 64 + ((i >> 4) & 1) * 32 + li;
+            const int m = m0 + (wm * MB + (i >> 5)) * 32 + 8 * ((i & 15) / 4) + 4 * elh + i % 4, n = n0 + wn * 64 + ((i >> 4) & 1) * 32 + eli;
             if (m >= mlim || n >= p.Ncols) continue;
             const int im = p.dHoWo.div(m), rem = m - im * HoWo, po = p.dWo.div(rem), qo = rem - po * p.Wo;
             float v = 0.f;
-            for (int r2 = 0, dy = 0; r2 < p.R0 && v == v; r2++, dy = dy + 1 == g.sh ? 0 : dy + 1) {
-                const int hh = po * g.sh - g.ph + r2;
-                for (int s2 = 0, dx = 0; s2 < p.S0 && v == v; s2++, dx = dx + 1 == g.sw ? 0 : dx + 1) {
-                    const int ww = qo * g.sw - g.pw + s2, kd = (dy * g.sw + dx) * g.C;
-                    const bool in = (unsigned)hh < (unsigned)g.H && (unsigned)ww < (unsigned)g.W;
-                    const float *xp = x + ((size_t)(im * g.H + (in ? hh : 0)) * g.W + (in ? ww : 0)) * g.C;
-                    const float *wp = w + ((size_t)(n * p.R0 + r2) * p.S0 + s2) * g.C;
-                    for (int c = max(0, kd_beg - kd); c < min(g.C, kd_end - kd); c++) v += (in ? xp[c] : 0.f) * wp[c];
+            if (LOAD == XC_BLOCKS) {
+                for (int r2 = 0, dy = 0; r2 < p.R0 && v == v; r2++, dy = dy + 1 == g.sh ? 0 : dy + 1) {
+                    const int hh = po * g.sh - g.ph + r2;
+                    for (int s2 = 0, dx = 0; s2 < p.S0 && v == v; s2++, dx = dx + 1 == g.sw ? 0 : dx + 1) {
+                        const int ww = qo * g.sw - g.pw + s2, kd = (dy * g.sw + dx) * g.C;
+                        const bool in = (unsigned)hh < (unsigned)g.H && (unsigned)ww < (unsigned)g.W;
+                        const float *xp = x + ((size_t)(im * g.H + (in ? hh : 0)) * g.W + (in ? ww : 0)) * g.C;
+                        const float *wp = w + ((size_t)(n * p.R0 + r2) * p.S0 + s2) * g.C;
+                        for (int c = max(0, kd_beg - kd); c < min(g.C, kd_end - kd); c++) v = fmaf(in ? xp[c] : 0.f, wp[c], v);
+                    }
+                }
+            } else {
+                for (int tap = 0, r = 0, s = 0; tap < RS && v == v; tap++) {
+                    const int hh = po - p.pah + r, ww = qo - p.paw + s;
+                    const bool in = (unsigned)hh < (unsigned)Hi && (unsigned)ww < (unsigned)Wi;
+                    const size_t at = ((size_t)(im * Hi + (in ? hh : 0)) * Wi + (in ? ww : 0)) * Cred;
+                    // forward: w[n][tap][c]; backward-data: w[c][RS-1-tap][n]
+                    const float *wp = w + (BWD ? (size_t)(RS - 1 - tap) * p.Ncols + n : ((size_t)n * RS + tap) * Cred);
+                    const size_t step = BWD ? (size_t)RS * p.Ncols : 1;
+                    for (int c = kd_beg; c < min(Cred, kd_end); c++)
+                        v = fmaf(in && (!MASKED || y[at + c] > 0.f) ? x[at + c] : 0.f, wp[c * step], v);
+                    if (++s == S) { s = 0; r++; }
                 }
             }
             if (!part) {
-                if (p.flags & 1u) v += p.bias[n];
+                if (!BWD && (p.flags & 1u)) v += p.bias[n];
                 if (relu) v = v > 0.f ? v : 0.f;
+                if (xm && !(((const float *)p.xmask)[(size_t)m * p.Ncols + n] > 0.f)) v = 0.f;
             }
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ors, (int)(((unsigned)m * (unsigned)p.Ncols + (unsigned)n) * 4u), 0, 0);
         }

@@ -46,8 +46,9 @@ hipError_t OWT_XFN(OWT_INST_VEC)(int variant, int pr, const GemmParams &p0, void
 #if OWT_INST_VEC == 2
     p.g.R = (g.R + g.sh - 1) / g.sh;                     // the kernel's taps are blocks
     p.g.S = (g.S + g.sw - 1) / g.sw;
-    p.b0 = p0.b; p.R0 = g.R; p.S0 = g.S;
+    p.R0 = g.R; p.S0 = g.S;
 #endif
+    p.b0 = p0.b;
     const int RS = p.g.R * p.g.S;
     const long threads = (long)p0.ksteps * RS * nblocks * 64;
     const unsigned blocks = (unsigned)((threads + 255) / 256 > 8192 ? 8192 : (threads + 255) / 256);

@@ -34,7 +34,8 @@ template <bool BF> struct XfcOps {
     // eight raw values of a lane: fp32 bits, or bf16 bits in the low halves
     struct Raw { uint32_t v[8]; };
 
-    static __device__ __forceinline__ Frag pack(const Raw &r)
+    // CAREFUL (fp32): the second run, with a test for large values
+    template <bool CAREFUL> static __device__ __forceinline__ Frag pack(const Raw &r, float scale)
     {
         Frag f;
         if constexpr (BF) {
@@ -42,10 +43,9 @@ template <bool BF> struct XfcOps {
         } else {
             float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; j++) v[j] = __uint_as_float(r.v[j]);
-            uint4 h, m, l;
-            split3_pack8(v, h, m, l);
-            f.p[0] = __builtin_bit_cast(split_frag, h); f.p[1] = __builtin_bit_cast(split_frag, m); f.p[2] = __builtin_bit_cast(split_frag, l);
+            for (int j = 0; j < 8; j++) v[j] = __uint_as_float(r.v[j]) * scale;
+            if constexpr (CAREFUL) split3_careful(v, f.p);
+            else split3_plain(v, f.p);
         }
         return f;
     }
@@ -93,10 +93,20 @@ template <bool BF> struct XfcOps {
     }
 };
 
+__device__ __forceinline__ void xfc_clear(split_acc (&a)[2][2], split_acc (&b)[2][2])
+{
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) a[i][j][e] = b[i][j][e] = 0.f;
+}
+
 // A 64 x 64 tile of one product by one wavefront: reduction steps step0, step0 + stride, ... below nsteps (16 deep each).
 // AROW / BROW: the operand is contiguous along the reduction.  Rows (A) and columns (B) past the end read harmlessly.
-template <bool BF, bool AROW, bool BROW, bool MASKED, bool DB>
-__device__ __forceinline__ void xfc_tile(const void *a, const void *y, const void *b, unsigned a_bytes, unsigned b_bytes, int a_len,
+template <bool BF, bool AROW, bool BROW, bool MASKED, bool DB, bool CAREFUL>
+__device__ __forceinline__ void xfc_tile_run(const void *a, const void *y, const void *b, unsigned a_bytes, unsigned b_bytes, int a_len,
                                          int b_len, int Kd, int m0, int n0, int step0, int stride, int nsteps,
                                          split_acc (&big)[2][2], split_acc (&small)[2][2], float (&db)[2])
 {
@@ -144,8 +154,8 @@ __device__ __forceinline__ void xfc_tile(const void *a, const void *y, const voi
                 const auto v = [&](int j) { return O::value(ra[t].v[j]); };
                 db[t] += ((v(0) + v(1)) + (v(2) + v(3))) + ((v(4) + v(5)) + (v(6) + v(7)));
             }
-            fa[t] = O::pack(ra[t]);
-            fb[t] = O::pack(rb[t]);
+            fa[t] = O::template pack<CAREFUL>(ra[t], CAREFUL ? kSplitDown : kSplitScale);
+            fb[t] = O::template pack<CAREFUL>(rb[t], CAREFUL ? 1.f : kSplitScale);
         }
         if (step + stride < nsteps) load(step + stride);
 #pragma unroll
@@ -166,19 +176,40 @@ __device__ __forceinline__ void xfc_tile(const void *a, const void *y, const voi
     }
 }
 
-__device__ __forceinline__ void xfc_clear(split_acc (&a)[2][2], split_acc (&b)[2][2])
+// The tile's sums in `big` (both to be cleared before) and what they are to be multiplied with: fp32 operands are scaled up, and
+// a wavefront whose sums are not finite starts over with products that no finite operands take out of the range.
+template <bool BF, bool AROW, bool BROW, bool MASKED, bool DB>
+__device__ __forceinline__ float xfc_tile(const void *a, const void *y, const void *b, unsigned a_bytes, unsigned b_bytes, int a_len,
+                                         int b_len, int Kd, int m0, int n0, int step0, int stride, int nsteps,
+                                         split_acc (&big)[2][2], split_acc (&small)[2][2], float (&db)[2])
 {
+    xfc_tile_run<BF, AROW, BROW, MASKED, DB, false>(a, y, b, a_bytes, b_bytes, a_len, b_len, Kd, m0, n0, step0, stride, nsteps, big, small, db);
+    if constexpr (BF) return 1.f;
+    auto add_up = [&]() __attribute__((always_inline)) {
+        float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 2; i++)
+        for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++)
+            for (int j = 0; j < 2; j++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) a[i][j][e] = b[i][j][e] = 0.f;
+                for (int e = 0; e < 16; e++) {
+                    big[i][j][e] += small[i][j][e];
+                    sum += big[i][j][e];
+                }
+        return sum;
+    };
+    if (__ballot(!(fabsf(add_up()) < __builtin_inff())) == 0) return kSplitUnscale;
+    xfc_clear(big, small);
+    xfc_tile_run<BF, AROW, BROW, MASKED, false, true>(a, y, b, a_bytes, b_bytes, a_len, b_len, Kd, m0, n0, step0, stride, nsteps, big, small, db);
+    add_up();
+    return kSplitUndown;
 }
 
-// The four wavefronts' sums of one tile, added in a fixed order; `store(row, column, value)` gets each value of the tile once.
-template <class Store>
-__device__ __forceinline__ void xfc_combine(float *red, const split_acc (&big)[2][2], const split_acc (&small)[2][2], Store store)
+// The four wavefronts' sums of one tile, each times its `scale` (SCALED), added in a fixed order; `store(row, column, value)` gets each
+// value of the tile once.
+constexpr int kXfcRed = 4 * 4096 + 4;
+template <bool SCALED, class Store>
+__device__ __forceinline__ void xfc_combine(float *red, const split_acc (&big)[2][2], float scale, Store store)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 31, lh = lane >> 5;
 #pragma unroll
@@ -187,19 +218,23 @@ __device__ __forceinline__ void xfc_combine(float *red, const split_acc (&big)[2
         for (int j = 0; j < 2; j++)
 #pragma unroll
             for (int e = 0; e < 16; e++)
-                red[wave * 4096 + (i * 32 + 8 * (e / 4) + 4 * lh + e % 4) * 64 + j * 32 + li] = big[i][j][e] + small[i][j][e];
+                red[wave * 4096 + (i * 32 + 8 * (e / 4) + 4 * lh + e % 4) * 64 + j * 32 + li] = big[i][j][e];
+    if (SCALED && lane == 0) red[4 * 4096 + wave] = scale;
     __syncthreads();
+    float s[4];
+#pragma unroll
+    for (int w = 0; w < 4; w++) s[w] = SCALED ? red[4 * 4096 + w] : 1.f;
 #pragma unroll 4
     for (int q = 0; q < 16; q++) {
         const int at = q * 256 + tid;
-        store(at >> 6, at & 63, (red[at] + red[4096 + at]) + (red[8192 + at] + red[12288 + at]));
+        store(at >> 6, at & 63, fmaf(red[4096 + at], s[1], red[at] * s[0]) + fmaf(red[12288 + at], s[3], red[8192 + at] * s[2]));
     }
 }
 
 template <class Epi, bool BF>
 __global__ void __launch_bounds__(256, 2) xfc_fwd_kernel(const GemmParams p)
 {
-    __shared__ float red[4 * 4096];
+    __shared__ float red[kXfcRed];
     typedef typename Epi::TOut T;
     const int tn = blockIdx.x % p.tiles_n, tm = blockIdx.x / p.tiles_n, split = blockIdx.y, wave = threadIdx.x >> 6;
     const int m0 = tm * 64, n0 = tn * 64, I = p.Kd;
@@ -207,9 +242,9 @@ __global__ void __launch_bounds__(256, 2) xfc_fwd_kernel(const GemmParams p)
     split_acc big[2][2], small[2][2];
     float db[2];
     xfc_clear(big, small);
-    xfc_tile<BF, true, true, false, false>(p.a, nullptr, p.b, (unsigned)p.M * I * XfcOps<BF>::ES, (unsigned)p.Ncols * I * XfcOps<BF>::ES, I, I,
+    const float scale = xfc_tile<BF, true, true, false, false>(p.a, nullptr, p.b, (unsigned)p.M * I * XfcOps<BF>::ES, (unsigned)p.Ncols * I * XfcOps<BF>::ES, I, I,
                                            I, m0, n0, beg + wave, 4, end, big, small, db);
-    xfc_combine(red, big, small, [&](int r, int c, float v) {
+    xfc_combine<!BF>(red, big, scale, [&](int r, int c, float v) {
         const int m = m0 + r, n = n0 + c;
         if (m >= p.M || n >= p.Ncols) return;
         if (p.splits > 1) p.partial[((size_t)split * p.M + m) * p.Ncols + n] = v;
@@ -221,7 +256,7 @@ __global__ void __launch_bounds__(256, 2) xfc_fwd_kernel(const GemmParams p)
 template <bool BF, bool MASKED>
 __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, const GemmParams pf)
 {
-    __shared__ float red[4 * 4096];
+    __shared__ float red[kXfcRed];
     typedef typename std::conditional<BF, bf16_t, float>::type T;
     constexpr unsigned ES = XfcOps<BF>::ES;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ndx = pd.tiles_m * pd.tiles_n;
@@ -231,9 +266,9 @@ __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, co
     xfc_clear(big, small);
     if ((int)blockIdx.x < ndx) {
         const int tn = blockIdx.x % pd.tiles_n, tm = blockIdx.x / pd.tiles_n, m0 = tm * 64, n0 = tn * 64;
-        xfc_tile<BF, true, false, MASKED, false>(pd.a, pd.mask, pd.b, (unsigned)N * O * ES, (unsigned)O * I * ES, O, I, O, m0, n0, wave, 4,
+        const float scale = xfc_tile<BF, true, false, MASKED, false>(pd.a, pd.mask, pd.b, (unsigned)N * O * ES, (unsigned)O * I * ES, O, I, O, m0, n0, wave, 4,
                                                  (O + 15) >> 4, big, small, db);
-        xfc_combine(red, big, small, [&](int r, int c, float v) {
+        xfc_combine<!BF>(red, big, scale, [&](int r, int c, float v) {
             const int m = m0 + r, n = n0 + c;
             if (m < N && n < I) store1((T *)pd.out, (size_t)m * I + n, EpiData<T>::op(pd, m, n, v));
         });
@@ -242,14 +277,15 @@ __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, co
     const int t = blockIdx.x - ndx, tm = t / pf.tiles_n, tn = t - tm * pf.tiles_n;
     const int m0 = tm * 64, n0 = tn * 64, tid = threadIdx.x, lane = tid & 63;
     const bool do_db = tn == 0 && pf.dbias != nullptr;
+    float scale;
     if (do_db)
-        xfc_tile<BF, false, false, MASKED, true>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
+        scale = xfc_tile<BF, false, false, MASKED, true>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
                                                  (N + 15) >> 4, big, small, db);
     else
-        xfc_tile<BF, false, false, MASKED, false>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
+        scale = xfc_tile<BF, false, false, MASKED, false>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
                                                   (N + 15) >> 4, big, small, db);
     float *out = (float *)pf.out;
-    xfc_combine(red, big, small, [&](int r, int c, float v) {
+    xfc_combine<!BF>(red, big, scale, [&](int r, int c, float v) {
         const int o = m0 + r, n = n0 + c;
         if (o >= O || n >= I) return;
         const size_t at = (size_t)o * I + n;

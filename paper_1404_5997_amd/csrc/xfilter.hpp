@@ -22,9 +22,10 @@
 // issue in their shadow.  Measured with one wavefront per SIMD, a 32-cycle matrix instruction hides 28 cycles of vector
 // issue, 5 cycles an instruction with a 4-byte encoding, 8 with an 8-byte one; a fragment's split is 256 cycles, so the
 // KB + 1 fragments of a position cost 9 (KB = 2, 3 taps: of 36 instructions' 28) and 6 (KB = 1, 5 taps: of 30) times 28.
-// Loads run one to two positions ahead, those of a row's start a whole row ahead.  The plain split has no test for values bf16 cannot hold (infinite, or finite above the
-// largest bf16): they turn into NaN, which reaches every accumulator they touch, so a wavefront whose sums are not
-// finite starts over with the careful split.
+// Loads run one to two positions ahead, those of a row's start a whole row ahead.  The plain split has no test for values bf16
+// cannot hold: infinite ones, or finite above the largest bf16, turn into NaN, which reaches every accumulator they touch, and
+// those below 2^-110 lose bits, which only a result as small can show.  A wavefront whose sums are not all finite, or some
+// below kSplitTiny and not zero, starts over with scaled operands and the careful split.
 //
 // Measured, 128 images, with the reduce pass, kernel on the fp32 instruction -> this one, us: 3x3 192->384 252 -> 151 (190
 // TFLOP/s), 384->256 334 -> 191, 256->256 228 -> 137; 5x5 64->192 450 -> 271 (212 TFLOP/s).  Four wavefronts to a
@@ -36,22 +37,6 @@
 #include "split3.hpp"
 
 namespace owt {
-
-// eight fp32 values -> h, m, l fragments, no test for large values
-__device__ __forceinline__ void split3_plain(const float (&v)[8], split_frag (&f)[3])
-{
-    uint32_t hh[4], mm[4], ll[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        hh[i] = f32x2_to_bf16x2(v[2 * i], v[2 * i + 1]);
-        const float ra = v[2 * i] - bf16_lo_f32(hh[i]), rb = v[2 * i + 1] - bf16_hi_f32(hh[i]);
-        mm[i] = f32x2_to_bf16x2(ra, rb);
-        ll[i] = f32x2_to_bf16x2(ra - bf16_lo_f32(mm[i]), rb - bf16_hi_f32(mm[i]));
-    }
-    f[0] = __builtin_bit_cast(split_frag, make_uint4(hh[0], hh[1], hh[2], hh[3]));
-    f[1] = __builtin_bit_cast(split_frag, make_uint4(mm[0], mm[1], mm[2], mm[3]));
-    f[2] = __builtin_bit_cast(split_frag, make_uint4(ll[0], ll[1], ll[2], ll[3]));
-}
 
 // (split, tile) pairs, split-major, four consecutive ones to the wavefronts of a work-group; the work-groups are dealt to
 // the XCDs as owt_split_major_wg does.  Returns false for wavefronts past the last pair (there are no barriers).
@@ -112,6 +97,7 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
 #pragma unroll
     for (int kb = 0; kb < KB; kb++) db[kb] = 0.f;
 
+    float sx = 1.f, sz = 1.f;                       // scales of x and dz in a careful run
     // DB: also sum dz over the positions (bias gradient).  CAREFUL: the second run, splits test for large values.
     auto walk = [&](auto db_tag, auto careful_tag) __attribute__((always_inline)) {
         constexpr bool DB = decltype(db_tag)::value, CAREFUL = decltype(careful_tag)::value;
@@ -154,11 +140,12 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
                 for (int e = 0; e < 8; e++) y[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ms, (int)zo[e] + kb * 128, (int)off, 0));
             }
         };
-        auto split = [&](const float (&v)[8], split_frag (&f)[3]) __attribute__((always_inline)) {
+        auto split = [&](const float (&v)[8], float scale, split_frag (&f)[3]) __attribute__((always_inline)) {
             if constexpr (CAREFUL) {
-                uint4 h, m, l;
-                split3_pack8(v, h, m, l);
-                f[0] = __builtin_bit_cast(split_frag, h); f[1] = __builtin_bit_cast(split_frag, m); f[2] = __builtin_bit_cast(split_frag, l);
+                float u[8];
+#pragma unroll
+                for (int e = 0; e < 8; e++) u[e] = v[e] * scale;
+                split3_careful(u, f);
             } else {
                 split3_plain(v, f);
             }
@@ -169,7 +156,7 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
                 for (int e = 0; e < 8; e++) v[e] = y[e] > 0.f ? v[e] : 0.f;
             }
             if (DB) db[kb] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-            split(v, f);
+            split(v, sz, f);
         };
 
         // win[0..S-1]: x fragments of the S columns this position's taps meet; win[S]: the next column's, being split.
@@ -198,7 +185,7 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
 #pragma unroll
                     for (int e = 0; e < 3; e++) win[i][e] = __builtin_bit_cast(split_frag, make_uint4(0u, 0u, 0u, 0u));
                 } else {
-                    split(xf[i], win[i]);
+                    split(xf[i], sx, win[i]);
                 }
             }
 #pragma unroll
@@ -216,7 +203,7 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
                 if (last) { tgt = ahead; ti = 1; }
 #pragma unroll
                 for (int f = 0; f <= KB; f++) {
-                    if (f == 0) { split(xr, win[S]); load_x(tgt, ti + S - 1, xr); }
+                    if (f == 0) { split(xr, sx, win[S]); load_x(tgt, ti + S - 1, xr); }
                     else { split_z(f - 1, zr[f - 1], yr[MASKED ? f - 1 : 0], nz[f - 1]); load_z(tgt, ti, f - 1, zr[f - 1], yr[MASKED ? f - 1 : 0]); }
 #pragma unroll
                     for (int i = f * PH; i < (f == KB ? M : (f + 1) * PH); i++) {
@@ -250,16 +237,38 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
     const bool do_db = ct == 0 && r == g.ph && p.dbias != nullptr;        // every output row has an input row there
     if (do_db) walk(std::true_type{}, std::false_type{});
     else walk(std::false_type{}, std::false_type{});
-    float sum = 0.f;
+    // Is every sum finite, and none but zero so small that operands may have lost bits?  If not, once more with the split that
+    // tests for large values: scaled up, and where that is not finite (or the first run was not) with products that no finite
+    // operands take out of the range.
+    float unscale = 1.f;
+    unsigned low;
+    auto all_finite = [&]() __attribute__((always_inline)) {
+        float sum = 0.f;
+        low = ~0u;                                   // of twice the bits, less one: zero counts as large
 #pragma unroll
-    for (int kb = 0; kb < KB; kb++)
+        for (int kb = 0; kb < KB; kb++)
 #pragma unroll
-        for (int s = 0; s < S; s++)
+            for (int s = 0; s < S; s++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) sum += big[kb][s][e] + small[kb][s][e];
-    if (__ballot(!(fabsf(sum) < __builtin_inff())) != 0) {
-        clear();
-        walk(std::false_type{}, std::true_type{});
+                for (int e = 0; e < 16; e++) {
+                    const float v = big[kb][s][e] + small[kb][s][e];
+                    sum += v;
+                    low = min(low, (__float_as_uint(v) << 1) - 1u);
+                }
+        return __ballot(!(fabsf(sum) < __builtin_inff())) == 0;
+    };
+    bool finite = all_finite();
+    if (!finite || __ballot(low < (__float_as_uint(kSplitTiny) << 1) - 1u) != 0) {
+        bool up = finite;
+        do {
+            sx = up ? kSplitScale : 1.f;
+            sz = up ? kSplitScale : kSplitDown;
+            unscale = up ? kSplitUnscale : kSplitUndown;
+            clear();
+            walk(std::false_type{}, std::true_type{});
+            finite = all_finite() || !up;
+            up = false;
+        } while (!finite);
     }
 
     // register e of lane (li, lh): filter 8*(e/4) + 4*lh + e%4 of its block, channel li
@@ -276,7 +285,7 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
                     const int k = k0 + kb * 32 + 8 * (e / 4) + 4 * lh + e % 4;
                     if (k >= g.K) continue;
                     const size_t o = ((size_t)k * RS + r * S + s) * g.C + c;
-                    const float v = big[kb][s][e] + small[kb][s][e];
+                    const float v = (big[kb][s][e] + small[kb][s][e]) * unscale;
                     if (part) out[o] = v;
                     else out[o] = p.alpha * v + (p.beta != 0.f ? p.beta * out[o] : 0.f);
                 }

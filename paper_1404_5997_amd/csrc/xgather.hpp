@@ -70,6 +70,7 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
 #pragma unroll
     for (int kb = 0; kb < KB; kb++) db[kb] = 0.f;
 
+    float sx = 1.f, sz = 1.f;                       // scales of x and dz in a careful run
     auto walk = [&](auto db_tag, auto careful_tag) __attribute__((always_inline)) {
         constexpr bool DB = decltype(db_tag)::value, CAREFUL = decltype(careful_tag)::value;
         if (o_beg >= o_end) return;
@@ -120,18 +121,19 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
                 }
             }
         };
-        auto split = [&](float (&v)[8], split_frag (&f)[3]) __attribute__((always_inline)) {
+        auto split = [&](float (&v)[8], float scale, split_frag (&f)[3]) __attribute__((always_inline)) {
             if constexpr (CAREFUL) {
-                uint4 h, m, l;
-                split3_pack8(v, h, m, l);
-                f[0] = __builtin_bit_cast(split_frag, h); f[1] = __builtin_bit_cast(split_frag, m); f[2] = __builtin_bit_cast(split_frag, l);
+                float u[8];
+#pragma unroll
+                for (int e = 0; e < 8; e++) u[e] = v[e] * scale;
+                split3_careful(u, f);
             } else {
                 split3_plain(v, f);
             }
         };
         auto split_f = [&](int set, int f, split_frag (&fz)[KB][3], split_frag (&fx)[CB][3]) __attribute__((always_inline)) {
             if (f < CB) {
-                split(xr[set][f < CB ? f : 0], fx[f < CB ? f : 0]);
+                split(xr[set][f < CB ? f : 0], sx, fx[f < CB ? f : 0]);
             } else {
                 const int kb = f - CB;
                 float (&z)[8] = zr[set][kb];
@@ -140,7 +142,7 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
                     for (int e = 0; e < 8; e++) z[e] = yr[set][MASKED ? kb : 0][e] > 0.f ? z[e] : 0.f;
                 }
                 if (DB) db[kb] += ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7]));
-                split(z, fz[kb]);
+                split(z, sz, fz[kb]);
             }
         };
 
@@ -199,16 +201,38 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
     const bool do_db = ct == 0 && p.dbias != nullptr;
     if (do_db) walk(std::true_type{}, std::false_type{});
     else walk(std::false_type{}, std::false_type{});
-    float sum = 0.f;
+    // Is every sum finite, and none but zero so small that operands may have lost bits?  If not, once more with the split that
+    // tests for large values: scaled up, and where that is not finite (or the first run was not) with products that no finite
+    // operands take out of the range.
+    float unscale = 1.f;
+    unsigned low;
+    auto all_finite = [&]() __attribute__((always_inline)) {
+        float sum = 0.f;
+        low = ~0u;                                   // of twice the bits, less one: zero counts as large
 #pragma unroll
-    for (int kb = 0; kb < KB; kb++)
+        for (int kb = 0; kb < KB; kb++)
 #pragma unroll
-        for (int cb = 0; cb < CB; cb++)
+            for (int cb = 0; cb < CB; cb++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) sum += big[kb][cb][e] + small[kb][cb][e];
-    if (__ballot(!(fabsf(sum) < __builtin_inff())) != 0) {       // see xfilter.hpp
-        clear();
-        walk(std::false_type{}, std::true_type{});
+                for (int e = 0; e < 16; e++) {
+                    const float v = big[kb][cb][e] + small[kb][cb][e];
+                    sum += v;
+                    low = min(low, (__float_as_uint(v) << 1) - 1u);
+                }
+        return __ballot(!(fabsf(sum) < __builtin_inff())) == 0;
+    };
+    bool finite = all_finite();
+    if (!finite || __ballot(low < (__float_as_uint(kSplitTiny) << 1) - 1u) != 0) {
+        bool up = finite;
+        do {
+            sx = up ? kSplitScale : 1.f;
+            sz = up ? kSplitScale : kSplitDown;
+            unscale = up ? kSplitUnscale : kSplitUndown;
+            clear();
+            walk(std::false_type{}, std::true_type{});
+            finite = all_finite() || !up;
+            up = false;
+        } while (!finite);
     }
 
     // register e of lane (li, lh): filter 8*(e/4) + 4*lh + e%4 of its block, place li
@@ -225,7 +249,7 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
                 const int k = k0 + kb * 32 + 8 * (e / 4) + 4 * lh + e % 4;
                 if (k >= g.K) continue;
                 const size_t at = (size_t)k * p.Ncols + j;
-                const float v = big[kb][cb][e] + small[kb][cb][e];
+                const float v = (big[kb][cb][e] + small[kb][cb][e]) * unscale;
                 if (part) out[at] = v;
                 else out[at] = p.alpha * v + (p.beta != 0.f ? p.beta * out[at] : 0.f);
             }

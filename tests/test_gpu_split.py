@@ -498,3 +498,131 @@ def test_tuned_shard_backward(dt, N, I, O):
             if dt == "bf16" and name == "dx":
                 bound += 2.0 ** -8 * np.abs(ref)
             assert np.max(np.abs(to_host(out[name]) - ref) / bound) <= 1.0, (name, again)
+
+
+# Operands at the ends of the fp32 range: (scale of the one, of the other) with results well inside it.  2^-118: normal and
+# subnormal values; 2^106 next to 2^-100; sums near 2^100 of operands near 2^50.  Every bit of an operand counts: the 2-norm bound
+# of the ordinary range has to hold (a sum beyond 2^80 may be an fp32 sum in order, whose roundings are L at random).
+ENDS = [(2.0 ** -118, 2.0 ** 20), (2.0 ** 20, 2.0 ** -118), (2.0 ** 106, 2.0 ** -100), (2.0 ** -100, 2.0 ** 106), (2.0 ** 50, 2.0 ** 50), (2.0 ** -60, 2.0 ** -50)]
+
+
+def check_ends(got, ref, L, what):
+    norm = np.linalg.norm((got - ref) / np.abs(ref).max()) / np.linalg.norm(ref / np.abs(ref).max())
+    bound = 2.0 ** -23 * np.sqrt((L if np.abs(ref).max() > 2.0 ** 79 else L / 16) + 4)
+    print("  %s: relative 2-norm error %.2e of %.2e" % (what, norm, bound))
+    sys.stdout.flush()
+    assert norm <= bound, what
+
+
+def conv64(x, w, stride, pad, P, Q):
+    (N, H, W, C), (K, R, S, _) = x.shape, w.shape
+    xp = np.zeros((N, H + 2 * pad, W + 2 * pad, C)); xp[:, pad:pad + H, pad:pad + W] = x
+    y, dw_of = np.zeros((N, P, Q, K)), []
+    for r in range(R):
+        for s in range(S):
+            xs = xp[:, r:r + (P - 1) * stride + 1:stride, s:s + (Q - 1) * stride + 1:stride]
+            y += xs @ w[:, r, s].astype(np.float64).T
+            dw_of.append((r, s, xs))
+    return y, dw_of
+
+
+@pytest.mark.parametrize("a,b", ENDS)
+def test_split_kernels_at_the_ends_of_the_range(a, b):
+    m = owt()
+    with np.errstate(under="ignore"):
+        for tiles, shape in (((40, 41, 42, 43), (2, 24, 9, 10, 40, 3, 3, 1, 1)), ((41, 43), (2, 3, 39, 43, 24, 5, 7, 4, 2))):
+            N, C, H, W, K, R, S, stride, pad = shape
+            g = np.random.default_rng(1200)
+            case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", False, False)
+            x = (g.standard_normal(case.shape_x) * a).astype(np.float32)
+            w = (g.standard_normal(case.shape_w) * b).astype(np.float32)
+            ref = conv64(x, w, stride, pad, case.P, case.Q)[0]
+            for tile in tiles:
+                for split in (1, 2):
+                    with force(tile, split):
+                        plan = m.owt_conv_plan_describe(case.desc, 0)
+                        assert plan.startswith(("xconv", "sconvx")), plan
+                        check_ends(case.fwd(x, w, None), ref, R * S * C, "y " + plan)
+            if stride == 1:           # dx of a symmetric layer is a forward pass with the filters turned round
+                dy = (g.standard_normal(case.shape_y) * a).astype(np.float32)
+                y = g.standard_normal(case.shape_y).astype(np.float32)
+                masked = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", False, True)
+                ref = conv64(dy * (y > 0), w[:, ::-1, ::-1].transpose(3, 1, 2, 0), 1, pad, H, W)[0]
+                for tile in tiles:
+                    for split in (1, 2):
+                        with force(tile, split):
+                            check_ends(masked.bwd_data(dy, y, w), ref, R * S * K, "dx")
+        for tile, shape in ((50, (18, 40, 6, 7, 70, 3, 3, 1, 1)), (51, (18, 40, 6, 7, 33, 5, 5, 1, 2)), (60, (18, 3, 23, 20, 64, 7, 7, 4, 2)), (61, (18, 3, 23, 20, 30, 7, 7, 4, 2))):
+            N, C, H, W, K, R, S, stride, pad = shape
+            g = np.random.default_rng(1210)
+            case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", False, False)
+            x = (g.standard_normal(case.shape_x) * a).astype(np.float32)
+            dy = (g.standard_normal(case.shape_y) * b).astype(np.float32)
+            ref = np.zeros(case.shape_w)
+            for r, s, xs in conv64(x, np.zeros(case.shape_w), stride, pad, case.P, case.Q)[1]:
+                ref[:, r, s] = dy.reshape(-1, K).astype(np.float64).T @ xs.reshape(-1, C)
+            for split in (1, 3):
+                with force(tile, split):
+                    plan = m.owt_conv_plan_describe(case.desc, 2)
+                    assert plan.startswith(("xfilter", "xgather", "sfilterx")), plan
+                    check_ends(case.bwd_filter(x, dy, None, want_db=False)[0], ref, N * case.P * case.Q, "dw " + plan)
+        N, I, O = 70, 300, 90
+        g = np.random.default_rng(1220)
+        x, w, dy = ((g.standard_normal(sh) * sc).astype(np.float32) for sh, sc in (((N, I), a), ((O, I), b), ((N, O), b)))
+        d = m.fc_desc(N, I, O, 1, 0, m.OWT_F32, 0)
+        d2 = m.fc_desc(N, O, I, 1, 0, m.OWT_F32, 0)            # its backward pass: dx and dw of operands scaled a and b, too
+        f64 = lambda t: t.astype(np.float64)
+        for split in (1, 2):
+            with force(70, split):
+                ws = workspace(max(m.owt_fc_workspace_bytes(q, p) for q in (d, d2) for p in (0, 1)))
+                y, dx, dw = empty((N, O)), empty((N, O)), empty((I, O))
+                m.owt_fc_shard_fwd(d, to_dev(x), to_dev(w), None, y, ws)
+                # layer O -> I: its dy is x (N, I), its weights w.T (I, O), its input dy (N, O)
+                m.owt_fc_shard_bwd(d2, to_dev(dy), to_dev(np.ascontiguousarray(w.T)), None, to_dev(x), 1.0, 0.0, dx, dw, None, ws)
+                torch.cuda.synchronize()
+            check_ends(to_host(y), f64(x) @ f64(w).T, I, "shard y")
+            check_ends(to_host(dx), f64(x) @ f64(w).T, I, "shard dx")
+            check_ends(to_host(dw), f64(x).T @ f64(dy), N, "shard dw")
+
+
+def test_a_product_just_below_the_largest_number_stays_finite():
+    # 0x1.ffp0 * 0x1.ffp126 = 0x1.fe01p127, each operand halfway between two bf16 values: their large parts alone give 2^128
+    m = owt()
+    one, big = np.float32(float.fromhex("0x1.ffp0")), np.float32(float.fromhex("0x1.ffp126"))
+    want = np.float32(float(one) * float(big))
+    assert np.isfinite(want)
+    for u, v in ((one, big), (big, one), (-one, big)):
+        want = np.float32(float(u) * float(v))
+        for tile, shape in ((40, (1, 20, 5, 6, 9, 3, 3, 1, 1)), (42, (1, 20, 5, 6, 9, 1, 1, 1, 0)), (43, (1, 20, 5, 6, 9, 3, 3, 1, 1)), (41, (1, 3, 24, 24, 9, 5, 5, 4, 2))):
+            N, C, H, W, K, R, S, stride, pad = shape
+            case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", False, False)
+            x, w = np.zeros(case.shape_x, np.float32), np.zeros(case.shape_w, np.float32)
+            x[0, 2, 2, 2] = u
+            w[4, R // 2, S // 2, 2] = v
+            with force(tile, 1):
+                got = case.fwd(x, w, None)
+            ref = conv64(x, w, stride, pad, case.P, case.Q)[0].astype(np.float32)
+            assert np.abs(ref).max() == abs(want) or stride > 1
+            assert np.array_equal(got, ref), (tile, got[np.abs(got) > 0], want)
+        for tile, shape in ((50, (3, 5, 4, 5, 9, 3, 3, 1, 1)), (51, (3, 5, 4, 5, 9, 5, 5, 1, 2)), (61, (3, 3, 9, 9, 9, 3, 3, 2, 1))):
+            N, C, H, W, K, R, S, stride, pad = shape
+            case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", False, False)
+            x, dy = np.zeros(case.shape_x, np.float32), np.zeros(case.shape_y, np.float32)
+            x[1, 2, 2, 1], dy[1, 1, 1, 3] = u, v
+            ref = np.zeros(case.shape_w)
+            for r, s, xs in conv64(x, np.zeros(case.shape_w), stride, pad, case.P, case.Q)[1]:
+                ref[:, r, s] = dy.reshape(-1, K).astype(np.float64).T @ xs.reshape(-1, C)
+            assert np.abs(ref).max() == abs(float(u) * float(v))
+            with force(tile, 1):
+                got, _ = case.bwd_filter(x, dy, None, want_db=False)
+            assert np.array_equal(got, ref.astype(np.float32)), tile
+        for split in (1, 2):
+            N, I, O = 5, 40, 7
+            x, w = np.zeros((N, I), np.float32), np.zeros((O, I), np.float32)
+            x[2, 3], w[4, 3] = u, v
+            d = m.fc_desc(N, I, O, 1, 0, m.OWT_F32, 0)
+            with force(70, split):
+                ws, y = workspace(m.owt_fc_workspace_bytes(d, 0)), empty((N, O))
+                m.owt_fc_shard_fwd(d, to_dev(x), to_dev(w), None, y, ws)
+                torch.cuda.synchronize()
+            assert np.array_equal(to_host(y), (x.astype(np.float64) @ w.astype(np.float64).T).astype(np.float32))
