@@ -150,12 +150,15 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
                 split3_plain(v, f);
             }
         };
+        float row_db[KB];                            // the bias gradient's sum of a row: one long chain of additions rounds more
+#pragma unroll
+        for (int kb = 0; kb < KB; kb++) row_db[kb] = 0.f;
         auto split_z = [&](int kb, float (&v)[8], const float (&y)[8], split_frag (&f)[3]) __attribute__((always_inline)) {
             if (MASKED) {
 #pragma unroll
                 for (int e = 0; e < 8; e++) v[e] = y[e] > 0.f ? v[e] : 0.f;
             }
-            if (DB) db[kb] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+            if (DB) row_db[kb] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
             split(v, sz, f);
         };
 
@@ -228,6 +231,10 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
                 for (int kb = 0; kb < KB; kb++)
 #pragma unroll
                     for (int e = 0; e < 3; e++) az[kb][e] = nz[kb][e];
+            }
+            if (DB) {
+#pragma unroll
+                for (int kb = 0; kb < KB; kb++) { db[kb] += row_db[kb]; row_db[kb] = 0.f; }
             }
             row = ahead;
         }

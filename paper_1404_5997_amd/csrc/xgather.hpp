@@ -131,6 +131,9 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
                 split3_plain(v, f);
             }
         };
+        float run_db[KB];                            // the bias gradient's sum of 16 positions: one long chain of additions rounds more
+#pragma unroll
+        for (int kb = 0; kb < KB; kb++) run_db[kb] = 0.f;
         auto split_f = [&](int set, int f, split_frag (&fz)[KB][3], split_frag (&fx)[CB][3]) __attribute__((always_inline)) {
             if (f < CB) {
                 split(xr[set][f < CB ? f : 0], sx, fx[f < CB ? f : 0]);
@@ -141,7 +144,7 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
 #pragma unroll
                     for (int e = 0; e < 8; e++) z[e] = yr[set][MASKED ? kb : 0][e] > 0.f ? z[e] : 0.f;
                 }
-                if (DB) db[kb] += ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7]));
+                if (DB) run_db[kb] += ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7]));
                 split(z, sz, fz[kb]);
             }
         };
@@ -193,6 +196,10 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
                 for (int cb = 0; cb < CB; cb++)
 #pragma unroll
                     for (int e = 0; e < 3; e++) bx[cb][e] = nx[cb][e];
+            }
+            if (DB && (((i - o_beg) & 14) == 14 || i + 2 >= o_end)) {
+#pragma unroll
+                for (int kb = 0; kb < KB; kb++) { db[kb] += run_db[kb]; run_db[kb] = 0.f; }
             }
         }
     };

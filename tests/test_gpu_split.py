@@ -626,3 +626,28 @@ def test_a_product_just_below_the_largest_number_stays_finite():
                 m.owt_fc_shard_fwd(d, to_dev(x), to_dev(w), None, y, ws)
                 torch.cuda.synchronize()
             assert np.array_equal(to_host(y), (x.astype(np.float64) @ w.astype(np.float64).T).astype(np.float32))
+
+
+@pytest.mark.parametrize("tile,shape", [(50, (128, 32, 13, 13, 384, 3, 3, 1, 1)), (50, (2, 32, 39, 46, 64, 3, 3, 1, 1)), (60, (64, 3, 55, 55, 64, 3, 3, 2, 1)), (61, (128, 4, 13, 13, 384, 3, 3, 1, 1))])
+def test_split_bias_gradient_is_no_single_chain(tile, shape):
+    # Sums of n normal values are sqrt(n) large, and an addition rounds by 0.29 * 2^-23 of its result (2-norm), at random.  Eight
+    # images in a tree: 7/8 n results of 3 squared; rows of L positions (or runs of L = 16): n/8 results of up to 8 L / 2; the whole:
+    # n / (8 L) results of n / 2.  Half as much again is allowed.  One chain of all positions has n/8 results of n / 2.
+    m = owt()
+    N, C, H, W, K, R, S, stride, pad = shape
+    case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", True, False)
+    g = torch.Generator(device="cuda").manual_seed(1250)
+    worst = 0.0
+    for seed in range(4):
+        x, dy = torch.randn(case.shape_x, generator=g, device="cuda"), torch.randn(case.shape_y, generator=g, device="cuda")
+        dw, db = empty(case.shape_w), empty((K,))
+        with force(tile, 1):
+            assert m.owt_conv_plan_describe(case.desc, 2).startswith(("xfilter", "xgather", "sfilterx"))
+            m.owt_conv_bwd_filter(case.desc, x, dy, None, 1.0, 0.0, dw, db, case.ws(2))
+            torch.cuda.synchronize()
+        ref = dy.double().view(-1, K).sum(0)
+        worst = max(worst, ((db - ref).norm() / ref.norm()).item())
+    n, L = N * case.P * case.Q, case.Q if tile < 60 else 16
+    bound = 1.5 * 0.29 * np.sqrt(7 / 8 * 3 + L / 2 + n / (16 * L))
+    print("  worst of four: %.2f * 2^-23 of %.2f" % (worst * 2 ** 23, bound))
+    assert worst * 2 ** 23 < bound < 1.5 * 0.29 * np.sqrt(n / 16)
