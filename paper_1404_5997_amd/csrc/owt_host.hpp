@@ -58,9 +58,9 @@ hipError_t owt_launch_xconv_fwd_blocks(int variant, int pr, const GemmParams &, 
 hipError_t owt_launch_xconv_data_vec0(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 hipError_t owt_launch_xconv_data_vec1(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 
-// Stride-1 filter gradient for fp32 storage on the bf16 MFMA with split operands (xfilter_inst.hip): one wavefront per
-// work-group holds KB filter blocks of 32 x 32 channels x the S taps of a filter row.  The test hook numbers the
-// variants from 50.
+// Stride-1 filter gradient for fp32 storage on the bf16 MFMA with split operands (xfilter_inst.hip): a wavefront holds KB
+// filter blocks of 32 x 32 channels x the S taps of a filter row, four wavefronts of neighbouring tiles to a work-group.  The
+// test hook numbers the variants from 50.
 struct XFilterVariant { int KB, S; };
 constexpr int kNumXFilterVariants = 2, kXFilterFirstTile = 50;
 constexpr XFilterVariant kXFilterVariants[kNumXFilterVariants] = {{2, 3}, {1, 5}};
