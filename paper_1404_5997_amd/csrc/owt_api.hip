@@ -1113,11 +1113,11 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     if (l.kind == KIND_XGATHER)
         return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilterx" : "xgather", pn[pass], ds,
                         32 * kXGatherVariants[l.tile].KB, 32 * kXGatherVariants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,
-                        (long)l.tiles_m * l.tiles_n * l.splits * 64);
+                        8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 64);
     if (l.kind == KIND_XFILTER)
         return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
-                        (long)l.tiles_m * l.tiles_n * l.splits * 64);
+                        8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4), 8) * 256);
     if (l.kind == KIND_SCONV16)
         return snprintf(buf, n, "sconv16 %s %s rows%d grid%dx%d threads%ld", pn[pass], ds, kSConv16TP, l.tiles_m, l.tiles_n,
                         (long)l.tiles_m * l.tiles_n * kSConv16NT);
