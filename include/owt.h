@@ -31,12 +31,14 @@
  *  - dtype names the STORAGE type of x, w, y, dy, dx.  Products are
  *    accumulated in fp32; bias, dw and dbias are always fp32.  bf16 results are
  *    rounded to nearest-even once, when stored.  fp32 operands may be
- *    multiplied as sums of three bf16 values, which hold every bit of them over
- *    the whole range; of the nine partial products the three smallest, at most
- *    2^-24 of the product together, are left out.  On normally distributed
- *    operands the 2-norm error against 64 bits measured 0.35 times that of the
- *    fp32 matrix instruction in sums of 576 to 23328 products; in sums of one or
- *    two products it can be the larger one, by less than one rounding.
+ *    multiplied as sums of three bf16 values, which hold every bit of them
+ *    (filter gradients may lose bits of an operand below 2^-110 that meets one
+ *    above 2^40, and take one below 2^-134 for zero); of the nine partial
+ *    products the three smallest, at most 2^-24 of the product together, are
+ *    left out.  On normally distributed operands the 2-norm error against 64
+ *    bits measured 0.35 times that of the fp32 matrix instruction in sums of 576
+ *    to 23328 products; in sums of one or two products it can be the larger one,
+ *    by less than one rounding.
  *  - Output size P = floor((H + 2*pad_h - R)/stride_h) + 1, Q likewise.
  */
 #ifndef OWT_H

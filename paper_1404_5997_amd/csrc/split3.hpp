@@ -3,10 +3,9 @@
 // which is exact (3 x 8 significant bits) where none of the parts leaves bf16's range, and of the nine products of two such
 // sums the six largest are taken:
 //     v*w ~ h*h' + (h*m' + m*h') + (m*m' + h*l' + l*h'),
-// leaving out m*l' + l*m' + l*l', at most 2^-24 |v*w| together (|m| <= 2^-8 |v|, |l| <= 2^-17 |v|).  A bf16 product is exact
-// in fp32, so what is left is the rounding of the
-// accumulators.  h*h' is added up in one accumulator and the five small products in another; the two are added once
-// at the end.  Each 16-deep matrix instruction rounds its accumulator once, so a reduction of length L rounds the large
+// leaving out m*l' + l*m' + l*l', at most 2^-24 |v*w| together (|m| <= 2^-8 |v|, |l| <= 2^-17 |v|).  A bf16 product is exact in
+// fp32, so what is left is the rounding of the accumulators.  h*h' is added up in one accumulator and the five small products in
+// another; the two are added once at the end.  Each 16-deep matrix instruction rounds its accumulator once, so a reduction of length L rounds the large
 // accumulator L/16 times where the fp32 matrix instruction (2 deep) rounds L/2 times.  Measured against 64 bits on
 // sums of normally distributed products, relative 2-norm error, fp32 instruction -> this scheme: length 576
 // 4.3e-7 -> 1.4e-7, 1728 7.4e-7 -> 2.5e-7, 4800 1.2e-6 -> 4.3e-7, 23328 2.7e-6 -> 9.8e-7.  (All six products in one
@@ -30,8 +29,9 @@ __device__ __forceinline__ float bf16_lo_f32(uint32_t pair) { return __uint_as_f
 __device__ __forceinline__ float bf16_hi_f32(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
 
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
-// A result below this is worked out again scaled.  A larger one has lost less than 2^-24 of it to operands below 2^-110 as long
-// as the values these were multiplied with add up to less than 2^46.
+// A result below this, and not zero, is worked out again scaled.  A larger one has lost less than 2^-24 of it to operands below
+// 2^-110 as long as the values these were multiplied with add up to less than 2^46.  (A result of zero stays: the plain split takes
+// operands below 2^-134 for zero.)
 constexpr float kSplitTiny = 0x1p-64f;
 // Scales of the two operands for the second run of a result that was not finite: no product leaves the range that fits in it.
 constexpr float kSplitDown = 0x1p-2f, kSplitUndown = 4.f;
