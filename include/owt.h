@@ -150,9 +150,10 @@ owt_status owt_conv_bwd_filter_static(const owt_conv_desc *d, const void *x, con
                                       float alpha, float beta, float *dw, float *dbias_or_null, void *hip_stream);
 size_t owt_static_scratch_bytes(void);
 
-/* Optional tuning.  Runs every kernel variant the planner knows for this pass
- * on the caller's buffers (three timed repetitions each, HIP events on
- * hip_stream), and remembers the fastest: later owt_conv_* calls in this
+/* Optional tuning.  Runs the kernel variants that the planner's cost model puts
+ * within three times its own choice (those that split fp32 operands and their
+ * reduction: twice) on the caller's buffers (three timed repetitions each, HIP
+ * events on hip_stream), and remembers the fastest: later owt_conv_* calls in this
  * process with an identical descriptor use it.  Blocks until the timing is
  * done.  Buffers are those of the pass itself (others may be NULL):
  *   OWT_PASS_FWD        reads x, w, bias              writes y
@@ -186,8 +187,9 @@ owt_status owt_fc_shard_bwd(const owt_fc_desc *d, const void *x, const void *w, 
                             void *hip_stream);
 
 /* Optional tuning of a dense shard, as owt_conv_autotune does for a convolution:
- * times every kernel variant of the three passes (forward; the two halves of
- * owt_fc_shard_bwd, and whether those two run faster as one launch or as two)
+ * times the variants of the three passes (forward; the two halves of
+ * owt_fc_shard_bwd) and then the ways to run those two halves together (each
+ * by itself, a pair of launches, or one launch of either kernel that has one)
  * on the caller's buffers and remembers the fastest for later
  * owt_fc_shard_* calls with an identical descriptor in this process.  Reads x,
  * w, bias, y (ReLU mask), dy; writes y, dx_partial, dw, dbias (alpha 1, beta 0).
