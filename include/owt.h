@@ -33,7 +33,8 @@
  *    rounded to nearest-even once, when stored.  fp32 operands may be
  *    multiplied as sums of three bf16 values, which hold every bit of them
  *    (filter gradients may lose bits of an operand below 2^-110 that meets one
- *    above 2^40, and take one below 2^-134 for zero); of the nine partial
+ *    above 2^40 or whose result lies beside one past 2^80, and take one below
+ *    2^-134 for zero); of the nine partial
  *    products the three smallest, at most 2^-24 of the product together, are
  *    left out.  On normally distributed operands the 2-norm error against 64
  *    bits measured 0.35 times that of the fp32 matrix instruction in sums of 576

@@ -31,7 +31,7 @@ __device__ __forceinline__ float bf16_hi_f32(uint32_t pair) { return __uint_as_f
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 // A result below this, and not zero, is worked out again scaled.  A larger one has lost less than 2^-24 of it to operands below
 // 2^-110 as long as the values these were multiplied with add up to less than 2^46.  (A result of zero stays: the plain split takes
-// operands below 2^-134 for zero.)
+// operands below 2^-134 for zero.  And a tile that holds such a result beside one past 2^80 keeps what the second scale gives.)
 constexpr float kSplitTiny = 0x1p-64f;
 // Scales of the two operands for the second run of a result that was not finite: no product leaves the range that fits in it.
 constexpr float kSplitDown = 0x1p-2f, kSplitUndown = 4.f;

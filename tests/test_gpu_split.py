@@ -707,3 +707,30 @@ def test_fully_connected_shard_of_large_tensors(N, I, O):
         err = ((got - want).norm() / want.norm()).item()
         print("  %s: %.2e" % (name, err))
         assert err < 2.0 ** -23 * np.sqrt(L / 16 + 4), name
+
+
+@pytest.mark.parametrize("tile,shape", [(50, (18, 40, 6, 7, 70, 3, 3, 1, 1)), (51, (18, 40, 6, 7, 33, 5, 5, 1, 2)), (60, (18, 3, 23, 20, 64, 7, 7, 4, 2)), (61, (18, 3, 23, 20, 30, 7, 7, 4, 2))])
+def test_both_ends_of_the_range_in_one_tile(tile, shape):
+    # channel 0 near 2^110, where scaled operands are infinite, channel 1 near 2^-118: the tile's second run is not finite, its third
+    # keeps 2^-13 of channel 1 (a part of 2^-118 that bf16 still holds is 2^-133, 2^-15 of it), everything of the others
+    m = owt()
+    N, C, H, W, K, R, S, stride, pad = shape
+    case = ConvCase(N, C, H, W, K, R, S, stride, pad, "f32", False, False)
+    g = np.random.default_rng(1230)
+    x, dy = g.standard_normal(case.shape_x), g.standard_normal(case.shape_y)
+    x[..., 0] *= 2.0 ** 110
+    x[..., 1] *= 2.0 ** -118
+    x, dy = x.astype(np.float32), dy.astype(np.float32)
+    ref = np.zeros(case.shape_w)
+    for r, s, xs in conv64(x, np.zeros(case.shape_w), stride, pad, case.P, case.Q)[1]:
+        ref[:, r, s] = dy.reshape(-1, K).astype(np.float64).T @ xs.reshape(-1, C)
+    for split in (1, 3):
+        with force(tile, split):
+            assert m.owt_conv_plan_describe(case.desc, 2).startswith(("xfilter", "xgather", "sfilterx"))
+            got = case.bwd_filter(x, dy, None, want_db=False)[0]
+        assert np.isfinite(got).all()
+        check_ends(got[..., 0], ref[..., 0], N * case.P * case.Q, "channel 0")
+        check_ends(got[..., 2:], ref[..., 2:], N * case.P * case.Q, "the others")
+        low = np.linalg.norm((got[..., 1] - ref[..., 1]) * 2.0 ** 118) / np.linalg.norm(ref[..., 1] * 2.0 ** 118)
+        print("  channel 1: %.2e" % low)
+        assert low < 2.0 ** -13
