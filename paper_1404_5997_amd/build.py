@@ -36,6 +36,8 @@ def _units():
         units.append(("dconv16_%s.o" % pname, "dconv_bf16_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
     units.append(("xfilter.o", "xfilter_inst.hip", []))
     units.append(("xgather.o", "xgather_inst.hip", []))
+    for masked in (0, 1):
+        units.append(("ifilter16_%d.o" % masked, "ifilter16_inst.hip", ["-DOWT_INST_MASKED=%d" % masked]))
     units.append(("xfc.o", "xfc_inst.hip", []))
     units.append(("fcgemm.o", "fcgemm_inst.hip", []))
     units.append(("dfilter2.o", "dfilter2_inst.hip", []))

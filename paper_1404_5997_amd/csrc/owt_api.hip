@@ -58,10 +58,14 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19 };
 
-// Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), and the shard's for either storage type.
-static inline bool is_split_kind(int kind) { return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC; }
+// Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), the shard's for either storage type, and those for
+// bf16 storage of any channel count: a call whose scratch is too small for one of them is served by the kernels before them.
+static inline bool is_split_kind(int kind)
+{
+    return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16;
+}
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
 
@@ -375,7 +379,7 @@ static const size_t kMaxPartialBytes = (size_t)192 << 20;
 static bool image_groups_fit(const Geom &g, bool xgather)
 {
     const double groups = 16.0 * (double)cdiv(g.N, 16), images = xgather && g.N + groups - 9.0 > groups ? g.N + groups - 9.0 : groups;
-    const double x = (double)g.H * g.W * g.C * 4.0, z = (double)g.P * g.Q * g.K * 4.0;
+    const double es = g.bf16 ? 2.0 : 4.0, x = (double)g.H * g.W * g.C * es, z = (double)g.P * g.Q * g.K * es;
     return g.N * x < 2147483644.0 && g.N * z < 2147483644.0 && images * x + 1024.0 <= 4294967296.0 && images * z + 1024.0 <= 4294967296.0;
 }
 
@@ -638,6 +642,43 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const double clocks = per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0;
                 l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
                 if (splits > 1) l.cost += 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
+    // bf16 storage, any channel counts: the same decomposition
+    if (pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
+        image_groups_fit(g, false)) {
+        for (int v = 0; v < kNumIFilter16Variants; v++) {
+            const IFilter16Variant &iv = kIFilter16Variants[v];
+            if ((force_tile >= 0 && force_tile != kIFilter16FirstTile + v) || g.S != iv.S) continue;
+            const long tm = cdiv(g.K, 32 * iv.KB), ctl = cdiv(g.C, 32 * iv.CB), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
+            const long slots = 1024L * ifilter16_occ(iv.KB, iv.CB, iv.S);
+            const int zl = iv.KB == 2 && g.K % 2 ? 16 : 8, xl = iv.CB == 2 && g.C % 2 ? 16 : 8;
+            for (long s0 : split_ladder(tiles, slots)) {
+                long s = s0;
+                if (force_split > 0) s = force_split < steps ? force_split : steps;
+                else if (s > 1 && (steps / s < 3 || tiles * s > 8192)) break;
+                const long per = cdiv(steps, s), splits = cdiv(steps, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_IFILTER16; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
+                l.tiles_m = (int)tm; l.tiles_n = (int)(ctl * g.R); l.ctiles = (int)ctl; l.taps = g.S; l.groups = g.R;
+                if (splits > 1) {
+                    l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                    l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
+                }
+                // Fitted to 430 timed launches of 42 drawn layers (0.20 in the logarithm; its choice is 1 % slower than the fastest
+                // timed): a column takes a wavefront 31 clocks a matrix instruction and 29 a load, times the wavefronts that
+                // share a SIMD, and 650 at least (latency); 19000 for launch, first loads and last stores, 1950 a block for
+                // its stores; the reduce pass 4 us and 0.24 us a MB.
+                const double resident = std::min((double)ifilter16_occ(iv.KB, iv.CB, iv.S), std::max(1.0, tiles * splits / 1024.0));
+                const double column = std::max(650.0, resident * (31.0 * iv.KB * iv.CB * iv.S + 29.0 * ((g.masked ? 2 : 1) * zl + xl)));
+                const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
+                l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
+                if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1056,6 +1097,9 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
     } else if (l.kind == KIND_XFILTER) {
         p.ctiles = l.ctiles;
         e = owt_launch_xfilter(l.tile, p, s);
+    } else if (l.kind == KIND_IFILTER16) {
+        p.ctiles = l.ctiles;
+        e = p.mask ? owt_launch_ifilter16_masked(l.tile, p, s) : owt_launch_ifilter16(l.tile, p, s);
     } else if (l.kind == KIND_DFILTER16B) {
         p.Hp = g.H + 2 * g.ph; p.Wp = g.W + 2 * g.pw; p.taps = l.taps; p.groups = l.groups; p.ctiles = l.ctiles;
         p.dWp.set(p.Wp); p.dHpWp.set(p.Hp * p.Wp);
@@ -1117,6 +1161,10 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     if (l.kind == KIND_XFILTER)
         return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
+                        8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4), 8) * 256);
+    if (l.kind == KIND_IFILTER16)
+        return snprintf(buf, n, "ifilter16 %s %s tile%dx%d taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
+                        32 * kIFilter16Variants[l.tile].KB, 32 * kIFilter16Variants[l.tile].CB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
                         8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4), 8) * 256);
     if (l.kind == KIND_SCONV16)
         return snprintf(buf, n, "sconv16 %s %s rows%d grid%dx%d threads%ld", pn[pass], ds, kSConv16TP, l.tiles_m, l.tiles_n,

@@ -74,6 +74,17 @@ constexpr int kNumXGatherVariants = 2, kXGatherFirstTile = 60;
 constexpr XGatherVariant kXGatherVariants[kNumXGatherVariants] = {{2, 3}, {1, 3}};
 hipError_t owt_launch_xgather(int variant, const GemmParams &, hipStream_t);
 
+// Stride-1 filter gradient for bf16 storage and any channel counts, reduction over images (ifilter16_inst.hip): a wavefront
+// holds KB filter blocks x CB channel blocks of 32 x the S taps of a filter row, four wavefronts to a work-group.  The test hook
+// numbers the variants from 80.
+struct IFilter16Variant { int KB, CB, S; };
+constexpr int kNumIFilter16Variants = 7, kIFilter16FirstTile = 80;
+constexpr IFilter16Variant kIFilter16Variants[kNumIFilter16Variants] = {{1, 1, 3}, {2, 1, 3}, {1, 2, 3}, {2, 2, 3}, {1, 1, 5}, {2, 1, 5}, {1, 2, 5}};
+// wavefronts per SIMD that a tile's registers allow
+constexpr int ifilter16_occ(int KB, int CB, int S) { return KB * CB * S <= 6 ? 2 : 1; }
+hipError_t owt_launch_ifilter16(int variant, const GemmParams &, hipStream_t);
+hipError_t owt_launch_ifilter16_masked(int variant, const GemmParams &, hipStream_t);
+
 // The fully-connected shard on the bf16 MFMA (xfc_inst.hip), both storage types; test-hook number 70.  Backward: one launch
 // for the products whose parameters are given.
 constexpr int kXFcTile = 70;
