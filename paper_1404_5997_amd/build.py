@@ -34,6 +34,8 @@ def _units():
                           ["-DOWT_INST_PASS=%d" % ps, "-DOWT_INST_VEC=%d" % vec]))
     for ps, pname in ((0, "fwd"), (1, "data")):
         units.append(("dconv16_%s.o" % pname, "dconv_bf16_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
+    for ps, pname in ((0, "fwd"), (1, "data"), (2, "blocks")):
+        units.append(("dconv16x_%s.o" % pname, "dconv16x_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
     units.append(("xfilter.o", "xfilter_inst.hip", []))
     units.append(("xgather.o", "xgather_inst.hip", []))
     for masked in (0, 1):

@@ -58,13 +58,13 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20 };
 
 // Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), the shard's for either storage type, and those for
 // bf16 storage of any channel count: a call whose scratch is too small for one of them is served by the kernels before them.
 static inline bool is_split_kind(int kind)
 {
-    return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16;
+    return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16 || kind == KIND_DIRECT16X;
 }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
@@ -503,6 +503,35 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             }
             if (pass == OWT_PASS_BWD_DATA)
                 for (size_t i = n0; i < out.size(); i++) out[i].pre_bytes = pad256((size_t)g.K * g.R * g.S * g.C * 2);
+        }
+    }
+    // bf16 storage where the pipelined kernel above is no candidate (channels not in whole chunks of 32, maps wider than its panel,
+    // strided layers): the same loop with panel pieces at any address.  Against the 64-channel kernel, which takes multiples of
+    // eight, the model decides between the two; it chose the faster one in 71 of 72 timed passes.
+    bool whole = false;                                 // the pipelined kernel takes it as it is
+    for (const Launch &o : out) whole |= o.kind == KIND_DIRECT16 && (o.tile == TILE_512x64 || o.tile == TILE_256x64P);
+    if (g.bf16 && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs >= 2 && xr * xs <= 32 &&
+        (force_tile < 0 ? !whole : force_tile == kDirect16xTile) &&
+        (!blocks || (pass == OWT_PASS_FWD && 2L * g.R * g.S >= xr * xs * g.sh * g.sw && g.sh * g.sw <= 32 && xred <= 256)) &&
+        (size_t)g.N * g.H * g.W * g.C < 0x3ffffff0ull && (size_t)g.N * g.P * g.Q * g.K < 0x3ffffff0ull) {
+        const long rows = panel_rows(g, pass, dm, 256, blocks), chunks = cdiv(xred, 32), tm = cdiv(dm.M, 256), tn = cdiv(dm.Ncols, 64);
+        const size_t packed = (size_t)dm.Ncols * xr * xs * chunks * 64;
+        if (rows >= 0 && rows <= 512 && packed < 0x7fffffffull) {
+            for (long s0 : kSplits) {
+                if (s0 > 1 && force_split <= 0 && (s0 > chunks || s0 > 16)) break;
+                const long s = force_split > 0 ? (force_split < chunks ? force_split : chunks) : s0;
+                const long per = cdiv(chunks, s), splits = cdiv(chunks, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_DIRECT16X; l.tile = 0; l.pr = rows <= 288 ? 288 : rows <= 384 ? 384 : 512; l.blocks = blocks;
+                l.splits = (int)splits; l.steps = (int)chunks; l.steps_per_split = (int)per; l.tiles_m = (int)tm; l.tiles_n = (int)tn;
+                l.pre_bytes = pad256(packed);
+                if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                l.cost = model_cost(tm * tn * splits, 4, 2, 256.0 * 64 * 32 * xr * xs * per / 9.0, 1.25, splits, dm.M, dm.Ncols) + 5000.0;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
         }
     }
     SConvGeom scg;
@@ -1048,6 +1077,11 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
         if (blocks) e = owt_launch_xconv_fwd_blocks(l.tile, l.pr, p, ws, s);
         else if (pass == OWT_PASS_FWD) e = vec ? owt_launch_xconv_fwd_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_fwd_vec0(l.tile, l.pr, p, ws, s);
         else e = vec ? owt_launch_xconv_data_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_data_vec0(l.tile, l.pr, p, ws, s);
+    } else if (l.kind == KIND_DIRECT16X) {
+        if (l.blocks) blocks_frame(g, p); else dconv_frame(g, pass, p);
+        p.dWp.set(p.Wi); p.dHpWp.set(p.Hi * p.Wi);
+        e = l.blocks ? owt_launch_dconv16x_blocks(l.pr, p, ws, s)
+                     : pass == OWT_PASS_FWD ? owt_launch_dconv16x_fwd(l.pr, p, ws, s) : owt_launch_dconv16x_data(l.pr, p, ws, s);
     } else if (l.kind == KIND_FCGEMM) {
         e = owt_launch_fcgemm(pass, l.tile, p, (float *)ws, s);
     } else if (l.kind == KIND_DIRECT16) {
@@ -1150,6 +1184,9 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         return snprintf(buf, n, "%s %s %s tile%dx%dx16 waves%dx%d panel%d splitk%d grid%dx%d threads%ld", l.blocks ? "sconvx" : "xconv", pn[pass], ds, 32 * v.MB * v.WM,
                         64 * v.WN, v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
     }
+    if (l.kind == KIND_DIRECT16X)
+        return snprintf(buf, n, "%s %s %s tile256x64x32 waves4x1 panel%d splitk%d grid%dx%d threads%ld", l.blocks ? "sconv16x" : "dconv16x", pn[pass], ds, l.pr,
+                        l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 256);
     if (l.kind == KIND_XFC) {
         const long wgs = (long)l.tiles_m * l.tiles_n * l.splits;
         return snprintf(buf, n, "xfc %s %s tile64x64x16 splitk%d grid%ld threads%ld", pn[pass], ds, l.splits, wgs, wgs * 256);

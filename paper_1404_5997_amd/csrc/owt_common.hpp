@@ -53,7 +53,7 @@ struct GemmParams {
     // (ho-pah+r, wo-paw+s), r < R, s < S.
     int Hi, Wi, Ho, Wo, pah, paw, Cred;
     FastDiv dWo, dHoWo;
-    // xconv kernel: the layer's filters; of a strided forward pass seen over blocks of pixels, their height and width
+    // xconv kernel, and dconv16p over blocks: the layer's filters; of a strided forward pass seen over blocks of pixels, their height and width
     const void *b0;
     int R0, S0;
     int tpi;                 // xconv kernel: pixel tiles per image, 0 = tiles run through the batch

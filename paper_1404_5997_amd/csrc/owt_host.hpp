@@ -96,6 +96,13 @@ hipError_t owt_launch_xfc_bwd(bool bf16, const GemmParams *data, const GemmParam
 hipError_t owt_launch_dconv16_fwd(int tile, int pr, const GemmParams &, hipStream_t);
 hipError_t owt_launch_dconv16_data(int tile, int pr, const GemmParams &, void *ws, hipStream_t);
 
+// The pipelined kernel for bf16 layers of any channel counts, and for strided forward passes of few channels seen over blocks
+// of pixels (dconv16x_inst.hip): 256 x 64 tile.  The zero-padded filters go to the front of `ws`.  Test-hook number 90.
+constexpr int kDirect16xTile = 90;
+hipError_t owt_launch_dconv16x_fwd(int pr, const GemmParams &, void *ws, hipStream_t);
+hipError_t owt_launch_dconv16x_data(int pr, const GemmParams &, void *ws, hipStream_t);
+hipError_t owt_launch_dconv16x_blocks(int pr, const GemmParams &, void *ws, hipStream_t);
+
 // Direct filter-gradient kernel (dfilter_inst.hip): wavefront grid WK x WC (32 filters x 32
 // channels each), exactly tmax taps per work-group, LDS panel of prf padded-image pixels.
 // occ = work-groups per CU; aligned = the 32-pixel chunks are cut per image (taken only when the short

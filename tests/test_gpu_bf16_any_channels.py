@@ -14,7 +14,7 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
-from gpu_util import ConvCase, force, owt  # noqa: E402
+from gpu_util import ConvCase, empty, force, owt, to_dev, to_host, workspace  # noqa: E402
 
 
 def check(got, ref, size, L, what, stored=0.0):
@@ -94,3 +94,130 @@ def case_dw(x, dy, R, S, pad):
                 xs = x[:, [i + r - pad for i in p]][:, :, [i + s - pad for i in q]].reshape(-1, C).astype(np.float64)
                 dw[:, r, s] = dy[:, p][:, :, q].reshape(-1, K).astype(np.float64).T @ xs
     return dw
+
+
+# N, C, H, W, K, R, S, pad: reduction channels odd, even and whole eights with a short last chunk or a single short one; result
+# columns odd, even, more than a tile; a tile of pixels less or more than full; rows that need the largest panel
+CONV = [(5, 37, 9, 7, 45, 3, 3, 1), (7, 70, 9, 11, 66, 3, 3, 1), (3, 33, 11, 6, 34, 5, 5, 2), (2, 1, 6, 7, 1, 3, 3, 1), (1, 31, 8, 55, 130, 5, 5, 2),
+        (2, 72, 13, 9, 5, 3, 5, (1, 2)), (3, 10, 5, 40, 3, 5, 3, (2, 1)), (1, 97, 1, 3, 35, 1, 3, (0, 1))]
+
+
+@pytest.mark.parametrize("split", [0, 1, 2])
+@pytest.mark.parametrize("shape", CONV)
+def test_convolution_of_any_channel_counts(shape, split):
+    m = owt()
+    N, C, H, W, K, R, S, pad = shape
+    x, w, b, dy, y = tensors(shape, 1, 1300)
+    for relu in (False, True):
+        case = ConvCase(N, C, H, W, K, R, S, 1, pad, "bf16", True, relu)
+        with force(90, split):
+            plans = [m.owt_conv_plan_describe(case.desc, p) for p in (0, 1)]
+            print("case", shape, "relu", relu, plans)
+            sys.stdout.flush()
+            assert all(p.startswith("dconv16x") for p in plans), plans
+            got, dx = case.fwd(x, w, b), case.bwd_data(dy, y, w)
+        size = oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), 1, pad, False)
+        check(got, oracle.conv_fwd(x, w, b, 1, pad, relu), size, R * S * C, "y", 2.0 ** -8)
+        size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad, y=y if relu else None)
+        check(dx, oracle.conv_bwd_data(dy, w, (H, W), 1, pad, y=y if relu else None), size, R * S * K, "dx", 2.0 ** -8)
+
+
+def test_convolution_of_any_channel_counts_with_the_mask_of_the_layer_below():
+    m = owt()
+    for shape in ((5, 37, 9, 7, 45, 3, 3, 1), (7, 70, 9, 11, 66, 3, 3, 1)):
+        N, C, H, W, K, R, S, pad = shape
+        x, w, b, dy, y = tensors(shape, 1, 1310)
+        case = ConvCase(N, C, H, W, K, R, S, 1, pad, "bf16", True, False)
+        for split in (1, 2):
+            with force(90, split):
+                dx = empty(case.shape_x, "bf16")
+                m.owt_conv_bwd_data_relu_in(case.desc, to_dev(dy, "bf16"), None, to_dev(w, "bf16"), to_dev(x, "bf16"), dx, case.ws(1))
+                torch.cuda.synchronize()
+            size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad)
+            check(to_host(dx), oracle.conv_bwd_data(dy, w, (H, W), 1, pad) * (x > 0), size, R * S * K, "dx masked by x > 0", 2.0 ** -8)
+
+
+def test_channels_of_the_next_pixel_do_not_reach_a_short_chunk():
+    # the last piece of a pixel's channels is loaded 16 bytes wide: what follows belongs to the next pixel and may be infinite
+    m = owt()
+    for shape in ((2, 37, 5, 6, 40, 3, 3, 1), (2, 38, 5, 6, 39, 3, 3, 1)):
+        N, C, H, W, K, R, S, pad = shape
+        x, w, b, dy, y = tensors(shape, 1, 1320)
+        case = ConvCase(N, C, H, W, K, R, S, 1, pad, "bf16", True, False)
+        x[1, 0, 0, :] = np.inf                                   # image 1's first pixel follows image 0's last
+        dy[1, 0, 0, :] = np.inf
+        with force(90):
+            got, dx = case.fwd(x, w, b), case.bwd_data(dy, None, w)
+        assert np.isfinite(got[0]).all() and np.isfinite(dx[0]).all()
+        assert np.isfinite(got[1, 2:]).all() and np.isfinite(got[1, :, 2:]).all() and not np.isfinite(got[1, :2, :2]).any()
+        assert np.isfinite(dx[1, 2:]).all() and np.isfinite(dx[1, :, 2:]).all() and not np.isfinite(dx[1, :2, :2]).any()
+
+
+# N, C, H, W, K, R, S, stride, pad: rows of any length, one to three chunks of a block's values, one split in three
+BLOCKS = [(3, 3, 51, 57, 33, 11, 11, 4, 2), (2, 3, 30, 31, 64, 7, 7, 4, 2), (2, 5, 19, 20, 70, 3, 3, 2, 1), (1, 7, 23, 17, 5, 5, 4, (3, 4), (2, 1)), (2, 1, 40, 9, 8, 6, 5, (4, 2), 0)]
+
+
+@pytest.mark.parametrize("split", [0, 1, 3])
+@pytest.mark.parametrize("shape", BLOCKS)
+def test_strided_forward_over_blocks(shape, split):
+    m = owt()
+    N, C, H, W, K, R, S, stride, pad = shape
+    x, w, b, dy, y = tensors((N, C, H, W, K, R, S, pad), stride, 1330)
+    for relu in (False, True):
+        case = ConvCase(N, C, H, W, K, R, S, stride, pad, "bf16", True, relu)
+        with force(90, split):
+            plan = m.owt_conv_plan_describe(case.desc, 0)
+            print("case", shape, "relu", relu, plan)
+            sys.stdout.flush()
+            assert plan.startswith("sconv16x"), plan
+            got = case.fwd(x, w, b)
+        size = oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), stride, pad, False)
+        check(got, oracle.conv_fwd(x, w, b, stride, pad, relu), size, R * S * C, "y", 2.0 ** -8)
+
+
+@pytest.mark.parametrize("split", [1, 2])
+def test_strided_forward_meets_no_value_outside_its_windows(split):
+    # a 5 x 7 filter at stride 4 x 4: blocks hold pixels that a window does not
+    N, C, H, W, K, R, S, stride, pad = 2, 3, 37, 41, 20, 5, 7, 4, 2
+    x, w, b, dy, y = tensors((N, C, H, W, K, R, S, pad), stride, 1340)
+    case = ConvCase(N, C, H, W, K, R, S, stride, pad, "bf16", True, False)
+    with force(90, split):
+        assert owt().owt_conv_plan_describe(case.desc, 0).startswith("sconv16x")
+        clean = case.fwd(x, w, b)
+        for value in (np.inf, -np.inf, np.nan):
+            for n, h, c in ((0, 0, 0), (0, 19, 22), (1, H - 1, W - 1)):
+                xi = x.copy()
+                xi[n, h, c, 1] = value
+                got = case.fwd(xi, w, b)
+                for p in range(case.P):
+                    for q in range(case.Q):
+                        meets = 0 <= h - (p * 4 - 2) < R and 0 <= c - (q * 4 - 2) < S
+                        assert not meets or not np.isfinite(got[n, p, q]).any()
+                        assert meets or np.array_equal(got[n, p, q], clean[n, p, q])
+                assert np.array_equal(got[1 - n], clean[1 - n])
+
+
+def test_calls_with_the_scratch_of_the_gather_kernel_still_run():
+    # the padded filters need workspace; a call that brings what the kernels before these asked for is served by those, to the bit
+    m = owt()
+    shape = N, C, H, W, K, R, S, pad = (40, 5, 9, 8, 6, 3, 3, 1)
+    x, w, b, dy, y = tensors(shape, 1, 1350)
+    case = ConvCase(N, C, H, W, K, R, S, 1, pad, "bf16", True, False)
+    dev = [to_dev(t, "bf16") for t in (x, w, dy)] + [to_dev(b)]
+    calls = (lambda out, ws: m.owt_conv_fwd(case.desc, dev[0], dev[1], dev[3], out, ws),
+             lambda out, ws: m.owt_conv_bwd_data(case.desc, dev[2], None, dev[1], out, ws),
+             lambda out, ws: m.owt_conv_bwd_filter(case.desc, dev[0], dev[2], None, 1.0, 0.0, out, None, ws))
+    for p, call in enumerate(calls):
+        assert m.owt_conv_plan_describe(case.desc, p).startswith("dconv16x" if p < 2 else "ifilter16")
+        out = [empty((case.shape_y, case.shape_x, case.shape_w)[p], "bf16" if p < 2 else "f32") for _ in range(2)]
+        with force(flags=m.OWT_FORCE_NO_BF16_MFMA):
+            assert m.owt_conv_plan_describe(case.desc, p).startswith("igemm")
+            need = m.owt_conv_workspace_bytes(case.desc, p)
+            assert p == 2 or need == 0
+            call(out[0], workspace(need) if need else None)
+        call(out[1], workspace(need) if need else None)
+        torch.cuda.synchronize()
+        if p < 2:
+            assert torch.equal(out[0], out[1])
+        else:
+            assert (out[0] - out[1]).norm() <= 1e-5 * out[0].norm()
