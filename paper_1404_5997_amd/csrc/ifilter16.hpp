@@ -24,7 +24,7 @@
 // Measured with the reduce pass, gather kernel -> this one, us: 267 images 17x24, 158 -> 32, 5x5 1553 -> 93 (296 TFLOP/s);
 // 148 images 56x12, 65 -> 32, 5x5 963 -> 81; 604 images 13x16, 96 -> 10, 3x3 578 -> 48; 149 images 14x43, 32 -> 32, 3x3
 // (rows too wide for the LDS kernels) 94 -> 29; 3 images 7x13, 160 -> 14 31 -> 18; whole blocks, 256 images: 13x13 256 -> 256
-// 103 (494 TFLOP/s; the kernel with operands streamed into LDS 55), 27x27 64 -> 192 5x5 187 (613).
+// 103 (494 TFLOP/s), 27x27 64 -> 192 5x5 187 (613), both slower than with operands streamed into LDS (dfilter16b.hpp).
 #pragma once
 #include "owt_host.hpp"
 #include "xfilter.hpp"

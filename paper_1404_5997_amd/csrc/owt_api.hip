@@ -678,43 +678,6 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             }
         }
     }
-    // bf16 storage, any channel counts: the same decomposition
-    if (pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
-        image_groups_fit(g, false)) {
-        for (int v = 0; v < kNumIFilter16Variants; v++) {
-            const IFilter16Variant &iv = kIFilter16Variants[v];
-            if ((force_tile >= 0 && force_tile != kIFilter16FirstTile + v) || g.S != iv.S) continue;
-            const long tm = cdiv(g.K, 32 * iv.KB), ctl = cdiv(g.C, 32 * iv.CB), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
-            const long slots = 1024L * ifilter16_occ(iv.KB, iv.CB, iv.S);
-            const int zl = iv.KB == 2 && g.K % 2 ? 16 : 8, xl = iv.CB == 2 && g.C % 2 ? 16 : 8;
-            for (long s0 : split_ladder(tiles, slots)) {
-                long s = s0;
-                if (force_split > 0) s = force_split < steps ? force_split : steps;
-                else if (s > 1 && (steps / s < 3 || tiles * s > 8192)) break;
-                const long per = cdiv(steps, s), splits = cdiv(steps, per);
-                Launch l; memset(&l, 0, sizeof(l));
-                l.kind = KIND_IFILTER16; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
-                l.tiles_m = (int)tm; l.tiles_n = (int)(ctl * g.R); l.ctiles = (int)ctl; l.taps = g.S; l.groups = g.R;
-                if (splits > 1) {
-                    l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
-                    l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
-                }
-                // Fitted to 430 timed launches of 42 drawn layers (0.20 in the logarithm; its choice is 1 % slower than the fastest
-                // timed): a column takes a wavefront 31 clocks a matrix instruction and 29 a load, times the wavefronts that
-                // share a SIMD, and 650 at least (latency); 19000 for launch, first loads and last stores, 1950 a block for
-                // its stores; the reduce pass 4 us and 0.24 us a MB.
-                const double resident = std::min((double)ifilter16_occ(iv.KB, iv.CB, iv.S), std::max(1.0, tiles * splits / 1024.0));
-                const double column = std::max(650.0, resident * (31.0 * iv.KB * iv.CB * iv.S + 29.0 * ((g.masked ? 2 : 1) * zl + xl)));
-                const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
-                l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
-                if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
-                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
-                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
-                if (!dup) out.push_back(l);
-                if (force_split > 0) break;
-            }
-        }
-    }
     // the same for any geometry, columns packed densely (not the fully-connected shard, whose two backward products share
     // a launch)
     if (pass == OWT_PASS_BWD_FILTER && !g.bf16 && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
@@ -868,6 +831,48 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup && (l.partial_bytes <= kMaxPartialBytes || force_split > 0) &&
                     (force_split > 0 || tm * ctl * groups * splits >= 64 || s0 == 256)) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
+    // bf16 storage where the kernels above are no candidates (channels or filters not in eights, rows too wide for their panels), or
+    // would leave most of their 128-wide tiles empty on a large batch: the reduction over images.  Timed, us, kernels above -> this one: 419 images
+    // 42x8, 32 -> 32 55 -> 36; 375 images 29x19, 64 -> 32 53 -> 41; 761 images 8x26, 96 -> 8 49 -> 39; but 43 images 17x22, 64 -> 8
+    // 18 -> 22; 53 images 25x7, 64 -> 192 27 -> 30; 89 images 20x12, 32 -> 120 5x5 35 -> 42, and whole tiles half as fast.
+    bool staged16 = false;
+    for (const Launch &o : out) staged16 |= (o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B) && (g.K > 64 || g.C > 96 || g.N < 128);
+    if ((force_tile < 0 ? !staged16 : force_tile >= kIFilter16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
+        image_groups_fit(g, false)) {
+        for (int v = 0; v < kNumIFilter16Variants; v++) {
+            const IFilter16Variant &iv = kIFilter16Variants[v];
+            if ((force_tile >= 0 && force_tile != kIFilter16FirstTile + v) || g.S != iv.S) continue;
+            const long tm = cdiv(g.K, 32 * iv.KB), ctl = cdiv(g.C, 32 * iv.CB), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
+            const long slots = 1024L * ifilter16_occ(iv.KB, iv.CB, iv.S);
+            const int zl = iv.KB == 2 && g.K % 2 ? 16 : 8, xl = iv.CB == 2 && g.C % 2 ? 16 : 8;
+            for (long s0 : split_ladder(tiles, slots)) {
+                long s = s0;
+                if (force_split > 0) s = force_split < steps ? force_split : steps;
+                else if (s > 1 && (steps / s < 3 || tiles * s > 8192)) break;
+                const long per = cdiv(steps, s), splits = cdiv(steps, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_IFILTER16; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
+                l.tiles_m = (int)tm; l.tiles_n = (int)(ctl * g.R); l.ctiles = (int)ctl; l.taps = g.S; l.groups = g.R;
+                if (splits > 1) {
+                    l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                    l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
+                }
+                // Fitted to 430 timed launches of 42 drawn layers (0.20 in the logarithm; its choice is 1 % slower than the fastest
+                // timed): a column takes a wavefront 31 clocks a matrix instruction and 29 a load, times the wavefronts that
+                // share a SIMD, and 650 at least (latency); 19000 for launch, first loads and last stores, 1950 a block for
+                // its stores; the reduce pass 4 us and 0.24 us a MB.
+                const double resident = std::min((double)ifilter16_occ(iv.KB, iv.CB, iv.S), std::max(1.0, tiles * splits / 1024.0));
+                const double column = std::max(650.0, resident * (31.0 * iv.KB * iv.CB * iv.S + 29.0 * ((g.masked ? 2 : 1) * zl + xl)));
+                const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
+                l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
+                if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
                 if (force_split > 0) break;
             }
         }
