@@ -1,6 +1,6 @@
-// Instantiations of the bf16 filter-gradient kernels with the reduction over images.
+// Instantiations of the bf16 filter-gradient kernels with the reduction over images (stride 1, and any geometry).
 // Built twice: -DOWT_INST_MASKED={0,1}.
-#include "ifilter16.hpp"
+#include "igather16.hpp"
 #include "owt_host.hpp"
 
 #ifndef OWT_INST_MASKED
@@ -47,6 +47,29 @@ hipError_t owt_launch_ifilter16(int variant, const GemmParams &p, hipStream_t s)
     case 4: return pairs<4>(p, s);
     case 5: return pairs<5>(p, s);
     case 6: return pairs<6>(p, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <int V, bool ZP>
+static hipError_t go_any(const GemmParams &p, hipStream_t s)
+{
+    constexpr IGather16Variant v = kIGather16Variants[V];
+    hipLaunchKernelGGL((igather16_kernel<v.KB, v.CB, ZP, OWT_INST_MASKED != 0>), dim3(owt_split_major_grid(p.tiles_m * p.tiles_n, p.splits)), dim3(64), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<EpiFilter>(p, s);
+    return e;
+}
+
+#if OWT_INST_MASKED
+hipError_t owt_launch_igather16_masked(int variant, const GemmParams &p, hipStream_t s)
+#else
+hipError_t owt_launch_igather16(int variant, const GemmParams &p, hipStream_t s)
+#endif
+{
+    switch (variant) {
+    case 0: return p.g.K % 2 ? go_any<0, false>(p, s) : go_any<0, true>(p, s);
+    case 1: return go_any<1, false>(p, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -58,13 +58,14 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21 };
 
 // Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), the shard's for either storage type, and those for
 // bf16 storage of any channel count: a call whose scratch is too small for one of them is served by the kernels before them.
 static inline bool is_split_kind(int kind)
 {
-    return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16 || kind == KIND_DIRECT16X;
+    return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16 || kind == KIND_DIRECT16X ||
+           kind == KIND_IGATHER16;
 }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
@@ -841,7 +842,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // 18 -> 22; 53 images 25x7, 64 -> 192 27 -> 30; 89 images 20x12, 32 -> 120 5x5 35 -> 42, and whole tiles half as fast.
     bool staged16 = false;
     for (const Launch &o : out) staged16 |= (o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B) && (g.K > 64 || g.C > 96 || g.N < 128);
-    if ((force_tile < 0 ? !staged16 : force_tile >= kIFilter16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
+    if ((force_tile < 0 ? !staged16 : force_tile >= kIFilter16FirstTile && force_tile < kIGather16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
         image_groups_fit(g, false)) {
         for (int v = 0; v < kNumIFilter16Variants; v++) {
             const IFilter16Variant &iv = kIFilter16Variants[v];
@@ -869,6 +870,41 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const double column = std::max(650.0, resident * (31.0 * iv.KB * iv.CB * iv.S + 29.0 * ((g.masked ? 2 : 1) * zl + xl)));
                 const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
                 l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
+                if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
+    // the same for any geometry (not the fully-connected shard), where no other kernel on the bf16 matrix unit is a candidate
+    bool rows16 = false;
+    for (const Launch &o : out)
+        rows16 |= o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B || o.kind == KIND_IFILTER16 || o.kind == KIND_SFILTER16 || o.kind == KIND_SFILTER16B;
+    if ((force_tile < 0 ? !rows16 : force_tile >= kIGather16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && (g.H > 1 || g.W > 1) && !no_direct &&
+        !forced(OWT_FORCE_NO_BF16_MFMA) && image_groups_fit(g, true)) {
+        for (int v = 0; v < kNumIGather16Variants; v++) {
+            const IGather16Variant &iv = kIGather16Variants[v];
+            if (force_tile >= 0 && force_tile != kIGather16FirstTile + v) continue;
+            const long tm = cdiv(g.K, 32 * iv.KB), tn = cdiv(dm.Ncols, 32 * iv.CB), tiles = tm * tn, steps = cdiv(g.N, 16) * g.P * g.Q;
+            const int zl = (iv.KB == 2 && g.K % 2 ? 16 : 8) * (g.masked ? 2 : 1), occ = zl == 32 ? 1 : 2;
+            const long slots = 1024L * occ;
+            for (long s0 : split_ladder(tiles, slots)) {
+                long s = s0;
+                if (force_split > 0) s = force_split < steps ? force_split : steps;
+                else if (s > 1 && (steps / s < 3 || tiles * s > 8192)) break;
+                const long per = cdiv(steps, s), splits = cdiv(steps, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_IGATHER16; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
+                l.tiles_m = (int)tm; l.tiles_n = (int)tn; l.blocks = g.sh > 1 || g.sw > 1;
+                if (splits > 1) {
+                    l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                    l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
+                }
+                const double resident = std::min((double)occ, std::max(1.0, tiles * splits / 1024.0));      // the clocks are ifilter16's
+                const double position = std::max(700.0, resident * (31.0 * iv.KB * iv.CB + 29.0 * (zl + 8 * iv.CB)));
+                l.cost = 0.6 * ((per * position + 1950.0 * iv.KB * iv.CB) * cdiv(tiles * splits, slots) + 19000.0);
                 if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
@@ -1136,6 +1172,8 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
     } else if (l.kind == KIND_XFILTER) {
         p.ctiles = l.ctiles;
         e = owt_launch_xfilter(l.tile, p, s);
+    } else if (l.kind == KIND_IGATHER16) {
+        e = p.mask ? owt_launch_igather16_masked(l.tile, p, s) : owt_launch_igather16(l.tile, p, s);
     } else if (l.kind == KIND_IFILTER16) {
         p.ctiles = l.ctiles;
         e = p.mask ? owt_launch_ifilter16_masked(l.tile, p, s) : owt_launch_ifilter16(l.tile, p, s);
@@ -1204,6 +1242,10 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
                         8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4), 8) * 256);
+    if (l.kind == KIND_IGATHER16)
+        return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilter16x" : "igather16", pn[pass], ds,
+                        32 * kIGather16Variants[l.tile].KB, 32 * kIGather16Variants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,
+                        8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 64);
     if (l.kind == KIND_IFILTER16)
         return snprintf(buf, n, "ifilter16 %s %s tile%dx%d taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kIFilter16Variants[l.tile].KB, 32 * kIFilter16Variants[l.tile].CB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,

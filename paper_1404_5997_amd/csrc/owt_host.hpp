@@ -85,6 +85,14 @@ constexpr int ifilter16_occ(int KB, int CB, int S) { return KB * CB * S <= 6 ? 2
 hipError_t owt_launch_ifilter16(int variant, const GemmParams &, hipStream_t);
 hipError_t owt_launch_ifilter16_masked(int variant, const GemmParams &, hipStream_t);
 
+// The same for any geometry: KB filter blocks x CB blocks of densely packed (r, s, c) places, one wavefront to a work-group, two
+// to a SIMD.  Test-hook numbers from 88.
+struct IGather16Variant { int KB, CB; };
+constexpr int kNumIGather16Variants = 2, kIGather16FirstTile = 88;
+constexpr IGather16Variant kIGather16Variants[kNumIGather16Variants] = {{2, 3}, {1, 3}};
+hipError_t owt_launch_igather16(int variant, const GemmParams &, hipStream_t);
+hipError_t owt_launch_igather16_masked(int variant, const GemmParams &, hipStream_t);
+
 // The fully-connected shard on the bf16 MFMA (xfc_inst.hip), both storage types; test-hook number 70.  Backward: one launch
 // for the products whose parameters are given.
 constexpr int kXFcTile = 70;

@@ -62,6 +62,35 @@ def test_filter_gradient_with_the_reduction_over_images(variant, S, split):
             check(db, rb, sb + 3.0, L, "dbias")
 
 
+# N, C, H, W, K, R, S, stride, pad: rows of any length, less and more than a tile of filters and of places, filters odd and even,
+# one tap, a stride along one side only, one position
+ANY = [(5, 3, 51, 57, 33, 11, 11, 4, 2), (17, 3, 30, 31, 64, 7, 7, 4, 2), (16, 5, 19, 20, 70, 3, 3, 2, 1), (33, 37, 6, 5, 45, 1, 1, 1, 0), (2, 7, 23, 17, 5, 5, 4, (3, 1), (2, 1)), (1, 2, 7, 7, 3, 7, 7, 1, 0)]
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("split", [0, 1, 4])
+def test_filter_gradient_of_any_geometry(variant, split):
+    m = owt()
+    for i, shape in enumerate(ANY):
+        N, C, H, W, K, R, S, stride, pad = shape
+        x, w, b, dy, y = tensors((N, C, H, W, K, R, S, pad), stride, 1220 + i)
+        for relu, alpha, beta in ((False, 1.0, 0.0), (True, 0.5, -0.25)):
+            case = ConvCase(N, C, H, W, K, R, S, stride, pad, "bf16", True, relu)
+            dw0, db0 = np.full(case.shape_w, 2.0, np.float32), np.full((K,), 3.0, np.float32)
+            with force(88 + variant, split):
+                plan = m.owt_conv_plan_describe(case.desc, 2)
+                print("case", shape, "relu", relu, plan)
+                sys.stdout.flush()
+                assert plan.startswith(("sfilter16x", "igather16")), plan
+                dw, db = case.bwd_filter(x, dy, y, alpha, beta, dw0, db0)
+            mask = y if relu else None
+            rw, rb = oracle.conv_bwd_filter(x, dy, (R, S), stride, pad, y=mask, alpha=alpha, beta=beta, dw=dw0, db=db0)
+            sw, sb = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), (R, S), stride, pad, y=mask)
+            L = N * case.P * case.Q
+            check(dw, rw, sw + 2.0, L, "dw")
+            check(db, rb, sb + 3.0, L, "dbias")
+
+
 def test_filter_gradient_over_images_keeps_infinities_to_the_taps_that_meet_them():
     # an infinite value of x at the last column of a row: taps left of it never meet it, although its column is the first
     # row's neighbour in memory and still in the wavefront's ring when the next row starts
