@@ -250,3 +250,25 @@ def test_calls_with_the_scratch_of_the_gather_kernel_still_run():
             assert torch.equal(out[0], out[1])
         else:
             assert (out[0] - out[1]).norm() <= 1e-5 * out[0].norm()
+
+
+# filters, taps, channels whose product leaves 0 to 3 results past the last group of four, times few, some and many splits
+@pytest.mark.parametrize("K,R,C", [(4, 3, 8), (5, 3, 5), (1, 3, 2), (7, 3, 13), (33, 1, 1), (3, 3, 9)])
+@pytest.mark.parametrize("split", [2, 6, 7, 32, 33, 70])
+def test_split_sums_of_any_length(K, R, C, split):
+    m = owt()
+    shape = (18, C, 7, 9, K, R, R, R // 2)
+    x, w, b, dy, y = tensors(shape, 1, 1400)
+    case = ConvCase(*shape[:7], 1, shape[7], "bf16", True, False)
+    dw0, db0 = np.full(case.shape_w, 2.0, np.float32), np.full((K,), 3.0, np.float32)
+    for tile in ((80, 83, 89) if R == 3 else (89,)):
+        with force(tile, split):
+            plan = m.owt_conv_plan_describe(case.desc, 2)
+            print("case", K, R, C, plan)
+            sys.stdout.flush()
+            assert plan.startswith(("ifilter16", "igather16")) and "splitk1 " not in plan, plan
+            dw, db = case.bwd_filter(x, dy, None, 0.5, -0.25, dw0, db0)
+        rw, rb = oracle.conv_bwd_filter(x, dy, (R, R), 1, R // 2, alpha=0.5, beta=-0.25, dw=dw0, db=db0)
+        sw, sb = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), (R, R), 1, R // 2)
+        check(dw, rw, sw + 2.0, 18 * 63, "dw")
+        check(db, rb, sb + 3.0, 18 * 63, "dbias")
