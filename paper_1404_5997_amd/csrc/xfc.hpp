@@ -1,5 +1,5 @@
-// The fully-connected column shard (Section 4 of the paper, forward step 3 / backward step 1) on the bf16 matrix unit:
-// bf16 storage as it is, fp32 storage with operands split in three (split3.hpp).
+// The fully-connected column shard (Section 4 of the paper, forward step 3 / backward step 1), fp32 storage, on the bf16 matrix
+// unit with operands split in three (split3.hpp).  xfc16.hpp is the same for bf16 storage.
 //
 //   forward    y[n][o]  = sum_i x[n][i] w[o][i]         both operands contiguous along the reduction
 //   data       dx[n][i] = sum_o dz[n][o] w[o][i]        dz contiguous, w strided
@@ -7,8 +7,8 @@
 //
 // At a batch of 128 these products are a few microseconds of matrix or memory time, so what counts is launches, latency
 // and wavefronts in flight.  Operands go from global memory straight into registers as matrix fragments (a fragment lane
-// holds eight reduction values of one row or column: 32 or 16 contiguous bytes, or eight 4- or 2-byte loads that are
-// contiguous across lanes); no LDS staging, no padding, no barrier in the loop, any N, I, O: what lies past the reduction
+// holds eight reduction values of one row or column: 32 contiguous bytes, or eight 4-byte loads that are contiguous across
+// lanes); no LDS staging, no padding, no barrier in the loop, any N, I, O: what lies past the reduction
 // is zeroed in the last step, rows and columns past the result read something harmless and are not stored.  dz = dy * [y > 0]
 // is formed on the way into the fragments and the bias gradient in the filter product's wavefronts, so a backward call
 // is one launch for both products.
@@ -18,68 +18,49 @@
 // whole batch as its reduction: 34 us instead of 30 for the backward call of 128 x 9216 -> 512, 18.3 instead of 8.4 for
 // 4096 -> 125.)
 //
-// Measured, 128 images, us, before (fp32: direct-to-LDS GEMM on the fp32 instruction and a launch for dz; bf16: gather
-// kernel) -> here: fp32 9216 -> 512 forward 20.1 -> 18.4, backward 32.6 -> 29.8; 4096 -> 512 16.0 -> 13.2 and 22.6 -> 16.2;
-// 4096 -> 125 10.6 -> 10.7 and 11.0 -> 8.4.  bf16 9216 -> 512 39 -> 17.5 and 107 -> 19.8; 4096 -> 512 27.5 -> 11.8 and 75 -> 13.0;
-// 4096 -> 125 19.3 -> 10.2 and 102 -> 8.4.
+// Measured, 128 images, us, direct-to-LDS GEMM on the fp32 instruction and a launch for dz -> here: 9216 -> 512 forward 20.1 -> 18.4,
+// backward 32.6 -> 29.8; 4096 -> 512 16.0 -> 13.2 and 22.6 -> 16.2; 4096 -> 125 10.6 -> 10.7 and 11.0 -> 8.4.  What bounds it is the chain of a
+// step: about 210 vector instructions that split its 4 x 8 values, then 24 matrix instructions.  Four steps' loads in flight at
+// one wavefront per SIMD: forward 20.5 -> 24.9, backward 33 -> 86 (664 spilled registers); two neighbouring columns with an 8-byte
+// load: backward 33 -> 38.
 #pragma once
 #include "igemm.hpp"
 #include "split3.hpp"
 
 namespace owt {
 
-template <bool BF> struct XfcOps {
-    static constexpr int NP = BF ? 1 : 3, ES = BF ? 2 : 4;       // fragment parts, bytes per value
-    struct Frag { split_frag p[NP]; };
-    // eight raw values of a lane: fp32 bits, or bf16 bits in the low halves
+// Eight raw values of a lane, and the fragments made of them.
+struct XfcOps {
+    struct Frag { split_frag p[3]; };
     struct Raw { uint32_t v[8]; };
 
-    // CAREFUL (fp32): the second run, with a test for large values
+    // CAREFUL: the second run, with a test for large values
     template <bool CAREFUL> static __device__ __forceinline__ Frag pack(const Raw &r, float scale)
     {
         Frag f;
-        if constexpr (BF) {
-            f.p[0] = __builtin_bit_cast(split_frag, make_uint4(r.v[0] | r.v[1] << 16, r.v[2] | r.v[3] << 16, r.v[4] | r.v[5] << 16, r.v[6] | r.v[7] << 16));
-        } else {
-            float v[8];
+        float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; j++) v[j] = __uint_as_float(r.v[j]) * scale;
-            if constexpr (CAREFUL) split3_careful(v, f.p);
-            else split3_plain(v, f.p);
-        }
+        for (int j = 0; j < 8; j++) v[j] = __uint_as_float(r.v[j]) * scale;
+        if constexpr (CAREFUL) split3_careful(v, f.p);
+        else split3_plain(v, f.p);
         return f;
     }
-    static __device__ __forceinline__ float value(uint32_t v) { return __uint_as_float(BF ? v << 16 : v); }
+    static __device__ __forceinline__ float value(uint32_t v) { return __uint_as_float(v); }
 
-    // Reduction values k .. k+7 of a row that is contiguous along the reduction; base = the row's byte offset.  wide: rows are
-    // aligned to 4 bytes.
-    static __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t rs, unsigned base, int k, bool wide, Raw &r)
+    // Reduction values k .. k+7 of a row that is contiguous along the reduction; base = the row's byte offset.
+    static __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t rs, unsigned base, int k, Raw &r)
     {
-        if constexpr (BF) {
-            if (wide) {
-                const owt_u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(base + (unsigned)k * 2u), 0, 0);
-                r.v[0] = q.x & 0xffffu; r.v[1] = q.x >> 16; r.v[2] = q.y & 0xffffu; r.v[3] = q.y >> 16;
-                r.v[4] = q.z & 0xffffu; r.v[5] = q.z >> 16; r.v[6] = q.w & 0xffffu; r.v[7] = q.w >> 16;
-            } else {
 #pragma unroll
-                for (int j = 0; j < 8; j++) r.v[j] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)(base + (unsigned)(k + j) * 2u), 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 2; q++) {
-                const owt_u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(base + (unsigned)(k + 4 * q) * 4u), 0, 0);
-                r.v[4 * q] = t.x; r.v[4 * q + 1] = t.y; r.v[4 * q + 2] = t.z; r.v[4 * q + 3] = t.w;
-            }
+        for (int q = 0; q < 2; q++) {
+            const owt_u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(base + (unsigned)(k + 4 * q) * 4u), 0, 0);
+            r.v[4 * q] = t.x; r.v[4 * q + 1] = t.y; r.v[4 * q + 2] = t.z; r.v[4 * q + 3] = t.w;
         }
     }
     // The same where consecutive reduction values are `pitch` bytes apart; base = the column's byte offset in row k.
     static __device__ __forceinline__ void load_col(__amdgpu_buffer_rsrc_t rs, unsigned base, unsigned pitch, Raw &r)
     {
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            if constexpr (BF) r.v[j] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)(base + (unsigned)j * pitch), 0, 0);
-            else r.v[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(base + (unsigned)j * pitch), 0, 0);
-        }
+        for (int j = 0; j < 8; j++) r.v[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(base + (unsigned)j * pitch), 0, 0);
     }
     static __device__ __forceinline__ void keep(Raw &r, int k, int end)     // zeroes values at and past the reduction's end
     {
@@ -105,13 +86,13 @@ __device__ __forceinline__ void xfc_clear(split_acc (&a)[2][2], split_acc (&b)[2
 
 // A 64 x 64 tile of one product by one wavefront: reduction steps step0, step0 + stride, ... below nsteps (16 deep each).
 // AROW / BROW: the operand is contiguous along the reduction.  Rows (A) and columns (B) past the end read harmlessly.
-template <bool BF, bool AROW, bool BROW, bool MASKED, bool DB, bool CAREFUL>
+template <bool AROW, bool BROW, bool MASKED, bool DB, bool CAREFUL>
 __device__ __forceinline__ void xfc_tile_run(const void *a, const void *y, const void *b, unsigned a_bytes, unsigned b_bytes, int a_len,
                                          int b_len, int Kd, int m0, int n0, int step0, int stride, int nsteps,
                                          split_acc (&big)[2][2], split_acc (&small)[2][2], float (&db)[2])
 {
-    typedef XfcOps<BF> O;
-    constexpr unsigned ES = O::ES;
+    typedef XfcOps O;
+    constexpr unsigned ES = 4;
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     const __amdgpu_buffer_rsrc_t ars = owt_make_rsrc(a, a_bytes), brs = owt_make_rsrc(b, b_bytes);
     const __amdgpu_buffer_rsrc_t yrs = owt_make_rsrc(MASKED ? y : a, a_bytes);
@@ -122,20 +103,19 @@ __device__ __forceinline__ void xfc_tile_run(const void *a, const void *y, const
         ao[t] = AROW ? (unsigned)(m0 + t * 32 + li) * (unsigned)a_len * ES : (unsigned)(m0 + t * 32 + li) * ES;
         bo[t] = BROW ? (unsigned)(n0 + t * 32 + li) * (unsigned)b_len * ES : (unsigned)(n0 + t * 32 + li) * ES;
     }
-    const bool awide = !BF || (a_len & 1) == 0, bwide = !BF || (b_len & 1) == 0;
     typename O::Raw ra[2], ry[2], rb[2];
     auto load = [&](int step) __attribute__((always_inline)) {
         const int k = step * 16 + 8 * lh;
 #pragma unroll
         for (int t = 0; t < 2; t++) {
             if constexpr (AROW) {
-                O::load_row(ars, ao[t], k, awide, ra[t]);
-                if (MASKED) O::load_row(yrs, ao[t], k, awide, ry[t]);
+                O::load_row(ars, ao[t], k, ra[t]);
+                if (MASKED) O::load_row(yrs, ao[t], k, ry[t]);
             } else {
                 O::load_col(ars, ao[t] + (unsigned)k * (unsigned)a_len * ES, (unsigned)a_len * ES, ra[t]);
                 if (MASKED) O::load_col(yrs, ao[t] + (unsigned)k * (unsigned)a_len * ES, (unsigned)a_len * ES, ry[t]);
             }
-            if constexpr (BROW) O::load_row(brs, bo[t], k, bwide, rb[t]);
+            if constexpr (BROW) O::load_row(brs, bo[t], k, rb[t]);
             else O::load_col(brs, bo[t] + (unsigned)k * (unsigned)b_len * ES, (unsigned)b_len * ES, rb[t]);
         }
     };
@@ -163,28 +143,25 @@ __device__ __forceinline__ void xfc_tile_run(const void *a, const void *y, const
 #pragma unroll
             for (int j = 0; j < 2; j++)
                 big[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].p[0], fb[j].p[0], big[i][j], 0, 0, 0);
-        if constexpr (!BF) {
-            constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
+        constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-            for (int q = 0; q < 5; q++)
+        for (int q = 0; q < 5; q++)
 #pragma unroll
-                for (int i = 0; i < 2; i++)
+            for (int i = 0; i < 2; i++)
 #pragma unroll
-                    for (int j = 0; j < 2; j++)
-                        small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].p[PA[q]], fb[j].p[PB[q]], small[i][j], 0, 0, 0);
-        }
+                for (int j = 0; j < 2; j++)
+                    small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].p[PA[q]], fb[j].p[PB[q]], small[i][j], 0, 0, 0);
     }
 }
 
 // The tile's sums in `big` (both to be cleared before) and what they are to be multiplied with: fp32 operands are scaled up, and
 // a wavefront whose sums are not finite starts over with products that no finite operands take out of the range.
-template <bool BF, bool AROW, bool BROW, bool MASKED, bool DB>
+template <bool AROW, bool BROW, bool MASKED, bool DB>
 __device__ __forceinline__ float xfc_tile(const void *a, const void *y, const void *b, unsigned a_bytes, unsigned b_bytes, int a_len,
                                          int b_len, int Kd, int m0, int n0, int step0, int stride, int nsteps,
                                          split_acc (&big)[2][2], split_acc (&small)[2][2], float (&db)[2])
 {
-    xfc_tile_run<BF, AROW, BROW, MASKED, DB, false>(a, y, b, a_bytes, b_bytes, a_len, b_len, Kd, m0, n0, step0, stride, nsteps, big, small, db);
-    if constexpr (BF) return 1.f;
+    xfc_tile_run<AROW, BROW, MASKED, DB, false>(a, y, b, a_bytes, b_bytes, a_len, b_len, Kd, m0, n0, step0, stride, nsteps, big, small, db);
     auto add_up = [&]() __attribute__((always_inline)) {
         float sum = 0.f;
 #pragma unroll
@@ -200,15 +177,15 @@ __device__ __forceinline__ float xfc_tile(const void *a, const void *y, const vo
     };
     if (__ballot(!(fabsf(add_up()) < __builtin_inff())) == 0) return kSplitUnscale;
     xfc_clear(big, small);
-    xfc_tile_run<BF, AROW, BROW, MASKED, false, true>(a, y, b, a_bytes, b_bytes, a_len, b_len, Kd, m0, n0, step0, stride, nsteps, big, small, db);
+    xfc_tile_run<AROW, BROW, MASKED, false, true>(a, y, b, a_bytes, b_bytes, a_len, b_len, Kd, m0, n0, step0, stride, nsteps, big, small, db);
     add_up();
     return kSplitUndown;
 }
 
-// The four wavefronts' sums of one tile, each times its `scale` (SCALED), added in a fixed order; `store(row, column, value)` gets each
+// The four wavefronts' sums of one tile, each times its `scale`, added in a fixed order; `store(row, column, value)` gets each
 // value of the tile once.
 constexpr int kXfcRed = 4 * 4096 + 4;
-template <bool SCALED, class Store>
+template <class Store>
 __device__ __forceinline__ void xfc_combine(float *red, const split_acc (&big)[2][2], float scale, Store store)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 31, lh = lane >> 5;
@@ -219,11 +196,11 @@ __device__ __forceinline__ void xfc_combine(float *red, const split_acc (&big)[2
 #pragma unroll
             for (int e = 0; e < 16; e++)
                 red[wave * 4096 + (i * 32 + 8 * (e / 4) + 4 * lh + e % 4) * 64 + j * 32 + li] = big[i][j][e];
-    if (SCALED && lane == 0) red[4 * 4096 + wave] = scale;
+    if (lane == 0) red[4 * 4096 + wave] = scale;
     __syncthreads();
     float s[4];
 #pragma unroll
-    for (int w = 0; w < 4; w++) s[w] = SCALED ? red[4 * 4096 + w] : 1.f;
+    for (int w = 0; w < 4; w++) s[w] = red[4 * 4096 + w];
 #pragma unroll 4
     for (int q = 0; q < 16; q++) {
         const int at = q * 256 + tid;
@@ -231,7 +208,7 @@ __device__ __forceinline__ void xfc_combine(float *red, const split_acc (&big)[2
     }
 }
 
-template <class Epi, bool BF>
+template <class Epi>
 __global__ void __launch_bounds__(256, 2) xfc_fwd_kernel(const GemmParams p)
 {
     __shared__ float red[kXfcRed];
@@ -242,9 +219,9 @@ __global__ void __launch_bounds__(256, 2) xfc_fwd_kernel(const GemmParams p)
     split_acc big[2][2], small[2][2];
     float db[2];
     xfc_clear(big, small);
-    const float scale = xfc_tile<BF, true, true, false, false>(p.a, nullptr, p.b, (unsigned)p.M * I * XfcOps<BF>::ES, (unsigned)p.Ncols * I * XfcOps<BF>::ES, I, I,
+    const float scale = xfc_tile<true, true, false, false>(p.a, nullptr, p.b, (unsigned)p.M * I * 4u, (unsigned)p.Ncols * I * 4u, I, I,
                                            I, m0, n0, beg + wave, 4, end, big, small, db);
-    xfc_combine<!BF>(red, big, scale, [&](int r, int c, float v) {
+    xfc_combine(red, big, scale, [&](int r, int c, float v) {
         const int m = m0 + r, n = n0 + c;
         if (m >= p.M || n >= p.Ncols) return;
         if (p.splits > 1) p.partial[((size_t)split * p.M + m) * p.Ncols + n] = v;
@@ -253,12 +230,12 @@ __global__ void __launch_bounds__(256, 2) xfc_fwd_kernel(const GemmParams p)
 }
 
 // Work-groups below pd.tiles_m * pd.tiles_n: a tile of dx; the others: a tile of dw.  Either range may be empty.
-template <bool BF, bool MASKED>
+template <bool MASKED>
 __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, const GemmParams pf)
 {
     __shared__ float red[kXfcRed];
-    typedef typename std::conditional<BF, bf16_t, float>::type T;
-    constexpr unsigned ES = XfcOps<BF>::ES;
+    typedef float T;
+    constexpr unsigned ES = 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ndx = pd.tiles_m * pd.tiles_n;
     const int N = pf.Kd, O = pf.M, I = pf.Ncols;
     split_acc big[2][2], small[2][2];
@@ -266,9 +243,9 @@ __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, co
     xfc_clear(big, small);
     if ((int)blockIdx.x < ndx) {
         const int tn = blockIdx.x % pd.tiles_n, tm = blockIdx.x / pd.tiles_n, m0 = tm * 64, n0 = tn * 64;
-        const float scale = xfc_tile<BF, true, false, MASKED, false>(pd.a, pd.mask, pd.b, (unsigned)N * O * ES, (unsigned)O * I * ES, O, I, O, m0, n0, wave, 4,
+        const float scale = xfc_tile<true, false, MASKED, false>(pd.a, pd.mask, pd.b, (unsigned)N * O * ES, (unsigned)O * I * ES, O, I, O, m0, n0, wave, 4,
                                                  (O + 15) >> 4, big, small, db);
-        xfc_combine<!BF>(red, big, scale, [&](int r, int c, float v) {
+        xfc_combine(red, big, scale, [&](int r, int c, float v) {
             const int m = m0 + r, n = n0 + c;
             if (m < N && n < I) store1((T *)pd.out, (size_t)m * I + n, EpiData<T>::op(pd, m, n, v));
         });
@@ -279,13 +256,13 @@ __global__ void __launch_bounds__(256, 2) xfc_bwd_kernel(const GemmParams pd, co
     const bool do_db = tn == 0 && pf.dbias != nullptr;
     float scale;
     if (do_db)
-        scale = xfc_tile<BF, false, false, MASKED, true>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
+        scale = xfc_tile<false, false, MASKED, true>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
                                                  (N + 15) >> 4, big, small, db);
     else
-        scale = xfc_tile<BF, false, false, MASKED, false>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
+        scale = xfc_tile<false, false, MASKED, false>(pf.a, pf.mask, pf.b, (unsigned)N * O * ES, (unsigned)N * I * ES, O, I, N, m0, n0, wave, 4,
                                                   (N + 15) >> 4, big, small, db);
     float *out = (float *)pf.out;
-    xfc_combine<!BF>(red, big, scale, [&](int r, int c, float v) {
+    xfc_combine(red, big, scale, [&](int r, int c, float v) {
         const int o = m0 + r, n = n0 + c;
         if (o >= O || n >= I) return;
         const size_t at = (size_t)o * I + n;
