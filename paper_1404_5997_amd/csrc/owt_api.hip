@@ -58,14 +58,14 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21, KIND_XCONVS = 22 };
 
 // Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), the shard's for either storage type, and those for
 // bf16 storage of any channel count: a call whose scratch is too small for one of them is served by the kernels before them.
 static inline bool is_split_kind(int kind)
 {
     return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16 || kind == KIND_DIRECT16X ||
-           kind == KIND_IGATHER16;
+           kind == KIND_IGATHER16 || kind == KIND_XCONVS;
 }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
@@ -476,6 +476,45 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                 l.cost = model_cost(tm * tn * splits, xv.WM * xv.WN, xv.occ, macs * per, xv.eff, splits, dm.M, dm.Ncols) + 5000.0;
                 if (splits > 1) l.cost -= 7500.0;             // the reduce pass measures about 5 us on these results
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
+    // the same for layers of few tiles.  They use no scratch but partial sums; they ask for what the laid-out filters of the kernels
+    // above take all the same, so that a call that brings less is served, to the bit, as it was before there were either.
+    if (!g.bf16 && !blocks && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
+        (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull && (size_t)g.K * g.R * g.S * g.C < 0x1fffffffull) {
+        for (int v = 0; v < kNumXConvSVariants; v++) {
+            const XConvSVariant &xv = kXConvSVariants[v];
+            if ((force_tile >= 0 && force_tile != kXConvSFirstTile + v) || xr * xs < xv.TG) continue;
+            const long BM = 32 * xv.WM, rows = panel_rows(g, pass, dm, BM);
+            if (rows < 0 || rows > xv.prs[2]) continue;
+            const long tm = cdiv(dm.M, BM), tn = cdiv(dm.Ncols, 32), chunks = cdiv(cred, 16);
+            for (long s0 : kSplits) {
+                const long s = force_split > 0 ? (force_split < chunks ? force_split : chunks) : s0;
+                const long per = cdiv(chunks, s), splits = cdiv(chunks, per);
+                if (force_split <= 0 && (s0 > chunks || s0 > 8 || tm * tn * splits * xv.WM * xv.TG > 8192)) break;
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_XCONVS; l.tile = v; l.pr = rows <= xv.prs[0] ? xv.prs[0] : rows <= xv.prs[1] ? xv.prs[1] : xv.prs[2];
+                l.splits = (int)splits; l.steps = (int)chunks; l.steps_per_split = (int)per; l.tiles_m = (int)tm; l.tiles_n = (int)tn;
+                l.pre_bytes = pad256((size_t)chunks * xr * xs * cdiv(dm.Ncols, 64) * 2 * 3072);
+                if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                // Fitted to 879 timed launches of 42 drawn layers (0.14 in the logarithm, its choice 2 % slower than the fastest): a tap
+                // of a chunk takes 367 clocks (backward-data, with its 4-byte filter loads, 545) times the wavefronts on a SIMD, a
+                // chunk's panel 1122 and a quarter of one a row and wavefront (twice that with the mask's loads); 10900 for launch, first loads and
+                // stores, the reduce pass 2.2 us and 0.85 us a MB.  More than 8192 wavefronts (two
+                // rounds of the chip), or a SIMD with more than 96 steps to take in all, are left to xconv.hpp: 75 us against 62 at 12912
+                // wavefronts, 34.6 against 29.8 at 112 steps, 42.1 against 37.6 at 168, while 10 % is the most that was won there.
+                const long wgs = tm * tn * splits, occ = std::max(1, 16 / (xv.WM * xv.TG)), full = cdiv(wgs, 256);
+                const double waves = std::min(occ, full) * xv.WM * xv.TG / 4.0, rounds = (double)cdiv(wgs, 256 * occ);
+                if (force_split <= 0 && force_tile < 0 && cdiv(xr * xs, xv.TG) * per * waves * rounds > 96.0) continue;
+                const double chunk = cdiv(xr * xs, xv.TG) * waves * (pass == OWT_PASS_FWD ? 367.0 : 545.0) + 1122.0 +
+                                     0.257 * l.pr * waves * (pass == OWT_PASS_BWD_DATA && g.masked ? 2.0 : 1.0);
+                l.cost = 0.6 * (rounds * per * chunk + 10900.0);
+                if (splits > 1) l.cost += 2770.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 933.0;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1118,6 +1157,9 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
         if (blocks) e = owt_launch_xconv_fwd_blocks(l.tile, l.pr, p, ws, s);
         else if (pass == OWT_PASS_FWD) e = vec ? owt_launch_xconv_fwd_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_fwd_vec0(l.tile, l.pr, p, ws, s);
         else e = vec ? owt_launch_xconv_data_vec1(l.tile, l.pr, p, ws, s) : owt_launch_xconv_data_vec0(l.tile, l.pr, p, ws, s);
+    } else if (l.kind == KIND_XCONVS) {
+        dconv_frame(g, pass, p);
+        e = pass == OWT_PASS_FWD ? owt_launch_xconvs_fwd(l.tile, l.pr, p, s) : owt_launch_xconvs_data(l.tile, l.pr, p, s);
     } else if (l.kind == KIND_DIRECT16X) {
         if (l.blocks) blocks_frame(g, p); else dconv_frame(g, pass, p);
         p.dWp.set(p.Wi); p.dHpWp.set(p.Hi * p.Wi);
@@ -1226,6 +1268,11 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         const XConvVariant &v = kXConvVariants[l.tile];
         return snprintf(buf, n, "%s %s %s tile%dx%dx16 waves%dx%d panel%d splitk%d grid%dx%d threads%ld", l.blocks ? "sconvx" : "xconv", pn[pass], ds, 32 * v.MB * v.WM,
                         64 * v.WN, v.WM, v.WN, l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.WN);
+    }
+    if (l.kind == KIND_XCONVS) {
+        const XConvSVariant &v = kXConvSVariants[l.tile];
+        return snprintf(buf, n, "xconvs %s %s tile%dx32x16 waves%dx1x%d panel%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.WM, v.WM, v.TG,
+                        l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.TG);
     }
     if (l.kind == KIND_DIRECT16X)
         return snprintf(buf, n, "%s %s %s tile256x64x32 waves4x1 panel%d splitk%d grid%dx%d threads%ld", l.blocks ? "sconv16x" : "dconv16x", pn[pass], ds, l.pr,

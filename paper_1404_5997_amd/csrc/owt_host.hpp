@@ -58,6 +58,15 @@ hipError_t owt_launch_xconv_fwd_blocks(int variant, int pr, const GemmParams &, 
 hipError_t owt_launch_xconv_data_vec0(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 hipError_t owt_launch_xconv_data_vec1(int variant, int pr, const GemmParams &, void *ws, hipStream_t);
 
+// The same convolutions for layers of few tiles (xconvs_inst.hip): TG groups of WM wavefronts of 32 pixels x 32 filters share
+// a work-group's taps; prs = the panel sizes it is built for.  (64 filters a wavefront, two groups of four: slower everywhere.  16
+// wavefronts as eight groups of two: never the fastest.)  No scratch but partial sums.  Test-hook numbers from 44.
+struct XConvSVariant { int WM, TG, prs[3]; };
+constexpr int kNumXConvSVariants = 3, kXConvSFirstTile = 44;
+constexpr XConvSVariant kXConvSVariants[kNumXConvSVariants] = {{4, 4, {160, 288, 352}}, {2, 4, {96, 224, 320}}, {1, 8, {96, 192, 288}}};
+hipError_t owt_launch_xconvs_fwd(int variant, int pr, const GemmParams &, hipStream_t);
+hipError_t owt_launch_xconvs_data(int variant, int pr, const GemmParams &, hipStream_t);
+
 // Stride-1 filter gradient for fp32 storage on the bf16 MFMA with split operands (xfilter_inst.hip): a wavefront holds KB
 // filter blocks of 32 x 32 channels x the S taps of a filter row, four wavefronts of neighbouring tiles to a work-group.  The
 // test hook numbers the variants from 50.
