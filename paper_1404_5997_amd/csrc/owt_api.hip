@@ -567,6 +567,9 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 l.pre_bytes = pad256(packed);
                 if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                 l.cost = model_cost(tm * tn * splits, 4, 2, 256.0 * 64 * 32 * xr * xs * per / 9.0, 1.25, splits, dm.M, dm.Ncols) + 5000.0;
+                // (first layers: 24 us for 4 taps of 2 chunks, 29 for 9, and 36 and 61 ns for each work-group past one a CU; where
+                // sconv16 takes the layer too, it is nearly always the faster one: 62 us against 124 for 89 images of 204x204)
+                if (blocks) l.cost = std::max(l.cost, 1260.0 * (20.0 + 0.5 * xr * xs * per + std::max(0L, tm * tn * splits - 256) * (0.009 + 0.0029 * xr * xs * per)));
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -626,7 +629,10 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             l.kind = KIND_SCONV16; l.splits = 1; l.steps = s16g.units; l.steps_per_split = (int)per;
             l.tiles_m = (int)ktiles; l.tiles_n = (int)n;
             l.partial_bytes = pad256((size_t)g.K * s16g.KSLOTS * 2);        // the re-laid-out filters
-            l.cost = model_cost(ktiles * n, 4, 1, 256.0 * 64 * s16g.KSLOTS * per / 6.0, 1.0, 1, dm.M, dm.Ncols);
+            // One work-group a CU (its LDS): 11.4 us for the launches, the filter bank and the first band, and a unit of four rows 3 us and
+            // a little more the longer reduction and rows are.  Two work-groups a CU go one after the other and load the bank twice:
+            // 128 images of 224x224 to 96 filters of 11x11 66 us with 256 work-groups, 76 with 512; 39 of 192x192 to 64 21.5 and 29.4.
+            l.cost = 1260.0 * cdiv(ktiles * n, 256) * (11.4 + per * (1.8 + 0.0027 * s16g.KSLOTS + 0.0048 * s16g.MPIX));
             bool dup = false;
             for (const Launch &o : out) dup |= o.kind == l.kind && o.tiles_n == l.tiles_n;
             if (!dup) out.push_back(l);

@@ -4,6 +4,7 @@ Bounds.  Products of bf16 values are exact in fp32, so what differs from the ora
 S = sum |a*b| of an output, (L/16 + 16) * 2^-24 * S for a reduction of length L, one rounding of S per 16-deep matrix
 instruction plus one instruction's worth (in practice the roundings are independent and far smaller).  Outputs stored as
 bf16 are rounded once more, by 2^-8 of the value at most."""
+import re
 import sys
 
 import numpy as np
@@ -272,3 +273,14 @@ def test_split_sums_of_any_length(K, R, C, split):
         sw, sb = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), (R, R), 1, R // 2)
         check(dw, rw, sw + 2.0, 18 * 63, "dw")
         check(db, rb, sb + 3.0, 18 * 63, "dbias")
+
+
+def test_first_layers_of_either_kernel_go_to_the_faster_one():
+    m = owt()
+    plan = lambda N, H, K, R: m.owt_conv_plan_describe(m.conv_desc(N, 3, H, H, K, R, R, 4, 2, m.OWT_BF16, m.OWT_BIAS), 0)
+    for layer in ((128, 224, 96, 11), (89, 204, 96, 11), (391, 204, 32, 7), (5, 204, 32, 11), (10, 80, 64, 7)):
+        text = plan(*layer)
+        a, b = re.search(r"grid(\d+)x(\d+)", text).groups()
+        assert text.startswith("sconv16 ") and int(a) * int(b) <= 256, text
+    for layer in ((349, 187, 64, 11), (490, 95, 32, 11), (257, 52, 96, 11)):   # rows that sconv16 cannot take, and maps it leaves mostly idle
+        assert plan(*layer).startswith("sconv16x"), plan(*layer)
