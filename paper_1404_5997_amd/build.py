@@ -38,6 +38,7 @@ def _units():
         units.append(("dconv16x_%s.o" % pname, "dconv16x_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
     for ps, pname in ((0, "fwd"), (1, "data")):
         units.append(("xconvs_%s.o" % pname, "xconvs_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
+        units.append(("dconv16s_%s.o" % pname, "dconv16s_inst.hip", ["-DOWT_INST_PASS=%d" % ps]))
     units.append(("xfilter.o", "xfilter_inst.hip", []))
     units.append(("xgather.o", "xgather_inst.hip", []))
     for masked in (0, 1):

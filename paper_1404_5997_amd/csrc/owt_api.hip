@@ -58,14 +58,14 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21, KIND_XCONVS = 22 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21, KIND_XCONVS = 22, KIND_DIRECT16S = 23 };
 
 // Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), the shard's for either storage type, and those for
 // bf16 storage of any channel count: a call whose scratch is too small for one of them is served by the kernels before them.
 static inline bool is_split_kind(int kind)
 {
     return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16 || kind == KIND_DIRECT16X ||
-           kind == KIND_IGATHER16 || kind == KIND_XCONVS;
+           kind == KIND_IGATHER16 || kind == KIND_XCONVS || kind == KIND_DIRECT16S;
 }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
@@ -572,6 +572,57 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 if (blocks) l.cost = std::max(l.cost, 1260.0 * (20.0 + 0.5 * xr * xs * per + std::max(0L, tm * tn * splits - 256) * (0.009 + 0.0029 * xr * xs * per)));
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
+    // bf16 layers of few tiles.  They ask for the scratch of the kernel above, so that a call that brings less is served as it was
+    // before there were either.  The costs above are those of layers that fill the chip; small ones take (fitted to 290 timed
+    // passes, 0.15 in the logarithm) 8 us, 3.8 us for each 512 work-groups and 0.31 us a tap of 32 channels, or 5.9 us and 0.11 us a
+    // tap more than the 8 with the layout launch.  So the kernel that would be chosen is priced in us, and these against it: with
+    // 1237 timed launches of 110 drawn layers the choice took 4151 us where those kernels took 5445 and the fastest of all 4030.
+    double best_cost = 0, best_us = 0;
+    for (const Launch &o : out) {
+        if (best_cost > 0 && o.cost >= best_cost) continue;
+        best_cost = o.cost;
+        const bool x = o.kind == KIND_DIRECT16X;
+        if (!x && o.kind != KIND_DIRECT16) { best_us = o.cost / 1260.0 + 10.0; continue; }
+        const double steps = xr * xs * cdiv(cdiv(cred, 32), o.splits);
+        best_us = x ? 13.9 + 0.42 * steps : 8.0 + 3.8 * cdiv((long)o.tiles_m * o.tiles_n * o.splits, 512) + 0.31 * steps;
+        if (o.splits > 1) best_us += 2.2 + 0.85 * o.splits * dm.M * dm.Ncols * 4e-6;
+    }
+    if (g.bf16 && !blocks && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
+        (size_t)g.N * g.H * g.W * g.C < 0x3ffffff0ull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull && (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull &&
+        (size_t)g.K * g.R * g.S * g.C < 0x3ffffff0ull) {
+        for (int v = 0; v < kNumDConv16SVariants; v++) {
+            const DConv16SVariant &xv = kDConv16SVariants[v];
+            if ((force_tile >= 0 && force_tile != kDConv16SFirstTile + v) || xr * xs < xv.TG) continue;
+            const long BM = 32 * xv.WM, rows = panel_rows(g, pass, dm, BM);
+            if (rows < 0 || rows > xv.prs[2]) continue;
+            const long tm = cdiv(dm.M, BM), tn = cdiv(dm.Ncols, 32), chunks = cdiv(cred, 32);
+            for (long s0 : kSplits) {
+                const long s = force_split > 0 ? (force_split < chunks ? force_split : chunks) : s0;
+                const long per = cdiv(chunks, s), splits = cdiv(chunks, per);
+                if (force_split <= 0 && (s0 > chunks || s0 > 8 || tm * tn * splits * xv.WM * xv.TG > 8192)) break;
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_DIRECT16S; l.tile = v; l.pr = rows <= xv.prs[0] ? xv.prs[0] : rows <= xv.prs[1] ? xv.prs[1] : xv.prs[2];
+                l.splits = (int)splits; l.steps = (int)chunks; l.steps_per_split = (int)per; l.tiles_m = (int)tm; l.tiles_n = (int)tn;
+                l.pre_bytes = pad256((size_t)dm.Ncols * xr * xs * chunks * 64);
+                if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                // 5.15 us; a tap's step 150 clocks times the wavefronts on a SIMD and 36 more a filter load (98 where the 32 lanes' loads of
+                // 2 or 4 bytes fall in as many lines), a chunk's panel 866 and its loads; the reduce pass 3.4 us and 0.43 us a MB.
+                const int e = cred % 8 == 0 ? 8 : cred % 2 == 0 ? 2 : 1, mk = pass == OWT_PASS_BWD_DATA && g.masked ? 2 : 1;
+                const bool fwd = pass == OWT_PASS_FWD;
+                const double loads = (!fwd || e == 1 ? 16 : e == 2 ? 8 : 2) * (cred <= 16 ? 0.5 : 1.0), piece = (e == 8 ? 1 : e == 2 ? 4 : 8) * mk * l.pr / 64.0;
+                const long wgs = tm * tn * splits, occ = std::max(1, 16 / (xv.WM * xv.TG)), full = cdiv(wgs, 256);
+                const double waves = std::min(occ, full) * xv.WM * xv.TG / 4.0, rounds = (double)cdiv(wgs, 256 * occ), taps = cdiv(xr * xs, xv.TG);
+                double us = 5.15 + rounds * per * (taps * waves * (150.0 + (fwd && e < 8 ? 98.4 : 36.2) * loads) + 866.0 + 13.0 * piece * waves) / 2100.0;
+                if (splits > 1) us += 3.35 + 0.426 * splits * dm.M * dm.Ncols * 4e-6;
+                if (force_tile < 0 && (us > 0.92 * best_us || rounds * per * taps * waves > 96.0)) continue;
+                l.cost = best_cost > 0 ? best_cost * us / best_us : 1260.0 * us;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
                 if (force_split > 0) break;
             }
@@ -1166,6 +1217,9 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
     } else if (l.kind == KIND_XCONVS) {
         dconv_frame(g, pass, p);
         e = pass == OWT_PASS_FWD ? owt_launch_xconvs_fwd(l.tile, l.pr, p, s) : owt_launch_xconvs_data(l.tile, l.pr, p, s);
+    } else if (l.kind == KIND_DIRECT16S) {
+        dconv_frame(g, pass, p);
+        e = pass == OWT_PASS_FWD ? owt_launch_dconv16s_fwd(l.tile, l.pr, p, s) : owt_launch_dconv16s_data(l.tile, l.pr, p, s);
     } else if (l.kind == KIND_DIRECT16X) {
         if (l.blocks) blocks_frame(g, p); else dconv_frame(g, pass, p);
         p.dWp.set(p.Wi); p.dHpWp.set(p.Hi * p.Wi);
@@ -1278,6 +1332,11 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     if (l.kind == KIND_XCONVS) {
         const XConvSVariant &v = kXConvSVariants[l.tile];
         return snprintf(buf, n, "xconvs %s %s tile%dx32x16 waves%dx1x%d panel%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.WM, v.WM, v.TG,
+                        l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.TG);
+    }
+    if (l.kind == KIND_DIRECT16S) {
+        const DConv16SVariant &v = kDConv16SVariants[l.tile];
+        return snprintf(buf, n, "dconv16s %s %s tile%dx32x32 waves%dx1x%d panel%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.WM, v.WM, v.TG,
                         l.pr, l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 64 * v.WM * v.TG);
     }
     if (l.kind == KIND_DIRECT16X)

@@ -67,6 +67,13 @@ constexpr XConvSVariant kXConvSVariants[kNumXConvSVariants] = {{4, 4, {160, 288,
 hipError_t owt_launch_xconvs_fwd(int variant, int pr, const GemmParams &, hipStream_t);
 hipError_t owt_launch_xconvs_data(int variant, int pr, const GemmParams &, hipStream_t);
 
+// The same for bf16 storage (dconv16s_inst.hip).  Test-hook numbers from 92.
+typedef XConvSVariant DConv16SVariant;
+constexpr int kNumDConv16SVariants = 3, kDConv16SFirstTile = 92;
+constexpr DConv16SVariant kDConv16SVariants[kNumDConv16SVariants] = {{4, 4, {160, 288, 352}}, {2, 4, {96, 224, 320}}, {1, 8, {96, 192, 288}}};
+hipError_t owt_launch_dconv16s_fwd(int variant, int pr, const GemmParams &, hipStream_t);
+hipError_t owt_launch_dconv16s_data(int variant, int pr, const GemmParams &, hipStream_t);
+
 // Stride-1 filter gradient for fp32 storage on the bf16 MFMA with split operands (xfilter_inst.hip): a wavefront holds KB
 // filter blocks of 32 x 32 channels x the S taps of a filter row, four wavefronts of neighbouring tiles to a work-group.  The
 // test hook numbers the variants from 50.

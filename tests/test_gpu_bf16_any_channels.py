@@ -238,7 +238,7 @@ def test_calls_with_the_scratch_of_the_gather_kernel_still_run():
              lambda out, ws: m.owt_conv_bwd_data(case.desc, dev[2], None, dev[1], out, ws),
              lambda out, ws: m.owt_conv_bwd_filter(case.desc, dev[0], dev[2], None, 1.0, 0.0, out, None, ws))
     for p, call in enumerate(calls):
-        assert m.owt_conv_plan_describe(case.desc, p).startswith("dconv16x" if p < 2 else "ifilter16")
+        assert m.owt_conv_plan_describe(case.desc, p).startswith(("dconv16x", "dconv16s") if p < 2 else "ifilter16")
         out = [empty((case.shape_y, case.shape_x, case.shape_w)[p], "bf16" if p < 2 else "f32") for _ in range(2)]
         with force(flags=m.OWT_FORCE_NO_BF16_MFMA):
             assert m.owt_conv_plan_describe(case.desc, p).startswith("igemm")
@@ -284,3 +284,67 @@ def test_first_layers_of_either_kernel_go_to_the_faster_one():
         assert text.startswith("sconv16 ") and int(a) * int(b) <= 256, text
     for layer in ((349, 187, 64, 11), (490, 95, 32, 11), (257, 52, 96, 11)):   # rows that sconv16 cannot take, and maps it leaves mostly idle
         assert plan(*layer).startswith("sconv16x"), plan(*layer)
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("split", [1, 2])
+def test_convolution_of_few_tiles(variant, split):
+    m = owt()
+    ran = 0
+    for shape in CONV + [(4, 64, 13, 13, 136, 3, 3, 1), (1, 16, 7, 45, 33, 5, 5, 2), (3, 40, 6, 7, 24, 3, 3, 1)]:
+        N, C, H, W, K, R, S, pad = shape
+        x, w, b, dy, y = tensors(shape, 1, 1350)
+        for relu in (False, True):
+            case = ConvCase(N, C, H, W, K, R, S, 1, pad, "bf16", True, relu)
+            with force(92 + variant, split):
+                plans = [m.owt_conv_plan_describe(case.desc, p) for p in (0, 1)]
+                print("case", shape, "relu", relu, plans)
+                sys.stdout.flush()
+                if plans[0].startswith("dconv16s"):
+                    size = oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), 1, pad, False)
+                    check(case.fwd(x, w, b), oracle.conv_fwd(x, w, b, 1, pad, relu), size, R * S * C, "y", 2.0 ** -8)
+                    ran += 1
+                if plans[1].startswith("dconv16s"):
+                    size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad, y=y if relu else None)
+                    check(case.bwd_data(dy, y, w), oracle.conv_bwd_data(dy, w, (H, W), 1, pad, y=y if relu else None), size, R * S * K, "dx", 2.0 ** -8)
+                    ran += 1
+            if not relu and plans[1].startswith("dconv16s"):
+                with force(92 + variant, split):
+                    dx = empty(case.shape_x, "bf16")
+                    m.owt_conv_bwd_data_relu_in(case.desc, to_dev(dy, "bf16"), None, to_dev(w, "bf16"), to_dev(x, "bf16"), dx, case.ws(1))
+                    torch.cuda.synchronize()
+                size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad)
+                check(to_host(dx), oracle.conv_bwd_data(dy, w, (H, W), 1, pad) * (x > 0), size, R * S * K, "dx masked by x > 0", 2.0 ** -8)
+    assert ran >= 4 * 9                                  # (all but the one of three taps and one whose rows fit no panel)
+
+
+def test_few_tiles_meet_no_channel_of_the_next_pixel_or_tap():
+    m = owt()
+    for C in (5, 18, 33):                                # loads of one and of two values, one short chunk and a second one
+        shape = (2, C, 6, 7, 9, 3, 3, 1)
+        x, w, _, dy, y = tensors(shape, 1, 1360)
+        x[0, 2, 3, 0] = np.inf
+        w[4, 1, 1, 0] = np.nan
+        ref = np.zeros((2, 6, 7, 9))
+        xp = np.zeros((2, 8, 9, C)); xp[:, 1:-1, 1:-1] = x
+        with np.errstate(invalid="ignore"):
+            for r in range(3):
+                for s in range(3):
+                    ref += xp[:, r:r + 6, s:s + 7] @ w[:, r, s].astype(np.float64).T
+        for variant in (0, 1, 2):
+            with force(92 + variant, 1):
+                case = ConvCase(2, C, 6, 7, 9, 3, 3, 1, 1, "bf16", False, False)
+                assert m.owt_conv_plan_describe(case.desc, 0).startswith("dconv16s")
+                got = case.fwd(x, w, None)
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+            assert np.array_equal(np.isneginf(got), np.isneginf(ref)) and np.isfinite(got).any()
+
+
+def test_small_bf16_layers_go_to_the_kernel_of_few_tiles_and_large_ones_do_not():
+    m = owt()
+    plan = lambda s, p: m.owt_conv_plan_describe(m.conv_desc(*s[:7], 1, s[7], m.OWT_BF16, m.OWT_BIAS), p)
+    for p in (0, 1):
+        for shape in ((3, 160, 7, 19, 43, 3, 3, 1), (2, 64, 17, 16, 32, 3, 3, 1), (1, 32, 15, 49, 32, 5, 5, 2)):
+            assert plan(shape, p).startswith("dconv16s"), plan(shape, p)
+        for shape in ((128, 192, 13, 13, 384, 3, 3, 1), (128, 64, 27, 27, 192, 5, 5, 2), (405, 57, 38, 26, 32, 3, 3, 1)):
+            assert not plan(shape, p).startswith("dconv16s"), plan(shape, p)
