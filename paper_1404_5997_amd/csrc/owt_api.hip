@@ -936,7 +936,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // would leave most of their 128-wide tiles empty on a large batch: the reduction over images.  Timed, us, kernels above -> this one: 419 images
     // 42x8, 32 -> 32 55 -> 36; 375 images 29x19, 64 -> 32 53 -> 41; 761 images 8x26, 96 -> 8 49 -> 39; but 43 images 17x22, 64 -> 8
     // 18 -> 22; 53 images 25x7, 64 -> 192 27 -> 30; 89 images 20x12, 32 -> 120 5x5 35 -> 42, and whole tiles half as fast.
-    bool staged16 = false;
+    bool staged16 = false, few_images = false;
     for (const Launch &o : out) staged16 |= (o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B) && (g.K > 64 || g.C > 96 || g.N < 128);
     if ((force_tile < 0 ? !staged16 : force_tile >= kIFilter16FirstTile && force_tile < kIGather16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
         image_groups_fit(g, false)) {
@@ -967,6 +967,10 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
                 l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
                 if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
+                // Of a group of 16 images one to four leave most empty; the kernel that gathers pixels, 36 us and from there on 20 and 78 us
+                // a GMAC, is the faster one where filters are many: one image 30x20, 130 -> 200 of 5x5 68 us here, 50 there; 13x13 49
+                // and 37; but 96 -> 130 of 3x3 21 and 41, and three images of the first 67 and 124.
+                if (force_tile < 0 && g.N <= 4 && l.cost > 1260.0 * std::max(36.0, 20.0 + 78e-9 * dm.M * dm.Ncols * dm.Kd)) { few_images = true; continue; }
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -975,7 +979,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         }
     }
     // the same for any geometry (not the fully-connected shard), where no other kernel on the bf16 matrix unit is a candidate
-    bool rows16 = false;
+    bool rows16 = few_images;
     for (const Launch &o : out)
         rows16 |= o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B || o.kind == KIND_IFILTER16 || o.kind == KIND_SFILTER16 || o.kind == KIND_SFILTER16B;
     if ((force_tile < 0 ? !rows16 : force_tile >= kIGather16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && (g.H > 1 || g.W > 1) && !no_direct &&
