@@ -578,7 +578,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         }
     }
     // bf16 layers of few tiles.  They ask for the scratch of the kernel above, so that a call that brings less is served as it was
-    // before there were either.  The costs above are those of layers that fill the chip; small ones take (fitted to 290 timed
+    // before there were either.  The costs above are those of layers that fill the chip; small ones take (fitted to 220 timed
     // passes, 0.15 in the logarithm) 8 us, 3.8 us for each 512 work-groups and 0.31 us a tap of 32 channels, or 5.9 us and 0.11 us a
     // tap more than the 8 with the layout launch.  So the kernel that would be chosen is priced in us, and these against it: with
     // 1237 timed launches of 110 drawn layers the choice took 4151 us where those kernels took 5445 and the fastest of all 4030.
