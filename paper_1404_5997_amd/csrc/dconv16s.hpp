@@ -8,9 +8,9 @@
 // filters as they are, two steps ahead: no launch before, and no barrier but the two that change the panel.  Every wavefront
 // loads its own filters, which is why layers that fill the chip stay with the other kernels; the planner's cost model draws the line.
 //
-// Measured against those kernels, us: 3 images 7x19, 160 -> 43 channels of 3x3 22.1 -> 7.5 forward, 19.3 -> 9.3 backward-data; 2 of 17x16,
-// 64 -> 32 11.1 -> 5.8 and 11.5 -> 6.6; 4 of 6x52, 32 -> 172 of 5x5 26.2 -> 6.2 and 25.7 -> 15.3; all passes of 110 drawn layers under
-// 15 GFLOP 5445 -> 4151.  What is left is latency: a step's panel reads and filter loads (150 clocks and 36 a load).
+// Measured against those kernels, us: 3 images 7x19, 160 -> 43 channels of 3x3 22.1 -> 7.5 forward, 19.3 -> 9.3 backward-data; 4 of 6x52,
+// 32 -> 172 of 5x5 26.2 -> 6.2 and 25.7 -> 15.3; all passes of 110 drawn layers under 15 GFLOP 5445 -> 4151.  What is left is latency: a
+// step's panel reads and filter loads (150 clocks and 36 a load).
 #pragma once
 #include "dconv_bf16.hpp"
 

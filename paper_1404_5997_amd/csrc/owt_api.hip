@@ -582,6 +582,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // passes, 0.15 in the logarithm) 8 us, 3.8 us for each 512 work-groups and 0.31 us a tap of 32 channels, or 5.9 us and 0.11 us a
     // tap more than the 8 with the layout launch.  So the kernel that would be chosen is priced in us, and these against it: with
     // 1237 timed launches of 110 drawn layers the choice took 4151 us where those kernels took 5445 and the fastest of all 4030.
+    // Layers that the pipelined kernel takes whole keep it all the same (11.1 us against 5.8 for 2 images of 17x16, 64 -> 32): sums in
+    // another order round a few bf16 activations the other way, and in a network of a few images one of them moves a pool's maximum.
     double best_cost = 0, best_us = 0;
     for (const Launch &o : out) {
         if (best_cost > 0 && o.cost >= best_cost) continue;
@@ -592,8 +594,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         best_us = x ? 13.9 + 0.42 * steps : 8.0 + 3.8 * cdiv((long)o.tiles_m * o.tiles_n * o.splits, 512) + 0.31 * steps;
         if (o.splits > 1) best_us += 2.2 + 0.85 * o.splits * dm.M * dm.Ncols * 4e-6;
     }
-    if (g.bf16 && !blocks && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
-        (size_t)g.N * g.H * g.W * g.C < 0x3ffffff0ull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull && (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull &&
+    if (g.bf16 && !blocks && (force_tile >= 0 || !whole) && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
+        (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull &&
         (size_t)g.K * g.R * g.S * g.C < 0x3ffffff0ull) {
         for (int v = 0; v < kNumDConv16SVariants; v++) {
             const DConv16SVariant &xv = kDConv16SVariants[v];
