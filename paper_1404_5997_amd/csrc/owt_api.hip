@@ -1164,6 +1164,7 @@ static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per g
 // times: past twice they only raise the bound (the first layer's forward pass 0.3 -> 199 MB).  choose() sees every candidate.
 static bool worth_timing(const Launch &l, double least)
 {
+    if (l.kind == KIND_XCONVS || l.kind == KIND_DIRECT16S) return l.cost <= 1.4 * least;      // (three tiles, up to eight splits; modelled to 0.14-0.17 in the logarithm)
     return l.cost <= (is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 3.0) * least;
 }
 static bool worth_workspace(const Launch &l, double least) { return !is_split_kind(l.kind) || l.splits == 1 || worth_timing(l, least); }
