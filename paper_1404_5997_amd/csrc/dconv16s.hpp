@@ -103,18 +103,12 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) dconv16s_kernel
             if (MASKED) load8(mrs, std::integral_constant<int, E>(), rowok[i], rowat[i] + c, 1u, c, yreg[MASKED ? i : 0]);
         }
     };
-    auto pass = [](uint32_t x, uint32_t y) __attribute__((always_inline)) {          // each half of x where that of y is positive
-        return (__uint_as_float(y << 16) > 0.f ? x & 0xffffu : 0u) | (__uint_as_float(y & 0xffff0000u) > 0.f ? x & 0xffff0000u : 0u);
-    };
     auto store_panel = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < PU; i++) {
             const int u = tid + i * NT, row = u >> 2;
             uint4 v = words(preg[i], E == 1);
-            if (MASKED) {
-                const uint4 y = words(yreg[MASKED ? i : 0], E == 1);
-                v = make_uint4(pass(v.x, y.x), pass(v.y, y.y), pass(v.z, y.z), pass(v.w, y.w));
-            }
+            if (MASKED) v = mask_words16(v, words(yreg[MASKED ? i : 0], E == 1));
             if (row < PR) panel[(u & 3) * PL + row] = v;
         }
     };

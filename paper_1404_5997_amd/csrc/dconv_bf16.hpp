@@ -19,14 +19,6 @@ namespace owt {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// zero the bf16 lanes of v whose mask value (bf16 bits in y) is not > 0
-__device__ __forceinline__ uint32_t mask_pair(uint32_t v, uint32_t y)
-{
-    const uint32_t lo = y & 0xffffu, hi = y >> 16;
-    const bool plo = lo != 0u && lo < 0x8000u, phi = hi != 0u && hi < 0x8000u;   // positive, non-zero
-    return (plo ? (v & 0xffffu) : 0u) | (phi ? (v & 0xffff0000u) : 0u);
-}
-
 template <class Epi, bool BWD, int WM, int WN, int PR>
 __global__ void __launch_bounds__(64 * WM * WN, (WM * WN >= 4 ? 2 : 1)) dconv_bf16_kernel(const GemmParams p)
 {
@@ -89,8 +81,7 @@ __global__ void __launch_bounds__(64 * WM * WN, (WM * WN >= 4 ? 2 : 1)) dconv_bf
                 v = *(const uint4 *)(in + off);
                 if (BWD && mask) {
                     const uint4 y = *(const uint4 *)(mask + off);
-                    v.x = mask_pair(v.x, y.x); v.y = mask_pair(v.y, y.y);
-                    v.z = mask_pair(v.z, y.z); v.w = mask_pair(v.w, y.w);
+                    v = mask_words16(v, y);
                 }
             }
             preg[i] = v;

@@ -239,8 +239,7 @@ __global__ void __launch_bounds__(256, OCC) dconv16p_kernel(const GemmParams p)
                 v = *(const uint4 *)(in + off);
                 if (BWD && mask) {
                     const uint4 y = *(const uint4 *)(mask + off);
-                    v.x = mask_pair(v.x, y.x); v.y = mask_pair(v.y, y.y);
-                    v.z = mask_pair(v.z, y.z); v.w = mask_pair(v.w, y.w);
+                    v = mask_words16(v, y);
                 }
             }
             preg[i] = v;
@@ -525,8 +524,7 @@ __global__ void __launch_bounds__(256, OCC) dconv16p_kernel(const GemmParams p)
                     const size_t o = (size_t)m * p.Ncols + n;
                     if (BWD && xm) {
                         const uint4 x = *(const uint4 *)(xm + o);
-                        v.x = mask_pair(v.x, x.x); v.y = mask_pair(v.y, x.y);
-                        v.z = mask_pair(v.z, x.z); v.w = mask_pair(v.w, x.w);
+                        v = mask_words16(v, x);
                     }
                     *(uint4 *)(out + o) = v;
                 }

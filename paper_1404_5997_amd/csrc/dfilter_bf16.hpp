@@ -31,14 +31,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef short short8_t __attribute__((ext_vector_type(8)));
 
-// zero the bf16 halves of v whose mask value (bf16 bits in y) is not > 0
-__device__ __forceinline__ uint32_t relu_mask_pair(uint32_t v, uint32_t y)
-{
-    const uint32_t lo = y & 0xffffu, hi = y >> 16;
-    const bool plo = lo != 0u && lo < 0x8000u, phi = hi != 0u && hi < 0x8000u;
-    return (plo ? (v & 0xffffu) : 0u) | (phi ? (v & 0xffff0000u) : 0u);
-}
-
 __device__ __forceinline__ short4_t lds_read_tr16(const uint16_t *p)
 {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t *)p);
@@ -112,8 +104,7 @@ __global__ void __launch_bounds__(64 * WK * WC, (OCC * WK * WC >= 4 ? OCC * WK *
                 v = *(const uint4 *)(dzsrc + off);
                 if (mask) {
                     const uint4 y = *(const uint4 *)(mask + off);
-                    v.x = relu_mask_pair(v.x, y.x); v.y = relu_mask_pair(v.y, y.y);
-                    v.z = relu_mask_pair(v.z, y.z); v.w = relu_mask_pair(v.w, y.w);
+                    v = mask_words16(v, y);
                 }
             }
             areg[i] = v;

@@ -31,17 +31,6 @@
 
 namespace owt {
 
-typedef short owt_i16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short owt_u16x2 __attribute__((ext_vector_type(2)));
-
-// bf16 pair v where the pair y is positive, else zero: y clamped to 0..1 as integers, times v
-__device__ __forceinline__ uint32_t mask_pair16(uint32_t v, uint32_t y)
-{
-    const owt_i16x2 zero = {0, 0}, one = {1, 1};
-    const owt_i16x2 m = __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(owt_i16x2, y), zero), one);
-    return __builtin_bit_cast(uint32_t, (owt_u16x2)(__builtin_bit_cast(owt_u16x2, v) * __builtin_bit_cast(owt_u16x2, m)));
-}
-
 // Eight images' raw values of B blocks of 32 rows (or columns), and the fragments made of them.
 template <int B, bool PAIR> struct ImageRaw {
     static_assert(!PAIR || B == 2, "a pair is two blocks");
@@ -74,10 +63,6 @@ __device__ __forceinline__ float sum8_bf16(uint4 q)
 {
     return ((bf16_lo_f32(q.x) + bf16_hi_f32(q.x)) + (bf16_lo_f32(q.y) + bf16_hi_f32(q.y))) +
            ((bf16_lo_f32(q.z) + bf16_hi_f32(q.z)) + (bf16_lo_f32(q.w) + bf16_hi_f32(q.w)));
-}
-__device__ __forceinline__ uint4 mask_words16(uint4 v, uint4 y)
-{
-    return make_uint4(mask_pair16(v.x, y.x), mask_pair16(v.y, y.y), mask_pair16(v.z, y.z), mask_pair16(v.w, y.w));
 }
 
 // KB filter blocks x CB channel blocks x the S taps of one filter row per wavefront; ZP / XP: filters / channels in pairs.

@@ -88,6 +88,22 @@ __device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi)
 }
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return (uint16_t)(f32x2_to_bf16x2(f, 0.f) & 0xffffu); }
 
+// The ReLU mask on packed bf16: each half of v where that of y is greater than zero, else zero.  Bits 0x0001 to 0x7f80 are greater
+// than zero (subnormal numbers and infinity too), 0x7f81 to 0x7fff are NaN, which is not.  Four packed instructions: y + 0x7f, wrapping
+// round, takes what is greater than zero to 0x80 .. 0x7fff and all else below, so the sign of 0x7f minus that, saturating, is the mask.
+typedef short owt_i16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short owt_u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t mask_pair16(uint32_t v, uint32_t y)
+{
+    const owt_u16x2 up = {0x7f, 0x7f};
+    const owt_i16x2 top = {0x7f, 0x7f}, t = __builtin_bit_cast(owt_i16x2, (owt_u16x2)(__builtin_bit_cast(owt_u16x2, y) + up));
+    return v & __builtin_bit_cast(uint32_t, (owt_i16x2)(__builtin_elementwise_sub_sat(top, t) >> 15));
+}
+__device__ __forceinline__ uint4 mask_words16(uint4 v, uint4 y)
+{
+    return make_uint4(mask_pair16(v.x, y.x), mask_pair16(v.y, y.y), mask_pair16(v.z, y.z), mask_pair16(v.w, y.w));
+}
+
 __device__ __forceinline__ float4 load4(const float *p, int off) { return *(const float4 *)(p + off); }
 __device__ __forceinline__ float4 load4(const bf16_t *p, int off)
 {

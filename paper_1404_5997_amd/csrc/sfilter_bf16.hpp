@@ -118,8 +118,7 @@ __global__ void __launch_bounds__(kSFilter16NT, 1) sfilter16_kernel(const GemmPa
                 v = *(const uint4 *)(dzsrc + off);
                 if (mask) {
                     const uint4 y = *(const uint4 *)(mask + off);
-                    v.x = relu_mask_pair(v.x, y.x); v.y = relu_mask_pair(v.y, y.y);
-                    v.z = relu_mask_pair(v.z, y.z); v.w = relu_mask_pair(v.w, y.w);
+                    v = mask_words16(v, y);
                 }
             }
             dreg[it] = v;
