@@ -371,6 +371,55 @@ static double model_cost(long wgs, int waves_per_wg, int occ, double macs_per_wg
     return cost;
 }
 
+// Work-groups one after the other: the rounds they take at `occ` to a CU, and the work-groups of a CU added up over the rounds.
+static void wg_rounds(long wgs, int occ, double &rounds, double &resident)
+{
+    const long full = wgs / (256L * occ), rest = wgs % (256L * occ);
+    rounds = full + (rest > 0);
+    resident = full * occ + cdiv(rest, 256);
+}
+
+// Microseconds of a bf16 forward or backward-data launch of stride 1 where the kernels that take it differ in kind: what a tap of a
+// chunk takes per round and per resident work-group, what the panel takes, the results' stores (twice as long where their number
+// per pixel is odd), the reduce pass.  Fitted to 734 timed launches of 70 layers and of draws of other geometries, 0.08 to 0.15 in the
+// logarithm.  Held to the clocks of model_cost, which know no latencies, 31 of 103 passes took more than 5 % longer than the
+// fastest kernel, up to 1.36 times (49 images 13x9, 200 -> 72 of 5x5: 38 us where dconv16 takes 28); with this 6, up to 1.10 times.
+static double conv16_us(const Launch &l, int pass, const Geom &g, const PassDims &dm)
+{
+    const double mb = l.splits > 1 ? l.splits * dm.M * dm.Ncols * 4e-6 : 0.0;
+    const double outs = l.splits > 1 ? 0.0 : dm.M * dm.Ncols * (dm.Ncols % 2 ? 4e-6 : 2e-6);
+    const double steps = (double)g.R * g.S * l.steps_per_split, panel = l.steps_per_split * l.pr / 64.0;
+    const long wgs = (long)l.tiles_m * l.tiles_n * l.splits;
+    double rounds, resident;
+    if (l.kind == KIND_DIRECT16X) {
+        const bool odd = (pass == OWT_PASS_FWD ? g.C : g.K) % 2 != 0, masked = pass == OWT_PASS_BWD_DATA && g.masked;
+        wg_rounds(wgs, odd || masked ? 2 : 3, rounds, resident);
+        const double t = odd ? (masked ? 0.328 : 0.340) : (masked ? 0.363 : 0.318), r = odd == masked ? 0.055 : 0.002;
+        return 13.0 + steps * (t * rounds + r * resident) + (masked ? 0.0 : odd ? 0.097 : 0.05) * panel * resident + (l.splits > 1 ? 0.6 : 0.0) + 0.85 * mb + 0.35 * outs;
+    }
+    if (l.kind == KIND_DIRECT16) {
+        wg_rounds(wgs, 2, rounds, resident);
+        const double t = l.tile == TILE_128x128 ? 0.60 : l.tile == TILE_128x64 ? 0.62 : 0.46, r = l.tile == TILE_128x128 ? 0.073 : l.tile == TILE_128x64 ? 0.0 : 0.10;
+        const double q = l.tile == TILE_128x128 ? 0.18 : l.tile == TILE_128x64 ? 0.31 : 0.14;
+        return 8.7 + (pass == OWT_PASS_BWD_DATA ? 3.9 : 0.0) + steps * (t * rounds + r * resident) + q * panel * resident + (l.splits > 1 ? 0.6 : 0.0) + 0.56 * mb + 0.82 * outs;
+    }
+    return l.cost / 1260.0 + 10.0;                       // the kernels on the fp32 instruction
+}
+
+// Adds the same to the cost of every launch of a kind, so that the cheapest of them costs `us` microseconds.
+static void price_kind(std::vector<Launch> &out, int kind, double clocks_of_cheapest, double us)
+{
+    for (Launch &l : out)
+        if (l.kind == kind) l.cost += 1260.0 * us - clocks_of_cheapest;
+}
+static const Launch *cheapest_of(const std::vector<Launch> &out, int kind)
+{
+    const Launch *best = nullptr;
+    for (const Launch &l : out)
+        if (l.kind == kind && (!best || l.cost < best->cost)) best = &l;
+    return best;
+}
+
 static const size_t kMaxPartialBytes = (size_t)192 << 20;
 
 // The filter-gradient kernels that take 16 images per matrix instruction form 32-bit byte offsets for whole groups of 16 and
@@ -546,8 +595,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         }
     }
     // bf16 storage where the pipelined kernel above is no candidate (channels not in whole chunks of 32, maps wider than its panel,
-    // strided layers): the same loop with panel pieces at any address.  Against the 64-channel kernel, which takes multiples of
-    // eight, the model decides between the two; it chose the faster one in 71 of 72 timed passes.
+    // strided layers): the same loop with panel pieces at any address.
     bool whole = false;                                 // the pipelined kernel takes it as it is
     for (const Launch &o : out) whole |= o.kind == KIND_DIRECT16 && (o.tile == TILE_512x64 || o.tile == TILE_256x64P);
     if (g.bf16 && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs >= 2 && xr * xs <= 32 &&
@@ -577,23 +625,15 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             }
         }
     }
+    const bool priced16 = g.bf16 && pass != OWT_PASS_BWD_FILTER && !blocks && !whole && (g.H > 1 || g.W > 1);
+    if (priced16)
+        for (Launch &l : out) l.cost = 1260.0 * conv16_us(l, pass, g, dm);
     // bf16 layers of few tiles.  They ask for the scratch of the kernel above, so that a call that brings less is served as it was
-    // before there were either.  The costs above are those of layers that fill the chip; small ones take (fitted to 220 timed
-    // passes, 0.15 in the logarithm) 8 us, 3.8 us for each 512 work-groups and 0.31 us a tap of 32 channels, or 5.9 us and 0.11 us a
-    // tap more than the 8 with the layout launch.  So the kernel that would be chosen is priced in us, and these against it: with
-    // 1237 timed launches of 110 drawn layers the choice took 4151 us where those kernels took 5445 and the fastest of all 4030.
-    // Layers that the pipelined kernel takes whole keep it all the same (11.1 us against 5.8 for 2 images of 17x16, 64 -> 32): sums in
-    // another order round a few bf16 activations the other way, and in a network of a few images one of them moves a pool's maximum.
-    double best_cost = 0, best_us = 0;
-    for (const Launch &o : out) {
-        if (best_cost > 0 && o.cost >= best_cost) continue;
-        best_cost = o.cost;
-        const bool x = o.kind == KIND_DIRECT16X;
-        if (!x && o.kind != KIND_DIRECT16) { best_us = o.cost / 1260.0 + 10.0; continue; }
-        const double steps = xr * xs * cdiv(cdiv(cred, 32), o.splits);
-        best_us = x ? 13.9 + 0.42 * steps : 8.0 + 3.8 * cdiv((long)o.tiles_m * o.tiles_n * o.splits, 512) + 0.31 * steps;
-        if (o.splits > 1) best_us += 2.2 + 0.85 * o.splits * dm.M * dm.Ncols * 4e-6;
-    }
+    // before there were either.  Layers that the pipelined kernel takes whole keep it (11.1 us against 5.8 for 2 images of 17x16, 64 ->
+    // 32): sums in another order round a few bf16 activations the other way, and in a network of a few images one of them moves a
+    // pool's maximum.
+    double best_us = 0;
+    for (const Launch &o : out) best_us = best_us > 0 ? std::min(best_us, o.cost / 1260.0) : o.cost / 1260.0;
     if (g.bf16 && !blocks && (force_tile >= 0 || !whole) && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
         (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull &&
         (size_t)g.K * g.R * g.S * g.C < 0x3ffffff0ull) {
@@ -621,8 +661,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const double waves = std::min(occ, full) * xv.WM * xv.TG / 4.0, rounds = (double)cdiv(wgs, 256 * occ), taps = cdiv(xr * xs, xv.TG);
                 double us = 5.15 + rounds * per * (taps * waves * (150.0 + (fwd && e < 8 ? 98.4 : 36.2) * loads) + 866.0 + 13.0 * piece * waves) / 2100.0;
                 if (splits > 1) us += 3.35 + 0.426 * splits * dm.M * dm.Ncols * 4e-6;
-                if (force_tile < 0 && (us > 0.92 * best_us || rounds * per * taps * waves > 96.0)) continue;
-                l.cost = best_cost > 0 ? best_cost * us / best_us : 1260.0 * us;
+                if (force_tile < 0 && ((best_us > 0 && us > best_us) || rounds * per * taps * waves > 96.0)) continue;
+                l.cost = 1260.0 * us;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1088,6 +1128,11 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if (force_split > 0) break;
         }
     }
+    // bf16 storage: the kinds that know no microseconds, beside those that do.  Each kind's cheapest launch is priced, the order
+    // among its launches stays.
+    const Launch *gather = cheapest_of(out, KIND_GATHER);
+    if (priced16 && gather) price_kind(out, KIND_GATHER, gather->cost, gather->cost / 1260.0 + 10.0);
+
 }
 
 typedef std::array<int, 15> PlanKey;

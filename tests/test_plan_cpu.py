@@ -142,3 +142,14 @@ def test_workspace_bounds(m, shape, p, alone, most):
         assert m.owt_conv_workspace_bytes(d, p) <= alone * 1e6 + 1e5
     finally:
         m.owt_test_force_variant(-1, 0, 0)
+
+
+# bf16 layers whose kernels differ in kind, where one was timed well ahead of another: N, C, H, W, K, R, S, stride, pad, pass, the call
+# masks dy, the faster kernel, the slower one, microseconds of both
+@pytest.mark.parametrize("shape,p,relu,faster,slower,us", [
+    ((205, 96, 12, 4, 232, 3, 3, 1, 1), 1, True, "dconv16 ", "dconv16x", (28.9, 34.3)),
+    ((140, 232, 13, 9, 344, 3, 3, 1, 1), 1, False, "dconv16 ", "dconv16x", (50.9, 63.7)), ((49, 200, 13, 9, 72, 5, 5, 1, 2), 0, True, "dconv16 ", "dconv16x", (27.8, 37.7)),
+    ((293, 344, 35, 5, 72, 3, 3, 1, 1), 1, True, "dconv16x", "dconv16 ", (47.4, 76.0))])
+def test_bf16_layers_get_the_faster_kind_of_kernel(m, shape, p, relu, faster, slower, us):
+    got = plan(m, shape, p, relu, dtype=1)
+    assert got.startswith(faster) and not got.startswith(slower), (got, us)
