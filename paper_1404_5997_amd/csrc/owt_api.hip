@@ -615,9 +615,12 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 l.pre_bytes = pad256(packed);
                 if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                 l.cost = model_cost(tm * tn * splits, 4, 2, 256.0 * 64 * 32 * xr * xs * per / 9.0, 1.25, splits, dm.M, dm.Ncols) + 5000.0;
-                // (first layers: 24 us for 4 taps of 2 chunks, 29 for 9, and 36 and 61 ns for each work-group past one a CU; where
-                // sconv16 takes the layer too, it is nearly always the faster one: 62 us against 124 for 89 images of 204x204)
-                if (blocks) l.cost = std::max(l.cost, 1260.0 * (20.0 + 0.5 * xr * xs * per + std::max(0L, tm * tn * splits - 256) * (0.009 + 0.0029 * xr * xs * per)));
+                if (blocks) {                             // fitted to 294 launches of strided layers, 0.09 in the logarithm
+                    double rounds, resident;
+                    wg_rounds(tm * tn * splits, 2, rounds, resident);
+                    const double outs = dm.M * dm.Ncols * (dm.Ncols % 2 ? 4e-6 : 2e-6);
+                    l.cost = 1260.0 * (15.3 + 0.355 * xr * xs * per * rounds + 0.44 * per * l.pr / 64.0 * resident + (splits > 1 ? 0.6 + 0.85 * splits * dm.M * dm.Ncols * 4e-6 : 0.535 * outs));
+                }
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -722,10 +725,10 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             l.kind = KIND_SCONV16; l.splits = 1; l.steps = s16g.units; l.steps_per_split = (int)per;
             l.tiles_m = (int)ktiles; l.tiles_n = (int)n;
             l.partial_bytes = pad256((size_t)g.K * s16g.KSLOTS * 2);        // the re-laid-out filters
-            // One work-group a CU (its LDS): 11.4 us for the launches, the filter bank and the first band, and a unit of four rows 3 us and
-            // a little more the longer reduction and rows are.  Two work-groups a CU go one after the other and load the bank twice:
-            // 128 images of 224x224 to 96 filters of 11x11 66 us with 256 work-groups, 76 with 512; 39 of 192x192 to 64 21.5 and 29.4.
-            l.cost = 1260.0 * cdiv(ktiles * n, 256) * (11.4 + per * (1.8 + 0.0027 * s16g.KSLOTS + 0.0048 * s16g.MPIX));
+            // One work-group a CU (its LDS): the launches and the filter bank, and a unit of four rows what its reduction and its band take
+            // (fitted to 83 launches, 0.11 in the logarithm).  Two work-groups a CU go one after the other and load the bank twice: 128
+            // images of 224x224 to 96 filters of 11x11 66 us with 256 work-groups, 76 with 512; 39 of 192x192 to 64 21.5 and 29.4.
+            l.cost = 1260.0 * cdiv(ktiles * n, 256) * (8.7 + 0.0065 * s16g.KSLOTS + per * (2.17 + 0.003 * s16g.KSLOTS + 5.0e-5 * s16g.ROWS * g.W * g.C));
             bool dup = false;
             for (const Launch &o : out) dup |= o.kind == l.kind && o.tiles_n == l.tiles_n;
             if (!dup) out.push_back(l);
@@ -1130,7 +1133,20 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     }
     // bf16 storage: the kinds that know no microseconds, beside those that do.  Each kind's cheapest launch is priced, the order
     // among its launches stays.
+    const auto reduce_clocks = [&](const Launch &l) { return l.splits > 1 ? 14000.0 + (double)(l.splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0 : 0.0; };
+    const auto mb = [&](const Launch &l) { return l.splits > 1 ? l.splits * dm.M * dm.Ncols * 4e-6 : 0.0; };
     const Launch *gather = cheapest_of(out, KIND_GATHER);
+    if (g.bf16 && pass == OWT_PASS_FWD && blocks && !forced(OWT_FORCE_NO_BF16_MFMA)) {
+        // (strided layers, fitted to 2024 and 145 launches, 0.13 and 0.10 in the logarithm.  In clocks alone the gather kernel looked faster
+        // than sconv16 on layers of a few us: 13 -> 22 us for 25 images 72x75x16 to 36 filters of 2x2, stride 2)
+        if (gather) {
+            const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0;
+            const double us = 8.8 + 0.72 * core + 0.116 * gather->tiles_m * gather->tiles_n * gather->splits / 256.0 +
+                              (gather->splits > 1 ? 0.985 * mb(*gather) - 2.4 : 2.1e-6 * dm.M * dm.Ncols);
+            price_kind(out, KIND_GATHER, gather->cost, us);
+        }
+        if (const Launch *l = cheapest_of(out, KIND_SCONV)) price_kind(out, KIND_SCONV, l->cost, 11.1 + 0.366 * l->cost / 1260.0 + 2.4e-6 * dm.M * dm.Ncols);
+    }
     if (priced16 && gather) price_kind(out, KIND_GATHER, gather->cost, gather->cost / 1260.0 + 10.0);
 
 }

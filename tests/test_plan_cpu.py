@@ -147,6 +147,9 @@ def test_workspace_bounds(m, shape, p, alone, most):
 # bf16 layers whose kernels differ in kind, where one was timed well ahead of another: N, C, H, W, K, R, S, stride, pad, pass, the call
 # masks dy, the faster kernel, the slower one, microseconds of both
 @pytest.mark.parametrize("shape,p,relu,faster,slower,us", [
+    ((25, 16, 72, 75, 36, 2, 2, 2, 1), 0, True, "sconv16 ", "igemm", (13.1, 22.4)), ((2, 16, 59, 14, 56, 2, 2, 2, 1), 0, True, "sconv16 ", "igemm", (12.3, 18.1)),
+    ((4, 4, 72, 46, 184, 4, 4, 3, 2), 0, True, "sconv16 ", "igemm", (13.1, 19.3)), ((52, 12, 80, 6, 120, 5, 5, 2, 0), 0, True, "igemm", "sconv16 ", (21.6, 32.5)),
+    ((7, 32, 8, 12, 104, 4, 4, 2, 0), 0, True, "igemm", "sconv16x", (17.4, 23.2)), ((10, 3, 26, 107, 80, 4, 4, 2, 0), 0, True, "sconv16x", "igemm", (19.9, 25.3)),
     ((205, 96, 12, 4, 232, 3, 3, 1, 1), 1, True, "dconv16 ", "dconv16x", (28.9, 34.3)),
     ((140, 232, 13, 9, 344, 3, 3, 1, 1), 1, False, "dconv16 ", "dconv16x", (50.9, 63.7)), ((49, 200, 13, 9, 72, 5, 5, 1, 2), 0, True, "dconv16 ", "dconv16x", (27.8, 37.7)),
     ((293, 344, 35, 5, 72, 3, 3, 1, 1), 1, True, "dconv16x", "dconv16 ", (47.4, 76.0))])
