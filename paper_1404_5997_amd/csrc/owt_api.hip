@@ -981,7 +981,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // would leave most of their 128-wide tiles empty on a large batch: the reduction over images.  Timed, us, kernels above -> this one: 419 images
     // 42x8, 32 -> 32 55 -> 36; 375 images 29x19, 64 -> 32 53 -> 41; 761 images 8x26, 96 -> 8 49 -> 39; but 43 images 17x22, 64 -> 8
     // 18 -> 22; 53 images 25x7, 64 -> 192 27 -> 30; 89 images 20x12, 32 -> 120 5x5 35 -> 42, and whole tiles half as fast.
-    bool staged16 = false, few_images = false;
+    bool staged16 = false;
     for (const Launch &o : out) staged16 |= (o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B) && (g.K > 64 || g.C > 96 || g.N < 128);
     if ((force_tile < 0 ? !staged16 : force_tile >= kIFilter16FirstTile && force_tile < kIGather16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
         image_groups_fit(g, false)) {
@@ -1012,10 +1012,6 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
                 l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
                 if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
-                // Of a group of 16 images one to four leave most empty; the kernel that gathers pixels, 36 us and from there on 20 and 78 us
-                // a GMAC, is the faster one where filters are many: one image 30x20, 130 -> 200 of 5x5 68 us here, 50 there; 13x13 49
-                // and 37; but 96 -> 130 of 3x3 21 and 41, and three images of the first 67 and 124.
-                if (force_tile < 0 && g.N <= 4 && l.cost > 1260.0 * std::max(36.0, 20.0 + 78e-9 * dm.M * dm.Ncols * dm.Kd)) { few_images = true; continue; }
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1024,7 +1020,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         }
     }
     // the same for any geometry (not the fully-connected shard), where no other kernel on the bf16 matrix unit is a candidate
-    bool rows16 = few_images;
+    bool rows16 = false;
     for (const Launch &o : out)
         rows16 |= o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B || o.kind == KIND_IFILTER16 || o.kind == KIND_SFILTER16 || o.kind == KIND_SFILTER16B;
     if ((force_tile < 0 ? !rows16 : force_tile >= kIGather16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && (g.H > 1 || g.W > 1) && !no_direct &&
@@ -1148,7 +1144,26 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         if (const Launch *l = cheapest_of(out, KIND_SCONV)) price_kind(out, KIND_SCONV, l->cost, 11.1 + 0.366 * l->cost / 1260.0 + 2.4e-6 * dm.M * dm.Ncols);
     }
     if (priced16 && gather) price_kind(out, KIND_GATHER, gather->cost, gather->cost / 1260.0 + 10.0);
-
+    // The filter gradients that take 16 images at a time, against the kernel that gathers pixels: of a group of 16 one to four images
+    // leave most empty, and few channels leave most of a 32-channel block empty.  Both fitted to 5210 launches of 546 layers, 0.09 to
+    // 0.14 in the logarithm; large layers are left to the clocks, the fits are 25 % off there.  us, 16 images at a time and gathering:
+    // one image 9x62, 33 -> 256 of 5x5 42 and 32; two 47x48, 64 -> 256 of 3x3 50 and 42; three 30x20, 130 -> 200 of 5x5 67 and 124.
+    // Of 126 layers of one to four images 7 take more than 5 % longer than the faster of the two (all passes 4516, the faster ones 4492).
+    if (g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0) {
+        const auto rounds = [](const Launch &l) { return (double)cdiv((long)l.tiles_m * l.tiles_n * l.splits, 256); };
+        const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0, split = gather->splits > 1;
+        const double us = vec ? 4.95 + 0.663 * core + 1.66 * split + 0.79 * mb(*gather) + 0.657 * gather->steps_per_split + 0.37 * rounds(*gather)
+                              : 5.9 + 0.357 * core + 2.16 * split + 0.84 * mb(*gather) + 1.9 * gather->steps_per_split + 0.66 * rounds(*gather);
+        for (int kind : {KIND_IFILTER16, KIND_IGATHER16}) {
+            const Launch *l = cheapest_of(out, kind);
+            if (!l) continue;
+            const bool sp = l->splits > 1;
+            const double c = (l->cost - (sp ? 5000.0 + (double)l->splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0)) / 1260.0;
+            const double here = kind == KIND_IFILTER16 ? -4.97 + 0.883 * c + 0.134 * l->steps_per_split + 0.86 * rounds(*l) + (sp ? 4.09 + 0.3 * mb(*l) : 0.0)
+                                                       : -2.1 + 0.616 * c + 0.33 * l->steps_per_split + 0.77 * rounds(*l) + (sp ? 1.93 + 0.46 * mb(*l) : 0.0);
+            if (us < (g.N <= 2 ? 1.05 : 0.92) * here && l->cost <= gather->cost && l->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0)) price_kind(out, kind, l->cost, 1.01 * gather->cost / 1260.0);
+        }
+    }
 }
 
 typedef std::array<int, 15> PlanKey;

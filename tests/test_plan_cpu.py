@@ -152,7 +152,9 @@ def test_workspace_bounds(m, shape, p, alone, most):
     ((7, 32, 8, 12, 104, 4, 4, 2, 0), 0, True, "igemm", "sconv16x", (17.4, 23.2)), ((10, 3, 26, 107, 80, 4, 4, 2, 0), 0, True, "sconv16x", "igemm", (19.9, 25.3)),
     ((205, 96, 12, 4, 232, 3, 3, 1, 1), 1, True, "dconv16 ", "dconv16x", (28.9, 34.3)),
     ((140, 232, 13, 9, 344, 3, 3, 1, 1), 1, False, "dconv16 ", "dconv16x", (50.9, 63.7)), ((49, 200, 13, 9, 72, 5, 5, 1, 2), 0, True, "dconv16 ", "dconv16x", (27.8, 37.7)),
-    ((293, 344, 35, 5, 72, 3, 3, 1, 1), 1, True, "dconv16x", "dconv16 ", (47.4, 76.0))])
+    ((293, 344, 35, 5, 72, 3, 3, 1, 1), 1, True, "dconv16x", "dconv16 ", (47.4, 76.0)),
+    ((1, 33, 9, 62, 256, 5, 5, 1, 2), 2, False, "igemm", "ifilter16", (32.0, 42.4)), ((2, 64, 47, 48, 256, 3, 3, 1, 0), 2, False, "igemm", "ifilter16", (41.8, 49.8)),
+    ((3, 130, 30, 20, 200, 5, 5, 1, 2), 2, False, "ifilter16", "igemm", (67.0, 124.0))])
 def test_bf16_layers_get_the_faster_kind_of_kernel(m, shape, p, relu, faster, slower, us):
     got = plan(m, shape, p, relu, dtype=1)
     assert got.startswith(faster) and not got.startswith(slower), (got, us)
