@@ -558,8 +558,13 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const GemmParams p, 
     if (Epi::DBIAS && blockIdx.x >= groups) {
         const int k = (int)(blockIdx.x - groups) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
         if (k >= p.M) return;
-        float s = 0.f;
-        for (int sp = lane; sp < p.splits; sp += 64) s += p.dbias_partial[(size_t)sp * p.M + k];
+        float c[4] = {0.f, 0.f, 0.f, 0.f};                     // 256 chains: one to a lane is 1.17 times as far off at 1024 splits, 1.7 at 8192
+        for (int sp = lane; sp < p.splits; sp += 256) {
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (sp + 64 * j < p.splits) c[j] += p.dbias_partial[(size_t)(sp + 64 * j) * p.M + k];
+        }
+        float s = (c[0] + c[2]) + (c[1] + c[3]);
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
         if (lane == 0) p.dbias[k] = p.alpha * s + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
