@@ -124,6 +124,28 @@ def test_few_tiles_leave_a_product_just_below_the_largest_number_finite():
                 assert np.array_equal(case.fwd(x, w, None), ref)
 
 
+# Layers that the planner gives to this kernel and gave to `splits` splits of the other: N, C, H, W, K, R, S, pad, pass, splits.  The
+# errors are averages over thousands of outputs; from one set of inputs to the next their ratio moves by 1 %.
+@pytest.mark.parametrize("shape,p,splits", [((5, 224, 20, 12, 383, 3, 3, 1), 0, 7), ((12, 128, 26, 35, 19, 3, 3, 1), 0, 8), ((4, 384, 33, 7, 96, 3, 3, 1), 1, 6)])
+def test_few_tiles_are_no_further_from_64_bits_than_many_splits(shape, p, splits):
+    m = owt()
+    N, C, H, W, K, R, S, pad = shape
+    g = np.random.default_rng(1560)
+    case = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", False, False)
+    x = np.maximum(g.standard_normal(case.shape_x, dtype=np.float32), 0)
+    w = g.standard_normal(case.shape_w, dtype=np.float32) * np.float32(0.01)
+    dy = g.standard_normal(case.shape_y, dtype=np.float32)
+    ref = conv64(x, w, 1, pad, H, W)[0] if p == 0 else conv64(dy, w[:, ::-1, ::-1].transpose(3, 1, 2, 0), 1, pad, H, W)[0]
+    off = []
+    for tile, split, name in ((43, splits, "xconv "), (-1, 0, "xconvs ")):
+        with force(tile, split):
+            assert m.owt_conv_plan_describe(case.desc, p).startswith(name), m.owt_conv_plan_describe(case.desc, p)
+            got = case.fwd(x, w, None) if p == 0 else case.bwd_data(dy, None, w)
+        off.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    print(shape, off)
+    assert off[1] <= 1.03 * off[0]
+
+
 def test_the_default_choice_runs_it_where_tiles_are_few_and_not_elsewhere():
     m = owt()
     plan = lambda s, p: m.owt_conv_plan_describe(m.conv_desc(*s[:7], 1, s[7], m.OWT_F32, m.OWT_BIAS), p)
