@@ -32,9 +32,10 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
     constexpr int PU = (2 * PR + NT - 1) / NT;
     constexpr unsigned OOB = 0x80000000u;
 
-    // the groups' sums, and until the end each wavefront's sums put by (its own 16 bytes a lane, four times); the panel
-    __shared__ __attribute__((aligned(16))) uint4 lds[RED + PANEL];
-    uint4 *panel = lds + RED;
+    // the groups' sums; the panel, in the same place unless each wavefront's sums put by (its own 16 bytes a lane, four times) are in the first
+    constexpr bool PUT_LDS = MASKED && PU > 1;                                       // (16 more registers would not fit)
+    __shared__ __attribute__((aligned(16))) uint4 lds[PUT_LDS ? RED + PANEL : PANEL > RED ? PANEL : RED];
+    uint4 *panel = lds + (PUT_LDS ? RED : 0);
     float *red = (float *)lds;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -162,21 +163,30 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
     // A chain of n instructions rounds off more the longer it is, and layers that come here from many splits of xconv.hpp had short ones
     // there.  So the high parts' sums are put by at the first change of panel after kRun steps, and those sums added up.  Error of y
     // against 64 bits, xconv.hpp, one chain, this: 5 images 20x12, 224 -> 383 of 3x3 9.1e-8, 1.10e-7, 8.3e-8; 12 of 26x35, 128 -> 19 7.8e-8, 8.9e-8,
-    // 7.8e-8; none of 320 passes is off by more than with xconv.hpp now, 7 of 140 were.  After 8 steps up to 2 % slower, after 12 one pass off by 2 % more.
+    // 7.8e-8; none of 320 passes is off by more than with xconv.hpp now, 7 of 140 were.  After 12 steps one pass is off by 2 % more.  The sums in LDS
+    // instead of 16 registers: 180 passes of drawn layers 5043 us instead of 5001.
     constexpr int kRun = 10;
     float4 *mine = (float4 *)lds + wave * 256 + lane;
+    split_acc total;
+#pragma unroll
+    for (int q = 0; q < 16; q++) total[q] = 0.f;
     int since = 0;
     bool put = false;
     auto put_by = [&]() __attribute__((always_inline)) {
+        if (PUT_LDS) {
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            float4 t = put ? mine[64 * q] : make_float4(0.f, 0.f, 0.f, 0.f);
-            t.x += big[4 * q]; t.y += big[4 * q + 1]; t.z += big[4 * q + 2]; t.w += big[4 * q + 3];
-            mine[64 * q] = t;
+            for (int q = 0; q < 4; q++) {
+                float4 t = put ? mine[64 * q] : make_float4(0.f, 0.f, 0.f, 0.f);
+                t.x += big[4 * q]; t.y += big[4 * q + 1]; t.z += big[4 * q + 2]; t.w += big[4 * q + 3];
+                mine[64 * q] = t;
+            }
+            put = true;
         }
 #pragma unroll
-        for (int q = 0; q < 16; q++) big[q] = 0.f;
-        put = true;
+        for (int q = 0; q < 16; q++) {
+            if (!PUT_LDS) total[q] += big[q];
+            big[q] = 0.f;
+        }
         since = 0;
     };
     int ch = ch_beg, tap = grp;
@@ -223,13 +233,15 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
     constexpr int QN = 16 / TG;
     const int q0 = grp * QN;
     float v[QN];
-    if (put) {
+    if (PUT_LDS && put) {
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const float4 t = mine[64 * q];
-            big[4 * q] += t.x; big[4 * q + 1] += t.y; big[4 * q + 2] += t.z; big[4 * q + 3] += t.w;
+            total[4 * q] = t.x; total[4 * q + 1] = t.y; total[4 * q + 2] = t.z; total[4 * q + 3] = t.w;
         }
     }
+#pragma unroll
+    for (int q = 0; q < 16; q++) big[q] += total[q];
 #pragma unroll
     for (int half = 0; half < 2; half++) {
         __syncthreads();
