@@ -596,9 +596,15 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const GemmParams p, 
         if (SG > 1) {
             red[sg][e] = s;
             __syncthreads();
-            if (sg == 0) {
+            if (sg == 0) {                                     // in pairs: one chain of sixteen rounds off more
+                float4 t[SG];
 #pragma unroll
-                for (int j = 1; j < SG; j++) { const float4 t = red[j][e]; s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w; }
+                for (int j = 0; j < SG; j++) t[j] = red[j][e];
+#pragma unroll
+                for (int d = 1; d < SG; d *= 2)
+#pragma unroll
+                    for (int j = 0; j < SG; j += 2 * d) { t[j].x += t[j + d].x; t[j].y += t[j + d].y; t[j].z += t[j + d].z; t[j].w += t[j + d].w; }
+                s = t[0];
             }
         }
         if (sg == 0 && n > 0) {

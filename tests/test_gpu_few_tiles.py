@@ -124,8 +124,11 @@ def test_few_tiles_leave_a_product_just_below_the_largest_number_finite():
                 assert np.array_equal(case.fwd(x, w, None), ref)
 
 
-# Layers that the planner gives to this kernel and gave to `splits` splits of the other: N, C, H, W, K, R, S, pad, pass, splits.  The
-# errors are averages over thousands of outputs; from one set of inputs to the next their ratio moves by 1 %.
+# Layers that the planner gives to this kernel and gave to `splits` splits of the other: N, C, H, W, K, R, S, pad, pass, splits.
+# Bound: a rounding of the sum of i of n equal random products counts i/n, so the second layer's 72 instructions count 5 in eight
+# chains of nine and 3 in adding those up; here 6 in chains of 12, 10 and 6 and 2 in adding them up, against 10 and 2 in four chains
+# of 24 and 16.  Ratios of the roots: 1.02 here, 1.23 with four chains; 1.1 lies between, and the errors are averages over thousands of
+# outputs whose ratio moves by 1 % from one set of inputs to the next.
 @pytest.mark.parametrize("shape,p,splits", [((5, 224, 20, 12, 383, 3, 3, 1), 0, 7), ((12, 128, 26, 35, 19, 3, 3, 1), 0, 8), ((4, 384, 33, 7, 96, 3, 3, 1), 1, 6)])
 def test_few_tiles_are_no_further_from_64_bits_than_many_splits(shape, p, splits):
     m = owt()
@@ -143,7 +146,7 @@ def test_few_tiles_are_no_further_from_64_bits_than_many_splits(shape, p, splits
             got = case.fwd(x, w, None) if p == 0 else case.bwd_data(dy, None, w)
         off.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
     print(shape, off)
-    assert off[1] <= 1.03 * off[0]
+    assert off[1] <= 1.1 * off[0]
 
 
 def test_the_default_choice_runs_it_where_tiles_are_few_and_not_elsewhere():
