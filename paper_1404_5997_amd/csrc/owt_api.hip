@@ -645,6 +645,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if ((force_tile >= 0 && force_tile != kDConv16SFirstTile + v) || xr * xs < xv.TG) continue;
             const long BM = 32 * xv.WM, rows = panel_rows(g, pass, dm, BM);
             if (rows < 0 || rows > xv.prs[2]) continue;
+            if (pass == OWT_PASS_BWD_DATA && g.masked && cred % 2 && !dconv16s_masked_fits(xv, (int)rows)) continue;
             const long tm = cdiv(dm.M, BM), tn = cdiv(dm.Ncols, 32), chunks = cdiv(cred, 32);
             for (long s0 : kSplits) {
                 const long s = force_split > 0 ? (force_split < chunks ? force_split : chunks) : s0;
@@ -660,9 +661,13 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const int e = cred % 8 == 0 ? 8 : cred % 2 == 0 ? 2 : 1, mk = pass == OWT_PASS_BWD_DATA && g.masked ? 2 : 1;
                 const bool fwd = pass == OWT_PASS_FWD;
                 const double loads = (!fwd || e == 1 ? 16 : e == 2 ? 8 : 2) * (cred <= 16 ? 0.5 : 1.0), piece = (e == 8 ? 1 : e == 2 ? 4 : 8) * mk * l.pr / 64.0;
-                const long wgs = tm * tn * splits, occ = std::max(1, 16 / (xv.WM * xv.TG)), full = cdiv(wgs, 256);
+                const bool heavy = e == 1 && mk == 2 && l.pr == xv.prs[2] && xv.WM == 1;      // registers for one work-group a CU
+                const long wgs = tm * tn * splits, occ = heavy ? 1 : std::max(1, 16 / (xv.WM * xv.TG)), full = cdiv(wgs, 256);
                 const double waves = std::min(occ, full) * xv.WM * xv.TG / 4.0, rounds = (double)cdiv(wgs, 256 * occ), taps = cdiv(xr * xs, xv.TG);
                 double us = 5.15 + rounds * per * (taps * waves * (150.0 + (fwd && e < 8 ? 98.4 : 36.2) * loads) + 866.0 + 13.0 * piece * waves) / 2100.0;
+                // (values and masks one by one: wavefronts wait for a panel's loads in front of their filters, those of the smaller tiles longer.
+                // Over 164 passes of wide and of odd layers the choice takes 2512 us, 2592 without this, the fastest kernels 2428)
+                if (e == 1 && mk == 2) us = 1.1 * (us + (xv.WM == 4 ? 0.0 : rounds * per * (heavy ? 2.5 : xv.WM == 2 ? 1.0 : 0.5)));
                 if (splits > 1) us += 3.35 + 0.426 * splits * dm.M * dm.Ncols * 4e-6;
                 if (force_tile < 0 && ((best_us > 0 && us > best_us) || rounds * per * taps * waves > 96.0)) continue;
                 l.cost = 1260.0 * us;

@@ -71,6 +71,10 @@ hipError_t owt_launch_xconvs_data(int variant, int pr, const GemmParams &, hipSt
 typedef XConvSVariant DConv16SVariant;
 constexpr int kNumDConv16SVariants = 3, kDConv16SFirstTile = 92;
 constexpr DConv16SVariant kDConv16SVariants[kNumDConv16SVariants] = {{4, 4, {160, 288, 352}}, {2, 4, {96, 224, 320}}, {1, 8, {96, 192, 288}}};
+// Masked calls whose values are loaded one by one (an odd number of reduction channels) hold a panel's values and masks in twice as
+// many registers, which the widest panel of the 64-pixel tile does not leave (22 spilled): us, that tile and the 128-pixel one: 13
+// images 37x52, 11 -> 55 of 5x5 35 and 26; 5 of 24x53, 11 -> 96 18.6 and 12.8; 3 of 34x47, 131 -> 64 48 and 35.
+constexpr bool dconv16s_masked_fits(const DConv16SVariant &v, int pr) { return v.WM != 2 || pr <= v.prs[1]; }
 hipError_t owt_launch_dconv16s_fwd(int variant, int pr, const GemmParams &, hipStream_t);
 hipError_t owt_launch_dconv16s_data(int variant, int pr, const GemmParams &, hipStream_t);
 

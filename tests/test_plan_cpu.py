@@ -158,3 +158,16 @@ def test_workspace_bounds(m, shape, p, alone, most):
 def test_bf16_layers_get_the_faster_kind_of_kernel(m, shape, p, relu, faster, slower, us):
     got = plan(m, shape, p, relu, dtype=1)
     assert got.startswith(faster) and not got.startswith(slower), (got, us)
+
+
+# the widest panel of the 64-pixel tile holds the loads of a masked call with an odd number of filters in scratch memory
+@pytest.mark.parametrize("shape", [(13, 55, 37, 52, 11, 5, 5, 1, 2), (5, 96, 24, 53, 11, 5, 5, 1, 2), (3, 64, 34, 47, 131, 5, 5, 1, 2), (2, 47, 51, 45, 83, 5, 5, 1, 2)])
+def test_wide_masked_bf16_layers_of_odd_filters_stay_off_the_tile_that_spills(m, shape):
+    for tile in (-1, 93):
+        m.owt_test_force_variant(tile, 0, 0)
+        try:
+            masked, plain = plan(m, shape, 1, True, dtype=1), plan(m, shape, 1, False, dtype=1)
+        finally:
+            m.owt_test_force_variant(-1, 0, 0)
+        assert "waves2x1x4 panel320" not in masked, masked
+        assert tile < 0 or "waves2x1x4 panel320" in plain, plain
