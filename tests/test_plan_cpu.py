@@ -59,6 +59,52 @@ def test_images_that_do_not_wrap_keep_those_kernels(m):
     assert plan(m, (8, 64, 1000, 1040, 64, 3, 3, 1, 1), 2).startswith("xfilter")
 
 
+# bf16 storage: the same images in bytes with twice the channels
+@pytest.mark.parametrize("shape", WRAPPING)
+def test_large_bf16_images_stay_off_the_kernels_that_address_16_at_a_time(m, shape):
+    N, C, H, W, K, R, S, stride, pad = shape
+    shape = (N, 2 * C, H, W, 2 * K, R, S, stride, pad)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    assert wraps(N, H * W * C * 4, N * H * W * C * 4) or wraps(N, P * Q * K * 4, N * P * Q * K * 4)
+    for relu in (False, True):
+        for tile in [-1] + list(range(80, 87)) + [88, 89]:
+            m.owt_test_force_variant(tile, 0, 0)
+            try:
+                p = plan(m, shape, 2, relu, dtype=1)
+            finally:
+                m.owt_test_force_variant(-1, 0, 0)
+            assert not p.startswith(("ifilter16", "igather16", "sfilter16x")), (tile, p)
+
+
+# just below the line that such an image crosses: tile, kernel, shape
+@pytest.mark.parametrize("tile,kernel,shape", [
+    (80, "ifilter16", (8, 128, 1000, 1040, 128, 3, 3, 1, 1)), (83, "ifilter16", (1, 128, 1000, 1040, 128, 3, 3, 1, 1)), (82, "ifilter16", (17, 64, 992, 992, 8, 3, 3, 1, 1)),
+    (84, "ifilter16", (7, 37, 1100, 1300, 45, 5, 5, 1, 2)), (88, "igather16", (24, 64, 800, 860, 64, 3, 3, 1, 1)), (89, "igather16", (16, 10, 2000, 2100, 14, 3, 3, 1, 1)),
+    (89, "sfilter16x", (16, 10, 2000, 2100, 14, 3, 3, 2, 1)), (-1, "ifilter16", (8, 128, 1000, 1040, 128, 3, 3, 1, 1))])
+def test_bf16_images_that_do_not_wrap_keep_those_kernels(m, tile, kernel, shape):
+    N, C, H, W, K, R, S, stride, pad = shape
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    assert not wraps(N, H * W * C * 2, N * H * W * C * 2) and not wraps(N, P * Q * K * 2, N * P * Q * K * 2)
+    m.owt_test_force_variant(tile, 0, 0)
+    try:
+        assert plan(m, shape, 2, dtype=1).startswith(kernel), shape
+    finally:
+        m.owt_test_force_variant(-1, 0, 0)
+
+
+# the bf16 kernels with 32-bit byte offsets: tensors below 2 GB, and below 1 GB for the one of few tiles, whose partial sums take 4 bytes
+@pytest.mark.parametrize("tile,kernel,images,p", [(90, "dconv16x", 8061, 0), (90, "dconv16x", 8061, 1), (92, "dconv16s", 4030, 0), (94, "dconv16s", 4030, 1)])
+@pytest.mark.parametrize("C,K", [(37, 5), (5, 37)])
+def test_bf16_tensors_past_32_bit_offsets_stay_off_the_kernels_that_use_them(m, tile, kernel, images, p, C, K):
+    for n, takes in ((images, True), (images + 1, False)):
+        m.owt_test_force_variant(tile, 1, 0)
+        try:
+            name = plan(m, (n, C, 60, 60, K, 3, 3, 1, 1), p, dtype=1)
+        finally:
+            m.owt_test_force_variant(-1, 0, 0)
+        assert name.startswith(kernel) == takes, (n, name)
+
+
 # the 1x1 filter has no kernel but those and the gather kernel, which flag 2 (only the direct kernels) leaves out
 @pytest.mark.parametrize("tile,flags,shape", [(t, 0, (2, 32, 13, 13, 64, 3, 3, 1, 1)) for t in (40, 41, 43, 50, 61)] +
                          [(40, 2, (2, 32, 13, 13, 64, 3, 3, 1, 1)), (-1, 2, (2, 32, 13, 13, 64, 1, 1, 1, 0)), (70, 0, (20, 512, 1, 1, 64, 1, 1, 1, 0))])
