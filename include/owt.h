@@ -22,8 +22,10 @@
  *    default stream) and the call returns without waiting for it.
  *  - `ws` is caller-provided device scratch of at least the number of bytes the
  *    matching *_workspace_bytes query returns (may be NULL when that is 0).
- *    Its contents are undefined after the call.  An fp32 convolution that is
- *    given less runs on a kernel that fits, where there is one.
+ *    Its contents are undefined after the call.  A convolution that is given
+ *    less runs on a kernel that fits, where there is one.
+ *  - A bf16 tensor of an odd number of values may be read up to the end of its
+ *    last 4-byte word; what lies there has no influence.
  *  - Return value OWT_OK, or an error code; on error nothing was launched and
  *    no output was touched.  owt_last_error() gives a message for the calling
  *    thread's most recent error.
@@ -152,8 +154,9 @@ owt_status owt_conv_bwd_filter_static(const owt_conv_desc *d, const void *x, con
 size_t owt_static_scratch_bytes(void);
 
 /* Optional tuning.  Runs the kernel variants that the planner's cost model puts
- * within three times its own choice (those that split fp32 operands and their
- * reduction: twice) on the caller's buffers (three timed repetitions each, HIP
+ * within three times its own choice (those that split their reduction and either
+ * split fp32 operands or take bf16 layers of any channel counts: twice; those for
+ * layers of few tiles: 1.4 times) on the caller's buffers (three timed repetitions each, HIP
  * events on hip_stream), and remembers the fastest: later owt_conv_* calls in this
  * process with an identical descriptor use it.  Blocks until the timing is
  * done.  Buffers are those of the pass itself (others may be NULL):
@@ -272,8 +275,10 @@ const char *owt_last_error(void);
  * 22/23 the two fp32 first-layer forward / filter-gradient kernels, 24/25 the two bf16 first-layer
  * filter-gradient kernels, 30..36 the bf16 filter gradient that
  * streams its operands into LDS; fp32 with split operands on the bf16 matrix unit: 40..43 stride-1 forward /
- * backward-data and strided forward, 50/51 stride-1 filter gradient, 60/61 filter gradient of any geometry,
- * 70 the dense shard, both storage types), `splitk` > 0 forces the
+ * backward-data and strided forward, 44..46 the same for layers of few tiles, 50/51 stride-1 filter gradient,
+ * 60/61 filter gradient of any geometry; 70 the dense shard, both storage types; bf16 of any channel counts:
+ * 80..86 stride-1 filter gradient, 88/89 filter gradient of any geometry, 90 forward / backward-data and strided
+ * forward, 92..94 forward / backward-data of layers of few tiles), `splitk` > 0 forces the
  * split count of the reduction (clamped to the number of reduction steps), `flags` is a set of
  * OWT_FORCE_* bits.  While an override is active, tuned and cached plans are ignored.  The three
  * values are stored atomically, but a launch that runs concurrently with this call may see the old

@@ -9,7 +9,8 @@
 // loads its own filters, which is why layers that fill the chip stay with the other kernels; the planner's cost model draws the line.
 //
 // Measured against those kernels, us: 3 images 7x19, 160 -> 43 channels of 3x3 22.1 -> 7.5 forward, 19.3 -> 9.3 backward-data; 4 of 6x52,
-// 32 -> 172 of 5x5 26.2 -> 6.2 and 25.7 -> 15.3; all passes of 110 drawn layers under 15 GFLOP 5445 -> 4151.  What is left is latency: a
+// 32 -> 172 of 5x5 26.2 -> 6.2 and 25.7 -> 15.3; of 110 drawn layers under 15 GFLOP it takes 79 passes,
+// 1553 -> 812 (all 220 5304 -> 4548).  What is left is latency: a
 // step's panel reads and filter loads (150 clocks and 36 a load).
 #pragma once
 #include "dconv_bf16.hpp"
@@ -18,7 +19,7 @@ namespace owt {
 
 // E: elements a load may take at once (8, 2 or 1: reduction channels a multiple of it).  R * S >= TG (host-checked), at most 32 taps;
 // 32-bit byte offsets in every tensor (host-checked).
-template <class Epi, bool BWD, int WM, int TG, int PR, int E, bool MASKED>
+template <bool BWD, int WM, int TG, int PR, int E, bool MASKED>
 __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) dconv16s_kernel(const GemmParams p)
 {
     constexpr int NT = 64 * WM * TG, BM = 32 * WM, CH = 32;

@@ -19,11 +19,11 @@ static hipError_t go(const GemmParams &p, hipStream_t s)
     const dim3 grid(p.tiles_m * p.tiles_n, p.splits), block(64 * v.WM * v.TG);
 #if OWT_INST_PASS == 1
     if (p.mask) {
-        if constexpr (E > 1 || dconv16s_masked_fits(v, PR)) hipLaunchKernelGGL((dconv16s_kernel<OE, kBwd, v.WM, v.TG, PR, E, true>), grid, block, 0, s, p);
+        if constexpr (E > 1 || dconv16s_masked_fits(v, PR)) hipLaunchKernelGGL((dconv16s_kernel<kBwd, v.WM, v.TG, PR, E, true>), grid, block, 0, s, p);
         else return hipErrorInvalidValue;
     } else
 #endif
-    hipLaunchKernelGGL((dconv16s_kernel<OE, kBwd, v.WM, v.TG, PR, E, false>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((dconv16s_kernel<kBwd, v.WM, v.TG, PR, E, false>), grid, block, 0, s, p);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<OE>(p, s);
     return e;

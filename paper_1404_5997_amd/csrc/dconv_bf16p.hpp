@@ -39,13 +39,10 @@
 // 3x3 141 -> 95, 40 -> 40 5x5 62 -> 48 and 83 -> 55.  On whole chunks the 16-byte form is 5-18 % faster than this one.  Small layers are
 // bound by the chain of taps: a tap's slice is requested a tap and a half ahead, about 0.7 us a tap where few wavefronts run.
 #pragma once
-#include "ifilter16.hpp"
 #include "dconv_bf16.hpp"
 
 namespace owt {
 
-// MB = 32-pixel blocks per wavefront (4: the 512 x 64 tile, two work-groups per CU; 2: 256 x 64, fewer
-// registers, three work-groups per CU), OCC = work-groups per CU the register budget is cut for.
 enum { DP_WHOLE = 0, DP_EVEN = 1, DP_ODD = 2, DP_BLOCKS = 3 };
 
 // Filters for the modes other than DP_WHOLE: out[n][tap][c], c zero-padded to whole chunks of 32.  n is a filter in forward, an
@@ -75,6 +72,8 @@ __global__ void __launch_bounds__(256) dconv16x_pack_kernel(const uint16_t *__re
     }
 }
 
+// MB = 32-pixel blocks per wavefront (4: the 512 x 64 tile, two work-groups per CU; 2: 256 x 64, fewer
+// registers, three work-groups per CU), OCC = work-groups per CU the register budget is cut for.
 // MASKED: dy is masked by y > 0 on its way in (modes other than DP_WHOLE, which asks at run time).
 template <class Epi, bool BWD, int PR, int MB, int OCC, int LOAD = DP_WHOLE, bool MASKED = false>
 __global__ void __launch_bounds__(256, OCC) dconv16p_kernel(const GemmParams p)

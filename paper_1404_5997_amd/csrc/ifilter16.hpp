@@ -59,12 +59,6 @@ template <int B, bool PAIR> struct ImageRaw {
     }
 };
 
-__device__ __forceinline__ float sum8_bf16(uint4 q)
-{
-    return ((bf16_lo_f32(q.x) + bf16_hi_f32(q.x)) + (bf16_lo_f32(q.y) + bf16_hi_f32(q.y))) +
-           ((bf16_lo_f32(q.z) + bf16_hi_f32(q.z)) + (bf16_lo_f32(q.w) + bf16_hi_f32(q.w)));
-}
-
 // KB filter blocks x CB channel blocks x the S taps of one filter row per wavefront; ZP / XP: filters / channels in pairs.
 template <int KB, int CB, int S, bool ZP, bool XP, bool MASKED>
 __global__ void __launch_bounds__(256, ifilter16_occ(KB, CB, S)) ifilter16_kernel(const GemmParams p)

@@ -27,6 +27,11 @@ typedef float split_acc __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ float bf16_lo_f32(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float bf16_hi_f32(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
+__device__ __forceinline__ float sum8_bf16(uint4 q)
+{
+    return ((bf16_lo_f32(q.x) + bf16_hi_f32(q.x)) + (bf16_lo_f32(q.y) + bf16_hi_f32(q.y))) +
+           ((bf16_lo_f32(q.z) + bf16_hi_f32(q.z)) + (bf16_lo_f32(q.w) + bf16_hi_f32(q.w)));
+}
 
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 // A result below this, and not zero, is worked out again scaled.  A larger one has lost less than 2^-24 of it to operands below

@@ -24,7 +24,7 @@ namespace owt {
 
 // VEC: panel values 16 bytes at a time (reduction channels a multiple of four).  R * S >= TG (host-checked), at most 32 taps; 32-bit byte
 // offsets in every tensor (host-checked).
-template <class Epi, bool BWD, int WM, int TG, int PR, bool VEC, bool MASKED>
+template <bool BWD, int WM, int TG, int PR, bool VEC, bool MASKED>
 __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(const GemmParams p)
 {
     constexpr int NT = 64 * WM * TG, BM = 32 * WM;

@@ -18,10 +18,10 @@ static hipError_t go(const GemmParams &p, hipStream_t s)
     constexpr XConvSVariant v = kXConvSVariants[V];
     const dim3 grid(p.tiles_m * p.tiles_n, p.splits), block(64 * v.WM * v.TG);
 #if OWT_INST_PASS == 1
-    if (p.mask) hipLaunchKernelGGL((xconvs_kernel<OE, kBwd, v.WM, v.TG, PR, VEC, true>), grid, block, 0, s, p);
+    if (p.mask) hipLaunchKernelGGL((xconvs_kernel<kBwd, v.WM, v.TG, PR, VEC, true>), grid, block, 0, s, p);
     else
 #endif
-    hipLaunchKernelGGL((xconvs_kernel<OE, kBwd, v.WM, v.TG, PR, VEC, false>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((xconvs_kernel<kBwd, v.WM, v.TG, PR, VEC, false>), grid, block, 0, s, p);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<OE>(p, s);
     return e;

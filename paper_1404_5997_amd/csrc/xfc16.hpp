@@ -8,7 +8,8 @@
 // Measured, us, one step's loads in flight and 2-byte loads of columns -> here, forward and backward: 128 x 9216 -> 512
 // 22.6, 20.9 -> 13.7, 20.2; 256 x 9216 -> 512 37.5, 35.5 -> 18.5, 30.4; 128 x 4096 -> 512 13.0, 13.5 -> 11.2, 10.8; 200 x 1024 -> 256 12.1, 8.7 -> 8.8, 7.4.
 #pragma once
-#include "ifilter16.hpp"
+#include "igemm.hpp"
+#include "split3.hpp"
 
 namespace owt {
 
