@@ -155,8 +155,9 @@ size_t owt_static_scratch_bytes(void);
 
 /* Optional tuning.  Runs the kernel variants that the planner's cost model puts
  * within three times its own choice (those that split their reduction and either
- * split fp32 operands or take bf16 layers of any channel counts: twice; those for
- * layers of few tiles: 1.4 times) on the caller's buffers (three timed repetitions each, HIP
+ * split fp32 operands or take bf16 layers of any channel counts: twice; bf16
+ * kernels whose modelled cost is fitted to timed launches: 1.6 times; those for
+ * layers of few tiles: 1.4) on the caller's buffers (three timed repetitions each, HIP
  * events on hip_stream), and remembers the fastest: later owt_conv_* calls in this
  * process with an identical descriptor use it.  Blocks until the timing is
  * done.  Buffers are those of the pass itself (others may be NULL):

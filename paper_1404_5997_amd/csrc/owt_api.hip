@@ -352,6 +352,7 @@ struct Launch {
     size_t partial_bytes, dbias_bytes;
     size_t pre_bytes;   // workspace in front of the partials (re-laid-out filters of the bf16 backward-data kernel)
     double cost;   // model estimate, ~clocks
+    bool fitted;   // ... 1260 times the microseconds that timed launches of the kind take, launch and latency included
     size_t ws_bytes() const { return pre_bytes + partial_bytes + dbias_bytes; }
 };
 
@@ -410,7 +411,7 @@ static double conv16_us(const Launch &l, int pass, const Geom &g, const PassDims
 static void price_kind(std::vector<Launch> &out, int kind, double clocks_of_cheapest, double us)
 {
     for (Launch &l : out)
-        if (l.kind == kind) l.cost += 1260.0 * us - clocks_of_cheapest;
+        if (l.kind == kind) { l.cost += 1260.0 * us - clocks_of_cheapest; l.fitted = true; }
 }
 static const Launch *cheapest_of(const std::vector<Launch> &out, int kind)
 {
@@ -619,6 +620,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     double rounds, resident;
                     wg_rounds(tm * tn * splits, 2, rounds, resident);
                     const double outs = dm.M * dm.Ncols * (dm.Ncols % 2 ? 4e-6 : 2e-6);
+                    l.fitted = true;
                     l.cost = 1260.0 * (15.3 + 0.355 * xr * xs * per * rounds + 0.44 * per * l.pr / 64.0 * resident + (splits > 1 ? 0.6 + 0.85 * splits * dm.M * dm.Ncols * 4e-6 : 0.535 * outs));
                 }
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
@@ -630,7 +632,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     }
     const bool priced16 = g.bf16 && pass != OWT_PASS_BWD_FILTER && !blocks && !whole && (g.H > 1 || g.W > 1);
     if (priced16)
-        for (Launch &l : out) l.cost = 1260.0 * conv16_us(l, pass, g, dm);
+        for (Launch &l : out) { l.cost = 1260.0 * conv16_us(l, pass, g, dm); l.fitted = true; }
     // bf16 layers of few tiles.  They ask for the scratch of the kernel above, so that a call that brings less is served as it was
     // before there were either.  Layers that the pipelined kernel takes whole keep it (11.1 us against 5.8 for 2 images of 17x16, 64 ->
     // 32): sums in another order round a few bf16 activations the other way, and in a network of a few images one of them moves a
@@ -733,6 +735,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             // One work-group a CU (its LDS): the launches and the filter bank, and a unit of four rows what its reduction and its band take
             // (fitted to 83 launches, 0.11 in the logarithm).  Two work-groups a CU go one after the other and load the bank twice: 128
             // images of 224x224 to 96 filters of 11x11 66 us with 256 work-groups, 76 with 512; 39 of 192x192 to 64 21.5 and 29.4.
+            l.fitted = true;
             l.cost = 1260.0 * cdiv(ktiles * n, 256) * (8.7 + 0.0065 * s16g.KSLOTS + per * (2.17 + 0.003 * s16g.KSLOTS + 5.0e-5 * s16g.ROWS * g.W * g.C));
             bool dup = false;
             for (const Launch &o : out) dup |= o.kind == l.kind && o.tiles_n == l.tiles_n;
@@ -1166,7 +1169,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             const double c = (l->cost - (sp ? 5000.0 + (double)l->splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0)) / 1260.0;
             const double here = kind == KIND_IFILTER16 ? -4.97 + 0.883 * c + 0.134 * l->steps_per_split + 0.86 * rounds(*l) + (sp ? 4.09 + 0.3 * mb(*l) : 0.0)
                                                        : -2.1 + 0.616 * c + 0.33 * l->steps_per_split + 0.77 * rounds(*l) + (sp ? 1.93 + 0.46 * mb(*l) : 0.0);
-            if (us < (g.N <= 2 ? 1.05 : 0.92) * here && l->cost <= gather->cost && l->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0)) price_kind(out, kind, l->cost, 1.01 * gather->cost / 1260.0);
+            if (us < (g.N <= 2 ? 1.05 : 0.92) * here && l->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0))      // (tuning times its nearest few)
+                price_kind(out, kind, l->cost, std::max(l->cost, 1.54 * gather->cost) / 1260.0);
         }
     }
 }
@@ -1242,11 +1246,13 @@ static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per g
 // fp32 passes, 1.75 in 200 bf16 passes, 1.57 in 150 of shards, so three times left none out; timing every candidate of the 418
 // passes took 32.7 s, these take 5.3 s (up to four times the cheapest 6.8 s, and a training step's tuning 0.79 s instead of
 // 0.63).  Split-operand kernels that split their reduction, too, were the fastest up to 1.85
-// times: past twice they only raise the bound (the first layer's forward pass 0.3 -> 199 MB).  choose() sees every candidate.
+// times: past twice they only raise the bound (the first layer's forward pass 0.3 -> 199 MB).  Costs that have the launch in them lie
+// nearer to each other, and to the truth: of 310 bf16 passes priced so 1 loses more than 2 % with 1.6 times (none with 2, three with
+// 1.4), 1675 instead of 2918 candidates.  choose() sees every candidate.
 static bool worth_timing(const Launch &l, double least)
 {
     if (l.kind == KIND_XCONVS || l.kind == KIND_DIRECT16S) return l.cost <= 1.4 * least;      // (three tiles, up to eight splits; modelled to 0.14-0.17 in the logarithm)
-    return l.cost <= (is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 3.0) * least;
+    return l.cost <= (l.fitted ? 1.6 : is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 3.0) * least;
 }
 static bool worth_workspace(const Launch &l, double least) { return !is_split_kind(l.kind) || l.splits == 1 || worth_timing(l, least); }
 static double least_cost(const std::vector<Launch> &c)
