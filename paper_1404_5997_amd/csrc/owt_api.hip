@@ -407,6 +407,9 @@ static double conv16_us(const Launch &l, int pass, const Geom &g, const PassDims
     return l.cost / 1260.0 + 10.0;                       // the kernels on the fp32 instruction
 }
 
+// The weight of a chain of matrix instructions in the choice of splits of the bf16 filter gradient over images.
+static double ifilter16_chain(int positions) { return 1.0 + std::min(400, std::max(0, positions - 40)) / 500.0; }
+
 // Adds the same to the cost of every launch of a kind, so that the cheapest of them costs `us` microseconds.
 static void price_kind(std::vector<Launch> &out, int kind, double clocks_of_cheapest, double us)
 {
@@ -1020,6 +1023,9 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
                 l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
                 if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
+                // Long chains of positions round off more, and over 105 drawn layers this is the faster choice, too: 4357 us, 4579 without, the
+                // fastest launches 3973; dw of 578 images 10x31, 10 -> 448 took 190 us and was off by 1.9e-7 with 64 splits, 148 and 1.6e-7 with 96.
+                l.cost *= ifilter16_chain((int)per);
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1156,7 +1162,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // leave most empty, and few channels leave most of a 32-channel block empty.  Both fitted to 5210 launches of 546 layers, 0.09 to
     // 0.14 in the logarithm; large layers are left to the clocks, the fits are 25 % off there.  us, 16 images at a time and gathering:
     // one image 9x62, 33 -> 256 of 5x5 42 and 32; two 47x48, 64 -> 256 of 3x3 50 and 42; three 30x20, 130 -> 200 of 5x5 67 and 124.
-    // Of 126 layers of one to four images 7 take more than 5 % longer than the faster of the two (all passes 4516, the faster ones 4492).
+    // Of 140 layers of one to four images 4 take more than 5 % longer than gathering (14 before); all 5868 us gathering, 4651 here.
     if (g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0) {
         const auto rounds = [](const Launch &l) { return (double)cdiv((long)l.tiles_m * l.tiles_n * l.splits, 256); };
         const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0, split = gather->splits > 1;
@@ -1166,7 +1172,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             const Launch *l = cheapest_of(out, kind);
             if (!l) continue;
             const bool sp = l->splits > 1;
-            const double c = (l->cost - (sp ? 5000.0 + (double)l->splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0)) / 1260.0;
+            const double cost = kind == KIND_IFILTER16 ? l->cost / ifilter16_chain(l->steps_per_split) : l->cost;
+            const double c = (cost - (sp ? 5000.0 + (double)l->splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0)) / 1260.0;
             const double here = kind == KIND_IFILTER16 ? -4.97 + 0.883 * c + 0.134 * l->steps_per_split + 0.86 * rounds(*l) + (sp ? 4.09 + 0.3 * mb(*l) : 0.0)
                                                        : -2.1 + 0.616 * c + 0.33 * l->steps_per_split + 0.77 * rounds(*l) + (sp ? 1.93 + 0.46 * mb(*l) : 0.0);
             if (us < (g.N <= 2 ? 1.05 : 0.92) * here && l->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0))      // (tuning times its nearest few)
