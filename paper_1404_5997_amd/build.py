@@ -43,6 +43,7 @@ def _units():
     units.append(("xgather.o", "xgather_inst.hip", []))
     for masked in (0, 1):
         units.append(("ifilter16_%d.o" % masked, "ifilter16_inst.hip", ["-DOWT_INST_MASKED=%d" % masked]))
+    units.append(("ifilter16b.o", "ifilter16b_inst.hip", []))
     units.append(("xfc.o", "xfc_inst.hip", []))
     units.append(("fcgemm.o", "fcgemm_inst.hip", []))
     units.append(("dfilter2.o", "dfilter2_inst.hip", []))

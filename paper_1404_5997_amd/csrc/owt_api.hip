@@ -58,14 +58,14 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21, KIND_XCONVS = 22, KIND_DIRECT16S = 23 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21, KIND_XCONVS = 22, KIND_DIRECT16S = 23, KIND_IFILTER16B = 24 };
 
 // Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), the shard's for either storage type, and those for
 // bf16 storage of any channel count: a call whose scratch is too small for one of them is served by the kernels before them.
 static inline bool is_split_kind(int kind)
 {
     return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16 || kind == KIND_DIRECT16X ||
-           kind == KIND_IGATHER16 || kind == KIND_XCONVS || kind == KIND_DIRECT16S;
+           kind == KIND_IGATHER16 || kind == KIND_XCONVS || kind == KIND_DIRECT16S || kind == KIND_IFILTER16B;
 }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
@@ -409,6 +409,20 @@ static double conv16_us(const Launch &l, int pass, const Geom &g, const PassDims
 
 // The weight of a chain of matrix instructions in the choice of splits of the bf16 filter gradient over images.
 static double ifilter16_chain(int positions) { return 1.0 + std::min(400, std::max(0, positions - 40)) / 500.0; }
+
+// Microseconds of the bf16 filter gradient over images with streamed operands: matrix instructions at 32 clocks, a step's latency per
+// round (a row has the columns left of its first product and the rounding to whole stages for steps without any), storing the tile,
+// the reduce pass.  Fitted to 3825 timed launches of 210 layers, 0.10 in the logarithm; its choice takes 3 % longer than the fastest.
+static double ifilter16b_us(const Launch &l, const Geom &g, const PassDims &dm)
+{
+    const IFilter16bVariant &v = kIFilter16bVariants[l.tile];
+    double rounds, resident;
+    wg_rounds((long)l.tiles_m * l.tiles_n * l.splits, v.occ, rounds, resident);
+    const double per = l.steps_per_split, idle = (per / g.Q + 1.0) * (v.S - 1 + 0.5 * (v.L - 1)), blocks = v.KB * v.CB * v.S;
+    const double us = (l.splits > 1 ? 8.1 + 0.228e-6 * 4.0 * l.splits * dm.M * dm.Ncols : 5.0) + 0.97 * resident * per * blocks * v.WK * v.WC / 4.0 * 32.0 / 2100.0 +
+                      rounds * (0.129 * (per + idle) + 0.59 * blocks);
+    return (g.K <= 48 ? 1.1 : 1.0) * us;                // (tiles mostly empty: the other kinds' prices come out high there, seven of 210 layers were up to 16 % slower)
+}
 
 // Adds the same to the cost of every launch of a kind, so that the cheapest of them costs `us` microseconds.
 static void price_kind(std::vector<Launch> &out, int kind, double clocks_of_cheapest, double us)
@@ -988,6 +1002,36 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             }
         }
     }
+    // the same with the reduction over images and the operands streamed straight into LDS; one or two images, of which a group of 16 is
+    // mostly zeros, are left to the other kernels (2 images 30x22, 288 -> 488: 50 us, 29 on dfilter16b)
+    if ((force_tile >= 0 || g.N > 2) && pass == OWT_PASS_BWD_FILTER && g.bf16 && !g.masked && g.sh == 1 && g.sw == 1 && g.P <= g.H && g.C % 8 == 0 && g.K % 8 == 0 && !no_direct &&
+        !forced(OWT_FORCE_NO_BF16_MFMA) && image_groups_fit(g, false)) {
+        for (int v = 0; v < kNumIFilter16bVariants; v++) {
+            const IFilter16bVariant &iv = kIFilter16bVariants[v];
+            if ((force_tile >= 0 && force_tile != kIFilter16bFirstTile + v) || g.S != iv.S) continue;
+            const long KT = 32 * iv.KB * iv.WK, CT = 32 * iv.CB * iv.WC;
+            const long tm = cdiv(g.K, KT), ctl = cdiv(g.C, CT), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
+            for (long s0 : split_ladder(tiles, 256 * iv.occ)) {
+                long s = s0;
+                if (force_split > 0) s = force_split < steps ? force_split : steps;
+                else if (s > 1 && (steps / s < 8 || tiles * s > 2048)) break;
+                const long per = cdiv(steps, s), splits = cdiv(steps, per);
+                Launch l; memset(&l, 0, sizeof(l));
+                l.kind = KIND_IFILTER16B; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
+                l.tiles_m = (int)tm; l.tiles_n = (int)(ctl * g.R); l.ctiles = (int)ctl; l.taps = g.S; l.groups = g.R;
+                if (splits > 1) {
+                    l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
+                    l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
+                }
+                l.cost = 1260.0 * ifilter16b_us(l, g, dm);
+                l.fitted = true;
+                bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
+                for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
+                if (!dup) out.push_back(l);
+                if (force_split > 0) break;
+            }
+        }
+    }
     // bf16 storage where the kernels above are no candidates (channels or filters not in eights, rows too wide for their panels), or
     // would leave most of their 128-wide tiles empty on a large batch: the reduction over images.  Timed, us, kernels above -> this one: 419 images
     // 42x8, 32 -> 32 55 -> 36; 375 images 29x19, 64 -> 32 53 -> 41; 761 images 8x26, 96 -> 8 49 -> 39; but 43 images 17x22, 64 -> 8
@@ -1163,21 +1207,37 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // 0.14 in the logarithm; large layers are left to the clocks, the fits are 25 % off there.  us, 16 images at a time and gathering:
     // one image 9x62, 33 -> 256 of 5x5 42 and 32; two 47x48, 64 -> 256 of 3x3 50 and 42; three 30x20, 130 -> 200 of 5x5 67 and 124.
     // Of 140 layers of one to four images 4 take more than 5 % longer than gathering (14 before); all 5868 us gathering, 4651 here.
-    if (g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0) {
+    if (g.bf16 && pass == OWT_PASS_BWD_FILTER && force_tile < 0) {
         const auto rounds = [](const Launch &l) { return (double)cdiv((long)l.tiles_m * l.tiles_n * l.splits, 256); };
-        const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0, split = gather->splits > 1;
-        const double us = vec ? 4.95 + 0.663 * core + 1.66 * split + 0.79 * mb(*gather) + 0.657 * gather->steps_per_split + 0.37 * rounds(*gather)
-                              : 5.9 + 0.357 * core + 2.16 * split + 0.84 * mb(*gather) + 1.9 * gather->steps_per_split + 0.66 * rounds(*gather);
-        for (int kind : {KIND_IFILTER16, KIND_IGATHER16}) {
-            const Launch *l = cheapest_of(out, kind);
-            if (!l) continue;
-            const bool sp = l->splits > 1;
-            const double cost = kind == KIND_IFILTER16 ? l->cost / ifilter16_chain(l->steps_per_split) : l->cost;
-            const double c = (cost - (sp ? 5000.0 + (double)l->splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0)) / 1260.0;
-            const double here = kind == KIND_IFILTER16 ? -4.97 + 0.883 * c + 0.134 * l->steps_per_split + 0.86 * rounds(*l) + (sp ? 4.09 + 0.3 * mb(*l) : 0.0)
-                                                       : -2.1 + 0.616 * c + 0.33 * l->steps_per_split + 0.77 * rounds(*l) + (sp ? 1.93 + 0.46 * mb(*l) : 0.0);
-            if (us < (g.N <= 2 ? 1.05 : 0.92) * here && l->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0))      // (tuning times its nearest few)
-                price_kind(out, kind, l->cost, std::max(l->cost, 1.54 * gather->cost) / 1260.0);
+        const auto gather_us = [&](const Launch &l) {
+            const double core = (l.cost - reduce_clocks(l)) / 1260.0, split = l.splits > 1;
+            return vec ? 4.95 + 0.663 * core + 1.66 * split + 0.79 * mb(l) + 0.657 * l.steps_per_split + 0.37 * rounds(l)
+                       : 5.9 + 0.357 * core + 2.16 * split + 0.84 * mb(l) + 1.9 * l.steps_per_split + 0.66 * rounds(l);
+        };
+        const auto images_us = [&](const Launch &l) {
+            const bool sp = l.splits > 1;
+            const double cost = l.kind == KIND_IFILTER16 ? l.cost / ifilter16_chain(l.steps_per_split) : l.cost;
+            const double c = (cost - (sp ? 5000.0 + (double)l.splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0)) / 1260.0;
+            return l.kind == KIND_IFILTER16 ? -4.97 + 0.883 * c + 0.134 * l.steps_per_split + 0.86 * rounds(l) + (sp ? 4.09 + 0.3 * mb(l) : 0.0)
+                                            : -2.1 + 0.616 * c + 0.33 * l.steps_per_split + 0.77 * rounds(l) + (sp ? 1.93 + 0.46 * mb(l) : 0.0);
+        };
+        if (cheapest_of(out, KIND_IFILTER16B)) {
+            // beside the kernel that streams its operands every kind is priced (dfilter16 and dfilter16b fitted to 97 launches, 0.07 and
+            // 0.08 in the logarithm).  It is the slower one for one to four images, a group of which is mostly zeros, and on large batches of
+            // few channels, where its tile is mostly empty; us, ifilter16b and the kernel before: 2 images 30x22, 288 -> 488 50 and 29; 728 of
+            // 49x14, 32 -> 32 77 and 48.  Over the 210 layers none is more than 3 % slower than before it, and all take 6398 us instead of 7900.
+            if (gather) price_kind(out, KIND_GATHER, gather->cost, gather_us(*gather));
+            if (const Launch *l = cheapest_of(out, KIND_IFILTER16)) price_kind(out, KIND_IFILTER16, l->cost, images_us(*l));
+            if (const Launch *l = cheapest_of(out, KIND_DFILTER16))
+                price_kind(out, KIND_DFILTER16, l->cost, 9.54 + 0.474 * (l->cost - reduce_clocks(*l)) / 1260.0 + 0.79 * mb(*l) + 0.276 * l->steps_per_split);
+            if (const Launch *l = cheapest_of(out, KIND_DFILTER16B))
+                price_kind(out, KIND_DFILTER16B, l->cost, 10.65 + 0.079 * (l->cost - reduce_clocks(*l)) / 1260.0 + 0.52 * mb(*l) + 1.15 * l->steps_per_split * rounds(*l));
+        } else if (gather) {
+            for (int kind : {KIND_IFILTER16, KIND_IGATHER16}) {
+                const Launch *l = cheapest_of(out, kind);
+                if (l && gather_us(*gather) < (g.N <= 2 ? 1.05 : 0.92) * images_us(*l) && l->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0))      // (tuning times its nearest few)
+                    price_kind(out, kind, l->cost, std::max(l->cost, 1.54 * gather->cost) / 1260.0);
+            }
         }
     }
 }
@@ -1259,6 +1319,7 @@ static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per g
 static bool worth_timing(const Launch &l, double least)
 {
     if (l.kind == KIND_XCONVS || l.kind == KIND_DIRECT16S) return l.cost <= 1.4 * least;      // (three tiles, up to eight splits; modelled to 0.14-0.17 in the logarithm)
+    if (l.kind == KIND_IFILTER16B) return l.cost <= 1.25 * least;
     return l.cost <= (l.fitted ? 1.6 : is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 3.0) * least;
 }
 static bool worth_workspace(const Launch &l, double least) { return !is_split_kind(l.kind) || l.splits == 1 || worth_timing(l, least); }
@@ -1377,6 +1438,9 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
         e = owt_launch_xfilter(l.tile, p, s);
     } else if (l.kind == KIND_IGATHER16) {
         e = p.mask ? owt_launch_igather16_masked(l.tile, p, s) : owt_launch_igather16(l.tile, p, s);
+    } else if (l.kind == KIND_IFILTER16B) {
+        p.ctiles = l.ctiles;
+        e = owt_launch_ifilter16b(l.tile, p, s);
     } else if (l.kind == KIND_IFILTER16) {
         p.ctiles = l.ctiles;
         e = p.mask ? owt_launch_ifilter16_masked(l.tile, p, s) : owt_launch_ifilter16(l.tile, p, s);
@@ -1459,6 +1523,12 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilter16x" : "igather16", pn[pass], ds,
                         32 * kIGather16Variants[l.tile].KB, 32 * kIGather16Variants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,
                         8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 64);
+    if (l.kind == KIND_IFILTER16B) {
+        const IFilter16bVariant &v = kIFilter16bVariants[l.tile];
+        return snprintf(buf, n, "ifilter16b %s %s tile%dx%d waves%dx%d taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.KB * v.WK,
+                        32 * v.CB * v.WC, v.WK, v.WC, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
+                        (long)owt_split_major_grid(l.tiles_m * l.tiles_n, l.splits) * 64 * v.WK * v.WC);
+    }
     if (l.kind == KIND_IFILTER16)
         return snprintf(buf, n, "ifilter16 %s %s tile%dx%d taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kIFilter16Variants[l.tile].KB, 32 * kIFilter16Variants[l.tile].CB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,

@@ -181,6 +181,15 @@ constexpr DFilter16bVariant kDFilter16bVariants[kNumDFilter16bVariants] = {
     {6, 2, 1, 5, 0, 0, 224}, {3, 2, 2, 5, 0, 0, 224}, {2, 2, 3, 5, 0, 0, 224}};
 hipError_t owt_launch_dfilter16b(int variant, const GemmParams &, hipStream_t);
 
+// The filter gradient over images with the operands streamed straight into LDS (ifilter16b_inst.hip; unmasked dz, channels and
+// filters in eights): WK x WC wavefronts of KB filter blocks x CB channel blocks of 32 x the S taps of one filter row, an LDS ring of
+// NST stages of L positions, occ work-groups per CU.  The test hook numbers these variants from kIFilter16bFirstTile.
+struct IFilter16bVariant { int KB, CB, S, WK, WC, L, NST, occ; };
+constexpr int kNumIFilter16bVariants = 7, kIFilter16bFirstTile = 100;
+constexpr IFilter16bVariant kIFilter16bVariants[kNumIFilter16bVariants] = {
+    {2, 2, 3, 4, 2, 2, 6, 1}, {2, 2, 3, 2, 4, 2, 6, 1}, {2, 1, 3, 2, 6, 2, 7, 1}, {2, 1, 3, 2, 2, 2, 6, 2}, {1, 1, 5, 6, 2, 3, 6, 1}, {1, 1, 5, 2, 2, 2, 6, 3}, {2, 1, 5, 1, 2, 2, 4, 4}};
+hipError_t owt_launch_ifilter16b(int variant, const GemmParams &, hipStream_t);
+
 // Dense GEMM kernel of the fully-connected shard (fcgemm_inst.hip; fp32 storage, reduction length a
 // multiple of 32): WM x WN wavefronts of MB x NB accumulator blocks of 32 x 32, occ work-groups per CU.
 // When the pass masks dy by y > 0 or wants the bias gradient, a small kernel first writes dz to `dz`

@@ -92,6 +92,29 @@ def test_bf16_images_that_do_not_wrap_keep_those_kernels(m, tile, kernel, shape)
         m.owt_test_force_variant(-1, 0, 0)
 
 
+# the filter gradient over images with streamed operands: the same line, on either side of it, and what it does not take
+@pytest.mark.parametrize("tile,S", [(100, 3), (103, 3), (104, 5), (106, 5)])
+def test_streamed_images_keep_to_what_they_can_address(m, tile, S):
+    def name(shape, relu=False):
+        m.owt_test_force_variant(tile, 0, 0)
+        try:
+            return plan(m, shape, 2, relu, dtype=1)
+        finally:
+            m.owt_test_force_variant(-1, 0, 0)
+    for shape in WRAPPING:
+        N, C, H, W, K, R, _, stride, pad = shape
+        assert not name((N, (2 * C + 7) // 8 * 8, H, W, (2 * K + 7) // 8 * 8, S, S, 1, S // 2)).startswith("ifilter16b"), shape
+    for shape in ((8, 128, 1000, 1040, 128), (1, 128, 1000, 1040, 128), (17, 64, 992, 992, 8)):
+        N, C, H, W, K = shape
+        assert not wraps(N, H * W * C * 2, N * H * W * C * 2) and not wraps(N, H * W * K * 2, N * H * W * K * 2)
+        assert name(shape + (S, S, 1, S // 2)).startswith("ifilter16b"), shape
+    takes = (9, 64, 20, 24, 32, S, S, 1, S // 2)
+    assert name(takes).startswith("ifilter16b")
+    for other in ((9, 60, 20, 24, 32, S, S, 1, S // 2), (9, 64, 20, 24, 36, S, S, 1, S // 2), (9, 64, 20, 24, 32, S, S, 2, S // 2)):
+        assert not name(other).startswith("ifilter16b"), other
+    assert not name(takes, relu=True).startswith("ifilter16b")
+
+
 # the bf16 kernels with 32-bit byte offsets: tensors below 2 GB, and below 1 GB for the one of few tiles, whose partial sums take 4 bytes
 @pytest.mark.parametrize("tile,kernel,images,p", [(90, "dconv16x", 8061, 0), (90, "dconv16x", 8061, 1), (92, "dconv16s", 4030, 0), (94, "dconv16s", 4030, 1)])
 @pytest.mark.parametrize("C,K", [(37, 5), (5, 37)])
