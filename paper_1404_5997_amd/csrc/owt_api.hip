@@ -424,6 +424,31 @@ static double ifilter16b_us(const Launch &l, const Geom &g, const PassDims &dm)
     return (g.K <= 48 ? 1.1 : 1.0) * us;                // (tiles mostly empty: the other kinds' prices come out high there, seven of 210 layers were up to 16 % slower)
 }
 
+// Microseconds of the fp32 filter gradients over images: a position takes a wavefront its fragments' loads and splits (a fragment of
+// masked dz half as long again), one after the other for the wavefronts of a SIMD, and a latency; rows of the walk have their first
+// columns, a launch its rounds and the tiles' stores.  Coefficients per variant, fitted to 6695 timed launches of 261 layers, 0.05 to
+// 0.08 in the logarithm; the choice by them takes 1 % longer than the fastest launches.  Long walks of xgather's two wavefronts a SIMD come
+// out low (the first layer at 128 images: 141 us, 169 to 180 measured, where 2 x 3 blocks take 154).
+struct Images32Us { double at, frag, lat, row, round, store, mb, split; };
+static const Images32Us kXFilterUs[kNumXFilterVariants] = {
+    {0.0, 0.238, 0.0, 0.149, 0.0, 1.18, 0.338, 8.94}, {0.0, 0.191, 0.231, 0.101, 0.0, 1.25, 0.325, 8.15},
+    {3.95, 0.178, 0.121, 0.153, 1.93, 0.423, 0.291, 3.44}, {0.0, 0.222, 0.147, 0.170, 0.0, 1.38, 0.385, 5.69}};
+static const Images32Us kXGatherUs[kNumXGatherVariants] = {
+    {4.92, 0.203, 0.215, 0.0, 0.0, 1.20, 0.379, 3.09}, {3.39, 0.0935, 0.543, 0.0, 0.0, 1.86, 0.433, 2.91},
+    {4.08, 0.0647, 0.799, 0.0, 0.695, 0.825, 0.428, 3.25}, {3.54, 0.0673, 0.616, 0.0, 0.729, 0.895, 0.356, 3.41}};
+static double images32_us(const Launch &l, const Images32Us &u, int TG, int occ, double frags, int cols, int blocks, const Geom &g, const PassDims &dm)
+{
+    double rounds, resident;
+    if (TG > 1) wg_rounds((long)l.tiles_m * l.tiles_n * l.splits, occ, rounds, resident);
+    else rounds = resident = (double)cdiv((long)l.tiles_m * l.tiles_n * l.splits, 1024);
+    const double pos = (double)cdiv(l.steps_per_split, TG), rows = cols * (pos / g.Q + 1.0);
+    const double walk = TG > 1 && cols == 0 && pos > 48.0 ? 1.0 + (pos - 48.0) / 400.0 : 1.0;
+    // (long chains of positions round off more: weighed a little)
+    const double chain = 1.0 + std::min(48.0, std::max(0.0, pos - 16.0)) / 400.0;
+    return chain * (u.at + walk * u.frag * resident * pos * frags + walk * u.lat * rounds * pos + u.row * resident * rows + u.round * rounds + u.store * resident * blocks +
+           (l.splits > 1 ? u.split + u.mb * 4e-6 * l.splits * dm.M * dm.Ncols : 0.0));
+}
+
 // Adds the same to the cost of every launch of a kind, so that the cheapest of them costs `us` microseconds.
 static void price_kind(std::vector<Launch> &out, int kind, double clocks_of_cheapest, double us)
 {
@@ -821,10 +846,10 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             const XFilterVariant &xv = kXFilterVariants[v];
             if ((force_tile >= 0 && force_tile != kXFilterFirstTile + v) || g.S != xv.S) continue;
             const long tm = cdiv(g.K, 32 * xv.KB), ctl = cdiv(g.C, 32), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
-            for (long s0 : split_ladder(tiles, 1024)) {
+            for (long s0 : split_ladder(tiles, xv.TG > 1 ? 512 : 1024)) {
                 long s = s0;
                 if (force_split > 0) s = force_split < steps ? force_split : steps;
-                else if (s > 1 && (steps / s < 4 || tiles * s > 4096)) break;
+                else if (s > 1 && (steps / s < 4 || tiles * s * xv.TG > 4096)) break;
                 const long per = cdiv(steps, s), splits = cdiv(steps, per);
                 Launch l; memset(&l, 0, sizeof(l));
                 l.kind = KIND_XFILTER; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
@@ -833,11 +858,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
-                // a wavefront's clocks: matrix instructions (32 each) per position, the row starts, loading and storing the
-                // tile; whole rounds of 1024 wavefronts (one per SIMD).  0.6 = the other kernels' model against their clocks
-                const double clocks = per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0;
-                l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
-                if (splits > 1) l.cost += 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+                l.cost = 1260.0 * images32_us(l, kXFilterUs[v], xv.TG, xfilter_occ(xv.KB, xv.S, xv.TG), (1.0 + xv.KB) + 0.5 * xv.KB * g.masked, xv.S, xv.KB * xv.S, g, dm);
+                l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -853,10 +875,10 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             const XGatherVariant &xv = kXGatherVariants[v];
             if (force_tile >= 0 && force_tile != kXGatherFirstTile + v) continue;
             const long tm = cdiv(g.K, 32 * xv.KB), tn = cdiv(dm.Ncols, 32 * xv.CB), tiles = tm * tn, steps = cdiv(g.N, 16) * g.P * g.Q;
-            for (long s0 : split_ladder(tiles, 1024)) {
+            for (long s0 : split_ladder(tiles, xv.TG > 1 ? 512 : 1024)) {
                 long s = s0;
                 if (force_split > 0) s = force_split < steps ? force_split : steps;
-                else if (s > 1 && (steps / s < 4 || tiles * s > 4096)) break;
+                else if (s > 1 && (steps / s < 4 || tiles * s * xv.TG > 4096)) break;
                 const long per = cdiv(steps, s), splits = cdiv(steps, per);
                 Launch l; memset(&l, 0, sizeof(l));
                 l.kind = KIND_XGATHER; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
@@ -865,10 +887,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
-                // as above; the vector instructions of a fragment take about 330 clocks
-                const double clocks = per * (330.0 * (xv.KB + xv.CB) + 100.0) + 6000.0;
-                l.cost = 0.6 * clocks * cdiv(tiles * splits, 1024);
-                if (splits > 1) l.cost += 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0;
+                l.cost = 1260.0 * images32_us(l, kXGatherUs[v], xv.TG, xv.TG > 1 ? 2 : 1, (xv.KB + xv.CB) + 0.5 * xv.KB * g.masked, 0, xv.KB * xv.CB, g, dm);
+                l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1201,6 +1221,13 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         }
         if (const Launch *l = cheapest_of(out, KIND_SCONV)) price_kind(out, KIND_SCONV, l->cost, 11.1 + 0.366 * l->cost / 1260.0 + 2.4e-6 * dm.M * dm.Ncols);
     }
+    // fp32 filter gradients: the gather kernel beside those over images, which one image leaves 15 zeros in 16 of (fitted to 160 launches,
+    // 0.09 and 0.20 in the logarithm): one image 12x17, 240 -> 224 of 5x5 34 us gathering, 73 over images.  A tenth dearer: its sums are the less exact ones
+    if (!g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0 && (cheapest_of(out, KIND_XFILTER) || cheapest_of(out, KIND_XGATHER))) {
+        const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0, split = gather->splits > 1, wgs = (double)cdiv((long)gather->tiles_m * gather->tiles_n * gather->splits, 256);
+        price_kind(out, KIND_GATHER, gather->cost, 1.1 * (vec ? 4.3 + 0.734 * core + 0.474 * mb(*gather) + 0.193 * gather->steps_per_split + 2.53 * wgs
+                                                              : 1.7 + 0.249 * core + 0.3 * split + 0.482 * mb(*gather) + 2.44 * gather->steps_per_split + 0.76 * wgs));
+    }
     if (priced16 && gather) price_kind(out, KIND_GATHER, gather->cost, gather->cost / 1260.0 + 10.0);
     // The filter gradients that take 16 images at a time, against the kernel that gathers pixels: of a group of 16 one to four images
     // leave most empty, and few channels leave most of a 32-channel block empty.  Both fitted to 5210 launches of 546 layers, 0.09 to
@@ -1514,11 +1541,11 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     if (l.kind == KIND_XGATHER)
         return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilterx" : "xgather", pn[pass], ds,
                         32 * kXGatherVariants[l.tile].KB, 32 * kXGatherVariants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,
-                        8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 64);
+                        8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 64 * kXGatherVariants[l.tile].TG);
     if (l.kind == KIND_XFILTER)
         return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
-                        8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4), 8) * 256);
+                        8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4 / kXFilterVariants[l.tile].TG), 8) * 256);
     if (l.kind == KIND_IGATHER16)
         return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilter16x" : "igather16", pn[pass], ds,
                         32 * kIGather16Variants[l.tile].KB, 32 * kIGather16Variants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,

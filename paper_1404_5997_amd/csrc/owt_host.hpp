@@ -79,19 +79,22 @@ hipError_t owt_launch_dconv16s_fwd(int variant, int pr, const GemmParams &, hipS
 hipError_t owt_launch_dconv16s_data(int variant, int pr, const GemmParams &, hipStream_t);
 
 // Stride-1 filter gradient for fp32 storage on the bf16 MFMA with split operands (xfilter_inst.hip): a wavefront holds KB
-// filter blocks of 32 x 32 channels x the S taps of a filter row, four wavefronts of neighbouring tiles to a work-group.  The
-// test hook numbers the variants from 50.
-struct XFilterVariant { int KB, S; };
-constexpr int kNumXFilterVariants = 2, kXFilterFirstTile = 50;
-constexpr XFilterVariant kXFilterVariants[kNumXFilterVariants] = {{2, 3}, {1, 5}};
+// filter blocks of 32 x 32 channels x the S taps of a filter row, four wavefronts to a work-group: of neighbouring tiles (TG = 1), or
+// of one tile, each a quarter of the work-group's positions, which add up through LDS (TG = 4).  The test hook numbers the variants
+// from 50.
+struct XFilterVariant { int KB, S, TG; };
+constexpr int kNumXFilterVariants = 4, kXFilterFirstTile = 50;
+constexpr XFilterVariant kXFilterVariants[kNumXFilterVariants] = {{2, 3, 1}, {1, 5, 1}, {1, 3, 4}, {1, 5, 4}};
+// wavefronts per SIMD that its registers are cut for
+constexpr int xfilter_occ(int KB, int S, int TG) { return TG > 1 && KB * S <= 3 ? 2 : 1; }
 hipError_t owt_launch_xfilter(int variant, const GemmParams &, hipStream_t);
 
-// Filter gradient of any geometry for fp32 storage on the bf16 MFMA with split operands (xgather_inst.hip): one wavefront
-// per work-group holds KB filter blocks x CB blocks of densely packed (r, s, c) places.  The test hook numbers the
-// variants from 60.
-struct XGatherVariant { int KB, CB; };
-constexpr int kNumXGatherVariants = 2, kXGatherFirstTile = 60;
-constexpr XGatherVariant kXGatherVariants[kNumXGatherVariants] = {{2, 3}, {1, 3}};
+// Filter gradient of any geometry for fp32 storage on the bf16 MFMA with split operands (xgather_inst.hip): a wavefront holds KB
+// filter blocks x CB blocks of densely packed (r, s, c) places, alone in its work-group or (TG = 4, two wavefronts to a SIMD) four to
+// a tile as above.  The test hook numbers the variants from 60.
+struct XGatherVariant { int KB, CB, TG; };
+constexpr int kNumXGatherVariants = 4, kXGatherFirstTile = 60;
+constexpr XGatherVariant kXGatherVariants[kNumXGatherVariants] = {{2, 3, 1}, {1, 3, 1}, {1, 3, 4}, {1, 2, 4}};
 hipError_t owt_launch_xgather(int variant, const GemmParams &, hipStream_t);
 
 // Stride-1 filter gradient for bf16 storage and any channel counts, reduction over images (ifilter16_inst.hip): a wavefront

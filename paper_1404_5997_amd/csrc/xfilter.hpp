@@ -27,6 +27,14 @@
 // those below 2^-110 lose bits, which only a result as small can show.  A wavefront whose sums are not all finite, or some
 // below kSplitTiny and not zero, starts over with scaled operands and the careful split.
 //
+// TG = 4: layers whose positions do not fill the chip with long walks.  A wavefront's position is about 29 clocks a load instruction
+// (16 to 24 of them), its splits and its products one after the other, so two wavefronts a SIMD (KB = 1, 3 taps) take less than twice
+// as long; and four that share a tile need a quarter of the partial sums for the same length of walk, which were what limited the
+// splits: 37 images 15x11, 100 -> 72, masked, 32.0 -> 23.4 us (42 splits of whole wavefronts, the fastest: 32.1); 16 images
+// 14x14, 128 -> 128 26.7 -> 17.4; 4 of 28x28, 64 -> 64 26.0 -> 16.8.  170 drawn and odd layers, with xgather's: 7397 -> 5708 us,
+// three of them more than 3 % slower (by 4 %).  At 128 images of 13x13 the two forms take the same (174 and 176).  KB = 2 (one wavefront a SIMD): 29 us
+// on the first of these.
+//
 // Measured, 128 images, with the reduce pass, kernel on the fp32 instruction -> this one, us: 3x3 192->384 252 -> 151 (190
 // TFLOP/s), 384->256 334 -> 191, 256->256 228 -> 137; 5x5 64->192 450 -> 271 (212 TFLOP/s).  Four wavefronts to a
 // work-group instead of one: 149, 188, - and 266.
@@ -34,6 +42,7 @@
 #include <type_traits>
 
 #include "igemm.hpp"
+#include "owt_host.hpp"
 #include "split3.hpp"
 
 namespace owt {
@@ -52,15 +61,15 @@ __device__ __forceinline__ bool owt_split_major_wave(int ntiles, int splits, int
     return true;
 }
 
-template <int KB, int S, bool MASKED>
-__global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
+template <int KB, int S, int TG, bool MASKED>
+__global__ void __launch_bounds__(256, xfilter_occ(KB, S, TG)) xfilter_kernel(const GemmParams p)
 {
     constexpr int M = 6 * KB * S;                  // matrix instructions per position
 
     const Geom &g = p.g;
-    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tile, split;
-    if (!owt_split_major_wave(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
+    if (TG > 1 ? !owt_split_major_wg(p.tiles_m * p.tiles_n, p.splits, tile, split) : !owt_split_major_wave(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
     const int kt = tile / p.tiles_n, rem = tile - kt * p.tiles_n;
     const int r = rem / p.ctiles, ct = rem - r * p.ctiles;
     const int k0 = kt * 32 * KB, c0 = ct * 32;
@@ -69,7 +78,8 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
     const int p_lo = max(0, g.ph - r), Pv = max(0, min(g.P, g.H + g.ph - r) - p_lo), Q = g.Q;
     const int groups = (g.N + 15) >> 4, total = groups * Pv * Q;
     const int per = (total + p.splits - 1) / p.splits;
-    const int o_beg = min(total, split * per), o_end = min(total, o_beg + per);
+    const int g_beg = min(total, split * per), g_end = min(total, g_beg + per), sub = (per + TG - 1) / TG;
+    const int o_beg = TG > 1 ? min(g_end, g_beg + wave * sub) : g_beg, o_end = TG > 1 ? min(g_end, o_beg + sub) : g_end;
 
     const unsigned imgx = (unsigned)(g.H * g.W * g.C) * 4u, imgz = (unsigned)(g.P * Q * g.K) * 4u;
     const unsigned xall = imgx * (unsigned)g.N, zall = imgz * (unsigned)g.N;
@@ -282,29 +292,52 @@ __global__ void __launch_bounds__(256, 1) xfilter_kernel(const GemmParams p)
     const bool part = p.splits > 1;
     float *out = part ? p.partial + (size_t)split * p.M * p.Ncols : (float *)p.out;
     const int c = c0 + li, RS = g.R * S;
-    if (c < g.C) {
+    auto store = [&](int kb, int s, int e, float v) __attribute__((always_inline)) {
+        const int k = k0 + kb * 32 + 8 * (e / 4) + 4 * lh + e % 4;
+        if (k >= g.K) return;
+        const size_t o = ((size_t)k * RS + r * S + s) * g.C + c;
+        if (part) out[o] = v;
+        else out[o] = p.alpha * v + (p.beta != 0.f ? p.beta * out[o] : 0.f);
+    };
+    auto store_db = [&](int kb, float v) __attribute__((always_inline)) {
+        const int k = k0 + kb * 32 + li;
+        if (lh || k >= g.K) return;
+        if (part) p.dbias_partial[(size_t)split * p.M + k] = v;
+        else p.dbias[k] = p.alpha * v + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
+    };
+    if constexpr (TG == 1) {
+        if (c < g.C) {
+#pragma unroll
+            for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+                for (int s = 0; s < S; s++)
+#pragma unroll
+                    for (int e = 0; e < 16; e++) store(kb, s, e, (big[kb][s][e] + small[kb][s][e]) * unscale);
+        }
+        if (do_db) {
+#pragma unroll
+            for (int kb = 0; kb < KB; kb++) store_db(kb, db[kb] + __shfl_xor(db[kb], 32));
+        }
+    } else {
+        // the wavefronts' sums, added in pairs
+        constexpr int V = KB * S * 16;
+        __shared__ float red[TG * (V + KB) * 64];
+        float *mine = red + wave * (V + KB) * 64 + lane;
 #pragma unroll
         for (int kb = 0; kb < KB; kb++)
 #pragma unroll
             for (int s = 0; s < S; s++)
 #pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    const int k = k0 + kb * 32 + 8 * (e / 4) + 4 * lh + e % 4;
-                    if (k >= g.K) continue;
-                    const size_t o = ((size_t)k * RS + r * S + s) * g.C + c;
-                    const float v = (big[kb][s][e] + small[kb][s][e]) * unscale;
-                    if (part) out[o] = v;
-                    else out[o] = p.alpha * v + (p.beta != 0.f ? p.beta * out[o] : 0.f);
-                }
-    }
-    if (do_db) {
+                for (int e = 0; e < 16; e++) mine[((kb * S + s) * 16 + e) * 64] = (big[kb][s][e] + small[kb][s][e]) * unscale;
 #pragma unroll
-        for (int kb = 0; kb < KB; kb++) {
-            const float v = db[kb] + __shfl_xor(db[kb], 32);
-            const int k = k0 + kb * 32 + li;
-            if (lh || k >= g.K) continue;
-            if (part) p.dbias_partial[(size_t)split * p.M + k] = v;
-            else p.dbias[k] = p.alpha * v + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
+        for (int kb = 0; kb < KB; kb++) mine[(V + kb) * 64] = db[kb] + __shfl_xor(db[kb], 32);
+        __syncthreads();
+        static_assert(TG == 4, "four wavefronts' sums in two pairs");
+        for (int v = wave; v < V + KB; v += TG) {
+            const float *at = red + v * 64 + lane;
+            const float sum = (at[0] + at[(V + KB) * 64]) + (at[2 * (V + KB) * 64] + at[3 * (V + KB) * 64]);
+            if (v >= V) { if (do_db) store_db(v - V, sum); }
+            else if (c < g.C) store(v / (S * 16), v / 16 % S, v % 16, sum);
         }
     }
 }

@@ -10,7 +10,9 @@
 // splits KB + CB fragments per position for 6 * KB * CB matrix instructions: at 2 x 3 the vector instructions take longer
 // than the matrix instructions they are issued between.
 //
-// Loads run two positions ahead (one was 3 us slower, and 2 x 4 blocks with one 4 us).
+// Loads run two positions ahead (one was 3 us slower, and 2 x 4 blocks with one 4 us).  Where four wavefronts share a tile (TG = 4,
+// as in xfilter.hpp), one position ahead, which leaves room for two wavefronts a SIMD: 8 images 32x32x3 -> 16, 5x5, masked 14.2 -> 10.9
+// us, 32x64 tiles; 3 images 224x224x3 -> 48, 11x11 stride 4 40 -> 31.  Long walks stay with 2 x 3 blocks (below: 154 us against 169).
 //
 // Measured, first layer (128 images, 224x224x3 -> 64, 11x11 stride 4) with the reduce pass: 159 us on the fp32 instruction,
 // 144 here (125 TFLOP/s); four wavefronts to a work-group, which helps xfilter.hpp by 2 %, cost small layers 2 us and won
@@ -22,20 +24,23 @@
 
 namespace owt {
 
-template <int KB, int CB, bool MASKED>
-__global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
+template <int KB, int CB, int TG, bool MASKED>
+__global__ void __launch_bounds__(64 * TG, TG > 1 ? 2 : 1) xgather_kernel(const GemmParams p)
 {
     constexpr int M = 6 * KB * CB, F = KB + CB;    // matrix instructions and fragments per position
+    constexpr int SETS = TG > 1 ? 1 : 2;           // positions whose loads are in flight; two wavefronts a SIMD have registers for one
 
     const Geom &g = p.g;
-    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5, wave = TG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     int tile, split;
     if (!owt_split_major_wg(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
     const int kt = tile / p.tiles_n, ct = tile - kt * p.tiles_n;
     const int k0 = kt * 32 * KB, j0 = ct * 32 * CB;
 
     const int P = g.P, Q = g.Q, total = ((g.N + 15) >> 4) * P * Q;
-    const int o_beg = min(total, split * p.ksteps_per_split), o_end = min(total, o_beg + p.ksteps_per_split);
+    // the work-group's positions, and this wavefront's part of them
+    const int g_beg = min(total, split * p.ksteps_per_split), g_end = min(total, g_beg + p.ksteps_per_split), sub = (p.ksteps_per_split + TG - 1) / TG;
+    const int o_beg = min(g_end, g_beg + wave * sub), o_end = min(g_end, o_beg + sub);
 
     const unsigned imgx = (unsigned)(g.H * g.W * g.C) * 4u, imgz = (unsigned)(P * Q * g.K) * 4u;
     // what must read as zero gets an offset of xall or zall, the end of its tensor; with the scalar part added it stays below
@@ -103,7 +108,7 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
             pp = image_end ? 0 : (row_end ? pp + 1 : pp);
             n0 = image_end ? n0 + 16 : n0;
         };
-        float xr[2][CB][8], zr[2][KB][8], yr[2][MASKED ? KB : 1][8];     // two positions in flight
+        float xr[SETS][CB][8], zr[SETS][KB][8], yr[SETS][MASKED ? KB : 1][8];
         auto load = [&](int set, int f) __attribute__((always_inline)) {
             if (f < CB) {
 #pragma unroll
@@ -152,25 +157,25 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
         split_frag az[KB][3], bx[CB][3];
         aim();
 #pragma unroll
-        for (int f = 0; f < F; f++) load(0, f);
-        aim();
+        for (int set = 0; set < SETS; set++) {
 #pragma unroll
-        for (int f = 0; f < F; f++) load(1, f);
-        aim();
+            for (int f = 0; f < F; f++) load(set, f);
+            aim();
+        }
 #pragma unroll
         for (int f = 0; f < F; f++) { split_f(0, f, az, bx); load(0, f); }
         aim();
         // (past the walk's end a position's operands are zeros: the second of the last pair may be one)
-        for (int i = o_beg; i < o_end; i += 2) {
+        for (int i = o_beg; i < o_end; i += SETS) {
 #pragma unroll
-            for (int u = 0; u < 2; u++) {
+            for (int u = 0; u < SETS; u++) {
                 // the products of position i + u, one phase per fragment of position i + u + 1: its vector instructions are
-                // spread between the phase's matrix instructions, then its raw registers are loaded for position i + u + 3
+                // spread between the phase's matrix instructions, then its raw registers are loaded for position i + u + 1 + SETS
                 split_frag nz[KB][3], nx[CB][3];
 #pragma unroll
                 for (int f = 0; f < F; f++) {
-                    split_f(u ^ 1, f, nz, nx);
-                    load(u ^ 1, f);
+                    split_f((u + 1) % SETS, f, nz, nx);
+                    load((u + 1) % SETS, f);
                     constexpr int PH = M / F;
 #pragma unroll
                     for (int q = f * PH; q < (f == F - 1 ? M : (f + 1) * PH); q++) {
@@ -197,7 +202,7 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
 #pragma unroll
                     for (int e = 0; e < 3; e++) bx[cb][e] = nx[cb][e];
             }
-            if (DB && (((i - o_beg) & 14) == 14 || i + 2 >= o_end)) {
+            if (DB && (((i - o_beg) & (16 - SETS)) == 16 - SETS || i + SETS >= o_end)) {
 #pragma unroll
                 for (int kb = 0; kb < KB; kb++) { db[kb] += run_db[kb]; run_db[kb] = 0.f; }
             }
@@ -245,30 +250,50 @@ __global__ void __launch_bounds__(64, 1) xgather_kernel(const GemmParams p)
     // register e of lane (li, lh): filter 8*(e/4) + 4*lh + e%4 of its block, place li
     const bool part = p.splits > 1;
     float *out = part ? p.partial + (size_t)split * p.M * p.Ncols : (float *)p.out;
+    auto store = [&](int kb, int cb, int e, float v) __attribute__((always_inline)) {
+        const int j = j0 + cb * 32 + li, k = k0 + kb * 32 + 8 * (e / 4) + 4 * lh + e % 4;
+        if (j >= p.Ncols || k >= g.K) return;
+        const size_t at = (size_t)k * p.Ncols + j;
+        if (part) out[at] = v;
+        else out[at] = p.alpha * v + (p.beta != 0.f ? p.beta * out[at] : 0.f);
+    };
+    auto store_db = [&](int kb, float v) __attribute__((always_inline)) {
+        const int k = k0 + kb * 32 + li;
+        if (lh || k >= g.K) return;
+        if (part) p.dbias_partial[(size_t)split * p.M + k] = v;
+        else p.dbias[k] = p.alpha * v + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
+    };
+    if constexpr (TG == 1) {
 #pragma unroll
-    for (int cb = 0; cb < CB; cb++) {
-        const int j = j0 + cb * 32 + li;
-        if (j >= p.Ncols) continue;
+        for (int cb = 0; cb < CB; cb++)
 #pragma unroll
-        for (int kb = 0; kb < KB; kb++)
+            for (int kb = 0; kb < KB; kb++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int k = k0 + kb * 32 + 8 * (e / 4) + 4 * lh + e % 4;
-                if (k >= g.K) continue;
-                const size_t at = (size_t)k * p.Ncols + j;
-                const float v = (big[kb][cb][e] + small[kb][cb][e]) * unscale;
-                if (part) out[at] = v;
-                else out[at] = p.alpha * v + (p.beta != 0.f ? p.beta * out[at] : 0.f);
-            }
-    }
-    if (do_db) {
+                for (int e = 0; e < 16; e++) store(kb, cb, e, (big[kb][cb][e] + small[kb][cb][e]) * unscale);
+        if (do_db) {
 #pragma unroll
-        for (int kb = 0; kb < KB; kb++) {
-            const float v = db[kb] + __shfl_xor(db[kb], 32);
-            const int k = k0 + kb * 32 + li;
-            if (lh || k >= g.K) continue;
-            if (part) p.dbias_partial[(size_t)split * p.M + k] = v;
-            else p.dbias[k] = p.alpha * v + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
+            for (int kb = 0; kb < KB; kb++) store_db(kb, db[kb] + __shfl_xor(db[kb], 32));
+        }
+    } else {
+        // the wavefronts' sums, added in pairs
+        constexpr int V = KB * CB * 16;
+        __shared__ float red[TG * (V + KB) * 64];
+        float *mine = red + wave * (V + KB) * 64 + lane;
+#pragma unroll
+        for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+            for (int kb = 0; kb < KB; kb++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) mine[((kb * CB + cb) * 16 + e) * 64] = (big[kb][cb][e] + small[kb][cb][e]) * unscale;
+#pragma unroll
+        for (int kb = 0; kb < KB; kb++) mine[(V + kb) * 64] = db[kb] + __shfl_xor(db[kb], 32);
+        __syncthreads();
+        static_assert(TG == 4, "four wavefronts' sums in two pairs");
+        for (int v = wave; v < V + KB; v += TG) {
+            const float *at = red + v * 64 + lane;
+            const float sum = (at[0] + at[(V + KB) * 64]) + (at[2 * (V + KB) * 64] + at[3 * (V + KB) * 64]);
+            if (v < V) store(v / (CB * 16), v / 16 % CB, v % 16, sum);
+            else if (do_db) store_db(v - V, sum);
         }
     }
 }

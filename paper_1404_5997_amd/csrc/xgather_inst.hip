@@ -9,8 +9,8 @@ static hipError_t go(const GemmParams &p, hipStream_t s)
 {
     constexpr XGatherVariant v = kXGatherVariants[V];
     const dim3 grid(owt_split_major_grid(p.tiles_m * p.tiles_n, p.splits));
-    if (p.mask) hipLaunchKernelGGL((xgather_kernel<v.KB, v.CB, true>), grid, dim3(64), 0, s, p);
-    else hipLaunchKernelGGL((xgather_kernel<v.KB, v.CB, false>), grid, dim3(64), 0, s, p);
+    if (p.mask) hipLaunchKernelGGL((xgather_kernel<v.KB, v.CB, v.TG, true>), grid, dim3(64 * v.TG), 0, s, p);
+    else hipLaunchKernelGGL((xgather_kernel<v.KB, v.CB, v.TG, false>), grid, dim3(64 * v.TG), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<EpiFilter>(p, s);
     return e;
@@ -21,6 +21,8 @@ hipError_t owt_launch_xgather(int variant, const GemmParams &p, hipStream_t s)
     switch (variant) {
     case 0: return go<0>(p, s);
     case 1: return go<1>(p, s);
+    case 2: return go<2>(p, s);
+    case 3: return go<3>(p, s);
     default: return hipErrorInvalidValue;
     }
 }

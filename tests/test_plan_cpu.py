@@ -59,6 +59,22 @@ def test_images_that_do_not_wrap_keep_those_kernels(m):
     assert plan(m, (8, 64, 1000, 1040, 64, 3, 3, 1, 1), 2).startswith("xfilter")
 
 
+# the same for the variants whose four wavefronts share a tile
+@pytest.mark.parametrize("tile", [52, 53, 62, 63])
+def test_large_images_stay_off_the_shared_tiles(m, tile):
+    for shape in WRAPPING + [(8, 64, 1000, 1040, 64, 3, 3, 1, 1), (8, 64, 1000, 1040, 64, 5, 5, 1, 2)]:
+        m.owt_test_force_variant(tile, 0, 0)
+        try:
+            p = plan(m, shape, 2)
+        finally:
+            m.owt_test_force_variant(-1, 0, 0)
+        takes = shape not in WRAPPING and (tile > 60 or shape[6] == (3 if tile == 52 else 5))
+        if not takes:
+            assert not p.startswith(("xfilter", "xgather", "sfilterx")), (shape, p)
+        elif tile < 60:                                # (xgather's line is a little lower)
+            assert p.startswith("xfilter"), (shape, p)
+
+
 # bf16 storage: the same images in bytes with twice the channels
 @pytest.mark.parametrize("shape", WRAPPING)
 def test_large_bf16_images_stay_off_the_kernels_that_address_16_at_a_time(m, shape):
