@@ -602,10 +602,12 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 // wavefronts, 34.6 against 29.8 at 112 steps, 42.1 against 37.6 at 168, while 10 % is the most that was won there.
                 const long wgs = tm * tn * splits, occ = std::max(1, 16 / (xv.WM * xv.TG)), full = cdiv(wgs, 256);
                 const double waves = std::min(occ, full) * xv.WM * xv.TG / 4.0, rounds = (double)cdiv(wgs, 256 * occ);
-                if (force_split <= 0 && force_tile < 0 && cdiv(xr * xs, xv.TG) * per * waves * rounds > 96.0) continue;
-                const double chunk = cdiv(xr * xs, xv.TG) * waves * (pass == OWT_PASS_FWD ? 367.0 : 545.0) + 1122.0 +
-                                     0.257 * l.pr * waves * (pass == OWT_PASS_BWD_DATA && g.masked ? 2.0 : 1.0);
-                l.cost = 0.6 * (rounds * per * chunk + 10900.0);
+                const long in_panel = xconvs_chunks(xv.WM, xv.TG, l.pr), panels = cdiv(per, in_panel);
+                const long steps = per / in_panel * cdiv(in_panel * xr * xs, xv.TG) + cdiv(per % in_panel * xr * xs, xv.TG);
+                if (force_split <= 0 && force_tile < 0 && steps * waves * rounds > 96.0) continue;
+                const double clocks = steps * waves * (pass == OWT_PASS_FWD ? 367.0 : 545.0) + 1122.0 * panels +
+                                      0.257 * per * l.pr * waves * (pass == OWT_PASS_BWD_DATA && g.masked ? 2.0 : 1.0);
+                l.cost = 0.6 * (rounds * clocks + 10900.0);
                 if (splits > 1) l.cost += 2770.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 933.0;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;

@@ -64,6 +64,8 @@ hipError_t owt_launch_xconv_data_vec1(int variant, int pr, const GemmParams &, v
 struct XConvSVariant { int WM, TG, prs[3]; };
 constexpr int kNumXConvSVariants = 3, kXConvSFirstTile = 44;
 constexpr XConvSVariant kXConvSVariants[kNumXConvSVariants] = {{4, 4, {160, 288, 352}}, {2, 4, {96, 224, 320}}, {1, 8, {96, 192, 288}}};
+// Chunks of 16 channels that a panel of xconvs holds: as many as leave a thread one piece of 8 channels to load
+constexpr int xconvs_chunks(int WM, int TG, int PR) { return 32 * WM * TG / PR > 1 ? 32 * WM * TG / PR : 1; }
 hipError_t owt_launch_xconvs_fwd(int variant, int pr, const GemmParams &, hipStream_t);
 hipError_t owt_launch_xconvs_data(int variant, int pr, const GemmParams &, hipStream_t);
 

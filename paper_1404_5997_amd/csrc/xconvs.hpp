@@ -9,6 +9,9 @@
 //  * a wavefront loads its filter fragments from the filters as they are, two steps ahead, and splits them itself: no
 //    launch before, no scratch, no slice in LDS and no barrier but the two that change the panel;
 //  * a wavefront owns 32 pixels x 32 filters, so layers of few filters waste less.
+//  * a panel holds as many 16-channel chunks as leave a thread one piece of it to load (two or three of the smallest panels): the
+//    groups share 18 taps, not 9, and barriers halve.  37 images 15x11, 100 -> 72 22.3 -> 20.3 us forward, 22.6 -> 20.1 backward-data;
+//    50 drawn layers 2 and 3 % on average.
 // Splitting filters per wavefront is 56 vector instructions a fragment (of 6 matrix instructions), which is why layers that fill the
 // chip stay with xconv.hpp; the planner's cost model draws the line.
 //
@@ -18,6 +21,7 @@
 // behind the other (367 clocks), the stores.
 #pragma once
 #include "igemm.hpp"
+#include "owt_host.hpp"
 #include "split3.hpp"
 
 namespace owt {
@@ -28,8 +32,9 @@ template <bool BWD, int WM, int TG, int PR, bool VEC, bool MASKED>
 __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(const GemmParams p)
 {
     constexpr int NT = 64 * WM * TG, BM = 32 * WM;
-    constexpr int PL = PR + 1, PANEL = 6 * PL, RED = TG * WM * 256;                   // 16-byte units
-    constexpr int PU = (2 * PR + NT - 1) / NT;
+    constexpr int CH = xconvs_chunks(WM, TG, PR), PC = 2 * CH;                        // 16-channel chunks in a panel, and pieces of 8 channels of a row
+    constexpr int PL = PR + 1, PANEL = 6 * CH * PL, RED = TG * WM * 256;              // 16-byte units
+    constexpr int PU = (PC * PR + NT - 1) / NT;
     constexpr unsigned OOB = 0x80000000u;
 
     // the groups' sums; the panel, in the same place unless each wavefront's sums put by (its own 16 bytes a lane, four times) are in the first
@@ -72,13 +77,13 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
         }
     }
 
-    // ---- panel: thread -> (row, 8-channel half) pairs u = tid + i * NT, as in xconv.hpp
+    // ---- panel: thread -> (row, piece of eight channels) pairs u = tid + i * NT, as in xconv.hpp
     const unsigned in_bytes = (unsigned)(p.g.N * Hi * Wi) * (unsigned)Cred * 4u;
     const __amdgpu_buffer_rsrc_t ars = owt_make_rsrc(p.a, in_bytes), mrs = owt_make_rsrc(MASKED ? p.mask : p.a, in_bytes);
     unsigned rowoff[PU];
 #pragma unroll
     for (int i = 0; i < PU; i++) {
-        const int u = tid + i * NT, row = u >> 1, pix = ps + row;
+        const int u = tid + i * NT, row = u / PC, pix = ps + row;
         rowoff[i] = row < nrows && (unsigned)pix < (unsigned)(p.g.N * Hi * Wi) ? (unsigned)pix * (unsigned)Cred * 4u : OOB;
     }
     float preg[PU][8], yreg[MASKED ? PU : 1][8];
@@ -96,9 +101,9 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
         }
     };
     auto load_panel = [&](int ch) __attribute__((always_inline)) {
-        const int c = ch * 16 + (tid & 1) * 8;
 #pragma unroll
         for (int i = 0; i < PU; i++) {
+            const int c = ch * 16 + (tid + i * NT) % PC * 8;
             load8(ars, rowoff[i], c, preg[i]);
             if (MASKED) load8(mrs, rowoff[i], c, yreg[MASKED ? i : 0]);
         }
@@ -106,7 +111,7 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
     auto store_panel = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < PU; i++) {
-            const int u = tid + i * NT, row = u >> 1, half = u & 1;
+            const int u = tid + i * NT, row = u / PC, piece = u % PC;
             if (MASKED) {
 #pragma unroll
                 for (int j = 0; j < 8; j++) preg[i][j] = yreg[MASKED ? i : 0][j] > 0.f ? preg[i][j] : 0.f;
@@ -114,7 +119,7 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
             uint4 h, m, l;
             split3_scaled(preg[i], h, m, l);
             if (row < PR) {
-                uint4 *q = panel + half * PL + row;
+                uint4 *q = panel + (piece / 2 * 6 + piece % 2) * PL + row;
                 q[0] = h; q[2 * PL] = m; q[4 * PL] = l;
             }
         }
@@ -148,14 +153,24 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
 #pragma unroll
     for (int q = 0; q < 16; q++) big[q] = small[q] = 0.f;
 
-    if (tid < 6) panel[tid * PL + PR] = make_uint4(0u, 0u, 0u, 0u);           // the row of zeros of every plane
-    const int per_chunk = (RS - grp + TG - 1) / TG;                           // this group's taps: grp, grp + TG, ...
-    const int nsteps = (ch_end - ch_beg) * per_chunk;
-    int lch = ch_beg, ltap = grp;                                             // the step whose filters are loaded next
+    if (tid < 6 * CH) panel[tid * PL + PR] = make_uint4(0u, 0u, 0u, 0u);      // the row of zeros of every plane
+    // A panel's steps are its chunks' taps one after the other, and this group's are grp, grp + TG, ...: (chunk in the panel, tap)
+    struct Step { int ch0, k, tap; };
+    auto advance = [&](Step &a) __attribute__((always_inline)) {
+        a.tap += TG;
+        if (CH == 1) {
+            if (a.tap >= RS) { a.tap = grp; a.ch0++; }
+            return;
+        }
+        if (a.tap >= RS) { a.tap -= RS; a.k++; }                              // (TG <= RS)
+        if (a.k >= min(CH, ch_end - a.ch0)) { a.ch0 += CH; a.k = 0; a.tap = grp; }
+    };
+    auto steps_of = [&](int chunks) { return (chunks * RS - grp + TG - 1) / TG; };
+    const int nch = ch_end - ch_beg, nsteps = nch / CH * steps_of(CH) + (nch % CH ? steps_of(nch % CH) : 0);
+    Step ld = {ch_beg, 0, grp};                                               // the step whose filters are loaded next
     auto load_next = [&](int u) __attribute__((always_inline)) {
-        if (lch < ch_end) load_b(lch, ltap, u);
-        ltap += TG;
-        if (ltap >= RS) { ltap = grp; lch++; }
+        if (ld.ch0 < ch_end) load_b(ld.ch0 + (CH > 1 ? ld.k : 0), ld.tap, u);
+        advance(ld);
     };
     load_panel(ch_beg);
     load_next(0);
@@ -189,21 +204,23 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
         }
         since = 0;
     };
-    int ch = ch_beg, tap = grp;
+    Step at = {ch_beg, 0, grp};
+    bool fresh = true;                                                        // the step is the first of its panel
     for (int i = 0; i < nsteps; i += 2) {
 #pragma unroll
         for (int u = 0; u < 2; u++) {
             if (i + u >= nsteps) break;
-            if (tap == grp) {                                                 // a new chunk; every wavefront comes here once a chunk
-                if (ch > ch_beg) __syncthreads();                             // everyone has its fragments of the old panel
+            const int k = CH > 1 ? at.k : 0, ch = at.ch0 + k, tap = at.tap;
+            if (fresh) {                                                      // a new panel; every wavefront comes here once a panel
+                if (at.ch0 > ch_beg) __syncthreads();                         // everyone has its fragments of the old panel
                 store_panel();
-                if (since >= kRun) put_by();
+                if (since + (CH > 1 ? steps_of(min(CH, ch_end - at.ch0)) - 3 : 0) >= kRun) put_by();
                 __syncthreads();
-                if (ch + 1 < ch_end) load_panel(ch + 1);
+                if (at.ch0 + CH < ch_end) load_panel(at.ch0 + CH);
             }
             since++;
             const int r = p.g.dS.div(tap), s = tap - r * S;
-            const uint4 *arow = panel + lh * PL + (((inside >> tap) & 1u) ? prow + r * Wi + s : PR);
+            const uint4 *arow = panel + (k * 6 + lh) * PL + (((inside >> tap) & 1u) ? prow + r * Wi + s : PR);
             split_frag a[3], f[3];
 #pragma unroll
             for (int q = 0; q < 3; q++) a[q] = __builtin_bit_cast(split_frag, arow[2 * q * PL]);
@@ -222,8 +239,9 @@ __global__ void __launch_bounds__(64 * WM * TG, TG == 8 ? 2 : 4) xconvs_kernel(c
                 split_acc &acc = e == 5 ? big : small;
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[e]], f[PB[e]], acc, 0, 0, 0);
             }
-            tap += TG;
-            if (tap >= RS) { tap = grp; ch++; }
+            const int ch0 = at.ch0;
+            advance(at);
+            fresh = at.ch0 != ch0;
         }
     }
 

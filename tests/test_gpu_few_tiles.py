@@ -157,3 +157,28 @@ def test_the_default_choice_runs_it_where_tiles_are_few_and_not_elsewhere():
         assert plan((2, 19, 19, 7, 160, 3, 3, 1), p).startswith("xconvs")
         assert plan((128, 192, 13, 13, 384, 3, 3, 1), p).startswith("xconv ")
         assert plan((128, 64, 27, 27, 192, 5, 5, 2), p).startswith("xconv ")
+
+
+# panels of two and three chunks: whole ones, a short last one of either length, a single short one, channels that end inside a chunk,
+# a panel whose taps the groups share evenly and not (N, C, H, W, K, R, S, pad; the smallest panel of each tile)
+@pytest.mark.parametrize("variant,chunks", [(0, 3), (1, 2), (2, 2)])
+@pytest.mark.parametrize("split", [1, 2])
+def test_panels_of_several_chunks(variant, chunks, split):
+    m = owt()
+    for i, (C, K) in enumerate([(16 * c - cut, 16 * (chunks + 1) - 5) for c in range(1, 2 * chunks + 2) for cut in (0, 3)]):
+        for R, S, pad in ((3, 3, 1), (2, 4, (1, 2))):
+            shape = N, _, H, W = (3, C, 7, 8)
+            shape += (K, R, S, pad)
+            x, w, b, dy, y = tensors(shape, 1580 + i)
+            case = ConvCase(N, C, H, W, K, R, S, 1, pad, "f32", True, True)
+            with force(44 + variant, split):
+                plans = [m.owt_conv_plan_describe(case.desc, p) for p in (0, 1)]
+                print("case", shape, plans)
+                sys.stdout.flush()
+                if plans[0].startswith("xconvs"):                # (eight groups want eight taps)
+                    size = oracle.conv_fwd(np.abs(x), np.abs(w), np.abs(b), 1, pad, False)
+                    check(case.fwd(x, w, b), oracle.conv_fwd(x, w, b, 1, pad, True), size, R * S * C, "y")
+                if plans[1].startswith("xconvs"):
+                    size = oracle.conv_bwd_data(np.abs(dy), np.abs(w), (H, W), 1, pad, y=y)
+                    check(case.bwd_data(dy, y, w), oracle.conv_bwd_data(dy, w, (H, W), 1, pad, y=y), size, R * S * K, "dx")
+            assert any(p.startswith("xconvs") for p in plans), plans
