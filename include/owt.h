@@ -277,7 +277,8 @@ const char *owt_last_error(void);
  * filter-gradient kernels, 30..36 the bf16 filter gradient that
  * streams its operands into LDS; fp32 with split operands on the bf16 matrix unit: 40..43 stride-1 forward /
  * backward-data and strided forward, 44..46 the same for layers of few tiles, 50..53 stride-1 filter gradient,
- * 60..63 filter gradient of any geometry; 70 the dense shard, both storage types; bf16 of any channel counts:
+ * 60..63 filter gradient of any geometry; 70 the dense shard, both storage types,
+ * 71 its forward pass in one launch; bf16 of any channel counts:
  * 80..86 stride-1 filter gradient, 88/89 filter gradient of any geometry, 90 forward / backward-data and strided
  * forward, 92..94 forward / backward-data of layers of few tiles; 100..106 the bf16 filter gradient over images
  * that streams its operands into LDS), `splitk` > 0 forces the

@@ -58,7 +58,7 @@ bool fill_geom(Geom &g, int N, int C, int H, int W, int K, int R, int S, int sh,
 // forward / backward-data, as the panel-resident kernel (dconv.hpp).  Every
 // (kernel, tile, split) that fits is a candidate; a cost model picks one unless
 // owt_conv_autotune has timed them for this descriptor.
-enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21, KIND_XCONVS = 22, KIND_DIRECT16S = 23, KIND_IFILTER16B = 24 };
+enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIND_SCONV = 4, KIND_DIRECT16 = 5, KIND_DFILTER16 = 6, KIND_SCONV16 = 7, KIND_SFILTER16 = 8, KIND_FCGEMM = 9, KIND_DFILTER2 = 10, KIND_SCONV2 = 11, KIND_SFILTER2 = 12, KIND_DFILTER16B = 13, KIND_SFILTER16B = 14, KIND_XCONV = 15, KIND_XFILTER = 16, KIND_XGATHER = 17, KIND_XFC = 18, KIND_IFILTER16 = 19, KIND_DIRECT16X = 20, KIND_IGATHER16 = 21, KIND_XCONVS = 22, KIND_DIRECT16S = 23, KIND_IFILTER16B = 24, KIND_XFCS = 25 };
 
 // Kernels that multiply fp32 operands on the bf16 matrix unit (split3.hpp), the shard's for either storage type, and those for
 // bf16 storage of any channel count: a call whose scratch is too small for one of them is served by the kernels before them.
@@ -840,6 +840,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if (force_split > 0) break;
         }
     }
+    double images_clocks = 1e30;                        // the cheapest filter gradient over images by the clocks of its matrix and vector instructions
     // fp32 storage on the bf16 matrix unit with split operands: stride 1, one wavefront per (filters, channels, filter row);
     // the bias gradient is summed by the filter row that meets every output row, which there is when P <= H
     if (pass == OWT_PASS_BWD_FILTER && !g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
@@ -860,6 +861,9 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
+                if (xv.TG == 1 && l.partial_bytes <= kMaxPartialBytes)
+                    images_clocks = std::min(images_clocks, 0.6 * (per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0) * cdiv(tiles * splits, 1024) +
+                                                                (splits > 1 ? 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0 : 0.0));
                 l.cost = 1260.0 * images32_us(l, kXFilterUs[v], xv.TG, xfilter_occ(xv.KB, xv.S, xv.TG), (1.0 + xv.KB) + 0.5 * xv.KB * g.masked, xv.S, xv.KB * xv.S, g, dm);
                 l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
@@ -889,6 +893,9 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
+                if (xv.TG == 1 && l.partial_bytes <= kMaxPartialBytes)
+                    images_clocks = std::min(images_clocks, 0.6 * (per * (330.0 * (xv.KB + xv.CB) + 100.0) + 6000.0) * cdiv(tiles * splits, 1024) +
+                                                                (splits > 1 ? 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0 : 0.0));
                 l.cost = 1260.0 * images32_us(l, kXGatherUs[v], xv.TG, xv.TG > 1 ? 2 : 1, (xv.KB + xv.CB) + 0.5 * xv.KB * g.masked, 0, xv.KB * xv.CB, g, dm);
                 l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
@@ -1189,6 +1196,24 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if (force_split > 0 || pass != OWT_PASS_FWD) break;
         }
     }
+    // its forward pass in one launch.  Microseconds of both, fitted to 132 and 147 launches of drawn shards, 0.11 in the logarithm; the other
+    // kernels' prices stay, so this one's stands to the cheapest launch above as the microseconds do.
+    const Launch *split_fc = cheapest_of(out, KIND_XFC);
+    if (plain && pass == OWT_PASS_FWD && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && (force_tile < 0 ? split_fc != nullptr : force_tile == kXFcSTile) && force_split <= 1 &&
+        (double)(g.N + 16) * g.C * 4 < 2147483647.0 && (double)(g.K + 16) * g.C * 4 < 2147483647.0) {
+        Launch l; memset(&l, 0, sizeof(l));
+        l.kind = KIND_XFCS; l.splits = 1; l.steps = l.steps_per_split = (int)cdiv(dm.Kd, 16);
+        l.tiles_m = (int)cdiv(dm.M, 16); l.tiles_n = (int)cdiv(dm.Ncols, 16);
+        const double tiles = (double)l.tiles_m * l.tiles_n, rounds = (double)cdiv((long)tiles, 256), I = 1e-3 * dm.Kd;
+        // (long reductions come out low: 48 rows of 4287 to 61 columns 11.7, 17.3 measured)
+        const double here = (g.bf16 ? 5.0 + I * (0.363 * rounds + 0.986 * tiles / 256.0) : 4.75 + I * (1.585 * rounds + 1.739 * tiles / 256.0)) * (I > (g.bf16 ? 4.5 : 3.0) ? 1.25 : 1.0);
+        l.cost = 1260.0 * here;
+        if (split_fc) {
+            const double steps = (double)cdiv(split_fc->steps_per_split, 4), sp = split_fc->splits > 1, mb = sp * split_fc->splits * dm.M * dm.Ncols * 4e-6;
+            l.cost = split_fc->cost * here / (g.bf16 ? 5.2 + 0.51 * steps + 4.34 * sp + 0.03 * mb : 4.8 + 0.676 * steps + 4.25 * sp + 0.923 * mb);
+        }
+        out.push_back(l);
+    }
     // the gather kernel is the fallback of the stride-1 forward / backward-data kernel, and an
     // alternative worth timing next to the direct filter-gradient kernel
     const bool have_direct = !out.empty() && (out[0].kind == KIND_DIRECT || out[0].kind == KIND_DIRECT16);
@@ -1224,11 +1249,16 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         if (const Launch *l = cheapest_of(out, KIND_SCONV)) price_kind(out, KIND_SCONV, l->cost, 11.1 + 0.366 * l->cost / 1260.0 + 2.4e-6 * dm.M * dm.Ncols);
     }
     // fp32 filter gradients: the gather kernel beside those over images, which one image leaves 15 zeros in 16 of (fitted to 160 launches,
-    // 0.09 and 0.20 in the logarithm): one image 12x17, 240 -> 224 of 5x5 34 us gathering, 73 over images.  A tenth dearer: its sums are the less exact ones
-    if (!g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0 && (cheapest_of(out, KIND_XFILTER) || cheapest_of(out, KIND_XGATHER))) {
+    // 0.09 and 0.20 in the logarithm): one image 12x17, 240 -> 224 of 5x5 34 us gathering, 73 over images.  Its sums are the less exact ones,
+    // so it is taken only where it is the cheaper one by clocks, too, whatever the launches take: 2 images 36x51, 281 -> 320 of 3x3 would
+    // be 100 us faster and 1.6 times as far from 64 bits.
+    const Launch *over = cheapest_of(out, KIND_XFILTER), *over2 = cheapest_of(out, KIND_XGATHER);
+    if (!over || (over2 && over2->cost < over->cost)) over = over2;
+    if (!g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0 && over) {
         const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0, split = gather->splits > 1, wgs = (double)cdiv((long)gather->tiles_m * gather->tiles_n * gather->splits, 256);
-        price_kind(out, KIND_GATHER, gather->cost, 1.1 * (vec ? 4.3 + 0.734 * core + 0.474 * mb(*gather) + 0.193 * gather->steps_per_split + 2.53 * wgs
-                                                              : 1.7 + 0.249 * core + 0.3 * split + 0.482 * mb(*gather) + 2.44 * gather->steps_per_split + 0.76 * wgs));
+        const double us = vec ? 4.3 + 0.734 * core + 0.474 * mb(*gather) + 0.193 * gather->steps_per_split + 2.53 * wgs
+                              : 1.7 + 0.249 * core + 0.3 * split + 0.482 * mb(*gather) + 2.44 * gather->steps_per_split + 0.76 * wgs;
+        price_kind(out, KIND_GATHER, gather->cost, gather->cost < images_clocks ? 1.1 * us : std::max(us, 1.7 * over->cost / 1260.0));
     }
     if (priced16 && gather) price_kind(out, KIND_GATHER, gather->cost, gather->cost / 1260.0 + 10.0);
     // The filter gradients that take 16 images at a time, against the kernel that gathers pixels: of a group of 16 one to four images
@@ -1393,7 +1423,9 @@ static owt_status launch(const Geom &g, int pass, owt_dtype dt, const PassDims &
     frame_params(g, dm, l, ws, p);
     const bool bf = dt == OWT_BF16;
     hipError_t e;
-    if (l.kind == KIND_XFC) {
+    if (l.kind == KIND_XFCS) {
+        e = owt_launch_xfcs_fwd(bf, p, s);
+    } else if (l.kind == KIND_XFC) {
         e = pass == OWT_PASS_FWD ? owt_launch_xfc_fwd(bf, p, s)
                                  : owt_launch_xfc_bwd(bf, pass == OWT_PASS_BWD_DATA ? &p : nullptr, pass == OWT_PASS_BWD_DATA ? nullptr : &p, s);
     } else if (l.kind == KIND_XCONV) {
@@ -1536,6 +1568,8 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     if (l.kind == KIND_DIRECT16X)
         return snprintf(buf, n, "%s %s %s tile256x64x32 waves4x1 panel%d splitk%d grid%dx%d threads%ld", l.blocks ? "sconv16x" : "dconv16x", pn[pass], ds, l.pr,
                         l.splits, l.tiles_m * l.tiles_n, l.splits, (long)l.tiles_m * l.tiles_n * l.splits * 256);
+    if (l.kind == KIND_XFCS)
+        return snprintf(buf, n, "xfcs %s %s tile16x16 waves16 splitk1 grid%d threads%ld", pn[pass], ds, l.tiles_m * l.tiles_n, (long)l.tiles_m * l.tiles_n * 1024);
     if (l.kind == KIND_XFC) {
         const long wgs = (long)l.tiles_m * l.tiles_n * l.splits;
         return snprintf(buf, n, "xfc %s %s tile64x64x16 splitk%d grid%ld threads%ld", pn[pass], ds, l.splits, wgs, wgs * 256);

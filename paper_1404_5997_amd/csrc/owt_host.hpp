@@ -122,6 +122,9 @@ hipError_t owt_launch_igather16_masked(int variant, const GemmParams &, hipStrea
 // for the products whose parameters are given.
 constexpr int kXFcTile = 70;
 hipError_t owt_launch_xfc_fwd(bool bf16, const GemmParams &, hipStream_t);
+// The forward pass in one launch, 16 x 16 tiles of sixteen wavefronts; test-hook number 71.
+constexpr int kXFcSTile = 71;
+hipError_t owt_launch_xfcs_fwd(bool bf16, const GemmParams &, hipStream_t);
 hipError_t owt_launch_xfc_bwd(bool bf16, const GemmParams *data, const GemmParams *filter, hipStream_t);
 
 // Panel-resident stride-1 kernels on the bf16 MFMA (dconv_bf16_inst.hip, dconv_bf16p.hpp for the 512x64 tile).  The backward-data

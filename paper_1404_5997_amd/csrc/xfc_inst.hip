@@ -1,6 +1,7 @@
 // Instantiations of the fully-connected shard's kernels on the bf16 matrix unit.
 #include "xfc.hpp"
 #include "xfc16.hpp"
+#include "xfcs.hpp"
 #include "owt_host.hpp"
 
 namespace owt {
@@ -35,6 +36,15 @@ static hipError_t bwd16(const GemmParams &pd, const GemmParams &pf, int wgs, hip
 {
     if (pf.mask) hipLaunchKernelGGL((xfc16_bwd_kernel<true, OE, IE>), dim3(wgs), dim3(256), 0, s, pd, pf);
     else hipLaunchKernelGGL((xfc16_bwd_kernel<false, OE, IE>), dim3(wgs), dim3(256), 0, s, pd, pf);
+    return hipGetLastError();
+}
+
+hipError_t owt_launch_xfcs_fwd(bool bf16, const GemmParams &p, hipStream_t s)
+{
+    const dim3 grid(p.tiles_m * p.tiles_n);
+    if (!bf16) hipLaunchKernelGGL((xfcs_fwd_kernel<float, false>), grid, dim3(1024), 0, s, p);
+    else if (p.Kd % 2) hipLaunchKernelGGL((xfcs_fwd_kernel<bf16_t, true>), grid, dim3(1024), 0, s, p);
+    else hipLaunchKernelGGL((xfcs_fwd_kernel<bf16_t, false>), grid, dim3(1024), 0, s, p);
     return hipGetLastError();
 }
 
