@@ -279,7 +279,7 @@ const char *owt_last_error(void);
  * backward-data and strided forward, 44..46 the same for layers of few tiles, 50..53 stride-1 filter gradient,
  * 60..63 filter gradient of any geometry; 70 the dense shard, both storage types,
  * 71 its forward pass in one launch; bf16 of any channel counts:
- * 80..86 stride-1 filter gradient, 88/89 filter gradient of any geometry, 90 forward / backward-data and strided
+ * 80..86 stride-1 filter gradient, 87..89 filter gradient of any geometry, 90 forward / backward-data and strided
  * forward, 92..94 forward / backward-data of layers of few tiles; 100..106 the bf16 filter gradient over images
  * that streams its operands into LDS), `splitk` > 0 forces the
  * split count of the reduction (clamped to the number of reduction steps), `flags` is a set of

@@ -4,8 +4,8 @@
 //
 // (Section 4 of the paper, backward step 2.)  As in xfilter.hpp a 16-deep matrix instruction takes 16 images at one output
 // position: a lane's eight reduction values are eight images at the same position and channel, so operands are used as they
-// are loaded, a filter tap is the neighbouring position's fragment, and there is no LDS, no barrier and no condition on
-// channel counts.  The kernels that stage pixels in LDS (dfilter_bf16.hpp, dfilter16b.hpp) move 16-byte pieces and are the
+// are loaded, a filter tap is the neighbouring position's fragment, and there is no LDS, no barrier (but at the walk's end) and no
+// condition on channel counts.  The kernels that stage pixels in LDS (dfilter_bf16.hpp, dfilter16b.hpp) move 16-byte pieces and are the
 // faster ones where channel counts are multiples of eight and a chunk's rows fit their panel; this one takes the rest, which
 // ran on the gather kernel with the fp32 instruction before.
 //  * Where a tile is two blocks of 32 channels (or filters) and their number is even, a lane loads two neighbouring channels
@@ -21,7 +21,13 @@
 // of matrix instructions, and where few wavefronts run the latency of loads, of which a wavefront can have 63 in flight.
 // (Packing and loads spread between the matrix instructions: up to 250 registers spilled, 5 % slower where none were.)
 //
-// Measured with the reduce pass, gather kernel -> this one, us: 267 images 17x24, 158 -> 32, 5x5 1553 -> 93 (296 TFLOP/s);
+// Four wavefronts of a work-group share a tile's positions and add their sums, in pairs, through LDS, a filter block by a channel block at
+// a time.  With a tile to every wavefront the partial sums were four times as many for the same length of walk, and their stores and the reduce pass
+// half of the time of layers that do not fill the chip: 127 layers that stayed with this kernel 9256 -> 8289 us, those under 30 us 0.78 of
+// before, three more than 4 % slower (by 8 % at most), error of dw 0.97 of before on average; 10 images 39x6, 68 -> 64 of 5x5 24.0 -> 17.9,
+// 126 of 37x38, 92 -> 191 of 5x5 366 -> 334.
+//
+// Measured with the reduce pass, a tile to a wavefront, gather kernel -> this one, us: 267 images 17x24, 158 -> 32, 5x5 1553 -> 93 (296 TFLOP/s);
 // 148 images 56x12, 65 -> 32, 5x5 963 -> 81; 604 images 13x16, 96 -> 10, 3x3 578 -> 48; 149 images 14x43, 32 -> 32, 3x3
 // (rows too wide for the LDS kernels) 94 -> 29; 3 images 7x13, 160 -> 14 31 -> 18; whole blocks, 256 images: 13x13 256 -> 256
 // 103 (494 TFLOP/s), 27x27 64 -> 192 5x5 187 (613), both slower than with operands streamed into LDS (dfilter16b.hpp).
@@ -59,6 +65,32 @@ template <int B, bool PAIR> struct ImageRaw {
     }
 };
 
+// A value of four wavefronts, `stride` floats apart in LDS, added in pairs.
+__device__ __forceinline__ float owt_shared_tile_sum(const float *red, int at, int stride)
+{
+    return (red[at] + red[at + stride]) + (red[at + 2 * stride] + red[at + 3 * stride]);
+}
+
+// The bias gradient of a tile's filters: a lane's half of the images, its wavefronts' positions.
+template <int KB, bool ZP>
+__device__ __forceinline__ void owt_images_db(const GemmParams &p, const float (&db)[KB], bool part, int split, int k0, int wave, float *red)
+{
+    const int lane = threadIdx.x & 63, li = lane & 31;
+    __syncthreads();                                // everyone has read the tile's sums
+#pragma unroll
+    for (int kb = 0; kb < KB; kb++) red[(wave * KB + kb) * 64 + lane] = db[kb] + __shfl_xor(db[kb], 32);
+    __syncthreads();
+    if (wave || lane >= 32) return;
+#pragma unroll
+    for (int kb = 0; kb < KB; kb++) {
+        const int k = k0 + (ZP ? 2 * li + kb : 32 * kb + li);
+        if (k >= p.g.K) continue;
+        const float v = owt_shared_tile_sum(red, kb * 64 + lane, KB * 64);
+        if (part) p.dbias_partial[(size_t)split * p.M + k] = v;
+        else p.dbias[k] = p.alpha * v + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
+    }
+}
+
 // KB filter blocks x CB channel blocks x the S taps of one filter row per wavefront; ZP / XP: filters / channels in pairs.
 template <int KB, int CB, int S, bool ZP, bool XP, bool MASKED>
 __global__ void __launch_bounds__(256, ifilter16_occ(KB, CB, S)) ifilter16_kernel(const GemmParams p)
@@ -69,9 +101,9 @@ __global__ void __launch_bounds__(256, ifilter16_occ(KB, CB, S)) ifilter16_kerne
     constexpr int AHEAD = 16 * KB * CB * S + RAW * RING + (SINGLE ? 72 : 60) > 512 / ifilter16_occ(KB, CB, S) ? RING / 2 : RING;
 
     const Geom &g = p.g;
-    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tile, split;
-    if (!owt_split_major_wave(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
+    if (!owt_split_major_wg(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
     const int kt = tile / p.tiles_n, rem = tile - kt * p.tiles_n;
     const int r = rem / p.ctiles, ct = rem - r * p.ctiles;
     const int k0 = kt * 32 * KB, c0 = ct * 32 * CB;
@@ -80,7 +112,8 @@ __global__ void __launch_bounds__(256, ifilter16_occ(KB, CB, S)) ifilter16_kerne
     const int p_lo = max(0, g.ph - r), Pv = max(0, min(g.P, g.H + g.ph - r) - p_lo), Q = g.Q;
     const int groups = (g.N + 15) >> 4, total = groups * Pv * Q;
     const int per = (total + p.splits - 1) / p.splits;
-    const int o_beg = min(total, split * per), o_end = min(total, o_beg + per);
+    const int g_beg = min(total, split * per), g_end = min(total, g_beg + per), sub = (per + 3) >> 2;
+    const int o_beg = min(g_end, g_beg + wave * sub), o_end = min(g_end, o_beg + sub);
 
     // Byte offsets.  Images past the last are past the descriptor and read as zeros (the host has checked that no offset of a
     // group of 16 wraps round); channels and filters past a ragged tile read whatever is there and only reach accumulator
@@ -195,34 +228,32 @@ __global__ void __launch_bounds__(256, ifilter16_occ(KB, CB, S)) ifilter16_kerne
     const bool part = p.splits > 1;
     float *out = part ? p.partial + (size_t)split * p.M * p.Ncols : (float *)p.out;
     const int RS = g.R * S;
+    auto store = [&](int kb, int s, int e, int c, float v) __attribute__((always_inline)) {
+        const int row = 8 * (e / 4) + 4 * lh + e % 4, k = k0 + (ZP ? 2 * row + kb : 32 * kb + row);
+        if (k >= g.K) return;
+        const size_t o = ((size_t)k * RS + r * S + s) * g.C + c;
+        if (part) out[o] = v;
+        else out[o] = p.alpha * v + (p.beta != 0.f ? p.beta * out[o] : 0.f);
+    };
+    __shared__ float red[4 * S * 16 * 64];
 #pragma unroll
     for (int cb = 0; cb < CB; cb++) {
         const int c = c0 + (XP ? 2 * li + cb : 32 * cb + li);
-        if (c >= g.C) continue;
 #pragma unroll
-        for (int kb = 0; kb < KB; kb++)
+        for (int kb = 0; kb < KB; kb++) {
+            if (cb + kb) __syncthreads();           // everyone has read the block before
 #pragma unroll
             for (int s = 0; s < S; s++)
 #pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    const int row = 8 * (e / 4) + 4 * lh + e % 4, k = k0 + (ZP ? 2 * row + kb : 32 * kb + row);
-                    if (k >= g.K) continue;
-                    const size_t o = ((size_t)k * RS + r * S + s) * g.C + c;
-                    const float v = acc[kb][cb][s][e];
-                    if (part) out[o] = v;
-                    else out[o] = p.alpha * v + (p.beta != 0.f ? p.beta * out[o] : 0.f);
-                }
-    }
-    if (do_db) {
-#pragma unroll
-        for (int kb = 0; kb < KB; kb++) {
-            const float v = db[kb] + __shfl_xor(db[kb], 32);
-            const int k = k0 + (ZP ? 2 * li + kb : 32 * kb + li);
-            if (lh || k >= g.K) continue;
-            if (part) p.dbias_partial[(size_t)split * p.M + k] = v;
-            else p.dbias[k] = p.alpha * v + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
+                for (int e = 0; e < 16; e++) red[((wave * S + s) * 16 + e) * 64 + lane] = acc[kb][cb][s][e];
+            __syncthreads();
+            for (int v = wave; v < S * 16; v += 4) {
+                const float sum = owt_shared_tile_sum(red, v * 64 + lane, S * 16 * 64);
+                if (c < g.C) store(kb, v / 16, v % 16, c, sum);
+            }
         }
     }
+    if (do_db) owt_images_db<KB, ZP>(p, db, part, split, k0, wave, red);
 }
 
 }  // namespace owt

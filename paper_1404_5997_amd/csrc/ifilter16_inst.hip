@@ -13,7 +13,7 @@ template <int V, bool ZP, bool XP>
 static hipError_t go(const GemmParams &p, hipStream_t s)
 {
     constexpr IFilter16Variant v = kIFilter16Variants[V];
-    const dim3 grid(owt_split_major_wave_grid(p.tiles_m * p.tiles_n, p.splits));
+    const dim3 grid(owt_split_major_grid(p.tiles_m * p.tiles_n, p.splits));
     hipLaunchKernelGGL((ifilter16_kernel<v.KB, v.CB, v.S, ZP, XP, OWT_INST_MASKED != 0>), grid, dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<EpiFilter>(p, s);
@@ -55,7 +55,7 @@ template <int V, bool ZP>
 static hipError_t go_any(const GemmParams &p, hipStream_t s)
 {
     constexpr IGather16Variant v = kIGather16Variants[V];
-    hipLaunchKernelGGL((igather16_kernel<v.KB, v.CB, ZP, OWT_INST_MASKED != 0>), dim3(owt_split_major_grid(p.tiles_m * p.tiles_n, p.splits)), dim3(64), 0, s, p);
+    hipLaunchKernelGGL((igather16_kernel<v.KB, v.CB, ZP, OWT_INST_MASKED != 0>), dim3(owt_split_major_grid(p.tiles_m * p.tiles_n, p.splits)), dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && p.splits > 1) e = launch_splitk_reduce<EpiFilter>(p, s);
     return e;
@@ -68,8 +68,9 @@ hipError_t owt_launch_igather16(int variant, const GemmParams &p, hipStream_t s)
 #endif
 {
     switch (variant) {
-    case 0: return p.g.K % 2 ? go_any<0, false>(p, s) : go_any<0, true>(p, s);
-    case 1: return go_any<1, false>(p, s);
+    case 0: return go_any<0, false>(p, s);
+    case 1: return p.g.K % 2 ? go_any<1, false>(p, s) : go_any<1, true>(p, s);
+    case 2: return go_any<2, false>(p, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -10,7 +10,9 @@
 // 64-filter tile spilled 56 registers and took 285 us where it takes 136).
 // Takes what the strided kernels that stage rows in LDS (sfilter_bf16.hpp, sfilter16b.hpp) do not: rows that are no multiple of
 // four values, odd filter counts, other strides and taps.
-// Measured with the reduce pass, gather kernel on the fp32 instruction -> this one, us: first layers, 332 images 179x179x3 -> 48, 11x11
+// Work-groups of four wavefronts a tile as in ifilter16.hpp; 91 layers 2113 -> 1744 us.  With them two blocks of places beside
+// three, which leave less of a tile idle.
+// Measured with the reduce pass, a tile to a wavefront, gather kernel on the fp32 instruction -> this one, us: first layers, 332 images 179x179x3 -> 48, 11x11
 // stride 4 1466 -> 136 (164 TFLOP/s), 72 images 133x133x3 -> 96, 7x7 208 -> 36, 54 images 83x83x3 -> 64 62 -> 27, 3 images 75x75x3 30 -> 13;
 // 1x1, 187 images 44x55, 21 -> 96 333 -> 58.
 #pragma once
@@ -19,19 +21,20 @@
 namespace owt {
 
 template <int KB, int CB, bool ZP, bool MASKED>
-__global__ void __launch_bounds__(64, KB == 2 && !ZP && MASKED ? 1 : 2) igather16_kernel(const GemmParams p)
+__global__ void __launch_bounds__(256, KB == 2 && !ZP && MASKED ? 1 : 2) igather16_kernel(const GemmParams p)
 {
     constexpr int AHEAD = MASKED || KB == 2 ? 2 : 4;
 
     const Geom &g = p.g;
-    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int tile, split;
     if (!owt_split_major_wg(p.tiles_m * p.tiles_n, p.splits, tile, split)) return;
     const int kt = tile / p.tiles_n, ct = tile - kt * p.tiles_n;
     const int k0 = kt * 32 * KB, j0 = ct * 32 * CB;
 
     const int P = g.P, Q = g.Q, total = ((g.N + 15) >> 4) * P * Q;
-    const int o_beg = min(total, split * p.ksteps_per_split), o_end = min(total, o_beg + p.ksteps_per_split);
+    const int per = p.ksteps_per_split, g_beg = min(total, split * per), g_end = min(total, g_beg + per), sub = (per + 3) >> 2;
+    const int o_beg = min(g_end, g_beg + wave * sub), o_end = min(g_end, o_beg + sub);
 
     // what must read as zero gets an offset of xall, the end of the tensor; with the scalar part added it stays below 2^32
     // (host-checked), as do the offsets of images past the last.  Ragged tiles: as in ifilter16.hpp.
@@ -134,32 +137,25 @@ __global__ void __launch_bounds__(64, KB == 2 && !ZP && MASKED ? 1 : 2) igather1
     // register e of lane (li, lh): row 8*(e/4) + 4*lh + e%4 of its filter block, place li of its block
     const bool part = p.splits > 1;
     float *out = part ? p.partial + (size_t)split * p.M * p.Ncols : (float *)p.out;
+    auto store = [&](int kb, int cb, int e, float v) __attribute__((always_inline)) {
+        const int row = 8 * (e / 4) + 4 * lh + e % 4, k = k0 + (ZP ? 2 * row + kb : 32 * kb + row), j = j0 + cb * 32 + li;
+        if (k >= g.K || j >= p.Ncols) return;
+        const size_t at = (size_t)k * p.Ncols + j;
+        if (part) out[at] = v;
+        else out[at] = p.alpha * v + (p.beta != 0.f ? p.beta * out[at] : 0.f);
+    };
+    __shared__ float red[4 * CB * 16 * 64];
 #pragma unroll
-    for (int cb = 0; cb < CB; cb++) {
-        const int j = j0 + cb * 32 + li;
-        if (j >= p.Ncols) continue;
+    for (int kb = 0; kb < KB; kb++) {
+        if (kb) __syncthreads();
 #pragma unroll
-        for (int kb = 0; kb < KB; kb++)
+        for (int cb = 0; cb < CB; cb++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int row = 8 * (e / 4) + 4 * lh + e % 4, k = k0 + (ZP ? 2 * row + kb : 32 * kb + row);
-                if (k >= g.K) continue;
-                const size_t at = (size_t)k * p.Ncols + j;
-                const float v = acc[kb][cb][e];
-                if (part) out[at] = v;
-                else out[at] = p.alpha * v + (p.beta != 0.f ? p.beta * out[at] : 0.f);
-            }
+            for (int e = 0; e < 16; e++) red[((wave * CB + cb) * 16 + e) * 64 + lane] = acc[kb][cb][e];
+        __syncthreads();
+        for (int v = wave; v < CB * 16; v += 4) store(kb, v / 16, v % 16, owt_shared_tile_sum(red, v * 64 + lane, CB * 16 * 64));
     }
-    if (do_db) {
-#pragma unroll
-        for (int kb = 0; kb < KB; kb++) {
-            const float v = db[kb] + __shfl_xor(db[kb], 32);
-            const int k = k0 + (ZP ? 2 * li + kb : 32 * kb + li);
-            if (lh || k >= g.K) continue;
-            if (part) p.dbias_partial[(size_t)split * p.M + k] = v;
-            else p.dbias[k] = p.alpha * v + (p.beta != 0.f ? p.beta * p.dbias[k] : 0.f);
-        }
-    }
+    if (do_db) owt_images_db<KB, ZP>(p, db, part, split, k0, wave, red);
 }
 
 }  // namespace owt

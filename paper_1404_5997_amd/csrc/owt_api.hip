@@ -407,9 +407,6 @@ static double conv16_us(const Launch &l, int pass, const Geom &g, const PassDims
     return l.cost / 1260.0 + 10.0;                       // the kernels on the fp32 instruction
 }
 
-// The weight of a chain of matrix instructions in the choice of splits of the bf16 filter gradient over images.
-static double ifilter16_chain(int positions) { return 1.0 + std::min(400, std::max(0, positions - 40)) / 500.0; }
-
 // Microseconds of the bf16 filter gradient over images with streamed operands: matrix instructions at 32 clocks, a step's latency per
 // round (a row has the columns left of its first product and the rounding to whole stages for steps without any), storing the tile,
 // the reduce pass.  Fitted to 3825 timed launches of 210 layers, 0.10 in the logarithm; its choice takes 3 % longer than the fastest.
@@ -449,6 +446,52 @@ static double images32_us(const Launch &l, const Images32Us &u, int TG, int occ,
            (l.splits > 1 ? u.split + u.mb * 4e-6 * l.splits * dm.M * dm.Ncols : 0.0));
 }
 
+// The same for bf16 storage: a column of the walk takes a wavefront 31 clocks a matrix instruction and 29 a load (`clocks`), one after the
+// other for the wavefronts of a SIMD, and a latency.  Fitted to 3029 timed launches of 130 layers, 0.06 to 0.11 in the logarithm; the choice
+// by them takes 1.5 % longer than the fastest launches.
+struct Images16Us { double at, work, lat, round, store, mb, split; };
+static const Images16Us kIFilter16Us[kNumIFilter16Variants] = {
+    {4.20, 0.400, 0.107, 0.0, 0.666, 0.292, 4.13}, {3.36, 0.404, 0.127, 2.17, 0.268, 0.402, 4.58}, {3.60, 0.369, 0.125, 2.38, 0.279, 0.437, 4.09},
+    {3.04, 0.396, 0.128, 0.0, 0.719, 0.552, 3.81}, {3.95, 0.316, 0.158, 1.62, 0.320, 0.586, 3.93}, {2.33, 0.517, 0.017, 0.0, 0.806, 0.461, 4.06},
+    {3.88, 0.448, 0.055, 0.0, 0.744, 0.625, 2.91}};
+static const Images16Us kIGather16Us[kNumIGather16Variants] = {
+    {3.25, 0.343, 0.177, 0.433, 0.919, 0.261, 3.64}, {2.24, 0.338, 0.242, 4.54, 0.130, 0.541, 3.34}, {2.72, 0.343, 0.210, 1.16, 0.787, 0.341, 3.69}};
+// Long chains of positions round off more; the weight is for the choice of splits alone.
+static double images16_chain(const Launch &l) { return 1.0 + std::min(400.0, std::max(0.0, (double)cdiv(l.steps_per_split, 4) - 40.0)) / 500.0; }
+static double images16_us(const Launch &l, const Images16Us &u, int occ, double clocks, int cols, int blocks, const Geom &g, const PassDims &dm)
+{
+    double rounds, resident;
+    wg_rounds((long)l.tiles_m * l.tiles_n * l.splits, occ, rounds, resident);
+    const double pos = (double)cdiv(l.steps_per_split, 4), columns = pos + (pos / g.Q + 1.0) * (cols - 1);
+    return images16_chain(l) * (u.at + u.work * 1e-3 * resident * columns * clocks + u.lat * rounds * columns + u.round * rounds + u.store * resident * blocks +
+           (l.splits > 1 ? u.split + u.mb * 4e-6 * l.splits * dm.M * dm.Ncols : 0.0));
+}
+
+// What decides whether a call's scratch is refused: the plans and their costs by the models that sizes have been handed out by.  Prices
+// and kernels that came later choose among the plans that fit and neither refuse a call nor take one that was refused.
+struct Demand { double cost; size_t need; bool passed_over; };      // (passed over where it does not fit: the split-operand kinds)
+
+static const size_t kMaxPartialBytes = (size_t)192 << 20;
+
+// The bf16 filter gradient over images by clocks, a tile to a wavefront: a column `least` clocks at least, 1950 a block for its
+// stores, 19000 for launch, first loads and last stores; the reduce pass 4 us and 0.24 us a MB.
+struct ImagesDemand { double cost, plain; long per, wgs, splits; size_t need; bool rows; };
+static void images16_demand(std::vector<ImagesDemand> &out, const std::vector<long> &ladder, const Geom &g, const PassDims &dm, bool want_db, long tiles, long steps, int occ,
+                            double least, double clocks, int cols, int blocks, bool rows)
+{
+    for (long s : ladder) {
+        if (s > 1 && (steps / s < 3 || tiles * s > 8192)) break;
+        const long per = cdiv(steps, s), splits = cdiv(steps, per);
+        const size_t partial = splits > 1 ? pad256((size_t)splits * dm.M * dm.Ncols * 4) : 0, need = partial + (splits > 1 && want_db ? pad256((size_t)splits * dm.M * 4) : 0);
+        if (partial > kMaxPartialBytes) continue;
+        const double resident = std::min((double)occ, std::max(1.0, tiles * splits / 1024.0)), column = std::max(least, resident * clocks);
+        const double walk = (per + (rows ? (per / g.Q + 1.0) * (cols - 1) : 0.0)) * column + 1950.0 * blocks;
+        const double plain = 0.6 * (walk * cdiv(tiles * splits, 1024L * occ) + 19000.0);
+        const double cost = plain + (splits > 1 ? 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0);
+        out.push_back({rows ? cost * (1.0 + std::min(400L, std::max(0L, per - 40)) / 500.0) : cost, plain, per, cdiv(tiles * splits, 256), splits, need, rows});
+    }
+}
+
 // Adds the same to the cost of every launch of a kind, so that the cheapest of them costs `us` microseconds.
 static void price_kind(std::vector<Launch> &out, int kind, double clocks_of_cheapest, double us)
 {
@@ -462,8 +505,6 @@ static const Launch *cheapest_of(const std::vector<Launch> &out, int kind)
         if (l.kind == kind && (!best || l.cost < best->cost)) best = &l;
     return best;
 }
-
-static const size_t kMaxPartialBytes = (size_t)192 << 20;
 
 // The filter-gradient kernels that take 16 images per matrix instruction form 32-bit byte offsets for whole groups of 16 and
 // leave it to the buffer descriptor to read the images past the last as zeros, so no offset may come round past 2^32 into the
@@ -481,7 +522,7 @@ static std::atomic<int> g_force_tile{-1}, g_force_split{-1};
 static std::atomic<unsigned> g_force_flags{0};
 static inline bool forced(unsigned bit) { return (g_force_flags.load(std::memory_order_relaxed) & bit) != 0; }
 
-static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db, std::vector<Launch> &out)
+static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db, std::vector<Launch> &out, std::vector<Demand> *demand = nullptr)
 {
     const int force_tile = g_force_tile.load(std::memory_order_relaxed);
     const int force_split = g_force_split.load(std::memory_order_relaxed);
@@ -604,11 +645,13 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 const double waves = std::min(occ, full) * xv.WM * xv.TG / 4.0, rounds = (double)cdiv(wgs, 256 * occ);
                 const long in_panel = xconvs_chunks(xv.WM, xv.TG, l.pr), panels = cdiv(per, in_panel);
                 const long steps = per / in_panel * cdiv(in_panel * xr * xs, xv.TG) + cdiv(per % in_panel * xr * xs, xv.TG);
+                const double reduce = splits > 1 ? 2770.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 933.0 : 0.0;
+                const double in_step = pass == OWT_PASS_FWD ? 367.0 : 545.0, in_row = 0.257 * l.pr * (pass == OWT_PASS_BWD_DATA && g.masked ? 2.0 : 1.0);
+                if (demand && cdiv(xr * xs, xv.TG) * per * waves * rounds <= 96.0 && l.partial_bytes <= kMaxPartialBytes)      // (a chunk to a panel)
+                    demand->push_back({0.6 * (rounds * per * (cdiv(xr * xs, xv.TG) * waves * in_step + 1122.0 + in_row * waves) + 10900.0) + reduce, l.ws_bytes(), true});
                 if (force_split <= 0 && force_tile < 0 && steps * waves * rounds > 96.0) continue;
-                const double clocks = steps * waves * (pass == OWT_PASS_FWD ? 367.0 : 545.0) + 1122.0 * panels +
-                                      0.257 * per * l.pr * waves * (pass == OWT_PASS_BWD_DATA && g.masked ? 2.0 : 1.0);
-                l.cost = 0.6 * (rounds * clocks + 10900.0);
-                if (splits > 1) l.cost += 2770.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 933.0;
+                const double clocks = steps * waves * in_step + 1122.0 * panels + in_row * per * waves;
+                l.cost = 0.6 * (rounds * clocks + 10900.0) + reduce;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -861,9 +904,12 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
-                if (xv.TG == 1 && l.partial_bytes <= kMaxPartialBytes)
-                    images_clocks = std::min(images_clocks, 0.6 * (per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0) * cdiv(tiles * splits, 1024) +
-                                                                (splits > 1 ? 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0 : 0.0));
+                if (xv.TG == 1 && l.partial_bytes <= kMaxPartialBytes) {
+                    const double clocks = 0.6 * (per * (192.0 * xv.KB * xv.S * 1.15) + (per / g.Q + 1.0) * 1600.0 + 6000.0) * cdiv(tiles * splits, 1024) +
+                                          (splits > 1 ? 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0 : 0.0);
+                    images_clocks = std::min(images_clocks, clocks);
+                    if (demand) demand->push_back({clocks, l.ws_bytes(), true});
+                }
                 l.cost = 1260.0 * images32_us(l, kXFilterUs[v], xv.TG, xfilter_occ(xv.KB, xv.S, xv.TG), (1.0 + xv.KB) + 0.5 * xv.KB * g.masked, xv.S, xv.KB * xv.S, g, dm);
                 l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
@@ -893,9 +939,12 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
-                if (xv.TG == 1 && l.partial_bytes <= kMaxPartialBytes)
-                    images_clocks = std::min(images_clocks, 0.6 * (per * (330.0 * (xv.KB + xv.CB) + 100.0) + 6000.0) * cdiv(tiles * splits, 1024) +
-                                                                (splits > 1 ? 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0 : 0.0));
+                if (xv.TG == 1 && l.partial_bytes <= kMaxPartialBytes) {
+                    const double clocks = 0.6 * (per * (330.0 * (xv.KB + xv.CB) + 100.0) + 6000.0) * cdiv(tiles * splits, 1024) +
+                                          (splits > 1 ? 6500.0 + (double)(splits + 1) * dm.M * dm.Ncols * 4.0 / 1300.0 : 0.0);
+                    images_clocks = std::min(images_clocks, clocks);
+                    if (demand) demand->push_back({clocks, l.ws_bytes(), true});
+                }
                 l.cost = 1260.0 * images32_us(l, kXGatherUs[v], xv.TG, xv.TG > 1 ? 2 : 1, (xv.KB + xv.CB) + 0.5 * xv.KB * g.masked, 0, xv.KB * xv.CB, g, dm);
                 l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
@@ -1067,18 +1116,21 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // 18 -> 22; 53 images 25x7, 64 -> 192 27 -> 30; 89 images 20x12, 32 -> 120 5x5 35 -> 42, and whole tiles half as fast.
     bool staged16 = false;
     for (const Launch &o : out) staged16 |= (o.kind == KIND_DFILTER16 || o.kind == KIND_DFILTER16B) && (g.K > 64 || g.C > 96 || g.N < 128);
+    std::vector<ImagesDemand> images16;
     if ((force_tile < 0 ? !staged16 : force_tile >= kIFilter16FirstTile && force_tile < kIGather16FirstTile) && pass == OWT_PASS_BWD_FILTER && g.bf16 && g.sh == 1 && g.sw == 1 && g.P <= g.H && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) &&
         image_groups_fit(g, false)) {
         for (int v = 0; v < kNumIFilter16Variants; v++) {
             const IFilter16Variant &iv = kIFilter16Variants[v];
             if ((force_tile >= 0 && force_tile != kIFilter16FirstTile + v) || g.S != iv.S) continue;
             const long tm = cdiv(g.K, 32 * iv.KB), ctl = cdiv(g.C, 32 * iv.CB), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
-            const long slots = 1024L * ifilter16_occ(iv.KB, iv.CB, iv.S);
-            const int zl = iv.KB == 2 && g.K % 2 ? 16 : 8, xl = iv.CB == 2 && g.C % 2 ? 16 : 8;
-            for (long s0 : split_ladder(tiles, slots)) {
+            const int occ = ifilter16_occ(iv.KB, iv.CB, iv.S), zl = iv.KB == 2 && g.K % 2 ? 16 : 8, xl = iv.CB == 2 && g.C % 2 ? 16 : 8;
+            const double column = 31.0 * iv.KB * iv.CB * iv.S + 29.0 * ((g.masked ? 2 : 1) * zl + xl);
+            if (demand)
+                images16_demand(images16, split_ladder(tiles, 1024L * occ), g, dm, want_db, tiles, steps, occ, 650.0, column, iv.S, iv.KB * iv.CB * iv.S, true);
+            for (long s0 : split_ladder(tiles, 256L * occ)) {
                 long s = s0;
                 if (force_split > 0) s = force_split < steps ? force_split : steps;
-                else if (s > 1 && (steps / s < 3 || tiles * s > 8192)) break;
+                else if (s > 1 && (steps / s < 4 || tiles * s > 2048)) break;
                 const long per = cdiv(steps, s), splits = cdiv(steps, per);
                 Launch l; memset(&l, 0, sizeof(l));
                 l.kind = KIND_IFILTER16; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
@@ -1087,18 +1139,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
-                // Fitted to 430 timed launches of 42 drawn layers (0.20 in the logarithm; its choice is 1 % slower than the fastest
-                // timed): a column takes a wavefront 31 clocks a matrix instruction and 29 a load, times the wavefronts that
-                // share a SIMD, and 650 at least (latency); 19000 for launch, first loads and last stores, 1950 a block for
-                // its stores; the reduce pass 4 us and 0.24 us a MB.
-                const double resident = std::min((double)ifilter16_occ(iv.KB, iv.CB, iv.S), std::max(1.0, tiles * splits / 1024.0));
-                const double column = std::max(650.0, resident * (31.0 * iv.KB * iv.CB * iv.S + 29.0 * ((g.masked ? 2 : 1) * zl + xl)));
-                const double clocks = (per + (per / g.Q + 1.0) * (iv.S - 1)) * column + 1950.0 * iv.KB * iv.CB * iv.S;
-                l.cost = 0.6 * (clocks * cdiv(tiles * splits, slots) + 19000.0);
-                if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
-                // Long chains of positions round off more, and over 105 drawn layers this is the faster choice, too: 4357 us, 4579 without, the
-                // fastest launches 3973; dw of 578 images 10x31, 10 -> 448 took 190 us and was off by 1.9e-7 with 64 splits, 148 and 1.6e-7 with 96.
-                l.cost *= ifilter16_chain((int)per);
+                l.cost = 1260.0 * images16_us(l, kIFilter16Us[v], occ, column, iv.S, iv.KB * iv.CB * iv.S, g, dm);
+                l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1117,11 +1159,13 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if (force_tile >= 0 && force_tile != kIGather16FirstTile + v) continue;
             const long tm = cdiv(g.K, 32 * iv.KB), tn = cdiv(dm.Ncols, 32 * iv.CB), tiles = tm * tn, steps = cdiv(g.N, 16) * g.P * g.Q;
             const int zl = (iv.KB == 2 && g.K % 2 ? 16 : 8) * (g.masked ? 2 : 1), occ = zl == 32 ? 1 : 2;
-            const long slots = 1024L * occ;
-            for (long s0 : split_ladder(tiles, slots)) {
+            const double position = 31.0 * iv.KB * iv.CB + 29.0 * (zl + 8 * iv.CB);
+            if (demand && iv.CB == 3)
+                images16_demand(images16, split_ladder(tiles, 1024L * occ), g, dm, want_db, tiles, steps, occ, 700.0, position, 1, iv.KB * iv.CB, false);
+            for (long s0 : split_ladder(tiles, 256L * occ)) {
                 long s = s0;
                 if (force_split > 0) s = force_split < steps ? force_split : steps;
-                else if (s > 1 && (steps / s < 3 || tiles * s > 8192)) break;
+                else if (s > 1 && (steps / s < 4 || tiles * s > 2048)) break;
                 const long per = cdiv(steps, s), splits = cdiv(steps, per);
                 Launch l; memset(&l, 0, sizeof(l));
                 l.kind = KIND_IGATHER16; l.tile = v; l.splits = (int)splits; l.steps = (int)steps; l.steps_per_split = (int)per;
@@ -1130,10 +1174,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                     l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
                     l.dbias_bytes = want_db ? pad256((size_t)splits * dm.M * 4) : 0;
                 }
-                const double resident = std::min((double)occ, std::max(1.0, tiles * splits / 1024.0));      // the clocks are ifilter16's
-                const double position = std::max(700.0, resident * (31.0 * iv.KB * iv.CB + 29.0 * (zl + 8 * iv.CB)));
-                l.cost = 0.6 * ((per * position + 1950.0 * iv.KB * iv.CB) * cdiv(tiles * splits, slots) + 19000.0);
-                if (splits > 1) l.cost += 5000.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 3270.0;
+                l.cost = 1260.0 * images16_us(l, kIGather16Us[v], occ, position, 1, iv.KB * iv.CB, g, dm);
+                l.fitted = true;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
@@ -1252,6 +1294,12 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // 0.09 and 0.20 in the logarithm): one image 12x17, 240 -> 224 of 5x5 34 us gathering, 73 over images.  Its sums are the less exact ones,
     // so it is taken only where it is the cheaper one by clocks, too, whatever the launches take: 2 images 36x51, 281 -> 320 of 3x3 would
     // be 100 us faster and 1.6 times as far from 64 bits.
+    if (demand && pass == OWT_PASS_BWD_FILTER) {
+        for (const Launch &l : out)
+            if (l.kind != KIND_XFILTER && l.kind != KIND_XGATHER && l.kind != KIND_IFILTER16 && l.kind != KIND_IGATHER16 && l.kind != KIND_IFILTER16B)
+                demand->push_back({l.cost, l.ws_bytes(), is_split_kind(l.kind)});
+    }
+    const double gather_clocks = gather ? gather->cost : 0.0;
     const Launch *over = cheapest_of(out, KIND_XFILTER), *over2 = cheapest_of(out, KIND_XGATHER);
     if (!over || (over2 && over2->cost < over->cost)) over = over2;
     if (!g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0 && over) {
@@ -1262,10 +1310,11 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     }
     if (priced16 && gather) price_kind(out, KIND_GATHER, gather->cost, gather->cost / 1260.0 + 10.0);
     // The filter gradients that take 16 images at a time, against the kernel that gathers pixels: of a group of 16 one to four images
-    // leave most empty, and few channels leave most of a 32-channel block empty.  Both fitted to 5210 launches of 546 layers, 0.09 to
-    // 0.14 in the logarithm; large layers are left to the clocks, the fits are 25 % off there.  us, 16 images at a time and gathering:
-    // one image 9x62, 33 -> 256 of 5x5 42 and 32; two 47x48, 64 -> 256 of 3x3 50 and 42; three 30x20, 130 -> 200 of 5x5 67 and 124.
-    // Of 140 layers of one to four images 4 take more than 5 % longer than gathering (14 before); all 5868 us gathering, 4651 here.
+    // leave most empty, and few channels leave most of a 32-channel block empty.  Gathering fitted to launches of 546 layers, 0.09 to
+    // 0.14 in the logarithm; large layers are left to the clocks, the fit is 25 % off there, and one or two images to gathering unless 16
+    // at a time are clearly the faster way.  us, 16 images at a time and gathering: one image 9x62, 33 -> 256 of 5x5 32 and 33; two
+    // 47x48, 64 -> 256 of 3x3 37 and 43; two 24x36, 39 -> 451 of 3x3 43 and 58; three 30x20, 130 -> 200 of 5x5 55 and 124.  258 layers, most of
+    // which stay with their kernel: 12315 -> 10768 us with four wavefronts to a tile, three more than 4 % slower (by 8 % at most).
     if (g.bf16 && pass == OWT_PASS_BWD_FILTER && force_tile < 0) {
         const auto rounds = [](const Launch &l) { return (double)cdiv((long)l.tiles_m * l.tiles_n * l.splits, 256); };
         const auto gather_us = [&](const Launch &l) {
@@ -1273,20 +1322,26 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             return vec ? 4.95 + 0.663 * core + 1.66 * split + 0.79 * mb(l) + 0.657 * l.steps_per_split + 0.37 * rounds(l)
                        : 5.9 + 0.357 * core + 2.16 * split + 0.84 * mb(l) + 1.9 * l.steps_per_split + 0.66 * rounds(l);
         };
-        const auto images_us = [&](const Launch &l) {
-            const bool sp = l.splits > 1;
-            const double cost = l.kind == KIND_IFILTER16 ? l.cost / ifilter16_chain(l.steps_per_split) : l.cost;
-            const double c = (cost - (sp ? 5000.0 + (double)l.splits * dm.M * dm.Ncols * 4.0 / 3270.0 : 0.0)) / 1260.0;
-            return l.kind == KIND_IFILTER16 ? -4.97 + 0.883 * c + 0.134 * l.steps_per_split + 0.86 * rounds(l) + (sp ? 4.09 + 0.3 * mb(l) : 0.0)
-                                            : -2.1 + 0.616 * c + 0.33 * l.steps_per_split + 0.77 * rounds(l) + (sp ? 1.93 + 0.46 * mb(l) : 0.0);
-        };
-        if (cheapest_of(out, KIND_IFILTER16B)) {
+        if (demand) {
+            const ImagesDemand *b = nullptr;
+            for (const ImagesDemand &d : images16)
+                if (!b || d.cost < b->cost) b = &d;
+            double more = 0.0;
+            if (b && gather) {
+                const double c = b->plain / 1260.0, sp = b->splits > 1, mbs = 4e-6 * b->splits * dm.M * dm.Ncols;
+                const double here = b->rows ? -4.97 + 0.883 * c + 0.134 * b->per + 0.86 * b->wgs + sp * (4.09 + 0.3 * mbs) : -2.1 + 0.616 * c + 0.33 * b->per + 0.77 * b->wgs + sp * (1.93 + 0.46 * mbs);
+                if (gather_us(*gather) < (g.N <= 2 ? 1.05 : 0.92) * here && b->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0)) more = std::max(b->cost, 1.54 * gather_clocks) - b->cost;
+            }
+            for (const ImagesDemand &d : images16) demand->push_back({d.cost + more, d.need, true});
+        }
+        if (cheapest_of(out, KIND_IFILTER16B) || (cheapest_of(out, KIND_IFILTER16) && (cheapest_of(out, KIND_DFILTER16) || cheapest_of(out, KIND_DFILTER16B)))) {
             // beside the kernel that streams its operands every kind is priced (dfilter16 and dfilter16b fitted to 97 launches, 0.07 and
             // 0.08 in the logarithm).  It is the slower one for one to four images, a group of which is mostly zeros, and on large batches of
             // few channels, where its tile is mostly empty; us, ifilter16b and the kernel before: 2 images 30x22, 288 -> 488 50 and 29; 728 of
             // 49x14, 32 -> 32 77 and 48.  Over the 210 layers none is more than 3 % slower than before it, and all take 6398 us instead of 7900.
+            // (Below 16 images its fit is up to 25 % high: three images 17x23, 32 -> 32 of 5x5 13.2, the other one 16.6.)
             if (gather) price_kind(out, KIND_GATHER, gather->cost, gather_us(*gather));
-            if (const Launch *l = cheapest_of(out, KIND_IFILTER16)) price_kind(out, KIND_IFILTER16, l->cost, images_us(*l));
+            if (const Launch *l = cheapest_of(out, KIND_IFILTER16)) price_kind(out, KIND_IFILTER16, l->cost, (g.N < 16 ? 1.25 : 1.04) * l->cost / images16_chain(*l) / 1260.0);
             if (const Launch *l = cheapest_of(out, KIND_DFILTER16))
                 price_kind(out, KIND_DFILTER16, l->cost, 9.54 + 0.474 * (l->cost - reduce_clocks(*l)) / 1260.0 + 0.79 * mb(*l) + 0.276 * l->steps_per_split);
             if (const Launch *l = cheapest_of(out, KIND_DFILTER16B))
@@ -1294,10 +1349,16 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         } else if (gather) {
             for (int kind : {KIND_IFILTER16, KIND_IGATHER16}) {
                 const Launch *l = cheapest_of(out, kind);
-                if (l && gather_us(*gather) < (g.N <= 2 ? 1.05 : 0.92) * images_us(*l) && l->cost < 1260.0 * (g.N <= 2 ? 150.0 : 60.0))      // (tuning times its nearest few)
-                    price_kind(out, kind, l->cost, std::max(l->cost, 1.54 * gather->cost) / 1260.0);
+                if (!l) continue;
+                const double us = l->cost / images16_chain(*l) / 1260.0;
+                price_kind(out, kind, l->cost, us);
+                price_kind(out, KIND_GATHER, gather->cost, us < (g.N <= 2 ? 150.0 : 60.0) ? gather_us(*gather) / (g.N <= 2 ? 1.2 : 1.0) : std::max(gather->cost / 1260.0, g.N <= 2 ? 0.0 : 1.05 * us));
             }
         }
+    }
+    if (demand && pass != OWT_PASS_BWD_FILTER) {
+        for (const Launch &l : out)
+            if (l.kind != KIND_XFCS && l.kind != KIND_XCONVS) demand->push_back({l.cost, l.ws_bytes(), is_split_kind(l.kind)});
     }
 }
 
@@ -1316,11 +1377,9 @@ static bool variants_forced()
            g_force_flags.load(std::memory_order_relaxed) != 0;
 }
 
-static std::map<PlanKey, Launch> g_modelled;   // the cost model's choice per geometry (untimed), so that a call plans once
-
-// The model's choice for scratch too small for some of the split-operand plans: any size in [lo, hi) admits the same plans.
-struct SmallScratchPlan { size_t lo, hi; Launch l; };
-static std::map<PlanKey, SmallScratchPlan> g_modelled_small;   // the last one per geometry
+// The model's choice per geometry (untimed), so that a call plans once: any scratch in [lo, hi) admits the same plans.
+struct ModelledPlan { size_t lo, hi; Launch l; };
+static std::map<PlanKey, ModelledPlan> g_modelled, g_modelled_small;   // scratch that the cheapest plans fit in, and the last one of less
 
 // ws_bytes: the scratch the call was given.  A plan of the kernels that split their operands is passed over when its
 // scratch does not fit, so a caller that sized its scratch for the kernels that multiply in fp32 is served by those.
@@ -1333,36 +1392,46 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
         auto it = g_tuned.find(plan_key(g, pass, dt));
         if (it != g_tuned.end() && fits(it->second)) return it->second;
         const bool tuned = it != g_tuned.end();
-        it = g_modelled.find(plan_key(g, pass, dt));
-        if (!tuned && it != g_modelled.end() && fits(it->second)) return it->second;
-        auto sm = g_modelled_small.find(plan_key(g, pass, dt));
-        if (sm != g_modelled_small.end() && sm->second.lo <= ws_bytes && ws_bytes < sm->second.hi) return sm->second.l;
+        for (const auto *plans : {&g_modelled, &g_modelled_small}) {
+            const auto sm = plans->find(plan_key(g, pass, dt));
+            if (sm != plans->end() && sm->second.lo <= ws_bytes && (ws_bytes < sm->second.hi || sm->second.hi == (size_t)-1) && (!tuned || plans != &g_modelled)) return sm->second.l;
+        }
     }
     std::vector<Launch> c;
-    enumerate(g, pass, dm, want_db, c);
+    std::vector<Demand> demand;
+    enumerate(g, pass, dm, want_db, c, variants_forced() ? nullptr : &demand);
     bool only_direct = forced(OWT_FORCE_ONLY_DIRECT), any_direct = false;   // test hook
     for (const Launch &l : c) any_direct |= l.kind != KIND_GATHER;
     // `fits`: the cheapest of those that may be taken; `any`: the scratch left out of account, for the caller's check to refuse
     // where nothing fits (the test hook can leave a geometry with split-operand kernels alone)
     size_t fits = c.size(), any = c.size();
-    SmallScratchPlan small = {0, (size_t)-1, {}};
+    ModelledPlan plan = {0, (size_t)-1, {}};
+    const auto bound = [&](size_t need) { if (need > ws_bytes) plan.hi = std::min(plan.hi, need); else plan.lo = std::max(plan.lo, need); };
     for (size_t i = 0; i < c.size(); i++) {
         if (only_direct && any_direct && c[i].kind == KIND_GATHER) continue;
         if (any == c.size() || c[i].cost < c[any].cost) any = i;
-        if (is_split_kind(c[i].kind)) {
-            const size_t need = c[i].ws_bytes();
-            if (need > ws_bytes) { small.hi = std::min(small.hi, need); continue; }
-            small.lo = std::max(small.lo, need);
-        }
+        const size_t need = c[i].ws_bytes();
+        bound(need);
+        if (need > ws_bytes && (is_split_kind(c[i].kind) || !demand.empty())) continue;
         if (fits == c.size() || c[i].cost < c[fits].cost) fits = i;
     }
-    const size_t best = fits < c.size() ? fits : any;
+    plan.l = c[fits < c.size() ? fits : any];
+    // refused by the plan that the scratch is asked for, and by no other
+    const Demand *asked = nullptr, *least = nullptr;
+    for (const Demand &d : demand) {
+        bound(d.need);
+        if (!least || d.cost < least->cost) least = &d;
+        if (!(d.passed_over && d.need > ws_bytes) && (!asked || d.cost < asked->cost)) asked = &d;
+    }
+    if (!asked) asked = least;
+    const size_t both = std::max(plan.l.ws_bytes(), asked ? asked->need : 0);
+    if (fits == any && asked == least && both <= ws_bytes) { plan.lo = both; plan.hi = (size_t)-1; }      // the same with any larger scratch
+    if (asked && asked->need > ws_bytes) { plan.l.pre_bytes = plan.l.dbias_bytes = 0; plan.l.partial_bytes = asked->need; }
     if (cached) {
         std::lock_guard<std::mutex> lk(g_tuned_mutex);
-        if (small.hi == (size_t)-1) g_modelled[plan_key(g, pass, dt)] = c[best];
-        else { small.l = c[best]; g_modelled_small[plan_key(g, pass, dt)] = small; }
+        (plan.hi == (size_t)-1 ? g_modelled : g_modelled_small)[plan_key(g, pass, dt)] = plan;
     }
-    return c[best];
+    return plan.l;
 }
 
 static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per geometry: listing the candidates takes 10-60 us
@@ -1399,7 +1468,12 @@ static size_t max_workspace(const Geom &g, int pass, const PassDims &dm, bool wa
         Geom gm = g;
         gm.masked = masked != 0;
         std::vector<Launch> c;
-        enumerate(gm, pass, dm, want_db, c);
+        std::vector<Demand> demand;
+        enumerate(gm, pass, dm, want_db, c, variants_forced() ? nullptr : &demand);
+        const Demand *asked = nullptr;
+        for (const Demand &d : demand)
+            if (!asked || d.cost < asked->cost) asked = &d;
+        if (asked) m = std::max(m, asked->need);
         const double least = least_cost(c);
         for (const Launch &l : c)
             if (worth_workspace(l, least) || variants_forced()) m = l.ws_bytes() > m ? l.ws_bytes() : m;
@@ -1585,7 +1659,7 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     if (l.kind == KIND_IGATHER16)
         return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilter16x" : "igather16", pn[pass], ds,
                         32 * kIGather16Variants[l.tile].KB, 32 * kIGather16Variants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,
-                        8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 64);
+                        8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 256);
     if (l.kind == KIND_IFILTER16B) {
         const IFilter16bVariant &v = kIFilter16bVariants[l.tile];
         return snprintf(buf, n, "ifilter16b %s %s tile%dx%d waves%dx%d taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds, 32 * v.KB * v.WK,
@@ -1595,7 +1669,7 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
     if (l.kind == KIND_IFILTER16)
         return snprintf(buf, n, "ifilter16 %s %s tile%dx%d taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
                         32 * kIFilter16Variants[l.tile].KB, 32 * kIFilter16Variants[l.tile].CB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
-                        8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4), 8) * 256);
+                        8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 256);
     if (l.kind == KIND_SCONV16)
         return snprintf(buf, n, "sconv16 %s %s rows%d grid%dx%d threads%ld", pn[pass], ds, kSConv16TP, l.tiles_m, l.tiles_n,
                         (long)l.tiles_m * l.tiles_n * kSConv16NT);

@@ -100,8 +100,8 @@ constexpr XGatherVariant kXGatherVariants[kNumXGatherVariants] = {{2, 3, 1}, {1,
 hipError_t owt_launch_xgather(int variant, const GemmParams &, hipStream_t);
 
 // Stride-1 filter gradient for bf16 storage and any channel counts, reduction over images (ifilter16_inst.hip): a wavefront
-// holds KB filter blocks x CB channel blocks of 32 x the S taps of a filter row, four wavefronts to a work-group.  The test hook
-// numbers the variants from 80.
+// holds KB filter blocks x CB channel blocks of 32 x the S taps of a filter row; the four wavefronts of a work-group share a tile as
+// above (TG = 4).  The test hook numbers the variants from 80.
 struct IFilter16Variant { int KB, CB, S; };
 constexpr int kNumIFilter16Variants = 7, kIFilter16FirstTile = 80;
 constexpr IFilter16Variant kIFilter16Variants[kNumIFilter16Variants] = {{1, 1, 3}, {2, 1, 3}, {1, 2, 3}, {2, 2, 3}, {1, 1, 5}, {2, 1, 5}, {1, 2, 5}};
@@ -110,11 +110,11 @@ constexpr int ifilter16_occ(int KB, int CB, int S) { return KB * CB * S <= 6 ? 2
 hipError_t owt_launch_ifilter16(int variant, const GemmParams &, hipStream_t);
 hipError_t owt_launch_ifilter16_masked(int variant, const GemmParams &, hipStream_t);
 
-// The same for any geometry: KB filter blocks x CB blocks of densely packed (r, s, c) places, one wavefront to a work-group, two
-// to a SIMD.  Test-hook numbers from 88.
+// The same for any geometry: KB filter blocks x CB blocks of densely packed (r, s, c) places, work-groups alike, two wavefronts
+// to a SIMD.  Test-hook numbers from 87.
 struct IGather16Variant { int KB, CB; };
-constexpr int kNumIGather16Variants = 2, kIGather16FirstTile = 88;
-constexpr IGather16Variant kIGather16Variants[kNumIGather16Variants] = {{2, 3}, {1, 3}};
+constexpr int kNumIGather16Variants = 3, kIGather16FirstTile = 87;
+constexpr IGather16Variant kIGather16Variants[kNumIGather16Variants] = {{1, 2}, {2, 3}, {1, 3}};
 hipError_t owt_launch_igather16(int variant, const GemmParams &, hipStream_t);
 hipError_t owt_launch_igather16_masked(int variant, const GemmParams &, hipStream_t);
 
