@@ -65,7 +65,7 @@ enum { KIND_GATHER = 0, KIND_DIRECT = 1, KIND_DFILTER = 2, KIND_SFILTER = 3, KIN
 static inline bool is_split_kind(int kind)
 {
     return kind == KIND_XCONV || kind == KIND_XFILTER || kind == KIND_XGATHER || kind == KIND_XFC || kind == KIND_IFILTER16 || kind == KIND_DIRECT16X ||
-           kind == KIND_IGATHER16 || kind == KIND_XCONVS || kind == KIND_DIRECT16S || kind == KIND_IFILTER16B;
+           kind == KIND_IGATHER16 || kind == KIND_XCONVS || kind == KIND_DIRECT16S || kind == KIND_IFILTER16B || kind == KIND_XFCS;
 }
 
 struct PassDims { long M, Ncols, Kd; bool va, vb; };
@@ -1251,6 +1251,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         const double here = (g.bf16 ? 5.0 + I * (0.363 * rounds + 0.986 * tiles / 256.0) : 4.75 + I * (1.585 * rounds + 1.739 * tiles / 256.0)) * (I > (g.bf16 ? 4.5 : 3.0) ? 1.25 : 1.0);
         l.cost = 1260.0 * here;
         if (split_fc) {
+            l.pre_bytes = split_fc->ws_bytes();          // asked for though not used: a call that brings less is served, or refused, as without this kernel
             const double steps = (double)cdiv(split_fc->steps_per_split, 4), sp = split_fc->splits > 1, mb = sp * split_fc->splits * dm.M * dm.Ncols * 4e-6;
             l.cost = split_fc->cost * here / (g.bf16 ? 5.2 + 0.51 * steps + 4.34 * sp + 0.03 * mb : 4.8 + 0.676 * steps + 4.25 * sp + 0.923 * mb);
         }
