@@ -1088,6 +1088,9 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             const IFilter16bVariant &iv = kIFilter16bVariants[v];
             if ((force_tile >= 0 && force_tile != kIFilter16bFirstTile + v) || g.S != iv.S) continue;
             const long KT = 32 * iv.KB * iv.WK, CT = 32 * iv.CB * iv.WC;
+            // dw is stored with 32-bit byte offsets, rows of a ragged tile included, and 2^31 stands for a channel past the last, to
+            // which a block's rows are added: no offset may come round past 2^32, nor that one lie inside dw
+            if ((double)cdiv(g.K, KT) * KT * dm.Ncols * 4.0 > 2147483648.0) continue;
             const long tm = cdiv(g.K, KT), ctl = cdiv(g.C, CT), tiles = tm * ctl * g.R, steps = cdiv(g.N, 16) * g.P * g.Q;
             for (long s0 : split_ladder(tiles, 256 * iv.occ)) {
                 long s = s0;

@@ -131,6 +131,27 @@ def test_streamed_images_keep_to_what_they_can_address(m, tile, S):
     assert not name(takes, relu=True).startswith("ifilter16b")
 
 
+# and it stores dw with 32-bit byte offsets: filters of up to 2 GB, rows of a ragged tile included (256, 128 and 64 filters)
+@pytest.mark.parametrize("tile,S,K,C", [(None, 3, 8200, 8200), (None, 3, 12000, 12000), (None, 3, 7680, 7768), (100, 3, 8200, 8200), (100, 3, 7680, 7768),
+                                        (103, 3, 7736, 7640), (104, 5, 5184, 4144), (106, 5, 4672, 4608), (106, 5, 4600, 4680), (103, 3, 8, 466040)])
+def test_streamed_images_leave_filters_that_they_cannot_address(m, tile, S, K, C):
+    shape = (16, C, 6 if C < 100000 else 3, 6 if C < 100000 else 3, K, S, S, 1, S // 2)
+    m.owt_test_force_variant(-1 if tile is None else tile, 0, 0)
+    try:
+        assert not plan(m, shape, 2, dtype=1).startswith("ifilter16b"), shape
+    finally:
+        m.owt_test_force_variant(-1, 0, 0)
+
+
+@pytest.mark.parametrize("tile,S,K,C", [(100, 3, 7680, 7760), (103, 3, 7736, 7632), (104, 5, 5184, 4136), (106, 5, 4608, 4656), (103, 3, 8, 466032)])
+def test_streamed_images_take_filters_up_to_that_line(m, tile, S, K, C):
+    m.owt_test_force_variant(tile, 0, 0)
+    try:
+        assert plan(m, (16, C, 6 if C < 100000 else 3, 6 if C < 100000 else 3, K, S, S, 1, S // 2), 2, dtype=1).startswith("ifilter16b"), (K, C)
+    finally:
+        m.owt_test_force_variant(-1, 0, 0)
+
+
 # the bf16 kernels with 32-bit byte offsets: tensors below 2 GB, and below 1 GB for the one of few tiles, whose partial sums take 4 bytes
 @pytest.mark.parametrize("tile,kernel,images,p", [(90, "dconv16x", 8061, 0), (90, "dconv16x", 8061, 1), (92, "dconv16s", 4030, 0), (94, "dconv16s", 4030, 1)])
 @pytest.mark.parametrize("C,K", [(37, 5), (5, 37)])
