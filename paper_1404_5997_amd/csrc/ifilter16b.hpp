@@ -133,12 +133,15 @@ __global__ void __launch_bounds__(64 * WK * WC, OCC * WK * WC / 4) ifilter16b_ke
         zo += L * zstep;
         if (lw >= lend) { next_row(ld); load_row(); }
     };
-    // waits until at most N of this wavefront's stages are still on their way, and for the others'
+    // Waits until at most N of this wavefront's stages are still on their way and all it has read from LDS is in registers, and for the
+    // others'.  What is loaded next goes into the stage before the one that is left here.  Its last fragments may not have been used: where a
+    // row begins or ends there are whole stages without products, which are what else would have waited for them.
     const bool fewer = wave >= PIECES % NW;
     auto arrived = [&](auto n) __attribute__((always_inline)) {
         constexpr int N = decltype(n)::value, A = N * LPW, B = N * (LPW - 1);
-        if (PIECES % NW && fewer) __builtin_amdgcn_s_waitcnt((B & 15) | ((B >> 4) << 14) | 0x0F70);
-        else __builtin_amdgcn_s_waitcnt((A & 15) | ((A >> 4) << 14) | 0x0F70);
+        asm volatile("" ::: "memory");
+        if (PIECES % NW && fewer) __builtin_amdgcn_s_waitcnt((B & 15) | ((B >> 4) << 14) | 0x0070);      // lgkmcnt(0), expcnt untouched
+        else __builtin_amdgcn_s_waitcnt((A & 15) | ((A >> 4) << 14) | 0x0070);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
