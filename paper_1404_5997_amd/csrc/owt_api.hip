@@ -1395,10 +1395,10 @@ static Launch choose(const Geom &g, int pass, owt_dtype dt, const PassDims &dm, 
         const auto fits = [&](const Launch &l) { return !is_split_kind(l.kind) || l.ws_bytes() <= ws_bytes; };
         auto it = g_tuned.find(plan_key(g, pass, dt));
         if (it != g_tuned.end() && fits(it->second)) return it->second;
-        const bool tuned = it != g_tuned.end();
+        // (not, or tuned to a plan that does not fit: the model's choice for this scratch, wherever it was put)
         for (const auto *plans : {&g_modelled, &g_modelled_small}) {
             const auto sm = plans->find(plan_key(g, pass, dt));
-            if (sm != plans->end() && sm->second.lo <= ws_bytes && (ws_bytes < sm->second.hi || sm->second.hi == (size_t)-1) && (!tuned || plans != &g_modelled)) return sm->second.l;
+            if (sm != plans->end() && sm->second.lo <= ws_bytes && (ws_bytes < sm->second.hi || sm->second.hi == (size_t)-1)) return sm->second.l;
         }
     }
     std::vector<Launch> c;
