@@ -353,6 +353,7 @@ struct Launch {
     size_t pre_bytes;   // workspace in front of the partials (re-laid-out filters of the bf16 backward-data kernel)
     double cost;   // model estimate, ~clocks
     bool fitted;   // ... 1260 times the microseconds that timed launches of the kind take, launch and latency included
+    double asked;  // what the cost was raised by for other reasons than time, which tuning leaves out
     size_t ws_bytes() const { return pre_bytes + partial_bytes + dbias_bytes; }
 };
 
@@ -1310,7 +1311,10 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0, split = gather->splits > 1, wgs = (double)cdiv((long)gather->tiles_m * gather->tiles_n * gather->splits, 256);
         const double us = vec ? 4.3 + 0.734 * core + 0.474 * mb(*gather) + 0.193 * gather->steps_per_split + 2.53 * wgs
                               : 1.7 + 0.249 * core + 0.3 * split + 0.482 * mb(*gather) + 2.44 * gather->steps_per_split + 0.76 * wgs;
-        price_kind(out, KIND_GATHER, gather->cost, gather->cost < images_clocks ? 1.1 * us : std::max(us, 1.7 * over->cost / 1260.0));
+        const double priced = gather->cost < images_clocks ? 1.1 * us : std::max(us, 1.7 * over->cost / 1260.0);
+        price_kind(out, KIND_GATHER, gather->cost, priced);
+        for (Launch &l : out)
+            if (l.kind == KIND_GATHER) l.asked = 1260.0 * (priced - us);
     }
     if (priced16 && gather) price_kind(out, KIND_GATHER, gather->cost, gather->cost / 1260.0 + 10.0);
     // The filter gradients that take 16 images at a time, against the kernel that gathers pixels: of a group of 16 one to four images
@@ -1447,12 +1451,14 @@ static std::map<PlanKey, size_t> g_workspace;  // owt_conv_workspace_bytes per g
 // 0.63).  Split-operand kernels that split their reduction, too, were the fastest up to 1.85
 // times: past twice they only raise the bound (the first layer's forward pass 0.3 -> 199 MB).  Costs that have the launch in them lie
 // nearer to each other, and to the truth: of 310 bf16 passes priced so 1 loses more than 2 % with 1.6 times (none with 2, three with
-// 1.4), 1675 instead of 2918 candidates.  choose() sees every candidate.
+// 1.4), 1675 instead of 2918 candidates; of 700 fp32 filter gradients none with 1.6 or 1.2, 16080 and 6218 instead of 31548 (with the gather
+// kernel weighed by the choice's cost, which is not of time alone, 36 lost up to 83 %); of 700 in bf16 with ifilter16 and igather16 to 1.6
+// and ifilter16b to 1.25 none (1.4: two; 1.15: two, 1.1: eight by up to 17 %).  choose() sees every candidate.
 static bool worth_timing(const Launch &l, double least)
 {
     if (l.kind == KIND_XCONVS || l.kind == KIND_DIRECT16S) return l.cost <= 1.4 * least;      // (three tiles, up to eight splits; modelled to 0.14-0.17 in the logarithm)
     if (l.kind == KIND_IFILTER16B) return l.cost <= 1.25 * least;
-    return l.cost <= (l.fitted ? 1.6 : is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 3.0) * least;
+    return l.cost - l.asked <= (l.fitted ? 1.6 : is_split_kind(l.kind) && l.splits > 1 ? 2.0 : 3.0) * least;
 }
 static bool worth_workspace(const Launch &l, double least) { return !is_split_kind(l.kind) || l.splits == 1 || worth_timing(l, least); }
 static double least_cost(const std::vector<Launch> &c)
