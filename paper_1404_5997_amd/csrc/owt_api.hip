@@ -1242,22 +1242,29 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             if (force_split > 0 || pass != OWT_PASS_FWD) break;
         }
     }
-    // its forward pass in one launch.  Microseconds of both, fitted to 132 and 147 launches of drawn shards, 0.11 in the logarithm; the other
-    // kernels' prices stay, so this one's stands to the cheapest launch above as the microseconds do.
+    // Its forward pass in one launch.  Microseconds of both kernels behind a busy device, fitted to 992 launches each of drawn shards of up to
+    // 16000 inputs, 0.06 and 0.10 in the logarithm; the other kernels' prices stay, so this one's stands to the cheapest launch above as
+    // the microseconds do.  A wavefront's steps are a chain of loads, one behind the other from the reduction's length on that its own
+    // sixteenth is longer than what is in flight: bf16, xfc and here: 16 x 5632 -> 19 7.4 and 11.9 us, 8 x 9379 -> 21 9.5 and 16.2, but 128 x 4096
+    // -> 512 11.2 and 10.2.  Of the 992 shards 7 are more than 3 % slower than without this kernel (by 22 % at most); with the line at 4500
+    // and 3000 inputs there was before, 83, by up to 85 %.
     const Launch *split_fc = cheapest_of(out, KIND_XFC);
     if (plain && pass == OWT_PASS_FWD && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && (force_tile < 0 ? split_fc != nullptr : force_tile == kXFcSTile) && force_split <= 1 &&
         (double)(g.N + 16) * g.C * 4 < 2147483647.0 && (double)(g.K + 16) * g.C * 4 < 2147483647.0) {
         Launch l; memset(&l, 0, sizeof(l));
         l.kind = KIND_XFCS; l.splits = 1; l.steps = l.steps_per_split = (int)cdiv(dm.Kd, 16);
         l.tiles_m = (int)cdiv(dm.M, 16); l.tiles_n = (int)cdiv(dm.Ncols, 16);
-        const double tiles = (double)l.tiles_m * l.tiles_n, rounds = (double)cdiv((long)tiles, 256), I = 1e-3 * dm.Kd;
-        // (long reductions come out low: 48 rows of 4287 to 61 columns 11.7, 17.3 measured)
-        const double here = (g.bf16 ? 5.0 + I * (0.363 * rounds + 0.986 * tiles / 256.0) : 4.75 + I * (1.585 * rounds + 1.739 * tiles / 256.0)) * (I > (g.bf16 ? 4.5 : 3.0) ? 1.25 : 1.0);
+        const double tiles = (double)l.tiles_m * l.tiles_n, more = (double)cdiv((long)tiles, 256) - 1.0, I = 1e-3 * dm.Kd, odd = dm.Kd % 2;
+        const double rows = (std::min(g.N, 16) + std::min(g.K, 16)) / 32.0;      // (rows past the end are no loads)
+        const double here = 1.06 * (g.bf16 ? 2.12 + I * (0.49 + 0.76 * rows + odd * (0.1 + 0.49 * rows) + 1.62 * more + 0.2 * tiles / 256.0) + 0.57 * more
+                                           : 2.47 + I * (1.52 + 1.04 * rows + 2.59 * more + 0.6 * tiles / 256.0) + 0.96 * more);
         l.cost = 1260.0 * here;
         if (split_fc) {
             l.pre_bytes = split_fc->ws_bytes();          // asked for though not used: a call that brings less is served, or refused, as without this kernel
             const double steps = (double)cdiv(split_fc->steps_per_split, 4), sp = split_fc->splits > 1, mb = sp * split_fc->splits * dm.M * dm.Ncols * 4e-6;
-            l.cost = split_fc->cost * here / (g.bf16 ? 5.2 + 0.51 * steps + 4.34 * sp + 0.03 * mb : 4.8 + 0.676 * steps + 4.25 * sp + 0.923 * mb);
+            const double rows64 = (std::min(g.N, 64) + std::min(g.K, 64)) / 128.0, more64 = (double)cdiv((long)split_fc->tiles_m * split_fc->tiles_n * split_fc->splits, 256) - 1.0;
+            l.cost = split_fc->cost * here / (g.bf16 ? 2.6 + steps * (0.21 + rows64 * (0.34 + 1.93 * odd)) + 4.28 * sp + 0.6 * mb + 21.9 * more64
+                                                     : 3.77 + steps * (0.34 + 0.86 * rows64) + 3.69 * sp + 0.785 * mb + 3.66 * more64);
         }
         out.push_back(l);
     }

@@ -78,3 +78,22 @@ def test_ends_of_the_fp32_range(a, b):
     g = np.random.default_rng(2160)
     x, w = (g.standard_normal((40, 300)) * a).astype(np.float32), (g.standard_normal((50, 300)) * b).astype(np.float32)
     f32.check_ends(run(m, x, w, None, "f32", 0), x.astype(np.float64) @ w.T.astype(np.float64), 300, "y")
+
+
+# the longest reductions that it is chosen for, and those that it was chosen for once: rows that start at 4 and at 16 bytes, and at any 2 in bf16
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_long_reductions(dt):
+    m = owt()
+    for i, (N, I, O) in enumerate([(9, 6000, 46), (16, 9216, 16), (128, 4096, 512), (128, 7680, 512), (5, 6483, 41), (33, 12001, 17)]):
+        g = np.random.default_rng(2180 + i)
+        x, w = (g.standard_normal(s, dtype=np.float32) for s in ((N, I), (O, I)))
+        if dt == "bf16":
+            x, w = oracle.round_bf16(x), oracle.round_bf16(w)
+        print("case", dt, (N, I, O))
+        sys.stdout.flush()
+        got, want = run(m, x, w, None, dt, 0), x.astype(np.float64) @ w.T.astype(np.float64)
+        size = np.abs(x).astype(np.float64) @ np.abs(w).T.astype(np.float64)
+        if dt == "bf16":
+            b16.check(got, want, size, I, "y", stored=2.0 ** -8)
+        else:
+            f32.check(got, want.astype(np.float32), size.astype(np.float32), I, "y")

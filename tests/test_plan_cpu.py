@@ -277,3 +277,15 @@ def test_wide_masked_bf16_layers_of_odd_filters_stay_off_the_tile_that_spills(m,
             m.owt_test_force_variant(-1, 0, 0)
         assert "waves2x1x4 panel320" not in masked, masked
         assert tile < 0 or "waves2x1x4 panel320" in plain, plain
+
+
+# the shard's forward pass in one launch: long reductions of few tiles are a chain of loads there (bf16, us, split over work-groups and in one
+# launch: 16 x 5632 -> 19 7.4 and 11.9, 2 x 9536 -> 430 8.0 and 13.5), and no line in the reduction's length alone parts them
+@pytest.mark.parametrize("dtype,shapes,one", [
+    (1, [(16, 9216, 16), (32, 8000, 64), (9, 6000, 46), (5, 6482, 41), (17, 5632, 19), (2, 9536, 430), (8, 9379, 21)], False),
+    (1, [(128, 4096, 512), (128, 4500, 512), (128, 4501, 512), (61, 1792, 210), (9, 439, 46), (252, 1494, 123)], True),
+    (0, [(50, 2720, 188), (16, 9216, 16), (128, 9216, 512), (8, 2614, 32)], False),
+    (0, [(128, 3000, 512), (128, 3001, 512), (61, 1792, 210), (19, 632, 193), (172, 376, 44)], True)])
+def test_shard_forward_in_one_launch_where_that_is_the_faster_way(m, dtype, shapes, one):
+    for N, I, O in shapes:
+        assert plan(m, (N, I, 1, 1, O, 1, 1, 1, 0), 0, True, dtype).startswith("xfcs" if one else "xfc "), (N, I, O)
