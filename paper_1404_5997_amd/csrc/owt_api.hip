@@ -422,6 +422,16 @@ static double ifilter16b_us(const Launch &l, const Geom &g, const PassDims &dm)
     return (g.K <= 48 ? 1.1 : 1.0) * us;                // (tiles mostly empty: the other kinds' prices come out high there, seven of 210 layers were up to 16 % slower)
 }
 
+// Microseconds of the fp32 forward and backward-data kernel of few tiles: a step (a tap of a chunk) of each wavefront of a SIMD, with the
+// rows of its panels where their values are loaded one by one, and its latency once a round; a panel's pieces of loads; what a work-group
+// begins and ends with, the groups' sums and the stores, for each of a CU's; the reduce pass.  Coefficients per pass and tile, fitted to
+// 14505 launches of 3000 drawn passes, 0.05 to 0.07 in the logarithm (the tile of 128 pixels, and backward-data's of 32, weighed 3 and 1 %
+// more, which is the better choice over these passes).
+struct XConvSUs { double at, work, rows, lat, load, wg, round, split, mb; };
+static const XConvSUs kXConvSUs[2][kNumXConvSVariants] = {
+    {{1.42, 0.22, 4.9e-4, 0.0, 0.0, 0.0, 3.7, 2.84, 0.614}, {2.6, 0.161, 8.5e-4, 0.181, 0.067, 0.785, 0.605, 2.92, 0.474}, {2.58, 0.157, 9.9e-4, 0.225, 0.037, 0.704, 0.632, 2.99, 0.428}},
+    {{1.12, 0.275, 7.4e-4, 0.0, 0.068, 3.79, 0.0, 2.9, 0.482}, {2.6, 0.164, 1.28e-3, 0.334, 0.182, 1.18, 0.0, 2.89, 0.365}, {2.66, 0.172, 1.55e-3, 0.333, 0.187, 0.897, 0.262, 2.86, 0.26}}};
+
 // Microseconds of the fp32 filter gradients over images: a position takes a wavefront its fragments' loads and splits (a fragment of
 // masked dz half as long again), one after the other for the wavefronts of a SIMD, and a latency; rows of the walk have their first
 // columns, a launch its rounds and the tiles' stores.  Coefficients per variant, fitted to 6695 timed launches of 261 layers, 0.05 to
@@ -621,6 +631,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // above take all the same, so that a call that brings less is served, to the bit, as it was before there were either.
     if (!g.bf16 && !blocks && pass != OWT_PASS_BWD_FILTER && (g.H > 1 || g.W > 1) && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && xr * xs <= 32 &&
         (size_t)g.N * g.H * g.W * g.C < 0x1fffffffull && (size_t)g.N * g.P * g.Q * g.K < 0x1fffffffull && (size_t)g.K * g.R * g.S * g.C < 0x1fffffffull) {
+        double clocks_of = 0.0, us_of = 0.0;            // the cheapest by clocks with a chunk to a panel
         for (int v = 0; v < kNumXConvSVariants; v++) {
             const XConvSVariant &xv = kXConvSVariants[v];
             if ((force_tile >= 0 && force_tile != kXConvSFirstTile + v) || xr * xs < xv.TG) continue;
@@ -636,29 +647,39 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 l.splits = (int)splits; l.steps = (int)chunks; l.steps_per_split = (int)per; l.tiles_m = (int)tm; l.tiles_n = (int)tn;
                 l.pre_bytes = pad256((size_t)chunks * xr * xs * cdiv(dm.Ncols, 64) * 2 * 3072);
                 if (splits > 1) l.partial_bytes = pad256((size_t)splits * dm.M * dm.Ncols * 4);
-                // Fitted to 879 timed launches of 42 drawn layers (0.14 in the logarithm, its choice 2 % slower than the fastest): a tap
-                // of a chunk takes 367 clocks (backward-data, with its 4-byte filter loads, 545) times the wavefronts on a SIMD, a
-                // chunk's panel 1122 and a quarter of one a row and wavefront (twice that with the mask's loads); 10900 for launch, first loads and
-                // stores, the reduce pass 2.2 us and 0.85 us a MB.  More than 8192 wavefronts (two
-                // rounds of the chip), or a SIMD with more than 96 steps to take in all, are left to xconv.hpp: 75 us against 62 at 12912
-                // wavefronts, 34.6 against 29.8 at 112 steps, 42.1 against 37.6 at 168, while 10 % is the most that was won there.
+                // More than 8192 wavefronts (two rounds of the chip), or a SIMD with more than 96 steps to take in all, are left to
+                // xconv.hpp: 75 us against 62 at 12912 wavefronts, 34.6 against 29.8 at 112 steps, 42.1 against 37.6 at 168, while 10 % is
+                // the most that was won there.
                 const long wgs = tm * tn * splits, occ = std::max(1, 16 / (xv.WM * xv.TG)), full = cdiv(wgs, 256);
                 const double waves = std::min(occ, full) * xv.WM * xv.TG / 4.0, rounds = (double)cdiv(wgs, 256 * occ);
                 const long in_panel = xconvs_chunks(xv.WM, xv.TG, l.pr), panels = cdiv(per, in_panel);
                 const long steps = per / in_panel * cdiv(in_panel * xr * xs, xv.TG) + cdiv(per % in_panel * xr * xs, xv.TG);
-                const double reduce = splits > 1 ? 2770.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 933.0 : 0.0;
-                const double in_step = pass == OWT_PASS_FWD ? 367.0 : 545.0, in_row = 0.257 * l.pr * (pass == OWT_PASS_BWD_DATA && g.masked ? 2.0 : 1.0);
-                if (demand && cdiv(xr * xs, xv.TG) * per * waves * rounds <= 96.0 && l.partial_bytes <= kMaxPartialBytes)      // (a chunk to a panel)
-                    demand->push_back({0.6 * (rounds * per * (cdiv(xr * xs, xv.TG) * waves * in_step + 1122.0 + in_row * waves) + 10900.0) + reduce, l.ws_bytes(), true});
+                // with a chunk to a panel, by clocks: a tap of a chunk 367 (backward-data, with its 4-byte filter loads, 545) times the
+                // wavefronts on a SIMD, a panel 1122 and a quarter of one a row and wavefront (twice that with the mask's loads)
+                const double loads = pass == OWT_PASS_BWD_DATA && g.masked ? 2.0 : 1.0;
+                const double clocks = 0.6 * (rounds * per * (cdiv(xr * xs, xv.TG) * waves * (pass == OWT_PASS_FWD ? 367.0 : 545.0) + 1122.0 + 0.257 * l.pr * loads * waves) + 10900.0) +
+                                      (splits > 1 ? 2770.0 + (double)splits * dm.M * dm.Ncols * 4.0 / 933.0 : 0.0);
+                const XConvSUs &u = kXConvSUs[pass == OWT_PASS_BWD_DATA][v];
+                const double on_simd = (double)full * xv.WM * xv.TG / 4.0, pieces = (double)cdiv(2 * in_panel * l.pr, 64 * xv.WM * xv.TG) * loads;
+                l.cost = u.at + on_simd * (u.work * steps + (cred % 4 ? u.rows * per * l.pr : 0.0)) + u.wg * full + rounds * (u.lat * steps + u.load * panels * pieces + u.round) +
+                         (splits > 1 ? u.split + u.mb * 4e-6 * splits * dm.M * dm.Ncols : 0.0);
+                if (l.partial_bytes <= kMaxPartialBytes && cdiv(xr * xs, xv.TG) * per * waves * rounds <= 96.0) {
+                    if (demand) demand->push_back({clocks, l.ws_bytes(), true});
+                    if (us_of == 0.0 || clocks < clocks_of) { clocks_of = clocks; us_of = l.cost; }
+                }
                 if (force_split <= 0 && force_tile < 0 && steps * waves * rounds > 96.0) continue;
-                const double clocks = steps * waves * in_step + 1122.0 * panels + in_row * per * waves;
-                l.cost = 0.6 * (rounds * clocks + 10900.0) + reduce;
                 bool dup = l.partial_bytes > kMaxPartialBytes && force_split <= 0;
                 for (const Launch &o : out) dup |= o.kind == l.kind && o.tile == l.tile && o.splits == l.splits;
                 if (!dup) out.push_back(l);
                 if (force_split > 0) break;
             }
         }
+        // xconv's prices stay, so these stand to them as the clocks did: the microseconds choose between tiles and splits, and what several
+        // chunks to a panel won counts.  Of the 3000 passes 51 take more than 3 % longer than before there were such panels, 10 more than 6 %,
+        // 246 less.  (Priced by clocks with panels of several chunks, which know of no cost of a work-group, 79, 50 and 227: 60 images
+        // 14x31, 32 -> 32 14.0 us in 814 tiles of 32 x 32, 11.0 in 407 of 64 x 32.  By the microseconds alone 53, 18 and 278.)
+        for (Launch &l : out)
+            if (l.kind == KIND_XCONVS) l.cost *= us_of > 0.0 ? clocks_of / us_of : 1260.0;
     }
     if (g.bf16 && cred % 8 == 0 && !forced(OWT_FORCE_NO_BF16_MFMA)) {      // the bf16 MFMA: 64-channel chunks, or 32 in the 512x64 tile
         for (int t : {TILE_128x128, TILE_128x64, TILE_256x64, TILE_512x64, TILE_256x64P}) {

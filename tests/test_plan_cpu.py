@@ -289,3 +289,13 @@ def test_wide_masked_bf16_layers_of_odd_filters_stay_off_the_tile_that_spills(m,
 def test_shard_forward_in_one_launch_where_that_is_the_faster_way(m, dtype, shapes, one):
     for N, I, O in shapes:
         assert plan(m, (N, I, 1, 1, O, 1, 1, 1, 0), 0, True, dtype).startswith("xfcs" if one else "xfc "), (N, I, O)
+
+
+# fp32 layers of few tiles: the 64-pixel tile where the one of 32 takes twice the work-groups for no more wavefronts (us, 64 and 32 pixels: 11.0
+# and 14.0, 11.3 and 14.3, 10.7 and 13.5, 11.7 and 14.6, 14.4 and 17.3); N, C, H, W, K, R, pass, masked
+@pytest.mark.parametrize("shape", [(60, 32, 14, 31, 32, 3, 1, False), (36, 13, 34, 21, 32, 3, 1, True), (16, 8, 56, 28, 32, 3, 1, False),
+                                   (4, 414, 38, 16, 32, 3, 1, False), (44, 64, 41, 17, 9, 3, 0, True)])
+def test_few_tiles_are_not_cut_smaller_for_a_panel_of_two_chunks(m, shape):
+    N, C, H, W, K, R, p, masked = shape
+    text = plan(m, (N, C, H, W, K, R, R, 1, R // 2), p, masked)
+    assert text.startswith("xconvs") and "tile64x32x16" in text, text
