@@ -1687,12 +1687,12 @@ static int describe(char *buf, size_t n, int pass, owt_dtype dt, const PassDims 
         return snprintf(buf, n, "xfc %s %s tile64x64x16 splitk%d grid%ld threads%ld", pn[pass], ds, l.splits, wgs, wgs * 256);
     }
     if (l.kind == KIND_XGATHER)
-        return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilterx" : "xgather", pn[pass], ds,
-                        32 * kXGatherVariants[l.tile].KB, 32 * kXGatherVariants[l.tile].CB, l.splits, l.tiles_m * l.tiles_n, l.splits,
+        return snprintf(buf, n, "%s %s %s tile%dx%d%s splitk%d grid%dx%d threads%ld", l.blocks ? "sfilterx" : "xgather", pn[pass], ds,
+                        32 * kXGatherVariants[l.tile].KB, 32 * kXGatherVariants[l.tile].CB, kXGatherVariants[l.tile].TG > 1 ? " shared4" : "", l.splits, l.tiles_m * l.tiles_n, l.splits,
                         8 * cdiv((long)l.tiles_m * l.tiles_n * l.splits, 8) * 64 * kXGatherVariants[l.tile].TG);
     if (l.kind == KIND_XFILTER)
-        return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d splitk%d grid%dx%d threads%ld", pn[pass], ds,
-                        32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, l.splits, l.tiles_m * l.tiles_n, l.splits,
+        return snprintf(buf, n, "xfilter %s %s tile%dx32 taps%dx%d%s splitk%d grid%dx%d threads%ld", pn[pass], ds,
+                        32 * kXFilterVariants[l.tile].KB, l.taps, l.groups, kXFilterVariants[l.tile].TG > 1 ? " shared4" : "", l.splits, l.tiles_m * l.tiles_n, l.splits,
                         8 * cdiv(cdiv((long)l.tiles_m * l.tiles_n * l.splits, 4 / kXFilterVariants[l.tile].TG), 8) * 256);
     if (l.kind == KIND_IGATHER16)
         return snprintf(buf, n, "%s %s %s tile%dx%d splitk%d grid%dx%d threads%ld", l.blocks ? "sfilter16x" : "igather16", pn[pass], ds,

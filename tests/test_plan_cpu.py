@@ -299,3 +299,17 @@ def test_few_tiles_are_not_cut_smaller_for_a_panel_of_two_chunks(m, shape):
     N, C, H, W, K, R, p, masked = shape
     text = plan(m, (N, C, H, W, K, R, R, 1, R // 2), p, masked)
     assert text.startswith("xconvs") and "tile64x32x16" in text, text
+
+
+# plans are told apart by their description without split count, grid and threads, as the benchmark groups them: a tile to a wavefront, and
+# the same tile shared by four
+@pytest.mark.parametrize("alone,shared,R", [(51, 53, 5), (61, 62, 3)])
+def test_descriptions_tell_shared_tiles_from_others(m, alone, shared, R):
+    names = []
+    for tile in (alone, shared):
+        m.owt_test_force_variant(tile, 0, 0)
+        try:
+            names.append(plan(m, (32, 64, 14, 14, 64, R, R, 1, R // 2), 2).split(" splitk")[0])
+        finally:
+            m.owt_test_force_variant(-1, 0, 0)
+    assert names[0] != names[1] and names[1] == names[0] + " shared4", names
