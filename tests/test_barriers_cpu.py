@@ -7,9 +7,9 @@ import os
 import re
 import subprocess
 
-import paper_1404_5997_amd as owt
-
-spec = importlib.util.spec_from_file_location("_owt_build", os.path.join(os.path.dirname(owt.__file__), "build.py"))
+# (by path: the package loads its library, and the HIP runtime with it, which has to come behind torch's for the GPU tests of the same process)
+PACKAGE = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1404_5997_amd")
+spec = importlib.util.spec_from_file_location("_owt_build", os.path.join(PACKAGE, "build.py"))
 build = importlib.util.module_from_spec(spec)
 spec.loader.exec_module(build)
 
