@@ -419,7 +419,8 @@ static double ifilter16b_us(const Launch &l, const Geom &g, const PassDims &dm)
     const double per = l.steps_per_split, idle = (per / g.Q + 1.0) * (v.S - 1 + 0.5 * (v.L - 1)), blocks = v.KB * v.CB * v.S;
     const double us = (l.splits > 1 ? 8.1 + 0.228e-6 * 4.0 * l.splits * dm.M * dm.Ncols : 5.0) + 0.97 * resident * per * blocks * v.WK * v.WC / 4.0 * 32.0 / 2100.0 +
                       rounds * (0.129 * (per + idle) + 0.59 * blocks);
-    return (g.K <= 48 ? 1.1 : 1.0) * us;                // (tiles mostly empty: the other kinds' prices come out high there, seven of 210 layers were up to 16 % slower)
+    const double few = (g.K <= 48 ? 1.1 : 1.0) * us;    // (tiles mostly empty: the other kinds' prices come out high there, seven of 210 layers were up to 16 % slower)
+    return 1.03 * (few - 3.0 * std::max(0.0, 1.0 - few / 25.0));      // (short ones came out a quarter high)
 }
 
 // Microseconds of the fp32 forward and backward-data kernel of few tiles: a step (a tap of a chunk) of each wavefront of a SIMD, with the
@@ -1371,17 +1372,23 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
             for (const ImagesDemand &d : images16) demand->push_back({d.cost + more, d.need, true});
         }
         if (cheapest_of(out, KIND_IFILTER16B) || (cheapest_of(out, KIND_IFILTER16) && (cheapest_of(out, KIND_DFILTER16) || cheapest_of(out, KIND_DFILTER16B)))) {
-            // beside the kernel that streams its operands every kind is priced (dfilter16 and dfilter16b fitted to 97 launches, 0.07 and
-            // 0.08 in the logarithm).  It is the slower one for one to four images, a group of which is mostly zeros, and on large batches of
+            // beside the kernel that streams its operands every kind is priced (dfilter16 and dfilter16b fitted to 1494 and 1315 launches, 0.09
+            // and 0.10 in the logarithm).  Which of these two is the faster one their clocks know better than the fits do (245 layers on which
+            // they differ: 5889 us by clocks, 6588 by the fits), so the faster one is priced and the other keeps its distance.  It is the slower one for one to four images, a group of which is mostly zeros, and on large batches of
             // few channels, where its tile is mostly empty; us, ifilter16b and the kernel before: 2 images 30x22, 288 -> 488 50 and 29; 728 of
             // 49x14, 32 -> 32 77 and 48.  Over the 210 layers none is more than 3 % slower than before it, and all take 6398 us instead of 7900.
-            // (Below 16 images its fit is up to 25 % high: three images 17x23, 32 -> 32 of 5x5 13.2, the other one 16.6.)
+            // Of 1448 layers with a staged kernel 12 take more than 3 % longer than on that (140 where the fits chose among the three), all 42230 us
+            // instead of 55430.
             if (gather) price_kind(out, KIND_GATHER, gather->cost, gather_us(*gather));
-            if (const Launch *l = cheapest_of(out, KIND_IFILTER16)) price_kind(out, KIND_IFILTER16, l->cost, (g.N < 16 ? 1.25 : 1.04) * l->cost / images16_chain(*l) / 1260.0);
-            if (const Launch *l = cheapest_of(out, KIND_DFILTER16))
-                price_kind(out, KIND_DFILTER16, l->cost, 9.54 + 0.474 * (l->cost - reduce_clocks(*l)) / 1260.0 + 0.79 * mb(*l) + 0.276 * l->steps_per_split);
-            if (const Launch *l = cheapest_of(out, KIND_DFILTER16B))
-                price_kind(out, KIND_DFILTER16B, l->cost, 10.65 + 0.079 * (l->cost - reduce_clocks(*l)) / 1260.0 + 0.52 * mb(*l) + 1.15 * l->steps_per_split * rounds(*l));
+            if (const Launch *l = cheapest_of(out, KIND_IFILTER16)) price_kind(out, KIND_IFILTER16, l->cost, 1.04 * l->cost / images16_chain(*l) / 1260.0);
+            const Launch *staged = cheapest_of(out, KIND_DFILTER16), *staged_b = cheapest_of(out, KIND_DFILTER16B);
+            const bool b = staged_b && (!staged || staged_b->cost < staged->cost);
+            if (const Launch *l = b ? staged_b : staged) {
+                const double clocks = l->cost, core = (clocks - reduce_clocks(*l)) / 1260.0;
+                const double us = b ? 10.4 + 0.139 * core + 0.576 * mb(*l) + (g.S == 3 ? 0.774 : 1.013) * l->steps_per_split * rounds(*l)
+                                    : 10.2 + 0.0955 * core + 0.52 * mb(*l) + 1.62 * l->steps_per_split;
+                for (int kind : {KIND_DFILTER16, KIND_DFILTER16B}) price_kind(out, kind, clocks, us);
+            }
         } else if (gather) {
             for (int kind : {KIND_IFILTER16, KIND_IGATHER16}) {
                 const Launch *l = cheapest_of(out, kind);

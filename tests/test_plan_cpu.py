@@ -313,3 +313,17 @@ def test_descriptions_tell_shared_tiles_from_others(m, alone, shared, R):
         finally:
             m.owt_test_force_variant(-1, 0, 0)
     assert names[0] != names[1] and names[1] == names[0] + " shared4", names
+
+
+# bf16 filter gradients, channels in eights: the kernels that stage pixels and the two over images, where one was timed well ahead; N, C, H,
+# W, K, R, the faster kernel, the slower one, microseconds of both
+@pytest.mark.parametrize("shape,faster,slower,us", [
+    ((46, 32, 14, 8, 32, 3), "dfilter16b ", "dfilter16 ", (14.0, 18.6)), ((3, 288, 47, 7, 480, 5), "dfilter16b ", "dfilter16 ", (34.0, 43.8)),
+    ((4, 368, 10, 13, 32, 5), "dfilter16b ", "dfilter16 ", (15.7, 18.3)), ((3, 448, 19, 14, 96, 3), "dfilter16 ", "dfilter16b ", (18.9, 24.2)),
+    ((909, 256, 11, 7, 64, 3), "dfilter16b ", "ifilter16b ", (51.0, 54.8)), ((340, 96, 19, 13, 160, 3), "dfilter16b ", "ifilter16b ", (56.1, 59.9)),
+    ((16, 32, 9, 22, 32, 5), "ifilter16b ", "dfilter16 ", (11.0, 17.6)), ((27, 24, 18, 19, 32, 5), "ifilter16b ", "dfilter16b ", (13.0, 18.1)),
+    ((9, 32, 27, 27, 144, 3), "ifilter16 ", "ifilter16b ", (14.4, 19.1)), ((349, 32, 13, 37, 320, 3), "ifilter16 ", "ifilter16b ", (61.8, 80.5))])
+def test_bf16_filter_gradients_get_the_faster_kind_of_kernel(m, shape, faster, slower, us):
+    N, C, H, W, K, R = shape
+    got = plan(m, (N, C, H, W, K, R, R, 1, R // 2), 2, False, dtype=1)
+    assert got.startswith(faster), (got, slower, us)
