@@ -1349,7 +1349,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // The filter gradients that take 16 images at a time, against the kernel that gathers pixels: of a group of 16 one to four images
     // leave most empty, and few channels leave most of a 32-channel block empty.  Gathering fitted to launches of 546 layers, 0.09 to
     // 0.14 in the logarithm; large layers are left to the clocks, the fit is 25 % off there, and one or two images to gathering unless 16
-    // at a time are clearly the faster way.  us, 16 images at a time and gathering: one image 9x62, 33 -> 256 of 5x5 32 and 33; two
+    // at a time are clearly the faster way (the fit knows no masks, with which gathering takes a tenth longer: 200 masked layers of one or
+    // two images 6903 -> 5904 us without).  us, 16 images at a time and gathering: one image 9x62, 33 -> 256 of 5x5 32 and 33; two
     // 47x48, 64 -> 256 of 3x3 37 and 43; two 24x36, 39 -> 451 of 3x3 43 and 58; three 30x20, 130 -> 200 of 5x5 55 and 124.  258 layers, most of
     // which stay with their kernel: 12315 -> 10768 us with four wavefronts to a tile, three more than 4 % slower (by 8 % at most).
     if (g.bf16 && pass == OWT_PASS_BWD_FILTER && force_tile < 0) {
@@ -1395,7 +1396,7 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 if (!l) continue;
                 const double us = l->cost / images16_chain(*l) / 1260.0;
                 price_kind(out, kind, l->cost, us);
-                price_kind(out, KIND_GATHER, gather->cost, us < (g.N <= 2 ? 150.0 : 60.0) ? gather_us(*gather) / (g.N <= 2 ? 1.2 : 1.0) : std::max(gather->cost / 1260.0, g.N <= 2 ? 0.0 : 1.05 * us));
+                price_kind(out, KIND_GATHER, gather->cost, us < (g.N <= 2 ? 150.0 : 60.0) ? gather_us(*gather) * (g.masked ? 1.1 : g.N <= 2 ? 1.0 / 1.2 : 1.0) : std::max(gather->cost / 1260.0, g.N <= 2 ? 0.0 : 1.05 * us));
             }
         }
     }

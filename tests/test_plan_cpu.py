@@ -327,3 +327,12 @@ def test_bf16_filter_gradients_get_the_faster_kind_of_kernel(m, shape, faster, s
     N, C, H, W, K, R = shape
     got = plan(m, (N, C, H, W, K, R, R, 1, R // 2), 2, False, dtype=1)
     assert got.startswith(faster), (got, slower, us)
+
+
+# masked bf16 filter gradients of one or two images, which load a mask beside every value that they gather; us over images and gathering
+@pytest.mark.parametrize("shape,us", [((2, 125, 31, 12, 416, 5), (66.4, 96.9)), ((2, 324, 21, 6, 350, 5), (62.5, 84.8)), ((1, 317, 37, 43, 18, 5), (44.9, 85.6)),
+                                      ((2, 47, 44, 20, 461, 3), (40.4, 62.4)), ((1, 65, 26, 28, 211, 3), (32.4, 48.7)), ((2, 96, 8, 8, 128, 5), (17.1, 24.4))])
+def test_masked_bf16_filter_gradients_of_few_images_are_not_gathered(m, shape, us):
+    N, C, H, W, K, R = shape
+    got = plan(m, (N, C, H, W, K, R, R, 1, R // 2), 2, True, dtype=1)
+    assert got.startswith("ifilter16 "), (got, us)
