@@ -675,12 +675,19 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
                 if (force_split > 0) break;
             }
         }
-        // xconv's prices stay, so these stand to them as the clocks did: the microseconds choose between tiles and splits, and what several
-        // chunks to a panel won counts.  Of the 3000 passes 51 take more than 3 % longer than before there were such panels, 10 more than 6 %,
-        // 246 less.  (Priced by clocks with panels of several chunks, which know of no cost of a work-group, 79, 50 and 227: 60 images
-        // 14x31, 32 -> 32 14.0 us in 814 tiles of 32 x 32, 11.0 in 407 of 64 x 32.  By the microseconds alone 53, 18 and 278.)
+        // xconv's prices stay, so these stand to its cheapest launch as the microseconds of both do.  xconv's: fitted to 2500 drawn passes that
+        // either may be the faster one on, 0.07 in the logarithm: its clocks, rounds, and values that are loaded one by one.  What is nearly as fast
+        // here stays here, the error is 0.8 times xconv's.  Of these passes 111 take more than 3 % longer than on the other kernel and all 61.4 ms,
+        // the fastest 60.9; with both by clocks 201 and 61.9, with the clocks of one chunk to a panel 264 and 62.1.  Where there is no xconv, as by clocks.
+        const Launch *xc = cheapest_of(out, KIND_XCONV);
+        double scale = us_of > 0.0 ? clocks_of / us_of : 1260.0;
+        if (xc) {
+            const bool masks = pass == OWT_PASS_BWD_DATA && g.masked;
+            const double rounds = (double)cdiv((long)xc->tiles_m * xc->tiles_n * xc->splits, 256), by_one = cred % 4 ? (masks ? 7.28e-3 : 2.25e-3) : 0.0;
+            scale = (masks ? 1.0 : 0.96) * xc->cost / (2.2 + 0.8 * xc->cost / 1260.0 - (xc->splits > 1 ? 1.1 : 0.0) + rounds * (1.1 + by_one * xc->steps_per_split * xc->pr));
+        }
         for (Launch &l : out)
-            if (l.kind == KIND_XCONVS) l.cost *= us_of > 0.0 ? clocks_of / us_of : 1260.0;
+            if (l.kind == KIND_XCONVS) l.cost *= scale;
     }
     if (g.bf16 && cred % 8 == 0 && !forced(OWT_FORCE_NO_BF16_MFMA)) {      // the bf16 MFMA: 64-channel chunks, or 32 in the 512x64 tile
         for (int t : {TILE_128x128, TILE_128x64, TILE_256x64, TILE_512x64, TILE_256x64P}) {

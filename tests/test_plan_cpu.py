@@ -336,3 +336,16 @@ def test_masked_bf16_filter_gradients_of_few_images_are_not_gathered(m, shape, u
     N, C, H, W, K, R = shape
     got = plan(m, (N, C, H, W, K, R, R, 1, R // 2), 2, True, dtype=1)
     assert got.startswith("ifilter16 "), (got, us)
+
+
+# fp32 passes that the kernel of few tiles and the one for layers that fill the chip are near each other on; N, C, H, W, K, R, pass, masked, the
+# faster kernel, microseconds of it and of the other
+@pytest.mark.parametrize("shape,faster,us", [
+    ((281, 53, 10, 12, 12, 3, 0, True), "xconvs ", (19.3, 29.3)), ((127, 64, 28, 12, 8, 3, 0, True), "xconvs ", (17.1, 25.1)), ((97, 23, 40, 11, 10, 3, 0, False), "xconvs ", (12.6, 17.8)),
+    ((242, 32, 12, 14, 13, 3, 0, True), "xconvs ", (11.9, 16.3)), ((58, 62, 36, 19, 10, 3, 0, True), "xconvs ", (23.4, 32.0)), ((113, 64, 12, 30, 8, 3, 0, False), "xconvs ", (19.7, 26.8)),
+    ((14, 32, 35, 13, 426, 3, 1, True), "xconvs ", (33.0, 38.0)), ((32, 238, 12, 11, 115, 3, 0, False), "xconv ", (29.3, 38.6)), ((73, 42, 6, 13, 154, 3, 1, True), "xconv ", (22.3, 27.7)),
+    ((116, 32, 11, 13, 212, 3, 1, False), "xconv ", (32.7, 38.4))])
+def test_fp32_layers_of_some_tiles_get_the_faster_kernel(m, shape, faster, us):
+    N, C, H, W, K, R, p, masked = shape
+    got = plan(m, (N, C, H, W, K, R, R, 1, R // 2), p, masked)
+    assert got.startswith(faster), (got, us)
