@@ -1275,8 +1275,8 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     // 16000 inputs, 0.06 and 0.10 in the logarithm; the other kernels' prices stay, so this one's stands to the cheapest launch above as
     // the microseconds do.  A wavefront's steps are a chain of loads, one behind the other from the reduction's length on that its own
     // sixteenth is longer than what is in flight: bf16, xfc and here: 16 x 5632 -> 19 7.4 and 11.9 us, 8 x 9379 -> 21 9.5 and 16.2, but 128 x 4096
-    // -> 512 11.2 and 10.2.  Of the 992 shards 7 are more than 3 % slower than without this kernel (by 22 % at most); with the line at 4500
-    // and 3000 inputs there was before, 83, by up to 85 %.
+    // -> 512 11.2 and 10.2.  Weighed by 4963 shards near the line, which take 50.7 ms, the faster kernel of each 50.1; with the line at 4500 and
+    // 3000 inputs there was before 16 x 5632 -> 19 and the like took up to 1.85 times as long.
     const Launch *split_fc = cheapest_of(out, KIND_XFC);
     if (plain && pass == OWT_PASS_FWD && !no_direct && !forced(OWT_FORCE_NO_BF16_MFMA) && (force_tile < 0 ? split_fc != nullptr : force_tile == kXFcSTile) && force_split <= 1 &&
         (double)(g.N + 16) * g.C * 4 < 2147483647.0 && (double)(g.K + 16) * g.C * 4 < 2147483647.0) {
@@ -1285,7 +1285,10 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
         l.tiles_m = (int)cdiv(dm.M, 16); l.tiles_n = (int)cdiv(dm.Ncols, 16);
         const double tiles = (double)l.tiles_m * l.tiles_n, more = (double)cdiv((long)tiles, 256) - 1.0, I = 1e-3 * dm.Kd, odd = dm.Kd % 2;
         const double rows = (std::min(g.N, 16) + std::min(g.K, 16)) / 32.0;      // (rows past the end are no loads)
-        const double here = 1.06 * (g.bf16 ? 2.12 + I * (0.49 + 0.76 * rows + odd * (0.1 + 0.49 * rows) + 1.62 * more + 0.2 * tiles / 256.0) + 0.57 * more
+        // (rows of whole 128-byte lines: 1.2 times as long near the line, 50 x 2600 -> 188 in fp32 9.4 us, 2720 12.0; a tile of few rows, which
+        // xfc is a little faster on than its price, 1.05)
+        const double weight = dm.Kd * (g.bf16 ? 2 : 4) % 128 == 0 ? 1.1 : g.bf16 ? 1.0 : rows < 1.0 ? 1.03 : 0.98;
+        const double here = weight * (g.bf16 ? 2.12 + I * (0.49 + 0.76 * rows + odd * (0.1 + 0.49 * rows) + 1.62 * more + 0.2 * tiles / 256.0) + 0.57 * more
                                            : 2.47 + I * (1.52 + 1.04 * rows + 2.59 * more + 0.6 * tiles / 256.0) + 0.96 * more);
         l.cost = 1260.0 * here;
         if (split_fc) {

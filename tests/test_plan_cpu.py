@@ -349,3 +349,11 @@ def test_fp32_layers_of_some_tiles_get_the_faster_kernel(m, shape, faster, us):
     N, C, H, W, K, R, p, masked = shape
     got = plan(m, (N, C, H, W, K, R, R, 1, R // 2), p, masked)
     assert got.startswith(faster), (got, us)
+
+
+# near the line between the two, us split over work-groups and in one launch: rows of whole 128-byte lines are the slower ones in one launch
+@pytest.mark.parametrize("dtype,shape,one,us", [(0, (57, 2452, 19), True, (11.9, 9.1)), (1, (129, 5285, 390), True, (25.9, 12.5)), (1, (30, 8062, 46), False, (7.8, 16.3)),
+                                                (0, (50, 2600, 188), True, (9.9, 9.5)), (0, (50, 2720, 188), False, (10.4, 12.0)), (1, (19, 4026, 25), True, (9.8, 7.6))])
+def test_shard_forward_near_the_line(m, dtype, shape, one, us):
+    N, I, O = shape
+    assert plan(m, (N, I, 1, 1, O, 1, 1, 1, 0), 0, True, dtype).startswith("xfcs" if one else "xfc "), us
