@@ -192,6 +192,8 @@ hipError_t owt_launch_dfilter16b(int variant, const GemmParams &, hipStream_t);
 // The filter gradient over images with the operands streamed straight into LDS (ifilter16b_inst.hip; unmasked dz, channels and
 // filters in eights): WK x WC wavefronts of KB filter blocks x CB channel blocks of 32 x the S taps of one filter row, an LDS ring of
 // NST stages of L positions, occ work-groups per CU.  The test hook numbers these variants from kIFilter16bFirstTile.
+// The untuned choice is 128 x 64 and 64 x 64 for most layers and hardly ever 192 x 64 (the fifth), which is for large batches of five taps: tuning
+// takes it for 1024 images 27x27, 64 -> 192, and of 1000 layers it was the fastest one on 28.
 struct IFilter16bVariant { int KB, CB, S, WK, WC, L, NST, occ; };
 constexpr int kNumIFilter16bVariants = 7, kIFilter16bFirstTile = 100;
 constexpr IFilter16bVariant kIFilter16bVariants[kNumIFilter16bVariants] = {

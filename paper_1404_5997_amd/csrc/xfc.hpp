@@ -22,7 +22,8 @@
 // backward 32.6 -> 29.8; 4096 -> 512 16.0 -> 13.2 and 22.6 -> 16.2; 4096 -> 125 10.6 -> 10.7 and 11.0 -> 8.4.  What bounds it is the chain of a
 // step: about 210 vector instructions that split its 4 x 8 values, then 24 matrix instructions.  Four steps' loads in flight at
 // one wavefront per SIMD: forward 20.5 -> 24.9, backward 33 -> 86 (664 spilled registers); two neighbouring columns with an 8-byte
-// load: backward 33 -> 38.
+// load: backward 33 -> 38.  The forward pass reads more than its operands, too: with the split in blockIdx.y the work-groups of a column tile
+// come to one XCD, and each of the eight reads all of x (9216 -> 512: 57 MB, the operands are 24).
 #pragma once
 #include "igemm.hpp"
 #include "split3.hpp"
