@@ -1346,6 +1346,21 @@ static void enumerate(const Geom &g, int pass, const PassDims &dm, bool want_db,
     const double gather_clocks = gather ? gather->cost : 0.0;
     const Launch *over = cheapest_of(out, KIND_XFILTER), *over2 = cheapest_of(out, KIND_XGATHER);
     if (!over || (over2 && over2->cost < over->cost)) over = over2;
+    // The strided kernels on the fp32 instruction, whose clocks know nothing of what a unit's two rows take to stage: 176 images 77x79, 8 -> 320 of 1x1,
+    // stride 2, masked, 766 us there and 147 over images, at a third of the clocks.  Fitted to 1000 and 612 launches, 0.11 and 0.05 in the logarithm;
+    // never below the clocks, as these are the less exact kernels; which of the two, their clocks say.  1000 strided layers 17403 -> 15640 us, the fastest 15560.
+    if (!g.bf16 && pass == OWT_PASS_BWD_FILTER && force_tile < 0 && over) {
+        const Launch *l = cheapest_of(out, KIND_SFILTER), *streamed = cheapest_of(out, KIND_SFILTER2);
+        const bool b = streamed && (!l || streamed->cost <= l->cost);
+        if (b) l = streamed;
+        if (l) {
+            const bool sp = l->splits > 1;
+            const double clocks = l->cost, core = (clocks - reduce_clocks(*l)) / 1260.0, steps = (double)l->steps_per_split * cdiv((long)l->tiles_m * l->splits, 256);
+            const double us = b ? 3.78 + 0.061 * core + 3.78 * sp + 0.553 * mb(*l) + steps * (0.343 + 1.0e-5 * (g.sh + g.R) * g.W * g.C + 0.218 * g.Q)
+                                : 4.14 + 0.133 * core + 4.14 * sp + 0.482 * mb(*l) + steps * (0.739 + 6.35e-4 * (g.sh + g.R) * g.W * g.C + 0.0806 * (1 + g.masked) * g.Q);
+            for (int kind : {KIND_SFILTER, KIND_SFILTER2}) price_kind(out, kind, clocks, std::max(clocks / 1260.0, us));
+        }
+    }
     if (!g.bf16 && pass == OWT_PASS_BWD_FILTER && gather && force_tile < 0 && over) {
         const double core = (gather->cost - reduce_clocks(*gather)) / 1260.0, split = gather->splits > 1, wgs = (double)cdiv((long)gather->tiles_m * gather->tiles_n * gather->splits, 256);
         const double us = vec ? 4.3 + 0.734 * core + 0.474 * mb(*gather) + 0.193 * gather->steps_per_split + 2.53 * wgs

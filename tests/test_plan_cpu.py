@@ -357,3 +357,13 @@ def test_fp32_layers_of_some_tiles_get_the_faster_kernel(m, shape, faster, us):
 def test_shard_forward_near_the_line(m, dtype, shape, one, us):
     N, I, O = shape
     assert plan(m, (N, I, 1, 1, O, 1, 1, 1, 0), 0, True, dtype).startswith("xfcs" if one else "xfc "), us
+
+
+# fp32 strided filter gradients of few channels: what a unit of the kernels on the fp32 instruction stages is not in its clocks; us over images and
+# there (N, C, H, W, K, R, S, stride, pad)
+@pytest.mark.parametrize("shape,masked,us", [((176, 8, 77, 79, 320, 1, 1, 2, 0), True, (147, 766)), ((43, 8, 32, 55, 160, 1, 1, 2, 0), False, (18, 41)), ((164, 8, 25, 6, 416, 1, 3, 2, 0), False, (16, 34)),
+                                             ((90, 8, 31, 79, 104, 2, 1, 3, 0), False, (20, 34)), ((235, 8, 76, 14, 504, 1, 1, 2, 0), False, (42, 273)), ((134, 16, 49, 37, 352, 1, 2, 2, 0), True, (38, 218)),
+                                             ((67, 8, 11, 34, 168, 3, 1, 2, 0), False, (15, 20))])
+def test_fp32_strided_filter_gradients_of_few_channels_are_taken_over_images(m, shape, masked, us):
+    got = plan(m, shape, 2, masked)
+    assert got.startswith("sfilterx "), (got, us)
